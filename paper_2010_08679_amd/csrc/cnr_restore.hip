@@ -381,38 +381,190 @@ void launch_restore(cnr_ctx *ctx, hipStream_t st, uint32_t dim, RestoreJob &a) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Error metric: || X - Q ||_2 per row in fp64, one wavefront per row, any dim; and its mean, added
-// up by one workgroup in a fixed order so that the result does not depend on scheduling.
+// Error metric: || X - Q ||_2 per row in fp64, any dim; and the mean over the rows, added up in an
+// order that the list length and the grid fix, so that it does not depend on scheduling.
+//
+// The mean of a long list needs many compute units (one workgroup reads 12 MB of row errors in 1.67 ms)
+// and therefore partial sums, and the call has no scratch buffer.  So every workgroup of the error
+// kernel adds up its own rows and leaves the sum in err[] in the place of its first row
+// (row w * rows_per_wg for workgroup w); one workgroup then adds up the partial sums, and a last launch
+// of the same kernel over just those rows puts their errors there.  Everything happens in the caller's
+// buffer, on the caller's stream.  Lists of up to kDirectMeanRows are added up by one workgroup as they
+// are: below that, it takes no longer than the two launches it saves.
 // ---------------------------------------------------------------------------------------------
-template <int BITS>
-__global__ void __launch_bounds__(kBlock)
-quant_error_kernel(const float *__restrict__ table, uint64_t n_rows, uint32_t dim,
-                   const uint32_t *__restrict__ row_ids, const uint64_t *__restrict__ n_dev, uint64_t n_max,
-                   const uint8_t *__restrict__ packed, const float *__restrict__ scale,
-                   const float *__restrict__ bias, double *__restrict__ err_out, cnr_dev_errors *err) {
-    constexpr uint32_t MASK = (1u << BITS) - 1u;
-    uint64_t n = n_max;
-    if (n_dev) {
-        const uint64_t nd = *n_dev;
-        n = nd < n_max ? nd : n_max;
+struct ErrorArgs {
+    const float *table;
+    uint64_t n_rows;
+    uint32_t dim;
+    const uint32_t *row_ids;
+    const uint64_t *n_dev;
+    uint64_t n_max;
+    const uint8_t *packed;
+    const float *scale, *bias;
+    double *err;
+    uint64_t stride;     // the launch covers rows 0, stride, 2 * stride, ... of the list
+    uint32_t partials;   // leave the workgroup's sum in the place of its first row's error
+    cnr_dev_errors *dev_err;
+};
+constexpr uint64_t kDirectMeanRows = 16384;
+// Workgroups of the error kernel at most, each with a partial sum: 2048 to 4096 are equally fast on 1.5 M
+// rows of 64 (108 us with the mean), 8192 cost more in the two launches behind it than they gain (115 us).
+constexpr unsigned kErrorMaxBlocks = 4096;
+
+// sum = this lane's share of what the workgroup's rows came to: the workgroup's total into err[first]
+// by thread 0, whose own earlier store to that place is ahead of it in program order.
+__device__ __forceinline__ void leave_partial_sum(double sum, double *err, uint64_t first, uint64_t n) {
+    __shared__ double wave_sum[kWavesPerBlock];
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+    if ((tid_x() & (kWave - 1)) == 0) wave_sum[tid_x() / kWave] = sum;
+    __syncthreads();
+    if (tid_x() == 0 && first < n) {
+        double total = 0.0;
+        for (int w = 0; w < kWavesPerBlock; ++w) total += wave_sum[w];
+        err[first] = total;
     }
+}
+
+// Rows of whole 16-byte units (dim % 4 == 0, table and codes 16-byte aligned): LPR lanes per row, lane j
+// takes the units j, j + LPR, ... of its row and their codes.  A wave holds kErrorSteps rows per lane
+// group at once, so that as many row loads are in flight per lane.  Bound by the gather of the rows
+// (fp64: two conversions, a subtraction and a fused multiply-add per element, a quarter of the time).
+// 1.5 M rows of 64 at 4 bits: a wave per row with byte loads 332 us, this 93 us (5.0 TB/s); with the mean
+// 2018 -> 107 us.
+constexpr int kErrorSteps = 4;
+template <int LPR, int BITS>
+__global__ void __launch_bounds__(kBlock) quant_error_units_kernel(const ErrorArgs a) {
+    constexpr int ST = kErrorSteps;
+    constexpr int RPS = kWave / LPR;         // rows per step
+    constexpr uint64_t GROUP = RPS * ST;     // rows per wave and pass
+    constexpr uint32_t MASK = (1u << BITS) - 1u;
+    const uint64_t n = live_rows(a.n_dev, a.n_max);
+    const uint64_t items = (n + a.stride - 1) / a.stride;
+    const uint32_t n4 = a.dim / 4;
+    const uint64_t P = (uint64_t)a.dim * BITS / 8;
+    const int lane = tid_x() & (kWave - 1);
+    const uint32_t j = lane % LPR, rho = lane / LPR;
+    const uint64_t n_waves = (uint64_t)grid_x() * kWavesPerBlock;
+    // What a lane needs of its rows of one pass: ids, scales and biases, requested one pass ahead.  Rows
+    // past the end repeat the list's last one, and nothing of theirs is kept.
+    uint32_t rid[ST];
+    float s[ST], b[ST];
+    auto item = [&](uint64_t pass, int t) {
+        const uint64_t i = pass * GROUP + rho + (uint32_t)(RPS * t);
+        return (i < items ? i : items - 1) * a.stride;
+    };
+    auto fetch = [&](uint64_t pass) {
+#pragma unroll
+        for (int t = 0; t < ST; ++t) {
+            const uint64_t k = item(pass, t);
+            rid[t] = a.row_ids ? a.row_ids[k] : k > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)k;  // beyond 2^32 - 1: outside any table
+            s[t] = a.scale[k];
+            b[t] = a.bias[k];
+        }
+    };
+    double sum = 0.0;
+    uint64_t pass = wave_in_grid();
+    if (pass * GROUP < items) fetch(pass);
+    for (; pass * GROUP < items; pass += n_waves) {
+        const uint64_t i0 = pass * GROUP + rho;
+        const float *row[ST];
+        const uint8_t *codes[ST];
+        float sc[ST], bi[ST];
+        bool in_table[ST];
+        double acc[ST];
+#pragma unroll
+        for (int t = 0; t < ST; ++t) {
+            in_table[t] = rid[t] < a.n_rows;
+            if (!in_table[t] && j == 0) raise_flag(a.dev_err, CNR_FLAG_ROW_ID);
+            row[t] = a.table + (uint64_t)(in_table[t] ? rid[t] : 0u) * a.dim;
+            codes[t] = a.packed + item(pass, t) * P;
+            sc[t] = s[t];
+            bi[t] = b[t];
+            acc[t] = 0.0;
+        }
+        if ((pass + n_waves) * GROUP < items) fetch(pass + n_waves);
+        for (uint32_t u0 = 0; u0 < n4; u0 += LPR) {
+            const uint32_t u = u0 + j;
+            const bool mine = u < n4;
+            const uint32_t uc = mine ? u : 0;
+            f32x4 x[ST];
+            uint32_t w[ST];
+#pragma unroll
+            for (int t = 0; t < ST; ++t) {
+                x[t] = load_stream<f32x4>(row[t] + 4u * uc);
+                const uint8_t *in = codes[t];
+                if constexpr (BITS == 8) {
+                    w[t] = *reinterpret_cast<const uint32_t *>(in + 4 * uc);
+                } else if constexpr (BITS == 4) {
+                    w[t] = *reinterpret_cast<const uint16_t *>(in + 2 * uc);
+                } else if constexpr (BITS == 2) {
+                    w[t] = in[uc];
+                } else {  // 12 bits from bit 12 * u on: in two bytes, from a byte boundary or the middle of a byte
+                    const uint8_t *i3 = in + (3 * uc) / 2;
+                    w[t] = ((uint32_t)i3[0] | ((uint32_t)i3[1] << 8)) >> (4 * (uc & 1));
+                }
+            }
+            if (mine) {
+#pragma unroll
+                for (int t = 0; t < ST; ++t)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float q = sc[t] * (float)((w[t] >> (e * BITS)) & MASK) + bi[t];
+                        const double d = (double)x[t][e] - (double)q;
+                        acc[t] = fma(d, d, acc[t]);
+                    }
+            }
+        }
+        // all lanes of a row get its sum; lane t of the row keeps that of step t
+        double mine = 0.0;
+        bool ok = false;
+#pragma unroll
+        for (int t = 0; t < ST; ++t) {
+            double v = acc[t];
+            v += dpp_d<0xB1>(v);
+            v += dpp_d<0x4E>(v);
+            if constexpr (LPR >= 8) v += dpp_d<0x141>(v);
+            if constexpr (LPR >= 16) v += dpp_d<0x140>(v);
+            if (j == (uint32_t)t) {
+                mine = v;
+                ok = in_table[t];
+            }
+        }
+        const uint64_t i = i0 + (uint64_t)(RPS * j);
+        if (j < ST && i < items) {
+            const double e = ok ? sqrt(mine) : 0.0;
+            a.err[i * a.stride] = e;
+            sum += e;
+        }
+    }
+    if (a.partials) leave_partial_sum(sum, a.err, (uint64_t)wg_x() * kWavesPerBlock * GROUP, n);
+}
+
+// Any other dim or alignment: one wavefront per row.
+template <int BITS>
+__global__ void __launch_bounds__(kBlock) quant_error_kernel(const ErrorArgs a) {
+    constexpr uint32_t MASK = (1u << BITS) - 1u;
+    const uint64_t n = live_rows(a.n_dev, a.n_max);
+    const uint64_t items = (n + a.stride - 1) / a.stride;
     const int lane = tid_x() & (kWave - 1);
     const uint64_t n_waves = (uint64_t)grid_x() * kWavesPerBlock;
-    const uint64_t P = (uint64_t)dim * BITS / 8;
-    for (uint64_t k = (uint64_t)wg_x() * kWavesPerBlock + tid_x() / kWave; k < n; k += n_waves) {
-        const uint64_t r = row_ids ? (uint64_t)row_ids[k] : k;
-        if (r >= n_rows) {
+    const uint64_t P = (uint64_t)a.dim * BITS / 8;
+    double sum = 0.0;
+    for (uint64_t i = wave_in_grid(); i < items; i += n_waves) {
+        const uint64_t k = i * a.stride;
+        const uint64_t r = a.row_ids ? (uint64_t)a.row_ids[k] : k;
+        if (r >= a.n_rows) {
             if (lane == 0) {
-                raise_flag(err, CNR_FLAG_ROW_ID);
-                err_out[k] = 0.0;
+                raise_flag(a.dev_err, CNR_FLAG_ROW_ID);
+                a.err[k] = 0.0;
             }
             continue;
         }
-        const uint8_t *__restrict__ in = packed + k * P;
-        const float s = scale[k], b = bias[k];
-        const float *__restrict__ x = table + r * (uint64_t)dim;
+        const uint8_t *__restrict__ in = a.packed + k * P;
+        const float s = a.scale[k], b = a.bias[k];
+        const float *__restrict__ x = a.table + r * (uint64_t)a.dim;
         double acc = 0.0;
-        for (uint32_t e = lane; e < dim; e += kWave) {
+        for (uint32_t e = lane; e < a.dim; e += kWave) {
             const uint64_t bit = (uint64_t)e * BITS;
             uint32_t two = in[bit >> 3];
             if (((bit & 7u) + BITS) > 8u) two |= (uint32_t)in[(bit >> 3) + 1] << 8;
@@ -421,28 +573,64 @@ quant_error_kernel(const float *__restrict__ table, uint64_t n_rows, uint32_t di
             acc += d * d;
         }
         for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-        if (lane == 0) err_out[k] = sqrt(acc);
+        if (lane == 0) {
+            const double e = sqrt(acc);
+            a.err[k] = e;
+            sum += e;
+        }
     }
+    if (a.partials) leave_partial_sum(sum, a.err, (uint64_t)wg_x() * kWavesPerBlock, n);
 }
 
-__global__ void __launch_bounds__(kBlock)
-mean_kernel(const double *__restrict__ v, const uint64_t *__restrict__ n_dev, uint64_t n_max,
-            double *__restrict__ mean_out) {
-    __shared__ double part[kBlock];
-    uint64_t n = n_max;
-    if (n_dev) {
-        const uint64_t nd = *n_dev;
-        n = nd < n_max ? nd : n_max;
-    }
+// (1/n) * the sum of v[0], v[stride], v[2 * stride], ..., at most `most` of them (the row errors
+// themselves, or the partial sums of the error kernel's workgroups), by one workgroup.
+constexpr int kMeanThreads = 1024;
+__global__ void __launch_bounds__(kMeanThreads) mean_kernel(const double *__restrict__ v, uint64_t stride, uint64_t most,
+                                                            const uint64_t *__restrict__ n_dev, uint64_t n_max,
+                                                            double *__restrict__ mean_out) {
+    __shared__ double part[kMeanThreads];
+    const uint64_t n = live_rows(n_dev, n_max);
+    uint64_t items = (n + stride - 1) / stride;
+    if (items > most) items = most;
     double acc = 0.0;
-    for (uint64_t i = tid_x(); i < n; i += kBlock) acc += v[i];
+    for (uint64_t i = tid_x(); i < items; i += kMeanThreads) acc += v[i * stride];
     part[tid_x()] = acc;
     __syncthreads();
-    for (int half = kBlock / 2; half > 0; half >>= 1) {
+    for (int half = kMeanThreads / 2; half > 0; half >>= 1) {
         if ((int)tid_x() < half) part[tid_x()] += part[tid_x() + half];
         __syncthreads();
     }
     if (tid_x() == 0) *mean_out = n ? part[0] / (double)n : 0.0;
+}
+
+template <int BITS>
+void launch_error_bits(const ErrorArgs &a, unsigned grid, uint32_t lanes, hipStream_t s) {
+    switch (lanes) {
+        case 4: hipLaunchKernelGGL((quant_error_units_kernel<4, BITS>), dim3(grid), dim3(kBlock), 0, s, a); break;
+        case 8: hipLaunchKernelGGL((quant_error_units_kernel<8, BITS>), dim3(grid), dim3(kBlock), 0, s, a); break;
+        case 16: hipLaunchKernelGGL((quant_error_units_kernel<16, BITS>), dim3(grid), dim3(kBlock), 0, s, a); break;
+        default: hipLaunchKernelGGL((quant_error_kernel<BITS>), dim3(grid), dim3(kBlock), 0, s, a); break;
+    }
+}
+void launch_error(const ErrorArgs &a, unsigned grid, uint32_t lanes, int bits, hipStream_t s) {
+    switch (bits) {
+        case 2: return launch_error_bits<2>(a, grid, lanes, s);
+        case 3: return launch_error_bits<3>(a, grid, lanes, s);
+        case 4: return launch_error_bits<4>(a, grid, lanes, s);
+        default: return launch_error_bits<8>(a, grid, lanes, s);
+    }
+}
+
+// Lanes per row of the error kernel: of 16, 8 and 4 the one that leaves the fewest idle lanes in the
+// last trip through a row (the most lanes among equals: wider runs per load instruction); 0 = one wave
+// per row, for rows that are not whole aligned 16-byte units.
+uint32_t error_lanes(uint32_t dim, const void *table, const void *packed) {
+    if (dim % 4 || (uintptr_t)table % 16 || (uintptr_t)packed % 4) return 0;
+    const uint32_t n4 = dim / 4;
+    uint32_t best = 16;
+    for (uint32_t l : {8u, 4u})
+        if ((n4 + l - 1) / l * l < (n4 + best - 1) / best * best) best = l;
+    return best;
 }
 
 }  // namespace
@@ -461,18 +649,33 @@ extern "C" cnr_status cnr_quant_error(cnr_ctx *ctx, const float *table, uint64_t
     hipStream_t s = as_stream(stream);
     if (n_max > 0) {
         if (!table || !packed || !scale || !bias || !err || n_rows == 0 || n_rows >= (1ull << 32)) return CNR_E_INVALID;
-        const unsigned grid = cnr_grid(ctx, n_max, kWavesPerBlock, 8);
-        switch (bits) {
-            case 2: hipLaunchKernelGGL(quant_error_kernel<2>, dim3(grid), dim3(kBlock), 0, s, table, n_rows, dim, row_ids, n_dev, n_max, packed, scale, bias, err, ctx->dev_err); break;
-            case 3: hipLaunchKernelGGL(quant_error_kernel<3>, dim3(grid), dim3(kBlock), 0, s, table, n_rows, dim, row_ids, n_dev, n_max, packed, scale, bias, err, ctx->dev_err); break;
-            case 4: hipLaunchKernelGGL(quant_error_kernel<4>, dim3(grid), dim3(kBlock), 0, s, table, n_rows, dim, row_ids, n_dev, n_max, packed, scale, bias, err, ctx->dev_err); break;
-            default: hipLaunchKernelGGL(quant_error_kernel<8>, dim3(grid), dim3(kBlock), 0, s, table, n_rows, dim, row_ids, n_dev, n_max, packed, scale, bias, err, ctx->dev_err); break;
+        const uint32_t lanes = error_lanes(dim, table, packed);
+        const uint64_t rows_per_wg = (lanes ? (uint64_t)kErrorSteps * (kWave / lanes) : 1u) * kWavesPerBlock;
+        ErrorArgs a = {table, n_rows, dim, row_ids, n_dev, n_max, packed, scale, bias, err, 1, 0, ctx->dev_err};
+        auto grid_for = [&](uint64_t rows) {
+            const uint64_t need = (rows + rows_per_wg - 1) / rows_per_wg;
+            return (unsigned)(need < kErrorMaxBlocks ? need : kErrorMaxBlocks);
+        };
+        const unsigned grid = grid_for(n_max);
+        const bool by_parts = mean_out && n_max > kDirectMeanRows;
+        a.partials = by_parts ? 1 : 0;
+        launch_error(a, grid, lanes, bits, s);
+        if ((st = cnr_launch_status(ctx)) != CNR_OK) return st;
+        if (by_parts) {
+            hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(kMeanThreads), 0, s, err, rows_per_wg, (uint64_t)grid, n_dev, n_max, mean_out);
+            if ((st = cnr_launch_status(ctx)) != CNR_OK) return st;
+            // the first row of every workgroup again, whose place held the workgroup's sum
+            const uint64_t firsts = grid;
+            const uint64_t covered = firsts * rows_per_wg;  // rows behind it are no workgroup's first
+            a.partials = 0;
+            a.stride = rows_per_wg;
+            if (covered < n_max) a.n_max = covered;
+            launch_error(a, grid_for(firsts), lanes, bits, s);
+            return cnr_launch_status(ctx);
         }
-        st = cnr_launch_status(ctx);
-        if (st != CNR_OK) return st;
     }
     if (mean_out) {
-        hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(kBlock), 0, s, err, n_dev, n_max, mean_out);
+        hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(kMeanThreads), 0, s, err, (uint64_t)1, n_max, n_dev, n_max, mean_out);
         st = cnr_launch_status(ctx);
     }
     return st;
