@@ -377,22 +377,24 @@ quantize_tile_kernel(const QuantBatchArgs b) {
 // row, so short lists, which cannot fill the SIMDs either way, keep G = 1.  The rows are read in this
 // layout directly (each lane its own 64 * G bytes): the kernel is far from the memory system's limits,
 // so the transpose through LDS that the tile kernel pays for coalesced loads would buy nothing.
-// A candidate is evaluated with the cheapest sequence that still ranks candidates as F_Q would.  On
-// this GPU a wave's add, subtract or multiply occupies a SIMD for two clocks, every other vector
-// instruction used here (fused multiply-add, median, round, conversion, all fp64) for four (measured
-// with single-instruction loops), so an element costs 26 clocks per candidate: clip (4), subtract (2),
-// multiply by the reciprocal of the scale (2), round (4), de-quantize (2 + 2), residual (2), convert
-// and accumulate its square in fp64 (4 + 4; d * d is exact in fp64, so fma(d, d, acc) is the
-// multiply-then-add of the definition).  The candidate's scale is range / (2^b - 1) correctly rounded
-// (reciprocal multiply plus one FMA residual step) and its reciprocal likewise; the quotient itself
-// is the plain product, within 1.5 ulp of the correctly rounded quotient, which can move a code of a
-// candidate only where the quotient lies that close to a half-integer (about 3 elements in a million
-// at 4 bits) and then changes the candidate's error by about 1e-7 of itself: a search leaves the path
-// of the divide-as-written sequence only if that coincides with two candidates that close, about one
-// row in a few million.  (Correcting the quotient too, two more FMAs per element, took 34 clocks per
-// element and candidate.)  A wave holding a row whose scale lies outside [2^-100, 2^100], or whose
-// span is only a few float spacings wide, divides instead.  The final codes of the chosen range are
-// produced by division, exactly as F_Q is written.
+// A candidate is evaluated with the cheapest sequence that still ranks candidates as F_Q would: eight
+// vector instructions per element (struct Candidate).  What they cost differs (a wave's add or subtract
+// occupies a SIMD for 0.92 ns, a multiply with the clamp modifier 1.31, a fused multiply-add 1.56, a
+// median, a round or a conversion 1.74, an fp64 fused multiply-add 1.9; single-instruction loops), so
+// the clip is the free clamp to [0, 1] of the multiply by 1 / (qmax * scale), the rounding is the fused
+// multiply-add by qmax onto 2^23, and that biased code, with -2^23 * scale as the addend, gives the
+// rounded product scale * code in one fused multiply-add more.  The sequence with a median for the clip
+// and a round instruction (nine instructions) took 12.8 ns per element and candidate, this one takes 9.3;
+// 1.5 M rows of 64, 199 candidates: 3.28 -> 2.70 ms.
+// The candidate's scale is range / (2^b - 1) correctly rounded (reciprocal multiply plus one FMA
+// residual step), 1 / (qmax * scale) likewise, and the quotient, three roundings in all, is within
+// 1.5 ulp of the exact one, which can move a code of a candidate only where the quotient lies that
+// close to a half-integer (about 3 elements in a million at 4 bits) and then changes the candidate's
+// error by about 1e-7 of itself: a search leaves the path of the divide-as-written sequence only if
+// that coincides with two candidates that close, about one row in a few million.  Everything behind the code (product, sum, difference, square, fp64 sum) is
+// rounded as the definition rounds it.  A wave holding a row whose scale lies outside [2^-100, 2^100], or
+// whose span is only a few float spacings wide, divides instead.  The final codes of the chosen range
+// are produced by division, exactly as F_Q is written.
 // ---------------------------------------------------------------------------------------------
 template <int L>
 __device__ __forceinline__ float lanes_min(float v) {
@@ -419,8 +421,60 @@ __device__ __forceinline__ double lanes_sum(double v) {
     return v;
 }
 
+// One candidate range: what the error of an element needs.
+template <int BITS>
+struct Candidate {
+    static constexpr float QMAXF = (float)((1 << BITS) - 1);
+    float lo, scale, inv;  // inv = 1 / (qmax * scale)
+    float unbias;          // -2^23 * scale
+    __device__ __forceinline__ Candidate(float c_lo, float c_hi) {
+        constexpr float INV_QMAX = 1.0f / QMAXF;
+        const float range = c_hi - c_lo;
+        const float q0 = range * INV_QMAX;
+        lo = c_lo;
+        scale = fmaf(fmaf(-q0, QMAXF, range), INV_QMAX, q0);
+        const float full = scale * QMAXF, rest = fmaf(scale, QMAXF, -full);  // qmax * scale in two pieces
+        const float r0 = __builtin_amdgcn_rcpf(full);
+        inv = scale == 0.0f ? 0.0f : fmaf(fmaf(-rest, r0, fmaf(-full, r0, 1.0f)), r0, r0);
+        unbias = scale * -0x1p23f;
+    }
+    // acc += (x - F_Q(x) de-quantized)^2 of eight elements.  Left to itself the compiler strings the
+    // eight instructions of one element behind each other, each waiting for the one before; the barriers
+    // keep them in stages of eight independent ones (2.99 -> 2.70 ms on the list above; stages of four or
+    // sixteen 2.97).
+    __device__ __forceinline__ void add_err(double &acc, const float (&x)[8]) const {
+        constexpr int N = 8;
+        float t[N];
+        double d[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) t[i] = x[i] - lo;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < N; ++i) t[i] = __builtin_amdgcn_fmed3f(t[i] * inv, 0.0f, 1.0f);  // the multiply's clamp modifier
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < N; ++i) t[i] = fmaf(t[i], QMAXF, 0x1p23f);  // 2^23 + code
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < N; ++i) t[i] = fmaf(t[i], scale, unbias);   // scale * code
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < N; ++i) t[i] = t[i] + lo;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < N; ++i) t[i] = x[i] - t[i];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < N; ++i) d[i] = (double)t[i];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < N; ++i) acc = fma(d[i], d[i], acc);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+};
+
 template <int L, int BITS, int G>
-__global__ void __launch_bounds__(kBlock) quantize_greedy_kernel(const QuantArgs a, uint64_t n_from, uint64_t n_below) {
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L == 1 && G == 4 ? 3 : G == 4 ? 4 : 5, 8))) quantize_greedy_kernel(const QuantArgs a, uint64_t n_from, uint64_t n_below) {
     constexpr int EPL = 16 * G;  // elements per lane
     constexpr int DIM = EPL * L;
     constexpr int kRowsPerPass = kWave / L;
@@ -467,34 +521,22 @@ __global__ void __launch_bounds__(kBlock) quantize_greedy_kernel(const QuantArgs
         // ---- the search: shrink from whichever side hurts less, remember the best range seen
         auto search = [&](auto fast_tag) {
             constexpr bool FAST = decltype(fast_tag)::value;
-            auto add_err = [&](double acc, float xv, float c_lo, float c_hi, float s, float inv) -> double {
-                if constexpr (FAST) {
-                    const float c = __builtin_amdgcn_fmed3f(xv, c_lo, c_hi);
-                    const float t = (c - c_lo) * inv;
-                    const float d = xv - fq_value(rintf(t), s, c_lo);
-                    return fma((double)d, (double)d, acc);
-                } else {
-                    return acc + fq_sq_err(xv, c_lo, c_hi, s, QMAXF);
-                }
-            };
             auto row_err = [&](float c_lo, float c_hi) -> double {
-                const float range = c_hi - c_lo;
-                float s, inv = 0.0f;
-                if constexpr (FAST) {
-                    const float q0 = range * INV_QMAX;
-                    s = fmaf(fmaf(-q0, QMAXF, range), INV_QMAX, q0);
-                    const float r0 = __builtin_amdgcn_rcpf(s);
-                    inv = s == 0.0f ? 0.0f : fmaf(fmaf(-s, r0, 1.0f), r0, r0);
-                } else {
-                    s = range / QMAXF;
-                }
                 double e = 0.0;
+                if constexpr (FAST) {
+                    const Candidate<BITS> c(c_lo, c_hi);
 #pragma unroll
-                for (int i = 0; i < 4 * G; ++i) {
-                    e = add_err(e, x[i].x, c_lo, c_hi, s, inv);
-                    e = add_err(e, x[i].y, c_lo, c_hi, s, inv);
-                    e = add_err(e, x[i].z, c_lo, c_hi, s, inv);
-                    e = add_err(e, x[i].w, c_lo, c_hi, s, inv);
+                    for (int i = 0; i < 4 * G; i += 2)
+                        c.add_err(e, {x[i].x, x[i].y, x[i].z, x[i].w, x[i + 1].x, x[i + 1].y, x[i + 1].z, x[i + 1].w});
+                } else {
+                    const float s = (c_hi - c_lo) / QMAXF;
+#pragma unroll
+                    for (int i = 0; i < 4 * G; ++i) {
+                        e += fq_sq_err(x[i].x, c_lo, c_hi, s, QMAXF);
+                        e += fq_sq_err(x[i].y, c_lo, c_hi, s, QMAXF);
+                        e += fq_sq_err(x[i].z, c_lo, c_hi, s, QMAXF);
+                        e += fq_sq_err(x[i].w, c_lo, c_hi, s, QMAXF);
+                    }
                 }
                 return lanes_sum<L>(e);
             };
@@ -522,8 +564,8 @@ __global__ void __launch_bounds__(kBlock) quantize_greedy_kernel(const QuantArgs
         // The bounds are moved by cumulative fp32 additions, each rounded to the spacing of the bounds'
         // magnitude, so after k moves a bound sits up to k/2 spacings off the exact lattice.  Where the
         // step is not many spacings wide (a row whose span is tiny against its magnitude) a candidate
-        // range can close or turn inside out before the search ends, and there the median-of-three
-        // clip of the fast sequence is no longer min(max(x, lo), hi): such rows take the sequence as
+        // range can close or turn inside out before the search ends, and there the clamped quotient
+        // of the fast sequence is no longer that of min(max(x, lo), hi): such rows take the sequence as
         // F_Q is written.  Safe when range >= num_bins^2 spacings (twice the drift num_bins moves allow).
         const float mag = fmaxf(fabsf(lo), fabsf(hi));
         const bool narrow = hi != lo && (hi - lo) < a.num_bins_f * a.num_bins_f * (mag * 0x1p-23f);
@@ -547,75 +589,63 @@ __global__ void __launch_bounds__(kBlock) quantize_greedy_kernel(const QuantArgs
             if (live && j == L - 1 && a.row_max) a.row_max[k] = X_max;
         }
 
-        // ---- final codes by F_Q as written; h[i] = the four codes of x[i], first element lowest
-        uint32_t h[4 * G], h8[4 * G];
-#pragma unroll
-        for (int i = 0; i < 4 * G; ++i) {
-            const uint32_t q0 = (uint32_t)fq_code_f(x[i].x, lo, hi, scale, QMAXF);
-            const uint32_t q1 = (uint32_t)fq_code_f(x[i].y, lo, hi, scale, QMAXF);
-            const uint32_t q2 = (uint32_t)fq_code_f(x[i].z, lo, hi, scale, QMAXF);
-            const uint32_t q3 = (uint32_t)fq_code_f(x[i].w, lo, hi, scale, QMAXF);
-            h[i] = q0 | (q1 << BITS) | (q2 << (2 * BITS)) | (q3 << (3 * BITS));
-            h8[i] = q0 | (q1 << 8) | (q2 << 16) | (q3 << 24);
-        }
-        if (a.codes && live) {
-#pragma unroll
-            for (int g = 0; g < G; ++g)
-                *reinterpret_cast<uint4 *>(a.codes + k * (uint64_t)DIM + EPL * j + 16 * g) =
-                    make_uint4(h8[4 * g], h8[4 * g + 1], h8[4 * g + 2], h8[4 * g + 3]);
-        }
-
-        // ---- packed codes: this lane's bits are bytes [2 * BITS * G * j, 2 * BITS * G * (j + 1)) of the row,
+        // ---- final codes by F_Q as written, sixteen elements at a time; h[i] = four codes, first element
+        // lowest.  Packed, this lane's bits are bytes [2 * BITS * G * j, 2 * BITS * G * (j + 1)) of the row,
         // 2 * BITS bytes per group of sixteen elements
-        if (a.packed) {
-            uint8_t *dst = a.packed + k * P + 2 * BITS * G * j;
+        uint8_t *const packed = a.packed ? a.packed + k * P + 2 * BITS * G * j : nullptr;
+        uint32_t even_w0 = 0, even_w1 = 0;  // 3 bits: the 48 bits of the group before
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            uint32_t h[4], h8[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float4 v = x[4 * g + i];
+                const uint32_t q0 = (uint32_t)fq_code_f(v.x, lo, hi, scale, QMAXF);
+                const uint32_t q1 = (uint32_t)fq_code_f(v.y, lo, hi, scale, QMAXF);
+                const uint32_t q2 = (uint32_t)fq_code_f(v.z, lo, hi, scale, QMAXF);
+                const uint32_t q3 = (uint32_t)fq_code_f(v.w, lo, hi, scale, QMAXF);
+                h[i] = q0 | (q1 << BITS) | (q2 << (2 * BITS)) | (q3 << (3 * BITS));
+                h8[i] = q0 | (q1 << 8) | (q2 << 16) | (q3 << 24);
+            }
+            if (a.codes && live)
+                *reinterpret_cast<uint4 *>(a.codes + k * (uint64_t)DIM + EPL * j + 16 * g) = make_uint4(h8[0], h8[1], h8[2], h8[3]);
+            if (!packed) continue;  // uniform
+            uint8_t *dst = packed + 2 * BITS * g;
             if constexpr (BITS == 8) {
-#pragma unroll
-                for (int g = 0; g < G; ++g)
-                    if (live) *reinterpret_cast<uint4 *>(dst + 16 * g) = make_uint4(h[4 * g], h[4 * g + 1], h[4 * g + 2], h[4 * g + 3]);
+                if (live) *reinterpret_cast<uint4 *>(dst) = make_uint4(h[0], h[1], h[2], h[3]);
             } else if constexpr (BITS == 4) {
-#pragma unroll
-                for (int g = 0; g < G; ++g)
-                    if (live)
-                        *reinterpret_cast<uint2 *>(dst + 8 * g) =
-                            make_uint2(h[4 * g] | (h[4 * g + 1] << 16), h[4 * g + 2] | (h[4 * g + 3] << 16));
+                if (live) *reinterpret_cast<uint2 *>(dst) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
             } else if constexpr (BITS == 2) {
-#pragma unroll
-                for (int g = 0; g < G; ++g)
-                    if (live)
-                        *reinterpret_cast<uint32_t *>(dst + 4 * g) =
-                            h[4 * g] | (h[4 * g + 1] << 8) | (h[4 * g + 2] << 16) | (h[4 * g + 3] << 24);
+                if (live) *reinterpret_cast<uint32_t *>(dst) = h[0] | (h[1] << 8) | (h[2] << 16) | (h[3] << 24);
             } else {  // 3 bits: 48 bits per group
-                uint32_t w0[G], w1[G];
-#pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    w0[g] = h[4 * g] | (h[4 * g + 1] << 12) | (h[4 * g + 2] << 24);  // stream bits 0..31 of the group
-                    w1[g] = (h[4 * g + 2] >> 8) | (h[4 * g + 3] << 4);               // stream bits 32..47
-                }
+                const uint32_t w0 = h[0] | (h[1] << 12) | (h[2] << 24);  // stream bits 0..31 of the group
+                const uint32_t w1 = (h[2] >> 8) | (h[3] << 4);           // stream bits 32..47
                 if constexpr (G >= 2) {  // two groups make three whole words
-#pragma unroll
-                    for (int g = 0; g < G; g += 2) {
-                        uint32_t *d3 = reinterpret_cast<uint32_t *>(dst + 6 * g);
+                    if (g & 1) {
+                        uint32_t *d3 = reinterpret_cast<uint32_t *>(dst - 6);
                         if (live) {
-                            d3[0] = w0[g];
-                            d3[1] = w1[g] | (w0[g + 1] << 16);
-                            d3[2] = (w0[g + 1] >> 16) | (w1[g + 1] << 16);
+                            d3[0] = even_w0;
+                            d3[1] = even_w1 | (w0 << 16);
+                            d3[2] = (w0 >> 16) | (w1 << 16);
                         }
+                    } else {
+                        even_w0 = w0;
+                        even_w1 = w1;
                     }
                 } else if constexpr (L == 1) {  // the row is this lane's 48 bits alone
                     uint16_t *d2 = reinterpret_cast<uint16_t *>(dst);
                     if (live) {
-                        d2[0] = (uint16_t)w0[0];
-                        d2[1] = (uint16_t)(w0[0] >> 16);
-                        d2[2] = (uint16_t)w1[0];
+                        d2[0] = (uint16_t)w0;
+                        d2[1] = (uint16_t)(w0 >> 16);
+                        d2[2] = (uint16_t)w1;
                     }
                 } else {  // even lanes append their right neighbour's 48 bits
-                    const uint32_t n0 = (uint32_t)dpp_i<0xB1>((int)w0[0]);  // lane ^ 1
-                    const uint32_t n1 = (uint32_t)dpp_i<0xB1>((int)w1[0]);
+                    const uint32_t n0 = (uint32_t)dpp_i<0xB1>((int)w0);  // lane ^ 1
+                    const uint32_t n1 = (uint32_t)dpp_i<0xB1>((int)w1);
                     if (live && !(j & 1)) {
                         uint32_t *d3 = reinterpret_cast<uint32_t *>(dst);
-                        d3[0] = w0[0];
-                        d3[1] = w1[0] | (n0 << 16);
+                        d3[0] = w0;
+                        d3[1] = w1 | (n0 << 16);
                         d3[2] = (n0 >> 16) | (n1 << 16);
                     }
                 }
