@@ -402,6 +402,8 @@ __device__ __forceinline__ float lanes_min(float v) {
     if constexpr (L >= 4) v = fminf(v, dpp_f<0x4E>(v));
     if constexpr (L >= 8) v = fminf(v, dpp_f<0x141>(v));
     if constexpr (L >= 16) v = fminf(v, dpp_f<0x140>(v));
+    if constexpr (L >= 32) v = fminf(v, __shfl_xor(v, 16));
+    if constexpr (L >= 64) v = fminf(v, __shfl_xor(v, 32));
     return v;
 }
 template <int L>
@@ -410,6 +412,8 @@ __device__ __forceinline__ float lanes_max(float v) {
     if constexpr (L >= 4) v = fmaxf(v, dpp_f<0x4E>(v));
     if constexpr (L >= 8) v = fmaxf(v, dpp_f<0x141>(v));
     if constexpr (L >= 16) v = fmaxf(v, dpp_f<0x140>(v));
+    if constexpr (L >= 32) v = fmaxf(v, __shfl_xor(v, 16));
+    if constexpr (L >= 64) v = fmaxf(v, __shfl_xor(v, 32));
     return v;
 }
 template <int L>
@@ -418,6 +422,8 @@ __device__ __forceinline__ double lanes_sum(double v) {
     if constexpr (L >= 4) v += dpp_d<0x4E>(v);
     if constexpr (L >= 8) v += dpp_d<0x141>(v);
     if constexpr (L >= 16) v += dpp_d<0x140>(v);
+    if constexpr (L >= 32) v += __shfl_xor(v, 16);
+    if constexpr (L >= 64) v += __shfl_xor(v, 32);
     return v;
 }
 
@@ -438,12 +444,12 @@ struct Candidate {
         inv = scale == 0.0f ? 0.0f : fmaf(fmaf(-rest, r0, fmaf(-full, r0, 1.0f)), r0, r0);
         unbias = scale * -0x1p23f;
     }
-    // acc += (x - F_Q(x) de-quantized)^2 of eight elements.  Left to itself the compiler strings the
+    // acc += (x - F_Q(x) de-quantized)^2 of N elements (eight, or four that are left over).  Left to itself the compiler strings the
     // eight instructions of one element behind each other, each waiting for the one before; the barriers
     // keep them in stages of eight independent ones (2.99 -> 2.70 ms on the list above; stages of four or
     // sixteen 2.97).
-    __device__ __forceinline__ void add_err(double &acc, const float (&x)[8]) const {
-        constexpr int N = 8;
+    template <int N>
+    __device__ __forceinline__ void add_err(double &acc, const float (&x)[N]) const {
         float t[N];
         double d[N];
 #pragma unroll
@@ -473,13 +479,52 @@ struct Candidate {
     }
 };
 
+// Whether a wave's rows (this lane's with range [lo, hi]) have to be searched with divisions, as F_Q is
+// written.  Scales outside [2^-100, 2^100] are: their reciprocals are no normal numbers.  So are narrow
+// rows: the bounds are moved by cumulative fp32 additions, each rounded to the spacing of the bounds'
+// magnitude, so after k moves a bound sits up to k/2 spacings off the exact lattice.  Where the step is not
+// many spacings wide (a row whose span is tiny against its magnitude) a candidate range can close or turn
+// inside out before the search ends, and there the clamped quotient of the fast sequence is no longer that
+// of min(max(x, lo), hi).  Safe when range >= num_bins^2 spacings (twice the drift num_bins moves allow).
+__device__ __forceinline__ bool search_divides(float lo, float hi, float num_bins_f, float qmaxf) {
+    const float s0 = (hi - lo) * (1.0f / qmaxf);
+    const bool odd_scale = s0 != 0.0f && !(s0 >= 0x1p-100f && s0 <= 0x1p100f);
+    const float mag = fmaxf(fabsf(lo), fabsf(hi));
+    const bool narrow = hi != lo && (hi - lo) < num_bins_f * num_bins_f * (mag * 0x1p-23f);
+    // the last candidates are up to num_bins times narrower than the first
+    return __builtin_amdgcn_ballot_w64(odd_scale || narrow) != 0 || num_bins_f > 0x1p20f;
+}
+
+// The 24 code bits of a pair of units at 3 bits.
+__device__ __forceinline__ void store_pair3(uint8_t *out, uint32_t pair, uint32_t w) {
+    uint8_t *o3 = out + 3 * pair;
+    o3[0] = (uint8_t)w;
+    o3[1] = (uint8_t)(w >> 8);
+    o3[2] = (uint8_t)(w >> 16);
+}
+// Stores the 4 * BITS code bits h of unit u (elements 4u .. 4u + 3) of a packed row.  At 3 bits units come
+// in pairs (dim % 8 == 0): unit u + 1 is lane + 1's, and the lane of the even one stores both; all lanes
+// have to call it.
+template <int BITS>
+__device__ __forceinline__ void store_unit_codes(uint8_t *out, uint32_t u, uint32_t h, bool store) {
+    if constexpr (BITS == 8) {
+        if (store) *reinterpret_cast<uint32_t *>(out + 4 * u) = h;
+    } else if constexpr (BITS == 4) {
+        if (store) *reinterpret_cast<uint16_t *>(out + 2 * u) = (uint16_t)h;
+    } else if constexpr (BITS == 2) {
+        if (store) out[u] = (uint8_t)h;
+    } else {
+        const uint32_t nb = (uint32_t)dpp_i<0xB1>((int)h);  // lane ^ 1: unit u + 1
+        if (store && !(u & 1)) store_pair3(out, u >> 1, h | (nb << 12));
+    }
+}
+
 template <int L, int BITS, int G>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L == 1 && G == 4 ? 3 : G == 4 ? 4 : 5, 8))) quantize_greedy_kernel(const QuantArgs a, uint64_t n_from, uint64_t n_below) {
     constexpr int EPL = 16 * G;  // elements per lane
     constexpr int DIM = EPL * L;
     constexpr int kRowsPerPass = kWave / L;
     constexpr float QMAXF = (float)((1 << BITS) - 1);
-    constexpr float INV_QMAX = 1.0f / QMAXF;
     constexpr uint64_t P = (uint64_t)DIM * BITS / 8;  // packed bytes per row
     const uint64_t n = row_count(a);
     if (n < n_from || n >= n_below) return;  // this list length is the other launch's (uniform over the grid)
@@ -527,7 +572,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L =
                     const Candidate<BITS> c(c_lo, c_hi);
 #pragma unroll
                     for (int i = 0; i < 4 * G; i += 2)
-                        c.add_err(e, {x[i].x, x[i].y, x[i].z, x[i].w, x[i + 1].x, x[i + 1].y, x[i + 1].z, x[i + 1].w});
+                        c.template add_err<8>(e, {x[i].x, x[i].y, x[i].z, x[i].w, x[i + 1].x, x[i + 1].y, x[i + 1].z, x[i + 1].w});
                 } else {
                     const float s = (c_hi - c_lo) / QMAXF;
 #pragma unroll
@@ -559,18 +604,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L =
                 }
             }
         };
-        const float s0 = (hi - lo) * INV_QMAX;
-        const bool odd_scale = s0 != 0.0f && !(s0 >= 0x1p-100f && s0 <= 0x1p100f);
-        // The bounds are moved by cumulative fp32 additions, each rounded to the spacing of the bounds'
-        // magnitude, so after k moves a bound sits up to k/2 spacings off the exact lattice.  Where the
-        // step is not many spacings wide (a row whose span is tiny against its magnitude) a candidate
-        // range can close or turn inside out before the search ends, and there the clamped quotient
-        // of the fast sequence is no longer that of min(max(x, lo), hi): such rows take the sequence as
-        // F_Q is written.  Safe when range >= num_bins^2 spacings (twice the drift num_bins moves allow).
-        const float mag = fmaxf(fabsf(lo), fabsf(hi));
-        const bool narrow = hi != lo && (hi - lo) < a.num_bins_f * a.num_bins_f * (mag * 0x1p-23f);
-        // the last candidates are up to num_bins times narrower than the first
-        if (__builtin_amdgcn_ballot_w64(odd_scale || narrow) != 0 || a.num_bins_f > 0x1p20f)
+        if (search_divides(lo, hi, a.num_bins_f, QMAXF))
             search(std::false_type{});
         else
             search(std::true_type{});
@@ -655,111 +689,191 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L =
 }
 
 // ---------------------------------------------------------------------------------------------
-// Greedy search at any other dim (dim % 4 == 0, dim * bits % 8 == 0): one wavefront per row, lanes
-// stride over the row, which is re-read from cache for each candidate.  Output bytes are produced
-// one per lane-visit from the codes they cover, so no staging or barrier is needed.  Divides as F_Q
-// is written.
+// Greedy search at any other dim (dim % 4 == 0, dim * bits % 8 == 0): L lanes per row, lane j holds the
+// row's 16-byte units j, j + L, ... in registers, up to UMAX of them that every lane has plus the last,
+// which only some have.  How many there are is known at run time and the same for all lanes, so the units
+// are walked in pairs (eight elements, as above) behind uniform branches; an odd unit and the partial one
+// follow as fours, and a lane without a partial unit evaluates elements that equal the candidate's lower
+// bound, whose error is zero.  Candidates go through one copy of the code: the un-shrunk range first,
+// then the two of every iteration in turn.  Same bound and same arithmetic as the kernel above.  (A wave
+// per row that re-read the row from cache and divided for every element: 100 K rows of 96 at 49
+// candidates 874 us, this 117 us.)
 // ---------------------------------------------------------------------------------------------
-__device__ __forceinline__ float wave_min(float v) {
-    for (int off = 32; off > 0; off >>= 1) v = fminf(v, __shfl_xor(v, off));
-    return v;
-}
-__device__ __forceinline__ float wave_max(float v) {
-    for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
-    return v;
-}
-__device__ __forceinline__ double wave_sum(double v) {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    return v;
-}
+template <int L, int UMAX>
+struct RowUnits {
+    static_assert(UMAX % 2 == 0, "units are walked in pairs");
+    float4 x[UMAX];   // units j + L * t, t < 2 * pairs
+    float4 odd;       // unit j + L * 2 * pairs, if has_odd
+    float4 tail;      // unit j + L * n_full, if in_tail
+    const float4 *row;
+    uint32_t n4, j;
+    uint32_t pairs;
+    bool has_odd, has_tail;  // uniform
+    bool in_tail;            // this lane
 
-__device__ __forceinline__ double row_sq_err(const float *__restrict__ x, uint32_t dim, int lane,
-                                             float lo, float hi, float qmaxf) {
-    const float s = (hi - lo) / qmaxf;
-    double e = 0.0;
-    for (uint32_t t = lane; t < dim; t += kWave) e += fq_sq_err(x[t], lo, hi, s, qmaxf);
-    return wave_sum(e);
-}
-
-template <int BITS>
-__global__ void __launch_bounds__(kBlock)
-quantize_rows_generic_kernel(const float *__restrict__ table, uint64_t n_rows, uint32_t dim,
-                             const uint32_t *__restrict__ row_ids, const uint64_t *__restrict__ n_dev,
-                             uint64_t n_max, int mode, uint32_t n_iter, float num_bins_f,
-                             float *__restrict__ scale_out, float *__restrict__ bias_out,
-                             float *__restrict__ min_out, float *__restrict__ max_out,
-                             uint8_t *__restrict__ codes_out, uint8_t *__restrict__ packed_out,
-                             cnr_dev_errors *err) {
-    constexpr int QMAX = (1 << BITS) - 1;
-    constexpr float QMAXF = (float)QMAX;
-    uint64_t n = n_max;
-    if (n_dev) {
-        const uint64_t nd = *n_dev;
-        n = nd < n_max ? nd : n_max;
+    __device__ __forceinline__ void load(const float4 *row_, uint32_t n4_, uint32_t j_) {
+        row = row_;
+        n4 = n4_;
+        j = j_;
+        const uint32_t n_full = n4 / L;
+        pairs = n_full / 2;
+        has_odd = n_full & 1;
+        has_tail = n4 % L != 0;
+        in_tail = j + L * n_full < n4;
+#pragma unroll
+        for (int t = 0; t < UMAX; t += 2)
+            if ((uint32_t)t < 2 * pairs) {
+                x[t] = row[j + L * t];
+                x[t + 1] = row[j + L * (t + 1)];
+            }
+        tail = row[in_tail ? j + L * n_full : n4 - 1];  // a unit of the row in any case: the row's range may count it twice
+        odd = tail;
+        if (has_odd) odd = row[j + L * (n_full - 1)];
     }
-    const int lane = tid_x() & (kWave - 1);
-    const uint64_t n_waves = (uint64_t)grid_x() * kWavesPerBlock;
-    const uint64_t P = (uint64_t)dim * BITS / 8;
-    for (uint64_t k = (uint64_t)wg_x() * kWavesPerBlock + tid_x() / kWave; k < n; k += n_waves) {
-        const uint64_t r = row_ids ? (uint64_t)row_ids[k] : k;
-        if (r >= n_rows) {  // uniform over the wave
-            if (lane == 0) raise_flag(err, CNR_FLAG_ROW_ID);
-            continue;
+    __device__ __forceinline__ void range(float &mn, float &mx) const {
+        auto take = [&](const float4 &v) {
+            mn = fminf(mn, fminf(fminf(v.x, v.y), fminf(v.z, v.w)));
+            mx = fmaxf(mx, fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w)));
+        };
+        mn = mx = tail.x;
+        take(tail);
+        take(odd);
+#pragma unroll
+        for (int t = 0; t < UMAX; t += 2)
+            if ((uint32_t)t < 2 * pairs) {
+                take(x[t]);
+                take(x[t + 1]);
+            }
+        mn = lanes_min<L>(mn) + 0.0f;  // -0.0 -> +0.0
+        mx = lanes_max<L>(mx) + 0.0f;
+    }
+    // Squared l2 error of the row under F_Q with the range [c_lo, c_hi], in every lane.
+    template <int BITS, bool FAST>
+    __device__ __forceinline__ double sq_err(float c_lo, float c_hi) const {
+        double e = 0.0;
+        if constexpr (FAST) {
+            const Candidate<BITS> c(c_lo, c_hi);
+#pragma unroll
+            for (int t = 0; t < UMAX; t += 2)
+                if ((uint32_t)t < 2 * pairs)
+                    c.template add_err<8>(e, {x[t].x, x[t].y, x[t].z, x[t].w, x[t + 1].x, x[t + 1].y, x[t + 1].z, x[t + 1].w});
+            if (has_odd) c.template add_err<4>(e, {odd.x, odd.y, odd.z, odd.w});
+            if (has_tail)
+                c.template add_err<4>(e, {in_tail ? tail.x : c_lo, in_tail ? tail.y : c_lo, in_tail ? tail.z : c_lo, in_tail ? tail.w : c_lo});
+        } else {
+            constexpr float QMAXF = (float)((1 << BITS) - 1);
+            const float s = (c_hi - c_lo) / QMAXF;
+            for (uint32_t u = j; u < n4; u += L) {  // rare, and its code is long: a loop that re-reads the row
+                const float4 v = row[u];
+                e += fq_sq_err(v.x, c_lo, c_hi, s, QMAXF);
+                e += fq_sq_err(v.y, c_lo, c_hi, s, QMAXF);
+                e += fq_sq_err(v.z, c_lo, c_hi, s, QMAXF);
+                e += fq_sq_err(v.w, c_lo, c_hi, s, QMAXF);
+            }
         }
-        const float *__restrict__ x = table + r * (uint64_t)dim;
-        float mn = x[0], mx = x[0];
-        for (uint32_t t = lane; t < dim; t += kWave) {
-            mn = fminf(mn, x[t]);
-            mx = fmaxf(mx, x[t]);
-        }
-        const float X_min = wave_min(mn) + 0.0f, X_max = wave_max(mx) + 0.0f;
-        float lo = X_min, hi = X_max;
-        if (mode == kModeSymmetric) {
-            const float a = fmaxf(fabsf(X_min), fabsf(X_max));
-            lo = -a + 0.0f;
-            hi = a;
-        } else if (mode == kModeGreedy) {
-            float cur_lo = lo, cur_hi = hi;
-            const float step = (hi - lo) / num_bins_f;
-            double best = row_sq_err(x, dim, lane, lo, hi, QMAXF);
-            for (uint32_t it = 0; it < n_iter; ++it) {
-                const float c_lo = cur_lo + step, c_hi = cur_hi - step;
-                const double e_lo = row_sq_err(x, dim, lane, c_lo, cur_hi, QMAXF);
-                const double e_hi = row_sq_err(x, dim, lane, cur_lo, c_hi, QMAXF);
-                const bool move_lo = e_lo < e_hi;
-                if (move_lo) cur_lo = c_lo; else cur_hi = c_hi;
-                const double e = move_lo ? e_lo : e_hi;
-                if (e < best) {
-                    best = e;
+        return lanes_sum<L>(e);
+    }
+    // The search (header: cnr_greedy_params): [lo, hi] comes in as the row's range and leaves as the chosen one.
+    template <int BITS, bool FAST>
+    __device__ __forceinline__ void search(uint32_t n_iter, float num_bins_f, float &lo, float &hi) const {
+        float cur_lo = lo, cur_hi = hi;
+        const float step = (hi - lo) / num_bins_f;
+        double best = 0.0, e_lo = 0.0;
+        for (uint32_t c = 0; c <= 2 * n_iter; ++c) {
+            const bool first = c == 0, raise = c & 1;  // uniform
+            const float c_lo = raise ? cur_lo + step : cur_lo;
+            const float c_hi = first || raise ? cur_hi : cur_hi - step;
+            const double e = sq_err<BITS, FAST>(c_lo, c_hi);
+            if (first) {
+                best = e;
+            } else if (raise) {
+                e_lo = e;
+            } else {
+                const bool move_lo = e_lo < e;
+                cur_lo = move_lo ? cur_lo + step : cur_lo;
+                cur_hi = move_lo ? cur_hi : c_hi;
+                const double better = move_lo ? e_lo : e;
+                if (better < best) {
+                    best = better;
                     lo = cur_lo;
                     hi = cur_hi;
                 }
             }
         }
-        const float s = (hi - lo) / QMAXF;
-        if (lane == 0) {
-            scale_out[k] = s;
-            bias_out[k] = lo;
-            if (min_out) min_out[k] = X_min;
-            if (max_out) max_out[k] = X_max;
-        }
-        if (codes_out)
-            for (uint32_t t = lane; t < dim; t += kWave)
-                codes_out[k * (uint64_t)dim + t] = (uint8_t)fq_code_f(x[t], lo, hi, s, QMAXF);
-        if (packed_out) {
-            uint8_t *out = packed_out + k * P;
-            for (uint64_t b = lane; b < P; b += kWave) {
-                const uint32_t first = (uint32_t)((8 * b) / BITS);
-                const uint32_t last = (uint32_t)((8 * b + 7) / BITS);
-                uint32_t byte = 0;
-                for (uint32_t e = first; e <= last; ++e) {
-                    const uint32_t code = (uint32_t)fq_code_f(x[e], lo, hi, s, QMAXF);
-                    const int shift = (int)(e * BITS) - (int)(8 * b);  // stream position of code bit 0
-                    byte |= shift >= 0 ? (code << shift) : (code >> -shift);
-                }
-                out[b] = (uint8_t)byte;
+    }
+};
+
+template <int L, int UMAX, int BITS>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(UMAX > 8 ? 3 : 4, 8)))
+quantize_greedy_units_kernel(const QuantArgs a, uint64_t n_from, uint64_t n_below) {
+    constexpr int kRowsPerPass = kWave / L;
+    constexpr float QMAXF = (float)((1 << BITS) - 1);
+    const uint64_t n = row_count(a);
+    if (n < n_from || n >= n_below) return;  // this list length is the other launch's (uniform over the grid)
+    const uint32_t dim = a.dim, n4 = dim / 4;
+    const uint64_t P = (uint64_t)dim * BITS / 8;
+    const int lane = tid_x() & (kWave - 1);
+    const uint32_t j = lane % L;
+    const uint32_t n_waves = a.n_waves;
+    for (uint64_t pass = wave_in_grid(); pass * kRowsPerPass < n; pass += n_waves) {
+        const uint64_t k = pass * kRowsPerPass + lane / L;
+        uint64_t rid = 0;
+        bool live = k < n;
+        if (live) {
+            rid = a.row_ids ? (uint64_t)a.row_ids[k] : k;
+            if (rid >= a.n_rows) {
+                if (j == 0) raise_flag(a.err, CNR_FLAG_ROW_ID);
+                live = false;
+                rid = 0;
             }
         }
+        RowUnits<L, UMAX> row;
+        row.load(reinterpret_cast<const float4 *>(a.table + rid * (uint64_t)dim), n4, j);
+        float X_min, X_max;
+        row.range(X_min, X_max);
+        float lo = X_min, hi = X_max;
+        if (search_divides(lo, hi, a.num_bins_f, QMAXF))
+            row.template search<BITS, false>(a.n_iter, a.num_bins_f, lo, hi);
+        else
+            row.template search<BITS, true>(a.n_iter, a.num_bins_f, lo, hi);
+
+        const float scale = (hi - lo) / QMAXF;
+        {
+            // lane j of the row writes parameter j, or with fewer than four lanes j, j + L, ...
+#pragma unroll
+            for (uint32_t p = j; p < 4; p += L) {
+                float *dst = p == 0 ? a.scale : p == 1 ? a.bias : p == 2 ? a.row_min : a.row_max;
+                const float v = p == 0 ? scale : p == 1 ? lo : p == 2 ? X_min : X_max;
+                if (dst && live) dst[k] = v;
+            }
+        }
+        // ---- final codes by F_Q as written, unit by unit; all lanes run it (3 bits: units u and u + 1, of
+        // neighbouring lanes or, where a lane has the whole row, behind each other, make three bytes)
+        uint32_t before = 0;
+        auto emit = [&](const float4 &v, uint32_t u, bool mine) {
+            const uint32_t q0 = (uint32_t)fq_code_f(v.x, lo, hi, scale, QMAXF);
+            const uint32_t q1 = (uint32_t)fq_code_f(v.y, lo, hi, scale, QMAXF);
+            const uint32_t q2 = (uint32_t)fq_code_f(v.z, lo, hi, scale, QMAXF);
+            const uint32_t q3 = (uint32_t)fq_code_f(v.w, lo, hi, scale, QMAXF);
+            const uint32_t h = q0 | (q1 << BITS) | (q2 << (2 * BITS)) | (q3 << (3 * BITS));
+            const bool store = mine && live;
+            if (a.codes && store)
+                *reinterpret_cast<uint32_t *>(a.codes + k * (uint64_t)dim + 4 * u) = q0 | (q1 << 8) | (q2 << 16) | (q3 << 24);
+            if (!a.packed) return;
+            uint8_t *const out = a.packed + k * P;
+            if constexpr (L == 1 && BITS == 3) {  // dim % 8 == 0: an even number of units
+                if (store && (u & 1)) store_pair3(out, u >> 1, before | (h << 12));
+                before = h;
+            } else {
+                store_unit_codes<BITS>(out, u, h, store);
+            }
+        };
+        const uint32_t n_full = n4 / L;
+#pragma unroll
+        for (int t = 0; t < UMAX; ++t)
+            if ((uint32_t)t < 2 * row.pairs) emit(row.x[t], j + L * t, true);
+        if (row.has_odd) emit(row.odd, j + L * (n_full - 1), true);
+        if (row.has_tail) emit(row.tail, j + L * n_full, row.in_tail);
     }
 }
 
@@ -867,25 +981,7 @@ __global__ void __launch_bounds__(kBlock) quantize_strided_kernel(const QuantArg
             if (a.codes && store)
                 *reinterpret_cast<uint32_t *>(a.codes + k * (uint64_t)dim + 4 * u) =
                     (((((b3 << 8) + b2) << 8) + b1) << 8) + b0 - MERGED_BIAS8;
-            if (a.packed) {
-                uint8_t *out = a.packed + k * P;
-                if constexpr (BITS == 8) {
-                    if (store) *reinterpret_cast<uint32_t *>(out + 4 * u) = h;
-                } else if constexpr (BITS == 4) {
-                    if (store) *reinterpret_cast<uint16_t *>(out + 2 * u) = (uint16_t)h;
-                } else if constexpr (BITS == 2) {
-                    if (store) out[u] = (uint8_t)h;
-                } else {  // 3 bits: units come in pairs (dim % 8 == 0); the even one stores both
-                    const uint32_t nb = (uint32_t)dpp_i<0xB1>((int)h);  // lane ^ 1: unit u + 1
-                    if (store && !(u & 1)) {
-                        const uint32_t w = h | (nb << 12);
-                        uint8_t *o3 = out + 3 * (u >> 1);
-                        o3[0] = (uint8_t)w;
-                        o3[1] = (uint8_t)(w >> 8);
-                        o3[2] = (uint8_t)(w >> 16);
-                    }
-                }
-            }
+            if (a.packed) store_unit_codes<BITS>(a.packed + k * P, u, h, store);
         }
     }
 }
@@ -974,6 +1070,41 @@ void launch_greedy_by_length(cnr_ctx *ctx, QuantArgs &a, hipStream_t s) {
     if (may_be_wide) launch_greedy<L_WIDE, BITS, G_WIDE>(ctx, a, s, may_be_narrow ? wide_rows : 0, ~0ull);
 }
 
+template <int L, int UMAX, int BITS>
+void launch_greedy_units_shape(QuantArgs &a, hipStream_t s, uint64_t n_from, uint64_t n_below) {
+    const uint64_t most = a.n_max < n_below ? a.n_max : n_below;
+    const unsigned grid = cnr_row_grid(most, (uint64_t)(kWave / L) * kWavesPerBlock);
+    a.n_waves = grid * kWavesPerBlock;
+    hipLaunchKernelGGL((quantize_greedy_units_kernel<L, UMAX, BITS>), dim3(grid), dim3(kBlock), 0, s, a, n_from, n_below);
+}
+// Other row lengths: long lists give a row as few lanes as hold it, short ones more (less time per row).
+// The line lies where the wide form's waves fill the chip: 768 waves of short rows, or, since a lane with
+// many units works longer on its row, 128 waves for every unit of a lane (measured break-evens: rows of 48
+// at 12 K rows, of 96 at 12 K, of 200 at 20 K, of 384 at 3.4 K, of 1000 at 10 K).
+template <int BITS>
+void launch_greedy_units(QuantArgs &a, hipStream_t s) {
+    const uint32_t n4 = a.dim / 4;
+    const uint32_t lanes = n4 <= 8 ? 1 : n4 <= 17 ? 2 : n4 < 68 ? 4 : n4 <= 271 ? 16 : 64;
+    const uint64_t fill = 49152u / lanes, busy = 8192ull * n4 / (lanes * lanes);
+    const uint64_t wide_rows = fill > busy ? fill : busy;
+    const bool may_be_wide = lanes == 64 || a.n_max >= wide_rows;
+    const bool may_be_narrow = lanes != 64 && (!may_be_wide || a.n_dev != nullptr);
+    const uint64_t below = may_be_wide ? wide_rows : ~0ull, from = may_be_narrow ? wide_rows : 0;
+    if (may_be_narrow) {
+        if (n4 <= 17) launch_greedy_units_shape<4, 8, BITS>(a, s, 0, below);
+        else if (n4 < 80) launch_greedy_units_shape<16, 4, BITS>(a, s, 0, below);
+        else launch_greedy_units_shape<64, 4, BITS>(a, s, 0, below);
+    }
+    if (may_be_wide) {
+        if (lanes == 1) launch_greedy_units_shape<1, 8, BITS>(a, s, from, ~0ull);
+        else if (lanes == 2) launch_greedy_units_shape<2, 8, BITS>(a, s, from, ~0ull);
+        else if (n4 < 36) launch_greedy_units_shape<4, 8, BITS>(a, s, from, ~0ull);
+        else if (lanes == 4) launch_greedy_units_shape<4, 16, BITS>(a, s, from, ~0ull);
+        else if (lanes == 16) launch_greedy_units_shape<16, 16, BITS>(a, s, from, ~0ull);
+        else launch_greedy_units_shape<64, 16, BITS>(a, s, from, ~0ull);
+    }
+}
+
 template <int LPR, int BITS>
 void launch_strided(cnr_ctx *ctx, QuantArgs &a, hipStream_t s) {
     const unsigned grid = cnr_grid(ctx, a.n_max, (uint64_t)(kWave / LPR) * kWavesPerBlock,
@@ -992,13 +1123,7 @@ void launch_bits(cnr_ctx *ctx, QuantArgs &a, hipStream_t s) {
     if (greedy && a.dim == 64) return launch_greedy_by_length<4, 1, 4, BITS>(ctx, a, s);
     if (greedy && a.dim == 128) return launch_greedy_by_length<8, 2, 4, BITS>(ctx, a, s);
     if (greedy && a.dim == 256) return launch_greedy_by_length<16, 4, 4, BITS>(ctx, a, s);
-    if (greedy) {  // other row lengths, greedy: one wave per row
-        const unsigned grid = cnr_grid(ctx, a.n_max, kWavesPerBlock, 8);
-        hipLaunchKernelGGL((quantize_rows_generic_kernel<BITS>), dim3(grid), dim3(kBlock), 0, s, a.table,
-                           a.n_rows, a.dim, a.row_ids, a.n_dev, a.n_max, a.mode, a.n_iter, a.num_bins_f,
-                           a.scale, a.bias, a.row_min, a.row_max, a.codes, a.packed, a.err);
-        return;
-    }
+    if (greedy) return launch_greedy_units<BITS>(a, s);
     const uint32_t n4 = a.dim / 4;
     if (n4 <= 4) return launch_strided<4, BITS>(ctx, a, s);
     if (n4 <= 8) return launch_strided<8, BITS>(ctx, a, s);

@@ -5,8 +5,10 @@ import numpy as np
 import pytest
 import torch
 
+import oracle as O
 import paper_2010_08679_amd as P
 from paper_2010_08679_amd import synth
+from util_parity import GpuTable, compare_quantized, gpu_encode_all_outputs
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -106,3 +108,77 @@ def test_error_metric_skips_ids_outside_the_table(ctx, n):
     assert torch.allclose(err, want, rtol=1e-14, atol=0)
     assert float(mean) == pytest.approx(float(want.mean()), rel=1e-13)
     _poll(ctx, P.CNR_FLAG_ROW_ID)
+
+
+# ---- greedy search at row lengths that are no power of two: lanes per row, units per lane, list length --
+
+def _special_rows(dim, seed):
+    """Rows a few float spacings wide, constant, huge and tiny rows: waves that hold one search by division."""
+    rng = np.random.default_rng(seed)
+    rows = [np.full((2, dim), 0.25, dtype=np.float32), np.float32(rng.normal(0, 1e30, size=(2, dim))),
+            np.float32(rng.normal(0, 1e-36, size=(2, dim)))]
+    for base in (np.float32(1.0), np.float32(-7.5)):
+        u = np.spacing(np.abs(base))
+        for span in (1, 7, 3000):
+            x = (base + u * rng.integers(0, span + 1, size=(2, dim)).astype(np.float32)).astype(np.float32)
+            x[:, 0], x[:, 1] = base, base + u * span
+            rows.append(x)
+    return np.concatenate(rows)
+
+
+@pytest.mark.parametrize("dim,bits,wide", [
+    (4, 8, 49_152), (8, 3, 49_152), (24, 3, 49_152), (28, 4, 49_152),               # a lane per row / four
+    (36, 2, 24_576), (40, 3, 24_576), (48, 8, 24_576), (68, 4, 34_816),             # two lanes / four
+    (72, 3, 12_288), (96, 3, 12_288), (100, 4, 12_800), (140, 2, 17_920),           # four / sixteen, eight units at most
+    (144, 3, 18_432), (268, 2, 34_304),                                             # four / sixteen, sixteen units
+    (272, 3, 3_072), (316, 4, 3_072), (320, 8, 3_072), (1084, 2, 8_672),            # sixteen / sixteen or sixty-four
+    (1088, 3, 1_000), (2044, 4, 500), (4096, 2, 300),                               # sixty-four
+])
+def test_greedy_routes_of_other_row_lengths(ctx, dim, bits, wide):
+    print("case greedy units dim=%d bits=%d" % (dim, bits), flush=True)
+    n_rows = wide + wide // 8 + 77
+    table = synth.table_outlier_mix(n_rows, dim, 0.02, dim + bits, DEV)
+    rng = np.random.default_rng(dim)
+    special = _special_rows(dim, dim + 1)
+    where = np.sort(rng.choice(n_rows, size=special.shape[0], replace=False))
+    table[torch.from_numpy(where).to(DEV)] = torch.from_numpy(special).to(DEV)
+    gt = GpuTable(ctx, table)
+    # A search ends in exact ties where a step is a whole number of code steps, qmax / (num_bins - k) an
+    # integer after k iterations: moving the range by a step then moves the grid onto itself, and the order
+    # of the fp64 sum decides (1 row in 1200 of 272 elements at 12 bins, 3 bits).  The searches here stop
+    # before that: num_bins - k stays off the divisors of qmax.
+    params = {2: (12, 0.6), 3: (12, 0.33), 4: (20, 0.2), 8: (12, 0.5)}[bits]
+    for n in (wide + 5, wide - 3, 17):  # on the device alone: the buffers' capacity allows the long form
+        ids = np.unique(np.concatenate([where[:min(n, len(where))], rng.choice(n_rows, size=n, replace=False)]))
+        gt.ck.clear()
+        gt.ck.mark(torch.from_numpy(ids).to(DEV))
+        gt.ck.compact()
+        got = gpu_encode_all_outputs(gt, bits, mode=P.CNR_RANGE_GREEDY, greedy=params)
+        assert got["n"] == ids.size
+        rows = gt.host[ids]
+        assert np.array_equal(got["row_min"], rows.min(axis=1)) and np.array_equal(got["row_max"], rows.max(axis=1))
+        assert np.array_equal(got["packed"], O.pack(got["codes"], bits))
+        pos = np.unique(np.concatenate([np.arange(min(40, ids.size)), np.arange(max(0, ids.size - 40), ids.size),
+                                        np.flatnonzero(np.isin(ids, where)), rng.integers(0, ids.size, size=1500)]))
+        ora = O.quantize_rows(rows[pos], None, bits, mode=O.RANGE_GREEDY, num_bins=params[0], ratio=params[1], n_threads=8)
+        compare_quantized(rows[pos], {k: got[k][pos] for k in ("scale", "bias", "row_min", "row_max", "codes")}, ora, bits,
+                          greedy=True, what="greedy units b%d d%d n%d" % (bits, dim, n))
+    _poll(ctx)
+
+
+@pytest.mark.parametrize("dim,bits", [(96, 3), (24, 4), (48, 2), (300, 8)])
+def test_greedy_skips_ids_outside_the_table(ctx, dim, bits):
+    n_rows, n = 500, 133
+    table = synth.table_outlier_mix(n_rows, dim, 0.02, 9, DEV)
+    ids = _ids(n_rows, n, 3)
+    bad = [0, 1, 63, n - 1]
+    for k in bad:
+        ids[k] = n_rows + k
+    prb = P.cnr_packed_row_bytes(dim, bits)
+    out = [torch.full((n, w), 0x5A, dtype=torch.uint8, device=DEV) for w in (4, 4, prb)]
+    P.cnr_quantize_rows(ctx, table, n_rows, dim, ids, None, n, bits, P.CNR_RANGE_GREEDY, (10, 1.0), out[0].view(torch.float32).reshape(-1),
+                        out[1].view(torch.float32).reshape(-1), packed=out[2].reshape(-1))
+    _poll(ctx, P.CNR_FLAG_ROW_ID)
+    keep = [k for k in range(n) if k not in bad]
+    for o in out:
+        assert bool((o[bad] == 0x5A).all()) and bool((o[keep] != 0x5A).any(1).all())
