@@ -878,73 +878,182 @@ quantize_greedy_units_kernel(const QuantArgs a, uint64_t n_from, uint64_t n_belo
 }
 
 // ---------------------------------------------------------------------------------------------
-// Other row lengths, min/max and symmetric range: LPR lanes per row (a power of two, at least the
-// row's number of 16-byte units up to 64), 64 / LPR rows per wave and pass; lane j takes the
-// units j, j + LPR, ... of its row.  The row is read twice, for its range and to quantize (the second
-// time from cache), so nothing depends on its length; a unit's four codes are 4 * BITS bits, stored
-// as one, two or four bytes, and at 3 bits even lanes store three bytes for themselves and their
-// right neighbour.  Same arithmetic as the tile kernel.
+// Other row lengths, min/max and symmetric range.  Same arithmetic as the tile kernel; bound by the
+// memory traffic.
+//
+// Up to 512 elements (quantize_units_kernel): LPR lanes per row, U 16-byte units of it per lane (unit j +
+// LPR * t, so that a load instruction reads 16 * LPR contiguous bytes per row), read once and held in
+// registers: SB steps of 64 / LPR rows are on their way at a time, and the other waves of the compute unit
+// hide their latency.  The row's range takes log2(LPR) cross-lane steps.  A unit's 4 * BITS code bits are
+// too few to store one by one, so a wave collects the codes of ROWS rows (a multiple of sixteen, hence
+// whole 16-byte pieces at any row length and width), which are one contiguous run of the output, in its
+// own piece of LDS and writes them out 16 bytes per lane.  750 K rows of 96, 4 bits: read twice and
+// stored by twos of bytes 130 us, this 66 us (5.1 TB/s); rows
+// of 8 to 512 elements 1.3 to 2.5 times as fast.
+//
+// Longer rows (quantize_strided_kernel): a wave per row, which reads it twice, for its range and to
+// quantize, the second time from cache; its stores are runs of at least 16 bytes.
 // ---------------------------------------------------------------------------------------------
-template <int LPR>
-__device__ __forceinline__ float lpr_min(float v) {
-    v = fminf(v, dpp_f<0xB1>(v));
-    v = fminf(v, dpp_f<0x4E>(v));
-    if constexpr (LPR >= 8) v = fminf(v, dpp_f<0x141>(v));
-    if constexpr (LPR >= 16) v = fminf(v, dpp_f<0x140>(v));
-    if constexpr (LPR >= 32) v = fminf(v, __shfl_xor(v, 16));
-    if constexpr (LPR >= 64) v = fminf(v, __shfl_xor(v, 32));
-    return v;
+// Code of one element, biased by the pattern of 1.5 * 2^23 (see the tile kernel).
+template <int BITS>
+__device__ __forceinline__ uint32_t biased_code(float x, float lo, float f, float fscale, float inv) {
+    const float d0 = (x - lo) * f;
+    float t = d0 * inv;
+    if constexpr (BITS == 8) t = fmaf(fmaf(-t, fscale, d0), inv, t);
+    return __float_as_uint(t + 12582912.0f);
 }
-template <int LPR>
-__device__ __forceinline__ float lpr_max(float v) {
-    v = fmaxf(v, dpp_f<0xB1>(v));
-    v = fmaxf(v, dpp_f<0x4E>(v));
-    if constexpr (LPR >= 8) v = fmaxf(v, dpp_f<0x141>(v));
-    if constexpr (LPR >= 16) v = fmaxf(v, dpp_f<0x140>(v));
-    if constexpr (LPR >= 32) v = fmaxf(v, __shfl_xor(v, 16));
-    if constexpr (LPR >= 64) v = fmaxf(v, __shfl_xor(v, 32));
-    return v;
-}
-
-template <int LPR, int BITS>
-__global__ void __launch_bounds__(kBlock) quantize_strided_kernel(const QuantArgs a) {
-    constexpr int kRowsPerPass = kWave / LPR;
-    constexpr float QMAXF = (float)((1 << BITS) - 1);
-    constexpr float MAGIC = 12582912.0f;          // 1.5 * 2^23 (see the tile kernel)
+// The 4 * BITS code bits of a unit, and its codes one per byte.
+template <int BITS>
+__device__ __forceinline__ uint32_t unit_codes(const f32x4 &v, float lo, float f, float fscale, float inv, uint32_t &bytes) {
     constexpr uint32_t MAGIC_BITS = 0x4B400000u;
     constexpr uint32_t MERGED_BIAS = MAGIC_BITS * (1u + (1u << BITS) + (1u << (2 * BITS)) + (1u << (3 * BITS)));
     constexpr uint32_t MERGED_BIAS8 = MAGIC_BITS * (1u + (1u << 8) + (1u << 16) + (1u << 24));
+    const uint32_t b0 = biased_code<BITS>(v.x, lo, f, fscale, inv), b1 = biased_code<BITS>(v.y, lo, f, fscale, inv);
+    const uint32_t b2 = biased_code<BITS>(v.z, lo, f, fscale, inv), b3 = biased_code<BITS>(v.w, lo, f, fscale, inv);
+    bytes = (((((b3 << 8) + b2) << 8) + b1) << 8) + b0 - MERGED_BIAS8;
+    uint32_t m = (b3 << BITS) + b2;
+    m = (m << BITS) + b1;
+    return (m << BITS) + b0 - MERGED_BIAS;
+}
+
+template <int LPR, int U, int SB, int BITS>
+struct UnitsShape {
+    static constexpr int RPS = kWave / LPR;                                  // rows per step
+    static constexpr int STEPS = LPR == 4 ? SB : LPR == 8 ? (SB > 2 ? SB : 2) : 4;
+    static constexpr int ROWS = RPS * STEPS;                                 // rows per wave and pass
+    static_assert(ROWS % 16 == 0 && STEPS % SB == 0, "whole 16-byte pieces");
+    static constexpr int STAGE = ROWS * LPR * U * BITS / 2;                  // LDS per wave
+};
+template <int LPR, int U, int SB, int BITS>
+__global__ void __launch_bounds__(kBlock) quantize_units_kernel(const QuantArgs a) {
+    using S = UnitsShape<LPR, U, SB, BITS>;
+    constexpr int RPS = S::RPS, ROWS = S::ROWS;
+    constexpr float QMAXF = (float)((1 << BITS) - 1);
+    __shared__ __align__(16) uint8_t stages[kWavesPerBlock * S::STAGE];
+    uint8_t *const stage = stages + (tid_x() / kWave) * S::STAGE;
+    const uint64_t n = row_count(a);
+    const uint32_t dim = a.dim, n4 = dim / 4;      // 16-byte units per row, at most LPR * U
+    const uint32_t P = dim * BITS / 8;             // packed bytes per row
+    const int lane = tid_x() & (kWave - 1);
+    const uint32_t j = lane % LPR, rho = lane / LPR;
+    const uint32_t last_row = (uint32_t)a.n_rows - 1u;
+    const uint32_t n_waves = a.n_waves;
+    for (uint64_t pass = wave_in_grid(); pass * ROWS < n; pass += n_waves) {
+        const uint64_t base = pass * ROWS;
+        const uint32_t left = n - base < (uint64_t)ROWS ? (uint32_t)(n - base) : (uint32_t)ROWS;  // uniform
+        bool all_in_table = true;
+#pragma unroll
+        for (int s0 = 0; s0 < S::STEPS; s0 += SB) {
+            uint32_t rid[SB];
+            f32x4 x[SB][U];
+#pragma unroll
+            for (int s = 0; s < SB; ++s) {
+                const uint32_t r = (s0 + s) * RPS + rho;
+                const uint64_t k = base + (r < left ? r : left - 1);  // rows past the end repeat the last one; nothing of theirs is stored
+                rid[s] = a.row_ids ? a.row_ids[k] : k > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)k;
+            }
+#pragma unroll
+            for (int s = 0; s < SB; ++s) {
+                const float *row = a.table + (uint64_t)(rid[s] < last_row ? rid[s] : last_row) * dim;
+#pragma unroll
+                for (int t = 0; t < U; ++t) {
+                    const uint32_t u = j + LPR * t;
+                    x[s][t] = load_stream<f32x4>(row + 4 * (u < n4 ? u : n4 - 1));  // past the row's end: its last unit again
+                }
+            }
+#pragma unroll
+            for (int s = 0; s < SB; ++s) {
+                const uint32_t r = (s0 + s) * RPS + rho;
+                const uint64_t k = base + r;
+                const bool in_table = rid[s] <= last_row, live = r < left && in_table;
+                if (r < left && !in_table) {
+                    all_in_table = false;
+                    if (j == 0) raise_flag(a.err, CNR_FLAG_ROW_ID);
+                }
+                // ---- row minimum / maximum, parameters
+                float mn = x[s][0].x, mx = x[s][0].x;
+#pragma unroll
+                for (int t = 0; t < U; ++t) {
+                    const f32x4 v = x[s][t];
+                    mn = fminf(fminf(mn, v.x), fminf(v.y, fminf(v.z, v.w)));
+                    mx = fmaxf(fmaxf(mx, v.x), fmaxf(v.y, fmaxf(v.z, v.w)));
+                }
+                const float X_min = lanes_min<LPR>(mn) + 0.0f;  // -0.0 -> +0.0
+                const float X_max = lanes_max<LPR>(mx) + 0.0f;
+                float lo = X_min, hi = X_max;
+                if (a.mode == kModeSymmetric) {
+                    const float m = fmaxf(fabsf(X_min), fabsf(X_max));
+                    lo = -m + 0.0f;
+                    hi = m;
+                }
+                const float scale = (hi - lo) / QMAXF;
+                {
+                    float *dst = j == 0 ? a.scale : j == 1 ? a.bias : j == 2 ? a.row_min : a.row_max;
+                    const float v = j == 0 ? scale : j == 1 ? lo : j == 2 ? X_min : X_max;
+                    if (j < 4 && dst && live) store_stream<float>(dst + k, v);
+                }
+                const float f = scale < 0x1p-100f ? 0x1p120f : scale > 0x1p100f ? 0x1p-120f : 1.0f;
+                const float fscale = scale * f;
+                const float inv = scale == 0.0f ? 0.0f : 1.0f / fscale;  // scale 0: every code 0
+                // ---- codes, into the wave's stage
+#pragma unroll
+                for (int t = 0; t < U; ++t) {
+                    const uint32_t u = j + LPR * t;
+                    uint32_t bytes;
+                    const uint32_t h = unit_codes<BITS>(x[s][t], lo, f, fscale, inv, bytes);
+                    if (a.codes && u < n4 && live) *reinterpret_cast<uint32_t *>(a.codes + k * (uint64_t)dim + 4 * u) = bytes;
+                    if (a.packed) store_unit_codes<BITS>(stage + r * P, u, h, u < n4);
+                }
+            }
+        }
+        if (!a.packed) continue;
+        // ---- the packed rows of the pass: one run of left * P bytes
+        __builtin_amdgcn_wave_barrier();  // LDS operations of one wave complete in order
+        uint8_t *const out = a.packed + base * P;
+        const uint32_t bytes = left * P;
+        if (__builtin_amdgcn_ballot_w64(!all_in_table) == 0) {
+            for (uint32_t off = 16u * lane; off + 16u <= bytes; off += 16u * kWave)
+                store_stream<u32x4>(out + off, *reinterpret_cast<const u32x4 *>(stage + off));
+            const uint32_t rest = bytes & 15u;
+            if ((uint32_t)lane < rest) out[bytes - rest + lane] = stage[bytes - rest + lane];
+        } else {  // rows outside the table leave their place in the output as it is
+            for (uint32_t r = 0; r < left; ++r) {
+                const uint64_t k = base + r;
+                const uint64_t id = a.row_ids ? (uint64_t)a.row_ids[k] : k;
+                if (id >= a.n_rows) continue;
+                for (uint32_t b = lane; b < P; b += kWave) out[r * P + b] = stage[r * P + b];
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+template <int BITS>
+__global__ void __launch_bounds__(kBlock) quantize_strided_kernel(const QuantArgs a) {
+    constexpr float QMAXF = (float)((1 << BITS) - 1);
     const uint64_t n = row_count(a);
     const uint32_t dim = a.dim, n4 = dim / 4;      // 16-byte units per row
     const uint64_t P = (uint64_t)dim * BITS / 8;   // packed bytes per row
-    const int lane = tid_x() & (kWave - 1);
-    const uint32_t j = lane % LPR;
+    const uint32_t j = tid_x() & (kWave - 1);
     const uint32_t last_row = (uint32_t)a.n_rows - 1u;
     const uint32_t n_waves = a.n_waves;
-    for (uint64_t pass = wave_in_grid(); pass * kRowsPerPass < n; pass += n_waves) {
-        const uint64_t k = pass * kRowsPerPass + lane / LPR;
-        const uint64_t kc = k < n ? k : n - 1;     // rows past the end repeat the last one; nothing of theirs is stored
-        uint32_t rid;
-        if (a.row_ids)
-            rid = a.row_ids[kc];
-        else
-            rid = kc > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)kc;
-        const bool in_table = rid <= last_row;
-        const bool live = k < n && in_table;
-        if (k < n && !in_table && j == 0) raise_flag(a.err, CNR_FLAG_ROW_ID);
-        const float4 *row = reinterpret_cast<const float4 *>(a.table + (uint64_t)(in_table ? rid : last_row) * dim);
+    for (uint64_t k = wave_in_grid(); k < n; k += n_waves) {
+        const uint32_t rid = a.row_ids ? a.row_ids[k] : k > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)k;
+        const bool live = rid <= last_row;
+        if (!live && j == 0) raise_flag(a.err, CNR_FLAG_ROW_ID);
+        const f32x4 *row = reinterpret_cast<const f32x4 *>(a.table + (uint64_t)(live ? rid : last_row) * dim);
 
         // ---- row minimum / maximum (every lane starts from the row's first unit, so idle lanes are neutral)
-        const float4 first = row[0];
+        const f32x4 first = row[0];
         float mn = fminf(fminf(first.x, first.y), fminf(first.z, first.w));
         float mx = fmaxf(fmaxf(first.x, first.y), fmaxf(first.z, first.w));
-        for (uint32_t u = j; u < n4; u += LPR) {
-            const float4 v = row[u];
+        for (uint32_t u = j; u < n4; u += kWave) {
+            const f32x4 v = row[u];
             mn = fminf(fminf(mn, v.x), fminf(v.y, fminf(v.z, v.w)));
             mx = fmaxf(fmaxf(mx, v.x), fmaxf(v.y, fmaxf(v.z, v.w)));
         }
-        const float X_min = lpr_min<LPR>(mn) + 0.0f;  // -0.0 -> +0.0
-        const float X_max = lpr_max<LPR>(mx) + 0.0f;
+        const float X_min = lanes_min<kWave>(mn) + 0.0f;  // -0.0 -> +0.0
+        const float X_max = lanes_max<kWave>(mx) + 0.0f;
         float lo = X_min, hi = X_max;
         if (a.mode == kModeSymmetric) {
             const float m = fmaxf(fabsf(X_min), fabsf(X_max));
@@ -960,27 +1069,16 @@ __global__ void __launch_bounds__(kBlock) quantize_strided_kernel(const QuantArg
         const float f = scale < 0x1p-100f ? 0x1p120f : scale > 0x1p100f ? 0x1p-120f : 1.0f;
         const float fscale = scale * f;
         const float inv = scale == 0.0f ? 0.0f : 1.0f / fscale;  // scale 0: every code 0
-        auto biased = [&](float xv) -> uint32_t {  // MAGIC_BITS + round((x - lo) / scale)
-            const float d0 = (xv - lo) * f;
-            float t = d0 * inv;
-            if constexpr (BITS == 8) t = fmaf(fmaf(-t, fscale, d0), inv, t);
-            return __float_as_uint(t + MAGIC);
-        };
 
         // ---- quantize unit by unit; all lanes take every trip so that the 3-bit exchange has partners
-        const uint32_t trips = (n4 + LPR - 1) / LPR;
+        const uint32_t trips = (n4 + kWave - 1) / kWave;
         for (uint32_t trip = 0; trip < trips; ++trip) {
-            const uint32_t u = j + trip * LPR;
+            const uint32_t u = j + trip * kWave;
             const bool mine = u < n4;
-            const float4 v = row[mine ? u : 0];
-            const uint32_t b0 = biased(v.x), b1 = biased(v.y), b2 = biased(v.z), b3 = biased(v.w);
-            uint32_t m = (b3 << BITS) + b2;
-            m = (m << BITS) + b1;
-            const uint32_t h = (m << BITS) + b0 - MERGED_BIAS;  // 4 * BITS bits
+            uint32_t bytes;
+            const uint32_t h = unit_codes<BITS>(row[mine ? u : 0], lo, f, fscale, inv, bytes);
             const bool store = mine && live;
-            if (a.codes && store)
-                *reinterpret_cast<uint32_t *>(a.codes + k * (uint64_t)dim + 4 * u) =
-                    (((((b3 << 8) + b2) << 8) + b1) << 8) + b0 - MERGED_BIAS8;
+            if (a.codes && store) *reinterpret_cast<uint32_t *>(a.codes + k * (uint64_t)dim + 4 * u) = bytes;
             if (a.packed) store_unit_codes<BITS>(a.packed + k * P, u, h, store);
         }
     }
@@ -1105,12 +1203,11 @@ void launch_greedy_units(QuantArgs &a, hipStream_t s) {
     }
 }
 
-template <int LPR, int BITS>
-void launch_strided(cnr_ctx *ctx, QuantArgs &a, hipStream_t s) {
-    const unsigned grid = cnr_grid(ctx, a.n_max, (uint64_t)(kWave / LPR) * kWavesPerBlock,
-                                   cnr_resident_blocks_per_cu<quantize_strided_kernel<LPR, BITS>>());
+template <int LPR, int U, int SB, int BITS>
+void launch_units(QuantArgs &a, hipStream_t s) {
+    const unsigned grid = cnr_row_grid(a.n_max, (uint64_t)UnitsShape<LPR, U, SB, BITS>::ROWS * kWavesPerBlock);
     a.n_waves = grid * kWavesPerBlock;
-    hipLaunchKernelGGL((quantize_strided_kernel<LPR, BITS>), dim3(grid), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL((quantize_units_kernel<LPR, U, SB, BITS>), dim3(grid), dim3(kBlock), 0, s, a);
 }
 
 // The kernels that take one table per launch: the greedy search at any row length, and min/max or
@@ -1124,12 +1221,26 @@ void launch_bits(cnr_ctx *ctx, QuantArgs &a, hipStream_t s) {
     if (greedy && a.dim == 128) return launch_greedy_by_length<8, 2, 4, BITS>(ctx, a, s);
     if (greedy && a.dim == 256) return launch_greedy_by_length<16, 4, 4, BITS>(ctx, a, s);
     if (greedy) return launch_greedy_units<BITS>(a, s);
+    // Few idle lanes at every length (units of a row: lanes x units per lane), and 64 registers of row data or
+    // fewer on their way per lane
     const uint32_t n4 = a.dim / 4;
-    if (n4 <= 4) return launch_strided<4, BITS>(ctx, a, s);
-    if (n4 <= 8) return launch_strided<8, BITS>(ctx, a, s);
-    if (n4 <= 16) return launch_strided<16, BITS>(ctx, a, s);
-    if (n4 <= 32) return launch_strided<32, BITS>(ctx, a, s);
-    return launch_strided<64, BITS>(ctx, a, s);
+    if (n4 <= 4) return launch_units<4, 1, 4, BITS>(a, s);
+    if (n4 <= 8) return launch_units<8, 1, 4, BITS>(a, s);
+    if (n4 <= 12) return launch_units<4, 3, 2, BITS>(a, s);
+    if (n4 <= 16) return launch_units<8, 2, 4, BITS>(a, s);
+    if (n4 <= 24) return launch_units<8, 3, 2, BITS>(a, s);
+    if (n4 <= 32) return launch_units<8, 4, 2, BITS>(a, s);
+    if (n4 <= 40) return launch_units<8, 5, 2, BITS>(a, s);
+    if (n4 <= 48) return launch_units<8, 6, 2, BITS>(a, s);
+    if (n4 <= 56) return launch_units<8, 7, 2, BITS>(a, s);
+    if (n4 <= 64) return launch_units<8, 8, 2, BITS>(a, s);
+    if (n4 <= 80) return launch_units<16, 5, 2, BITS>(a, s);
+    if (n4 <= 96) return launch_units<16, 6, 2, BITS>(a, s);
+    if (n4 <= 112) return launch_units<16, 7, 2, BITS>(a, s);
+    if (n4 <= 128) return launch_units<16, 8, 2, BITS>(a, s);
+    const unsigned grid = cnr_grid(ctx, a.n_max, kWavesPerBlock, cnr_resident_blocks_per_cu<quantize_strided_kernel<BITS>>());
+    a.n_waves = grid * kWavesPerBlock;
+    hipLaunchKernelGGL((quantize_strided_kernel<BITS>), dim3(grid), dim3(kBlock), 0, s, a);
 }
 
 }  // namespace

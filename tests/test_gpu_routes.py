@@ -182,3 +182,57 @@ def test_greedy_skips_ids_outside_the_table(ctx, dim, bits):
     keep = [k for k in range(n) if k not in bad]
     for o in out:
         assert bool((o[bad] == 0x5A).all()) and bool((o[keep] != 0x5A).any(1).all())
+
+
+# ---- min/max and symmetric ranges at row lengths that are no power of two: every shape's first and last -
+
+@pytest.mark.parametrize("dim,bits", [
+    (4, 2), (8, 3), (12, 8), (20, 4), (28, 2), (36, 4), (40, 3), (48, 8), (52, 2), (60, 4), (72, 3), (96, 8), (100, 2),
+    (120, 3), (132, 4), (160, 3), (164, 8), (192, 2), (196, 4), (224, 3), (228, 2), (252, 8), (260, 2), (320, 3), (324, 4),
+    (384, 8), (388, 2), (448, 3), (452, 4), (512, 8), (516, 2), (1000, 3)])
+def test_encode_of_other_row_lengths(ctx, dim, bits):
+    print("case units dim=%d bits=%d" % (dim, bits), flush=True)
+    n_rows = 1300
+    table = synth.table_normal(n_rows, dim, 0.05, dim, DEV)
+    special = _special_rows(dim, dim)
+    table[torch.arange(special.shape[0], device=DEV) * 61 + 3] = torch.from_numpy(special).to(DEV)
+    gt = GpuTable(ctx, table)
+    for mode, ora_mode in ((P.CNR_RANGE_MINMAX, O.RANGE_MINMAX), (P.CNR_RANGE_SYMMETRIC, O.RANGE_SYMMETRIC)):
+        for n in (1, 16, 63, 257, 1300):      # rows 0 .. n-1, and a list known on the device alone
+            got = gpu_encode_all_outputs(gt, bits, mode=mode, row_ids=None, n=n)
+            compare_quantized(gt.host[:n], got, O.quantize_rows(gt.host[:n], None, bits, mode=ora_mode), bits, what="units d%d n%d" % (dim, n))
+            assert np.array_equal(got["packed"], O.pack(got["codes"], bits))
+        ids = np.flatnonzero(np.random.default_rng(dim).random(n_rows) < 0.4)
+        gt.ck.clear()
+        gt.ck.mark(torch.from_numpy(ids).to(DEV))
+        gt.ck.compact()
+        got = gpu_encode_all_outputs(gt, bits, mode=mode)
+        assert got["n"] == ids.size
+        compare_quantized(gt.host[ids], got, O.quantize_rows(gt.host, ids.astype(np.uint32), bits, mode=ora_mode), bits, what="units d%d list" % dim)
+        assert np.array_equal(got["packed"], O.pack(got["codes"], bits))
+    _poll(ctx)
+
+
+@pytest.mark.parametrize("dim,bits", [(8, 3), (20, 2), (96, 4), (144, 8), (500, 4), (516, 2)])
+def test_encode_of_other_row_lengths_skips_ids_outside_the_table(ctx, dim, bits):
+    n_rows, n = 500, 133
+    table = synth.table_normal(n_rows, dim, 0.05, 9, DEV)
+    ids = _ids(n_rows, n, 3)
+    prb = P.cnr_packed_row_bytes(dim, bits)
+
+    def encode(ids):
+        out = [torch.full((n, w), 0x5A, dtype=torch.uint8, device=DEV) for w in (4, 4, prb, dim)]
+        P.cnr_quantize_rows(ctx, table, n_rows, dim, ids, None, n, bits, P.CNR_RANGE_MINMAX, None, out[0].view(torch.float32).reshape(-1),
+                            out[1].view(torch.float32).reshape(-1), codes_u8=out[3].reshape(-1), packed=out[2].reshape(-1))
+        return out
+
+    whole = encode(ids)
+    _poll(ctx)
+    bad = [0, 1, 63, n - 1]
+    for k in bad:
+        ids[k] = n_rows + k
+    some = encode(ids)
+    _poll(ctx, P.CNR_FLAG_ROW_ID)
+    keep = [k for k in range(n) if k not in bad]
+    for w, o in zip(whole, some):             # nothing of theirs is written, everything else as without them
+        assert bool((o[bad] == 0x5A).all()) and torch.equal(o[keep], w[keep])
