@@ -18,7 +18,7 @@ struct cnr_ctx {
     int n_cu;                  // compute units of the device
     cnr_dev_errors *dev_err;   // device
     cnr_dev_errors *host_err;  // pinned host mirror used by cnr_poll_errors
-    double *host_scalar;       // pinned host double (behind host_err) for results read back one at a time
+    double *host_means;        // pinned host doubles (behind host_err), one per grid point of a parameter selection
     void *static_scratch;      // this device's copy of the library's fixed compaction scratch
     int last_hip_error;
 };
@@ -39,6 +39,17 @@ cnr_status cnr_hip_status(cnr_ctx *ctx, hipError_t e);
 // Looks up, on ctx's device (which must be current), the address of the fixed scratch array that
 // cnr_compact_dirty_noalloc uses, and keeps it in the context.
 cnr_status cnr_bind_static_scratch(cnr_ctx *ctx);
+// One point of a parameter selection; n_iter = 0: the row's own range.
+struct cnr_search_params {
+    uint32_t n_iter;
+    float num_bins_f;
+};
+constexpr uint32_t kSearchBatch = 32;  // points per launch
+// mean_out[p] (device-accessible) = mean l2 error of rows row_ids[0 .. n) quantized with params[p].
+// sums: device, max_sums >= 1 doubles.  Arguments are checked by the caller.
+cnr_status cnr_sample_errors(cnr_ctx *ctx, const float *table, uint64_t n_rows, uint32_t dim, const uint32_t *row_ids,
+                             uint64_t n, int bits, const cnr_search_params *params, uint32_t n_params, double *sums,
+                             uint64_t max_sums, double *mean_out, hipStream_t s);
 // Status of the launch that was just enqueued.
 static inline cnr_status cnr_launch_status(cnr_ctx *ctx) { return cnr_hip_status(ctx, hipGetLastError()); }
 

@@ -38,7 +38,7 @@ cnr_status cnr_create(cnr_ctx **out, int device) {
     ctx->last_hip_error = 0;
     ctx->dev_err = nullptr;
     ctx->host_err = nullptr;
-    ctx->host_scalar = nullptr;
+    ctx->host_means = nullptr;
     ctx->static_scratch = nullptr;
     hipError_t e = hipSetDevice(device);
     hipDeviceProp_t prop;
@@ -48,8 +48,9 @@ cnr_status cnr_create(cnr_ctx **out, int device) {
         e = hipMalloc((void **)&ctx->dev_err, sizeof(cnr_dev_errors));
     }
     if (e == hipSuccess) {
-        e = hipHostMalloc((void **)&ctx->host_err, sizeof(cnr_dev_errors) + sizeof(double), hipHostMallocDefault);
-        if (e == hipSuccess) ctx->host_scalar = reinterpret_cast<double *>(ctx->host_err + 1);
+        e = hipHostMalloc((void **)&ctx->host_err, sizeof(cnr_dev_errors) + (1 + CNR_SELECT_MAX_GRID) * sizeof(double),
+                          hipHostMallocDefault);
+        if (e == hipSuccess) ctx->host_means = reinterpret_cast<double *>(ctx->host_err + 1);
     }
     if (e == hipSuccess) e = hipMemset(ctx->dev_err, 0, sizeof(cnr_dev_errors));
     if (e == hipSuccess && cnr_bind_static_scratch(ctx) != CNR_OK) e = (hipError_t)ctx->last_hip_error;

@@ -695,13 +695,28 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L =
 // are walked in pairs (eight elements, as above) behind uniform branches; an odd unit and the partial one
 // follow as fours, and a lane without a partial unit evaluates elements that equal the candidate's lower
 // bound, whose error is zero.  Candidates go through one copy of the code: the un-shrunk range first,
-// then the two of every iteration in turn.  Same bound and same arithmetic as the kernel above.  (A wave
+// then the two of every iteration, in turn or side by side.  Same bound and same arithmetic as the kernel
+// above.
+// Side by side (DUAL): a short list is bound not by issue but by one candidate's chain of dependent
+// instructions (range to scale to reciprocal, the sum over the lanes, the comparison), so two groups of L
+// lanes hold the row, one evaluates the raised lower bound and the other the lowered upper one.  (A wave
 // per row that re-read the row from cache and divided for every element: 100 K rows of 96 at 49
 // candidates 874 us, this 117 us.)
 // ---------------------------------------------------------------------------------------------
-template <int L, int UMAX>
+// What the same lane of the row's other group of L lanes holds.  (The mirrors reverse the lanes, which is
+// the same for values that all lanes of a group agree on.)
+template <int L>
+__device__ __forceinline__ double other_group(double v) {
+    if constexpr (L == 4) return dpp_d<0x141>(v);
+    else if constexpr (L == 8) return dpp_d<0x140>(v);
+    else return __shfl_xor(v, L);
+}
+
+template <int L, int UMAX, bool DUAL>
 struct RowUnits {
     static_assert(UMAX % 2 == 0, "units are walked in pairs");
+    static_assert(!DUAL || L <= 32, "two groups of lanes fit a wave");
+    static constexpr int LANES = DUAL ? 2 * L : L;  // per row
     float4 x[UMAX];   // units j + L * t, t < 2 * pairs
     float4 odd;       // unit j + L * 2 * pairs, if has_odd
     float4 tail;      // unit j + L * n_full, if in_tail
@@ -778,35 +793,45 @@ struct RowUnits {
     __device__ __forceinline__ void search(uint32_t n_iter, float num_bins_f, float &lo, float &hi) const {
         float cur_lo = lo, cur_hi = hi;
         const float step = (hi - lo) / num_bins_f;
+        const bool upper = DUAL && (tid_x() / L) & 1;  // this lane's group lowers the upper bound
         double best = 0.0, e_lo = 0.0;
-        for (uint32_t c = 0; c <= 2 * n_iter; ++c) {
-            const bool first = c == 0, raise = c & 1;  // uniform
+        for (uint32_t c = 0; c <= (DUAL ? n_iter : 2 * n_iter); ++c) {
+            const bool first = c == 0;                               // uniform
+            const bool raise = !first && (DUAL ? !upper : (c & 1));  // uniform, but for DUAL
+            const bool lower = !first && !raise;
             const float c_lo = raise ? cur_lo + step : cur_lo;
-            const float c_hi = first || raise ? cur_hi : cur_hi - step;
-            const double e = sq_err<BITS, FAST>(c_lo, c_hi);
+            const float c_hi = lower ? cur_hi - step : cur_hi;
+            double e = sq_err<BITS, FAST>(c_lo, c_hi);
             if (first) {
                 best = e;
+                continue;
+            }
+            if constexpr (DUAL) {
+                const double o = other_group<L>(e);
+                e_lo = upper ? o : e;
+                e = upper ? e : o;
             } else if (raise) {
                 e_lo = e;
-            } else {
-                const bool move_lo = e_lo < e;
-                cur_lo = move_lo ? cur_lo + step : cur_lo;
-                cur_hi = move_lo ? cur_hi : c_hi;
-                const double better = move_lo ? e_lo : e;
-                if (better < best) {
-                    best = better;
-                    lo = cur_lo;
-                    hi = cur_hi;
-                }
+                continue;
+            }
+            const bool move_lo = e_lo < e;
+            cur_hi = move_lo ? cur_hi : cur_hi - step;
+            cur_lo = move_lo ? cur_lo + step : cur_lo;
+            const double better = move_lo ? e_lo : e;
+            if (better < best) {
+                best = better;
+                lo = cur_lo;
+                hi = cur_hi;
             }
         }
     }
 };
 
-template <int L, int UMAX, int BITS>
+template <int L, int UMAX, bool DUAL, int BITS>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(UMAX > 8 ? 3 : 4, 8)))
 quantize_greedy_units_kernel(const QuantArgs a, uint64_t n_from, uint64_t n_below) {
-    constexpr int kRowsPerPass = kWave / L;
+    using Row = RowUnits<L, UMAX, DUAL>;
+    constexpr int kRowsPerPass = kWave / Row::LANES;
     constexpr float QMAXF = (float)((1 << BITS) - 1);
     const uint64_t n = row_count(a);
     if (n < n_from || n >= n_below) return;  // this list length is the other launch's (uniform over the grid)
@@ -816,18 +841,18 @@ quantize_greedy_units_kernel(const QuantArgs a, uint64_t n_from, uint64_t n_belo
     const uint32_t j = lane % L;
     const uint32_t n_waves = a.n_waves;
     for (uint64_t pass = wave_in_grid(); pass * kRowsPerPass < n; pass += n_waves) {
-        const uint64_t k = pass * kRowsPerPass + lane / L;
+        const uint64_t k = pass * kRowsPerPass + lane / Row::LANES;
         uint64_t rid = 0;
         bool live = k < n;
         if (live) {
             rid = a.row_ids ? (uint64_t)a.row_ids[k] : k;
             if (rid >= a.n_rows) {
-                if (j == 0) raise_flag(a.err, CNR_FLAG_ROW_ID);
+                if (lane % Row::LANES == 0) raise_flag(a.err, CNR_FLAG_ROW_ID);
                 live = false;
                 rid = 0;
             }
         }
-        RowUnits<L, UMAX> row;
+        Row row;
         row.load(reinterpret_cast<const float4 *>(a.table + rid * (uint64_t)dim), n4, j);
         float X_min, X_max;
         row.range(X_min, X_max);
@@ -837,6 +862,7 @@ quantize_greedy_units_kernel(const QuantArgs a, uint64_t n_from, uint64_t n_belo
         else
             row.template search<BITS, true>(a.n_iter, a.num_bins_f, lo, hi);
 
+        if constexpr (DUAL) live = live && !((lane / L) & 1);  // one of the row's two groups stores
         const float scale = (hi - lo) / QMAXF;
         {
             // lane j of the row writes parameter j, or with fewer than four lanes j, j + L, ...
@@ -875,6 +901,101 @@ quantize_greedy_units_kernel(const QuantArgs a, uint64_t n_from, uint64_t n_belo
         if (row.has_odd) emit(row.odd, j + L * (n_full - 1), true);
         if (row.has_tail) emit(row.tail, j + L * n_full, row.in_tail);
     }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Mean l2 error of a sample under several greedy parameters at once (parameter selection): the search of
+// the kernel above, the restored row's error in place of its codes, nothing stored but one sum per
+// workgroup.  Grid y = parameters, so that all of them run side by side: a sample of a few thousand rows
+// leaves the chip mostly idle, and the launch takes as long as its longest search.  One launch per set of
+// parameters with the codes stored, read back and compared (encode, error, mean and a synchronization
+// each) took 354 us for 2.5 K rows of 64 and eight sets, this 111 us.
+// ---------------------------------------------------------------------------------------------
+struct SelectArgs {
+    const float *table;
+    uint64_t n_rows;
+    uint32_t dim;
+    const uint32_t *row_ids;
+    uint64_t n;
+    double *sums;  // [parameters][workgroups along x]
+    cnr_dev_errors *err;
+    cnr_search_params params[kSearchBatch];
+};
+template <int L, int UMAX, bool DUAL, int BITS>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(UMAX > 8 ? 3 : 4, 8)))
+sample_error_kernel(const SelectArgs a) {
+    using Row = RowUnits<L, UMAX, DUAL>;
+    constexpr int kRowsPerPass = kWave / Row::LANES;
+    constexpr float QMAXF = (float)((1 << BITS) - 1);
+    __shared__ double wave_sum[kWavesPerBlock];
+    const uint32_t n_iter = a.params[wg_y()].n_iter;
+    const float num_bins_f = a.params[wg_y()].num_bins_f;
+    const uint32_t n4 = a.dim / 4;
+    const int lane = tid_x() & (kWave - 1);
+    const uint32_t j = lane % L;
+    const uint32_t n_waves = grid_x() * kWavesPerBlock;
+    double sum = 0.0;
+    for (uint64_t pass = wave_in_grid(); pass * kRowsPerPass < a.n; pass += n_waves) {
+        const uint64_t k = pass * kRowsPerPass + lane / Row::LANES;
+        uint64_t rid = 0;
+        bool live = k < a.n;
+        if (live) {
+            rid = a.row_ids ? (uint64_t)a.row_ids[k] : k;
+            if (rid >= a.n_rows) {
+                if (lane % Row::LANES == 0) raise_flag(a.err, CNR_FLAG_ROW_ID);
+                live = false;
+                rid = 0;
+            }
+        }
+        Row row;
+        row.load(reinterpret_cast<const float4 *>(a.table + rid * (uint64_t)a.dim), n4, j);
+        float lo, hi;
+        row.range(lo, hi);
+        if (n_iter) {
+            if (search_divides(lo, hi, num_bins_f, QMAXF))
+                row.template search<BITS, false>(n_iter, num_bins_f, lo, hi);
+            else
+                row.template search<BITS, true>(n_iter, num_bins_f, lo, hi);
+        }
+        const float scale = (hi - lo) / QMAXF;
+        double e = 0.0;
+        auto add = [&](const float4 &v) {
+            const float x[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const double d = (double)x[i] - (double)fq_value(fq_code_f(x[i], lo, hi, scale, QMAXF), scale, lo);
+                e = fma(d, d, e);
+            }
+        };
+#pragma unroll
+        for (int t = 0; t < UMAX; ++t)
+            if ((uint32_t)t < 2 * row.pairs) add(row.x[t]);
+        if (row.has_odd) add(row.odd);
+        if (row.has_tail && row.in_tail) add(row.tail);
+        e = lanes_sum<L>(e);
+        if (live && lane % Row::LANES == 0) sum += sqrt(e);
+    }
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+    if (lane == 0) wave_sum[tid_x() / kWave] = sum;
+    __syncthreads();
+    if (tid_x() == 0) {
+        double total = 0.0;
+        for (int w = 0; w < kWavesPerBlock; ++w) total += wave_sum[w];
+        a.sums[(uint64_t)wg_y() * grid_x() + wg_x()] = total;
+    }
+}
+// mean_out[p] = (the sums of parameters p, added up in a fixed order) / n; one workgroup per p.
+__global__ void __launch_bounds__(kBlock) sample_mean_kernel(const double *sums, uint32_t per_set, double n, double *mean_out) {
+    __shared__ double part[kBlock];
+    double acc = 0.0;
+    for (uint32_t i = tid_x(); i < per_set; i += kBlock) acc += sums[(uint64_t)wg_x() * per_set + i];
+    part[tid_x()] = acc;
+    __syncthreads();
+    for (int half = kBlock / 2; half > 0; half >>= 1) {
+        if ((int)tid_x() < half) part[tid_x()] += part[tid_x() + half];
+        __syncthreads();
+    }
+    if (tid_x() == 0) mean_out[wg_x()] = part[0] / n;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1168,38 +1289,40 @@ void launch_greedy_by_length(cnr_ctx *ctx, QuantArgs &a, hipStream_t s) {
     if (may_be_wide) launch_greedy<L_WIDE, BITS, G_WIDE>(ctx, a, s, may_be_narrow ? wide_rows : 0, ~0ull);
 }
 
-template <int L, int UMAX, int BITS>
+template <int L, int UMAX, bool DUAL, int BITS>
 void launch_greedy_units_shape(QuantArgs &a, hipStream_t s, uint64_t n_from, uint64_t n_below) {
     const uint64_t most = a.n_max < n_below ? a.n_max : n_below;
-    const unsigned grid = cnr_row_grid(most, (uint64_t)(kWave / L) * kWavesPerBlock);
+    const unsigned grid = cnr_row_grid(most, (uint64_t)(kWave / RowUnits<L, UMAX, DUAL>::LANES) * kWavesPerBlock);
     a.n_waves = grid * kWavesPerBlock;
-    hipLaunchKernelGGL((quantize_greedy_units_kernel<L, UMAX, BITS>), dim3(grid), dim3(kBlock), 0, s, a, n_from, n_below);
+    hipLaunchKernelGGL((quantize_greedy_units_kernel<L, UMAX, DUAL, BITS>), dim3(grid), dim3(kBlock), 0, s, a, n_from, n_below);
 }
-// Other row lengths: long lists give a row as few lanes as hold it, short ones more (less time per row).
-// The line lies where the wide form's waves fill the chip: 768 waves of short rows, or, since a lane with
-// many units works longer on its row, 128 waves for every unit of a lane (measured break-evens: rows of 48
-// at 12 K rows, of 96 at 12 K, of 200 at 20 K, of 384 at 3.4 K, of 1000 at 10 K).
+// Other row lengths: long lists give a row as few lanes as hold it; short ones give it two groups of 4 to
+// 32 lanes, which evaluate the two candidates of an iteration side by side (17 instead of 23 us for
+// the shortest lists of rows of 96 at 25 bins, a single group of 16 lanes taking one after the other).
+// The line lies where the long form's waves fill the chip: 768 waves of short rows, or, since a lane with
+// many units works longer on its row, a number in proportion to them.  Measured break-evens: rows of 24
+// at 57 K rows, of 48 at 28 K, of 96 at 30 K, of 200 at 42 K, of 384 at 8.4 K, of 1000 at 20 K.
 template <int BITS>
 void launch_greedy_units(QuantArgs &a, hipStream_t s) {
     const uint32_t n4 = a.dim / 4;
     const uint32_t lanes = n4 <= 8 ? 1 : n4 <= 17 ? 2 : n4 < 68 ? 4 : n4 <= 271 ? 16 : 64;
-    const uint64_t fill = 49152u / lanes, busy = 8192ull * n4 / (lanes * lanes);
+    const uint64_t fill = 49152u / lanes, busy = (lanes >= 4 ? 20480ull : 8192ull) * n4 / (lanes * lanes);
     const uint64_t wide_rows = fill > busy ? fill : busy;
     const bool may_be_wide = lanes == 64 || a.n_max >= wide_rows;
     const bool may_be_narrow = lanes != 64 && (!may_be_wide || a.n_dev != nullptr);
     const uint64_t below = may_be_wide ? wide_rows : ~0ull, from = may_be_narrow ? wide_rows : 0;
     if (may_be_narrow) {
-        if (n4 <= 17) launch_greedy_units_shape<4, 8, BITS>(a, s, 0, below);
-        else if (n4 < 80) launch_greedy_units_shape<16, 4, BITS>(a, s, 0, below);
-        else launch_greedy_units_shape<64, 4, BITS>(a, s, 0, below);
+        if (n4 <= 8) launch_greedy_units_shape<4, 2, true, BITS>(a, s, 0, below);
+        else if (n4 < 72) launch_greedy_units_shape<8, 8, true, BITS>(a, s, 0, below);
+        else launch_greedy_units_shape<32, 8, true, BITS>(a, s, 0, below);
     }
     if (may_be_wide) {
-        if (lanes == 1) launch_greedy_units_shape<1, 8, BITS>(a, s, from, ~0ull);
-        else if (lanes == 2) launch_greedy_units_shape<2, 8, BITS>(a, s, from, ~0ull);
-        else if (n4 < 36) launch_greedy_units_shape<4, 8, BITS>(a, s, from, ~0ull);
-        else if (lanes == 4) launch_greedy_units_shape<4, 16, BITS>(a, s, from, ~0ull);
-        else if (lanes == 16) launch_greedy_units_shape<16, 16, BITS>(a, s, from, ~0ull);
-        else launch_greedy_units_shape<64, 16, BITS>(a, s, from, ~0ull);
+        if (lanes == 1) launch_greedy_units_shape<1, 8, false, BITS>(a, s, from, ~0ull);
+        else if (lanes == 2) launch_greedy_units_shape<2, 8, false, BITS>(a, s, from, ~0ull);
+        else if (n4 < 36) launch_greedy_units_shape<4, 8, false, BITS>(a, s, from, ~0ull);
+        else if (lanes == 4) launch_greedy_units_shape<4, 16, false, BITS>(a, s, from, ~0ull);
+        else if (lanes == 16) launch_greedy_units_shape<16, 16, false, BITS>(a, s, from, ~0ull);
+        else launch_greedy_units_shape<64, 16, false, BITS>(a, s, from, ~0ull);
     }
 }
 
@@ -1243,7 +1366,54 @@ void launch_bits(cnr_ctx *ctx, QuantArgs &a, hipStream_t s) {
     hipLaunchKernelGGL((quantize_strided_kernel<BITS>), dim3(grid), dim3(kBlock), 0, s, a);
 }
 
+// Two groups of lanes per row while the sets of parameters together leave room on the chip; four lanes
+// beyond that.  Measured break-evens with five and three sets: 100 K rows of 16, 20 K rows of 64, 30 K of
+// 128, 60 K of 256.
+template <int BITS>
+cnr_status launch_sample_errors(cnr_ctx *ctx, SelectArgs &a, uint32_t n_sets, uint64_t max_sums, double *mean_out, hipStream_t s) {
+    const uint32_t n4 = a.dim / 4;
+    const bool wide = n4 < 68 && a.n * n_sets >= 131072;
+    const uint32_t lanes = wide ? 4 : n4 <= 8 ? 8 : n4 < 72 ? 16 : 64;
+    const uint64_t rows_per_wg = (uint64_t)(kWave / lanes) * kWavesPerBlock;
+    uint64_t grid = (a.n + rows_per_wg - 1) / rows_per_wg;
+    if (grid > 4096) grid = 4096;
+    if (grid > max_sums / n_sets) grid = max_sums / n_sets;  // at least 1: the caller sees to it
+    const dim3 g((unsigned)grid, n_sets);
+    if (wide && n4 < 36) hipLaunchKernelGGL((sample_error_kernel<4, 8, false, BITS>), g, dim3(kBlock), 0, s, a);
+    else if (wide) hipLaunchKernelGGL((sample_error_kernel<4, 16, false, BITS>), g, dim3(kBlock), 0, s, a);
+    else if (n4 <= 8) hipLaunchKernelGGL((sample_error_kernel<4, 2, true, BITS>), g, dim3(kBlock), 0, s, a);
+    else if (n4 < 72) hipLaunchKernelGGL((sample_error_kernel<8, 8, true, BITS>), g, dim3(kBlock), 0, s, a);
+    else if (n4 < 288) hipLaunchKernelGGL((sample_error_kernel<32, 8, true, BITS>), g, dim3(kBlock), 0, s, a);
+    else hipLaunchKernelGGL((sample_error_kernel<64, 16, false, BITS>), g, dim3(kBlock), 0, s, a);
+    cnr_status st = cnr_launch_status(ctx);
+    if (st != CNR_OK) return st;
+    hipLaunchKernelGGL(sample_mean_kernel, dim3(n_sets), dim3(kBlock), 0, s, a.sums, (uint32_t)grid, (double)a.n, mean_out);
+    return cnr_launch_status(ctx);
+}
+
 }  // namespace
+
+cnr_status cnr_sample_errors(cnr_ctx *ctx, const float *table, uint64_t n_rows, uint32_t dim, const uint32_t *row_ids,
+                             uint64_t n, int bits, const cnr_search_params *params, uint32_t n_params, double *sums,
+                             uint64_t max_sums, double *mean_out, hipStream_t s) {
+    for (uint32_t done = 0; done < n_params;) {
+        uint32_t m = n_params - done;
+        if (m > kSearchBatch) m = kSearchBatch;
+        if (m > max_sums) m = (uint32_t)max_sums;  // >= 1
+        SelectArgs a = {table, n_rows, dim, row_ids, n, sums, ctx->dev_err, {}};
+        for (uint32_t i = 0; i < m; ++i) a.params[i] = params[done + i];
+        cnr_status st;
+        switch (bits) {
+            case 2: st = launch_sample_errors<2>(ctx, a, m, max_sums, mean_out + done, s); break;
+            case 3: st = launch_sample_errors<3>(ctx, a, m, max_sums, mean_out + done, s); break;
+            case 4: st = launch_sample_errors<4>(ctx, a, m, max_sums, mean_out + done, s); break;
+            default: st = launch_sample_errors<8>(ctx, a, m, max_sums, mean_out + done, s); break;
+        }
+        if (st != CNR_OK) return st;
+        done += m;
+    }
+    return CNR_OK;
+}
 
 extern "C" {
 

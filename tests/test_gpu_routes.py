@@ -127,11 +127,11 @@ def _special_rows(dim, seed):
 
 
 @pytest.mark.parametrize("dim,bits,wide", [
-    (4, 8, 49_152), (8, 3, 49_152), (24, 3, 49_152), (28, 4, 49_152),               # a lane per row / four
-    (36, 2, 24_576), (40, 3, 24_576), (48, 8, 24_576), (68, 4, 34_816),             # two lanes / four
-    (72, 3, 12_288), (96, 3, 12_288), (100, 4, 12_800), (140, 2, 17_920),           # four / sixteen, eight units at most
-    (144, 3, 18_432), (268, 2, 34_304),                                             # four / sixteen, sixteen units
-    (272, 3, 3_072), (316, 4, 3_072), (320, 8, 3_072), (1084, 2, 8_672),            # sixteen / sixteen or sixty-four
+    (4, 8, 49_152), (8, 3, 49_152), (24, 3, 49_152), (28, 4, 57_344),               # a lane per row / twice four
+    (36, 2, 24_576), (40, 3, 24_576), (48, 8, 24_576), (68, 4, 34_816),             # two lanes / twice eight
+    (72, 3, 23_040), (96, 3, 30_720), (100, 4, 32_000), (140, 2, 44_800),           # four, eight units at most / twice eight
+    (144, 3, 46_080), (268, 2, 85_760),                                             # four, sixteen units / twice eight
+    (272, 3, 5_440), (284, 2, 5_680), (288, 4, 5_760), (320, 8, 6_400), (1084, 2, 21_680),   # sixteen / twice eight or thirty-two
     (1088, 3, 1_000), (2044, 4, 500), (4096, 2, 300),                               # sixty-four
 ])
 def test_greedy_routes_of_other_row_lengths(ctx, dim, bits, wide):
@@ -236,3 +236,27 @@ def test_encode_of_other_row_lengths_skips_ids_outside_the_table(ctx, dim, bits)
     keep = [k for k in range(n) if k not in bad]
     for w, o in zip(whole, some):             # nothing of theirs is written, everything else as without them
         assert bool((o[bad] == 0x5A).all()) and torch.equal(o[keep], w[keep])
+
+
+# ---- parameter selection: lanes per row, sets of parameters per launch, partial sums that fit the scratch --
+
+@pytest.mark.parametrize("dim,bits,n,bins", [
+    (64, 3, 1, tuple(range(2, 42))),       # a scratch of ten sums: several launches per grid
+    (64, 4, 301, tuple(range(3, 40))),     # more points than a launch takes
+    (64, 2, 44_000, (7, 20)), (96, 3, 43_691, (9, 16)), (200, 4, 43_800, (18, 30)),   # four lanes per row
+    (96, 4, 500, (18, 30)), (284, 2, 77, (9, 12)), (288, 8, 77, (9, 12)),              # twice eight, twice thirty-two
+    (1148, 2, 130, (8, 11)), (1152, 3, 65, (9, 12)), (4, 8, 40, (3, 20)), (32, 3, 300, (9, 12)),   # the same, sixty-four; twice four
+])
+def test_parameter_selection_routes(ctx, dim, bits, n, bins):
+    print("case select dim=%d bits=%d n=%d" % (dim, bits, n), flush=True)
+    n_rows, ratios = n + 50, (0.25, 0.5, 1.0)
+    table = synth.table_outlier_mix(n_rows, dim, 0.02, dim + n, DEV)
+    table[3] = 0.25                        # a constant row: searched by division
+    ids = _ids(n_rows, n, 11)
+    choice, report = P.select_greedy_params(ctx, table, n_rows, dim, ids, bits, bins, ratios)
+    want_choice, want = O.select_greedy_params(table[ids.long()].cpu().numpy(), bits, bins, ratios, n_threads=8)
+    assert set(report) == set(want)
+    for key in want:                       # fp64 sums in another order; a row that leaves the search's path at a
+        assert report[key] == pytest.approx(want[key], rel=max(1e-9, 0.1 / n if key != "naive" else 0)), key  # near-tie ends within a tenth of its error
+    assert choice == want_choice
+    _poll(ctx)
