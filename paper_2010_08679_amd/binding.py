@@ -10,7 +10,9 @@ GPU, these calls fail.
 from __future__ import annotations
 
 import ctypes
+import itertools
 import os
+import struct
 import threading
 
 import torch
@@ -337,6 +339,28 @@ def make_jobs(jobs):
         idx = d.get("indices")
         j.n_indices = int(d.get("n_indices", idx.numel() if idx is not None else 0))
     return arr
+
+
+def _ptr(t, dtype, name: str) -> int:
+    """Device address of a contiguous GPU tensor of the given dtype (None: any), 0 for None."""
+    if t is None:
+        return 0
+    if not (isinstance(t, torch.Tensor) and t.is_cuda and (dtype is None or t.dtype == dtype) and t.is_contiguous()):
+        _dev(t, t.dtype if dtype is None and isinstance(t, torch.Tensor) else dtype, name)  # raises with the reason
+    return t.data_ptr()
+
+
+_job_packers = {}
+
+
+def pack_jobs(rows):
+    """A ``cnr_table_job`` array from one 16-tuple of integers per job (the struct's fields in order): what
+    :func:`make_jobs` builds field by field, in one step, for callers that have checked their tensors."""
+    n = len(rows)
+    packer = _job_packers.get(n)
+    if packer is None:
+        packer = _job_packers[n] = (struct.Struct("%dQ" % (n * len(cnr_table_job._fields_))), cnr_table_job * n)
+    return packer[1].from_buffer_copy(packer[0].pack(*itertools.chain.from_iterable(rows)))
 
 
 def _jobs_arg(jobs):

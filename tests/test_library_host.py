@@ -204,3 +204,18 @@ def test_a_library_built_from_other_sources_is_rebuilt_before_loading(tmp_path, 
     assert B.is_stale()
     binding.ensure_built()
     assert len(built) == 3
+
+
+def test_packed_jobs_hold_the_struct_fields_in_order():
+    # pack_jobs writes whole structs at once: field k of job i must be the k-th integer of its tuple, up to
+    # the largest 64-bit address, and the array must be as long as the list
+    fields = [f for f, _ in binding.cnr_table_job._fields_]
+    for n in (1, 2, 16, 17):
+        rows = [tuple(1000 * i + k + 1 for k in range(len(fields))) for i in range(n)]
+        rows[-1] = rows[-1][:-1] + (2 ** 64 - 1,)
+        arr = binding.pack_jobs(rows)
+        assert len(arr) == n
+        for i, job in enumerate(arr):
+            assert [getattr(job, f) for f in fields] == list(rows[i])
+    empty = binding.pack_jobs([(0,) * len(fields)])[0]
+    assert all(not getattr(empty, f) for f in fields)
