@@ -260,3 +260,24 @@ def test_parameter_selection_routes(ctx, dim, bits, n, bins):
         assert report[key] == pytest.approx(want[key], rel=max(1e-9, 0.1 / n if key != "naive" else 0)), key  # near-tie ends within a tenth of its error
     assert choice == want_choice
     _poll(ctx)
+
+
+# ---- compaction: workgroups that count the tiles before theirs, up to 64 tiles; counted tiles beyond ------
+
+@pytest.mark.parametrize("n_rows", [16_384, 16_385, 8 * 16_384 + 1, 64 * 16_384, 64 * 16_384 + 1])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_compaction_around_the_self_counting_limit(ctx, n_rows, shift):
+    g = torch.Generator(device=DEV).manual_seed(n_rows)
+    words = P.cnr_bitmap_words(n_rows)
+    bitmap = torch.randint(-2**31, 2**31, (words + shift,), generator=g, device=DEV).to(torch.int32)[shift:]
+    bits = ((bitmap[:, None] >> torch.arange(32, device=DEV, dtype=torch.int32)) & 1).reshape(-1)[:n_rows]   # bits past n_rows are set too
+    want = torch.nonzero(bits).reshape(-1).to(torch.int32)
+    scratch = torch.empty((P.cnr_scratch_bytes(n_rows) + 7) // 8, dtype=torch.int64, device=DEV)
+    for capacity in (n_rows, want.numel() - 5):
+        ids = torch.full((n_rows,), -1, dtype=torch.int32, device=DEV)
+        n = torch.zeros(1, dtype=torch.int64, device=DEV)
+        P.cnr_compact_dirty(ctx, bitmap, n_rows, ids, capacity, n, scratch)
+        assert int(n) == want.numel()
+        m = min(capacity, want.numel())
+        assert torch.equal(ids[:m], want[:m]) and bool((ids[m:] == -1).all())
+        _poll(ctx, 0 if capacity >= want.numel() else P.CNR_FLAG_CAPACITY)
