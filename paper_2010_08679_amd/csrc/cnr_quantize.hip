@@ -1326,6 +1326,25 @@ void launch_greedy_units(QuantArgs &a, hipStream_t s) {
     }
 }
 
+// Lists so short that two groups of lanes per row, one candidate each, still leave room on the chip (three
+// waves per SIMD), at the lengths that the kernels above otherwise search with one: 45 bins, 1 K rows of
+// 16 to 128 elements 28-30 -> 14-25 us, of 256 30 -> 25; at the line both take the same.  Only where the
+// host's bound on the length says so: another launch to choose from on the device would cost the longer
+// lists more.
+template <int BITS>
+bool launch_greedy_short(QuantArgs &a, hipStream_t s) {
+    const uint32_t lanes = a.dim <= 32 ? 8 : a.dim <= 128 ? 16 : 32;
+    if (a.n_max > 196608u / lanes) return false;
+    switch (a.dim) {
+        case 16:
+        case 32: launch_greedy_units_shape<4, 2, true, BITS>(a, s, 0, ~0ull); return true;
+        case 64:
+        case 128: launch_greedy_units_shape<8, 8, true, BITS>(a, s, 0, ~0ull); return true;
+        case 256: launch_greedy_units_shape<16, 4, true, BITS>(a, s, 0, ~0ull); return true;
+        default: return false;
+    }
+}
+
 template <int LPR, int U, int SB, int BITS>
 void launch_units(QuantArgs &a, hipStream_t s) {
     const unsigned grid = cnr_row_grid(a.n_max, (uint64_t)UnitsShape<LPR, U, SB, BITS>::ROWS * kWavesPerBlock);
@@ -1338,6 +1357,7 @@ void launch_units(QuantArgs &a, hipStream_t s) {
 template <int BITS>
 void launch_bits(cnr_ctx *ctx, QuantArgs &a, hipStream_t s) {
     const bool greedy = a.mode == kModeGreedy && a.n_iter > 0;  // zero iterations: plain min/max
+    if (greedy && launch_greedy_short<BITS>(a, s)) return;
     if (greedy && a.dim == 16) return launch_greedy<1, BITS, 1>(ctx, a, s, 0, ~0ull);
     if (greedy && a.dim == 32) return launch_greedy_by_length<2, 1, 2, BITS>(ctx, a, s);
     if (greedy && a.dim == 64) return launch_greedy_by_length<4, 1, 4, BITS>(ctx, a, s);

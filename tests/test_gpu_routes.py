@@ -166,6 +166,27 @@ def test_greedy_routes_of_other_row_lengths(ctx, dim, bits, wide):
     _poll(ctx)
 
 
+@pytest.mark.parametrize("dim,bits,limit", [(16, 4, 24_576), (32, 3, 24_576), (64, 2, 12_288), (64, 8, 12_288), (128, 3, 12_288), (256, 4, 6_144)])
+def test_greedy_short_lists_of_power_of_two_rows(ctx, dim, bits, limit):
+    # up to `limit` rows (a bound the host knows) two groups of lanes per row, beyond it one
+    n_rows = limit + 3
+    table = synth.table_outlier_mix(n_rows, dim, 0.02, dim + bits, DEV)
+    rng = np.random.default_rng(dim)
+    special = _special_rows(dim, dim + 1)
+    where = np.sort(rng.choice(n_rows - 5, size=special.shape[0], replace=False))
+    table[torch.from_numpy(where).to(DEV)] = torch.from_numpy(special).to(DEV)
+    gt = GpuTable(ctx, table)
+    params = {2: (12, 0.6), 3: (12, 0.33), 4: (20, 0.2), 8: (12, 0.5)}[bits]  # no exact ties, as above
+    for n in (1, 77, limit, limit + 1):
+        got = gpu_encode_all_outputs(gt, bits, mode=P.CNR_RANGE_GREEDY, greedy=params, row_ids=None, n=n)
+        pos = np.unique(np.concatenate([np.arange(min(40, n)), np.arange(max(0, n - 40), n), where[where < n], rng.integers(0, n, size=1500)]))
+        ora = O.quantize_rows(gt.host[pos], None, bits, mode=O.RANGE_GREEDY, num_bins=params[0], ratio=params[1], n_threads=8)
+        compare_quantized(gt.host[pos], {k: got[k][pos] for k in ("scale", "bias", "row_min", "row_max", "codes")}, ora, bits,
+                          greedy=True, what="greedy short b%d d%d n%d" % (bits, dim, n))
+        assert np.array_equal(got["packed"], O.pack(got["codes"], bits))
+    _poll(ctx)
+
+
 @pytest.mark.parametrize("dim,bits", [(96, 3), (24, 4), (48, 2), (300, 8)])
 def test_greedy_skips_ids_outside_the_table(ctx, dim, bits):
     n_rows, n = 500, 133
