@@ -35,10 +35,10 @@ from paper_2010_08679_amd import synth  # noqa: E402
 
 HBM_PEAK_GBPS = 8000.0          # MI355X HBM3E, published
 FP32_VECTOR_PEAK_TFLOPS = 157.3  # MI355X fp32 vector, published
-# SIMD time the greedy search needs per element and candidate range: 26 clocks of a 16-lane SIMD for a
-# wave of 64 (add / subtract / multiply occupy it for 2 clocks, every other vector instruction of the
-# loop for 4: bench_ceilings.hip measures that), with 256 CUs x 4 SIMDs at 2.4 GHz
-GREEDY_SIMD_CLOCKS_PER_ELEMENT = 26.0
+# SIMD time the greedy search's inner loop takes per element and candidate range for a wave of 64: 9.84 ns
+# (23.6 clocks at 2.4 GHz) for a loop of nothing but its eight instructions (bench_ceilings.hip measures
+# that), with 256 CUs x 4 SIMDs
+GREEDY_SIMD_CLOCKS_PER_ELEMENT = 23.6
 SIMD_CLOCKS_PER_S = 256 * 4 * 2.4e9
 
 # HBM traffic of the two bandwidth-bound kernels from rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE, each
@@ -49,7 +49,7 @@ TRAFFIC_PER_ROW = {
     "a2e6a8cd8520d9e7bb6344cdfd2a382c27d08e95db09fef0a95bfb9a9a5ff999": {"cfg4/b4": 300.96, "cfg3/b2": 558.98, "cfg3/b3": 581.12, "cfg5/b8": 658.98, "cfg5/b4": 592.55},
 }
 RESTORE_TRAFFIC_PER_ROW = {
-    "0a151c3fed73be1daf849a41a37f121a6c0b73202cd2806cb848ad2850c9bc6b": {"cfg4/b4": 300.01, "cfg3/b2": 556.09, "cfg3/b3": 572.08, "cfg5/b8": 652.09, "cfg5/b4": 588.04},
+    "9da3bb04f0f026ab3b207f964f7a0115189d3f1db165cf721d16025fee224303": {"cfg4/b4": 300.01, "cfg3/b2": 556.09, "cfg3/b3": 572.08, "cfg5/b8": 652.09, "cfg5/b4": 588.04},
 }
 
 
@@ -70,7 +70,8 @@ def _kernel_hash() -> str:
 
 
 def _restore_kernel_hash() -> str:
-    return _source_hash("cnr_restore.hip")
+    """The restore kernels' source: everything in their file above the error metric's section."""
+    return _source_hash("cnr_restore.hip", "// Error metric")
 
 
 def encode_bytes_per_row(dim: int, bits: int) -> int:
@@ -416,7 +417,7 @@ def main() -> int:
             "roofline": {"bound": "alu", "achieved": round(flops / (g * 1e-3) / 1e12, 2),
                          "peak": FP32_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
                          "frac": round(flops / (g * 1e-3) / 1e12 / FP32_VECTOR_PEAK_TFLOPS, 4),
-                         # the same launch against the time its own instruction mix needs at full issue rate
+                         # the same launch against the time a loop of nothing but its own instructions takes
                          "issue_bound_ms": round(issue_ms, 3), "issue_frac": round(issue_ms / g, 4), "traffic": None},
         }
 

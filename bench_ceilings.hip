@@ -28,7 +28,7 @@
 #define OP2(op, d, s, t) asm volatile(op " %0, %1, %2" : "=v"(d) : "v"(s), "v"(t))
 #define OP3(op, d, s, t, u) asm volatile(op " %0, %1, %2, %3" : "=v"(d) : "v"(s), "v"(t), "v"(u))
 
-enum Kind { ADD, SUB, MUL, FMA, MED3, RNDNE, CVT_F64_F32, FMA_F64, ADD_F64, GREEDY_MIX };
+enum Kind { ADD, SUB, MUL, MUL_CLAMP, FMA, MED3, RNDNE, CVT_F64_F32, FMA_F64, ADD_F64, GREEDY_MIX };
 
 template <int KIND>
 __global__ void __launch_bounds__(256) rate_kernel(float x, double xd, int iters, float *out) {
@@ -42,26 +42,35 @@ __global__ void __launch_bounds__(256) rate_kernel(float x, double xd, int iters
             if (KIND == ADD) OP2("v_add_f32_e32", a[i], a[i], x);
             if (KIND == SUB) OP2("v_sub_f32_e32", a[i], a[i], x);
             if (KIND == MUL) OP2("v_mul_f32_e32", a[i], a[i], x);
+            if (KIND == MUL_CLAMP) asm volatile("v_mul_f32_e64 %0, %1, %2 clamp" : "=v"(a[i]) : "v"(a[i]), "v"(x));
             if (KIND == FMA) OP3("v_fma_f32", a[i], a[i], x, x);
             if (KIND == MED3) OP3("v_med3_f32", a[i], a[i], x, x);
             if (KIND == RNDNE) OP1("v_rndne_f32_e32", a[i], a[i]);
             if (KIND == CVT_F64_F32) OP1("v_cvt_f64_f32_e32", b[i % 16], a[i]);
             if (KIND == FMA_F64) OP3("v_fma_f64", b[i % 16], b[i % 16], xd, xd);
             if (KIND == ADD_F64) OP2("v_add_f64", b[i % 16], b[i % 16], xd);
-            if (KIND == GREEDY_MIX && i < 8) {
-                // one element of the greedy loop: clip, subtract, multiply, round, multiply, add, subtract,
-                // convert, accumulate the square (9 instructions)
-                float c, d;
-                double dd;
-                OP3("v_med3_f32", c, a[i], x, a[i + 8]);
-                OP2("v_sub_f32_e32", c, c, x);
-                OP2("v_mul_f32_e32", c, c, a[i + 16]);
-                OP1("v_rndne_f32_e32", c, c);
-                OP2("v_mul_f32_e32", c, c, a[i + 24]);
-                OP2("v_add_f32_e32", c, c, x);
-                OP2("v_sub_f32_e32", d, a[i], c);
-                OP1("v_cvt_f64_f32_e32", dd, d);
-                OP3("v_fma_f64", b[i], dd, dd, b[i]);
+            if (KIND == GREEDY_MIX && i == 0) {
+                // eight elements of the greedy loop, in stages as the kernel issues them: subtract, multiply
+                // with the clamp to [0, 1], round (by a multiply-add onto 2^23), product, add, subtract,
+                // convert, accumulate the square
+                float c[8];
+                double dd[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) OP2("v_sub_f32_e32", c[k], a[k], x);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) asm volatile("v_mul_f32_e64 %0, %1, %2 clamp" : "=v"(c[k]) : "v"(c[k]), "v"(a[8]));
+#pragma unroll
+                for (int k = 0; k < 8; ++k) OP3("v_fma_f32", c[k], c[k], a[9], a[10]);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) OP3("v_fma_f32", c[k], c[k], a[11], a[12]);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) OP2("v_add_f32_e32", c[k], c[k], x);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) OP2("v_sub_f32_e32", c[k], a[k], c[k]);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) OP1("v_cvt_f64_f32_e32", dd[k], c[k]);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) OP3("v_fma_f64", b[0], dd[k], dd[k], b[0]);
             }
         }
     }
@@ -317,13 +326,14 @@ int main() {
     rc |= run<ADD>("v_add_f32", 32, out);
     rc |= run<SUB>("v_sub_f32", 32, out);
     rc |= run<MUL>("v_mul_f32", 32, out);
+    rc |= run<MUL_CLAMP>("v_mul_f32 clamp", 32, out);
     rc |= run<FMA>("v_fma_f32", 32, out);
     rc |= run<MED3>("v_med3_f32", 32, out);
     rc |= run<RNDNE>("v_rndne_f32", 32, out);
     rc |= run<CVT_F64_F32>("v_cvt_f64_f32", 32, out);
     rc |= run<FMA_F64>("v_fma_f64", 32, out);
     rc |= run<ADD_F64>("v_add_f64", 32, out);
-    rc |= run<GREEDY_MIX>("greedy element (9 instructions)", 72, out);
+    rc |= run<GREEDY_MIX>("greedy element (8 instructions)", 64, out);
     rc |= memory_ceilings(out);
     rc |= host_link_ceilings(out);
     rc |= compute_unit_stream(out);

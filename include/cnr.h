@@ -224,7 +224,7 @@ cnr_status cnr_restore_rows(cnr_ctx *ctx, float *table, uint64_t n_rows, uint32_
  * when row_ids is NULL) of `table` and Q_k the same row as cnr_restore_rows would write it from
  * (packed, scale, bias); element differences, their squares and the sum are taken in fp64.  When
  * mean_out is not NULL, *mean_out receives (1/n) * sum_k err[k], added up in a fixed order (0 when
- * n == 0).  Rows with an id >= n_rows get err 0 and raise CNR_FLAG_ROW_ID.
+ * n == 0); while the call runs, some entries of err hold partial sums.  Rows with an id >= n_rows get err 0 and raise CNR_FLAG_ROW_ID.
  *   err       double [n_max], required
  *   mean_out  double [1] (device) or NULL */
 cnr_status cnr_quant_error(cnr_ctx *ctx, const float *table, uint64_t n_rows, uint32_t dim,

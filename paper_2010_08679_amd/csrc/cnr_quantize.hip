@@ -379,12 +379,13 @@ quantize_tile_kernel(const QuantBatchArgs b) {
 // so the transpose through LDS that the tile kernel pays for coalesced loads would buy nothing.
 // A candidate is evaluated with the cheapest sequence that still ranks candidates as F_Q would: eight
 // vector instructions per element (struct Candidate).  What they cost differs (a wave's add or subtract
-// occupies a SIMD for 0.92 ns, a multiply with the clamp modifier 1.31, a fused multiply-add 1.56, a
-// median, a round or a conversion 1.74, an fp64 fused multiply-add 1.9; single-instruction loops), so
+// occupies a SIMD for 1.3 ns, a multiply with the clamp modifier 1.2, a median, a round or a conversion
+// 1.9, a fused multiply-add 2.0, in fp64 2.05; single-instruction loops), so
 // the clip is the free clamp to [0, 1] of the multiply by 1 / (qmax * scale), the rounding is the fused
 // multiply-add by qmax onto 2^23, and that biased code, with -2^23 * scale as the addend, gives the
 // rounded product scale * code in one fused multiply-add more.  The sequence with a median for the clip
-// and a round instruction (nine instructions) took 12.8 ns per element and candidate, this one takes 9.3;
+// and a round instruction (nine instructions) took 12.2 ns per element and candidate, this one takes 9.8
+// in a loop of its own and 9.2 here;
 // 1.5 M rows of 64, 199 candidates: 3.28 -> 2.70 ms.
 // The candidate's scale is range / (2^b - 1) correctly rounded (reciprocal multiply plus one FMA
 // residual step), 1 / (qmax * scale) likewise, and the quotient, three roundings in all, is within
