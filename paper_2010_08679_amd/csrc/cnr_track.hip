@@ -187,6 +187,9 @@ __global__ void __launch_bounds__(kSeenThreads) mark_flags_kernel(const TrackBat
 // workgroups of a team read the same part of the stream.  Workgroups are dealt to the eight XCDs in
 // turn along x and the number of parts is a multiple of eight, so x & 7 names both the part (mod 8)
 // and the XCD: a team shares its part of the stream through one L2 and memory is read once.
+// Where every table is one slice there is no team to share with, and STREAM reads with the non-temporal
+// hint: 8 tables of 1 M rows, 8.2 M look-ups each, from memory 167 -> 107 us, 1 M look-ups 49 -> 38 (with
+// teams of four it costs 20 %: 415 -> 502 us for 8 x 5 M rows, 20 M look-ups).
 // ---------------------------------------------------------------------------------------------
 constexpr int kSliceThreads = 1024;
 constexpr uint32_t kSliceWords = 40960;
@@ -211,7 +214,7 @@ inline uint32_t slice_parts_max(uint64_t n_rows) {
     return (uint32_t)(fit > kStreamPartsMax ? kStreamPartsMax : fit < kStreamParts ? kStreamParts : fit);
 }
 
-template <typename IdxT>
+template <typename IdxT, bool STREAM>
 __global__ void __launch_bounds__(kSliceThreads) mark_slices_kernel(const TrackBatch b, cnr_dev_errors *err) {
     constexpr int kVec = 16 / (int)sizeof(IdxT);
     typedef IdxT vec_t __attribute__((ext_vector_type(kVec)));
@@ -263,7 +266,7 @@ __global__ void __launch_bounds__(kSliceThreads) mark_slices_kernel(const TrackB
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
                 const uint64_t q = p + (uint64_t)u * kSliceThreads;
-                if (q < v1) v[u] = vecs[q];
+                if (q < v1) v[u] = STREAM ? load_stream<vec_t>(vecs + q) : vecs[q];
             }
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
@@ -612,6 +615,8 @@ cnr_status cnr_mark_touched_batch(cnr_ctx *ctx, const cnr_table_job *jobs, uint3
                                 (double)elig_sum_idx * kFlagPsPerLookup;
         TrackBatch slices = {}, bulk = {}, direct = {};
         uint32_t n_slices = 0, n_bulk = 0, n_direct = 0;
+        bool slices_one = true;     // every table of the slices route is one slice
+        uint64_t slices_bytes = 0;  // their streams in all
         uint64_t slices_words = 0, slices_team = 0, bulk_idx = 0, bulk_words = 0, direct_idx = 0;
         for (uint32_t i = first; i < n_jobs && i < first + CNR_MAX_BATCH; ++i) {
             const cnr_table_job &j = jobs[i];
@@ -630,6 +635,8 @@ cnr_status cnr_mark_touched_batch(cnr_ctx *ctx, const cnr_table_job *jobs, uint3
                 const uint32_t most = slice_parts_max(j.n_rows);
                 t.parts = want_parts < most ? want_parts : most;
                 if (team * t.parts > slices_team) slices_team = team * t.parts;
+                if (team > 1) slices_one = false;
+                slices_bytes += j.n_indices * (type == CNR_IDX_I64 ? 8u : 4u);
                 if (words > slices_words) slices_words = words;
             } else if (long_stream) {
                 if (j.n_indices > bulk_idx) bulk_idx = j.n_indices;
@@ -640,10 +647,16 @@ cnr_status cnr_mark_touched_batch(cnr_ctx *ctx, const cnr_table_job *jobs, uint3
         }
         if (n_slices) {
             const dim3 grid((unsigned)slices_team, n_slices);  // the most workgroups any table of the launch has
+            // Streams too long to be found in the memory-side cache (256 MB, and the tables pass through it too) are read
+            // past it; shorter ones may be there still, from the writer or from a mark before this one, and
+            // then the plain loads are the faster ones (64 MB found there: 34 against 36 us).
+            const bool stream = slices_one && slices_bytes >= (64ull << 20);
             if (type == CNR_IDX_I64)
-                hipLaunchKernelGGL(mark_slices_kernel<int64_t>, grid, dim3(kSliceThreads), 0, s, slices, ctx->dev_err);
+                hipLaunchKernelGGL((stream ? mark_slices_kernel<int64_t, true> : mark_slices_kernel<int64_t, false>), grid,
+                                   dim3(kSliceThreads), 0, s, slices, ctx->dev_err);
             else
-                hipLaunchKernelGGL(mark_slices_kernel<int32_t>, grid, dim3(kSliceThreads), 0, s, slices, ctx->dev_err);
+                hipLaunchKernelGGL((stream ? mark_slices_kernel<int32_t, true> : mark_slices_kernel<int32_t, false>), grid,
+                                   dim3(kSliceThreads), 0, s, slices, ctx->dev_err);
             if ((st = cnr_launch_status(ctx)) != CNR_OK) return st;
             slices.grid_x = batch_grid_x(ctx, slices_words, kBlock, 8, n_slices);
             hipLaunchKernelGGL(fold_slabs_kernel, dim3(slices.grid_x, n_slices), dim3(kBlock), 0, s, slices);

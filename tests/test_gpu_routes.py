@@ -302,3 +302,27 @@ def test_compaction_around_the_self_counting_limit(ctx, n_rows, shift):
         m = min(capacity, want.numel())
         assert torch.equal(ids[:m], want[:m]) and bool((ids[m:] == -1).all())
         _poll(ctx, 0 if capacity >= want.numel() else P.CNR_FLAG_CAPACITY)
+
+
+# ---- bulk mark of one-slice tables: streams from 64 MB on are read past the caches -------------------------
+
+@pytest.mark.parametrize("dtype,n_idx", [(torch.int64, 1_048_576), (torch.int64, 1_048_577), (torch.int32, 2_097_151), (torch.int32, 2_097_160)])
+@pytest.mark.parametrize("n_rows", [1_310_720, 200_001])
+def test_bulk_mark_around_the_streaming_limit(ctx, dtype, n_idx, n_rows):
+    tables, shift = 8, 3   # the streams start off a 16-byte boundary: head and tail elements
+    g = torch.Generator(device=DEV).manual_seed(n_idx)
+    cks = [P.TableCheckpointer(ctx, n_rows, 64, capacity=1, device=DEV, mark_scratch=P.TableCheckpointer.new_mark_scratch(n_rows)) for _ in range(tables)]
+    idx = [torch.randint(-2, n_rows + 2, (n_idx + shift,), generator=g, device=DEV).to(dtype)[shift:] for _ in range(tables)]
+    batch = P.BatchCheckpointer(ctx, cks)
+    batch.mark(idx)
+    bad = 0
+    for ck, t in zip(cks, idx):
+        inside = (t >= 0) & (t < n_rows)
+        bad += int((~inside).sum())
+        want = torch.zeros(32 * ck.bitmap.numel(), dtype=torch.bool, device=DEV)
+        want[t[inside].long()] = True
+        bits = ((ck.bitmap[:, None] >> torch.arange(32, device=DEV, dtype=torch.int32)) & 1).bool().reshape(-1)
+        assert torch.equal(bits, want)
+        assert not bool(ck.mark_scratch.any())
+    st, n_bad, flags = P.cnr_poll_errors(ctx)
+    assert (n_bad, flags) == (bad, 0)
