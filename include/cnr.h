@@ -100,7 +100,9 @@ typedef enum {
  * never lets the range collapse.  Each iteration tries [lo + step, hi] and [lo, hi - step], keeps
  * the one with the smaller squared l2 error (the lower bound moves only on a strictly smaller
  * error); the result is the range of the iteration with the smallest error, the un-shrunk range
- * included (an earlier iteration wins ties). */
+ * included (an earlier iteration wins ties).  Errors that differ by no more than the rounding of
+ * their fp64 sums (a relative min(dim, 72) * 2^-52) are equal, so that a tie does not depend on the
+ * list a row is in. */
 typedef struct {
     uint32_t num_bins;
     float ratio;

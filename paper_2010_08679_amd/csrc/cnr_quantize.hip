@@ -25,6 +25,7 @@ struct QuantArgs {
     int mode;
     uint32_t n_iter;   // greedy iterations
     float num_bins_f;  // greedy num_bins
+    double less;       // greedy: tie_factor(dim)
     float *scale, *bias, *row_min, *row_max;
     uint8_t *codes, *packed;
     cnr_dev_errors *err;
@@ -480,6 +481,17 @@ struct Candidate {
     }
 };
 
+// An error counts as the smaller of two when it is below tie_factor(dim) times the other.  Two candidate
+// ranges can have exactly the same error: where a step is a whole number of code steps, moving the range by
+// a step moves its grid onto itself, and the row's two ends, clipped by a step each, swap their errors.  The
+// fp64 sums of such a pair differ by their rounding alone, which depends on the lanes that a row is spread
+// over, that is on the length of the list; taken for a difference it gave the same row another range in a
+// longer list (rows with one far element at either end: 12 in 1000 of 16 floats at 2 bits and 4 bins, 2 of 200 at 3 and 12).  A sum has at most min(dim, 72) roundings
+// on its way in every kernel here (17 units in one lane, and the exchange between lanes), so equal sums are
+// found equal, and a tie moves the upper bound wherever the row is searched.  (CPU emulation, 120 K rows of
+// 4 to 1000 elements: sums that differ at all do so by more than 2^-47 of themselves.)
+inline double tie_factor(uint32_t dim) { return 1.0 - (double)(dim < 72u ? dim : 72u) * 0x1p-52; }
+
 // Whether a wave's rows (this lane's with range [lo, hi]) have to be searched with divisions, as F_Q is
 // written.  Scales outside [2^-100, 2^100] are: their reciprocals are no normal numbers.  So are narrow
 // rows: the bounds are moved by cumulative fp32 additions, each rounded to the spacing of the bounds'
@@ -594,11 +606,11 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L =
                 const float c_hi = cur_hi - step;
                 const double e_lo = row_err(c_lo, cur_hi);
                 const double e_hi = row_err(cur_lo, c_hi);
-                const bool move_lo = e_lo < e_hi;
+                const bool move_lo = e_lo < e_hi * a.less;
                 cur_lo = move_lo ? c_lo : cur_lo;
                 cur_hi = move_lo ? cur_hi : c_hi;
                 const double e = move_lo ? e_lo : e_hi;
-                if (e < best) {
+                if (e < best * a.less) {
                     best = e;
                     lo = cur_lo;
                     hi = cur_hi;
@@ -791,7 +803,7 @@ struct RowUnits {
     }
     // The search (header: cnr_greedy_params): [lo, hi] comes in as the row's range and leaves as the chosen one.
     template <int BITS, bool FAST>
-    __device__ __forceinline__ void search(uint32_t n_iter, float num_bins_f, float &lo, float &hi) const {
+    __device__ __forceinline__ void search(uint32_t n_iter, float num_bins_f, double less, float &lo, float &hi) const {
         float cur_lo = lo, cur_hi = hi;
         const float step = (hi - lo) / num_bins_f;
         const bool upper = DUAL && (tid_x() / L) & 1;  // this lane's group lowers the upper bound
@@ -815,11 +827,11 @@ struct RowUnits {
                 e_lo = e;
                 continue;
             }
-            const bool move_lo = e_lo < e;
+            const bool move_lo = e_lo < e * less;
             cur_hi = move_lo ? cur_hi : cur_hi - step;
             cur_lo = move_lo ? cur_lo + step : cur_lo;
             const double better = move_lo ? e_lo : e;
-            if (better < best) {
+            if (better < best * less) {
                 best = better;
                 lo = cur_lo;
                 hi = cur_hi;
@@ -859,9 +871,9 @@ quantize_greedy_units_kernel(const QuantArgs a, uint64_t n_from, uint64_t n_belo
         row.range(X_min, X_max);
         float lo = X_min, hi = X_max;
         if (search_divides(lo, hi, a.num_bins_f, QMAXF))
-            row.template search<BITS, false>(a.n_iter, a.num_bins_f, lo, hi);
+            row.template search<BITS, false>(a.n_iter, a.num_bins_f, a.less, lo, hi);
         else
-            row.template search<BITS, true>(a.n_iter, a.num_bins_f, lo, hi);
+            row.template search<BITS, true>(a.n_iter, a.num_bins_f, a.less, lo, hi);
 
         if constexpr (DUAL) live = live && !((lane / L) & 1);  // one of the row's two groups stores
         const float scale = (hi - lo) / QMAXF;
@@ -918,6 +930,7 @@ struct SelectArgs {
     uint32_t dim;
     const uint32_t *row_ids;
     uint64_t n;
+    double less;   // tie_factor(dim)
     double *sums;  // [parameters][workgroups along x]
     cnr_dev_errors *err;
     cnr_search_params params[kSearchBatch];
@@ -954,9 +967,9 @@ sample_error_kernel(const SelectArgs a) {
         row.range(lo, hi);
         if (n_iter) {
             if (search_divides(lo, hi, num_bins_f, QMAXF))
-                row.template search<BITS, false>(n_iter, num_bins_f, lo, hi);
+                row.template search<BITS, false>(n_iter, num_bins_f, a.less, lo, hi);
             else
-                row.template search<BITS, true>(n_iter, num_bins_f, lo, hi);
+                row.template search<BITS, true>(n_iter, num_bins_f, a.less, lo, hi);
         }
         const float scale = (hi - lo) / QMAXF;
         double e = 0.0;
@@ -1422,7 +1435,7 @@ cnr_status cnr_sample_errors(cnr_ctx *ctx, const float *table, uint64_t n_rows, 
         uint32_t m = n_params - done;
         if (m > kSearchBatch) m = kSearchBatch;
         if (m > max_sums) m = (uint32_t)max_sums;  // >= 1
-        SelectArgs a = {table, n_rows, dim, row_ids, n, sums, ctx->dev_err, {}};
+        SelectArgs a = {table, n_rows, dim, row_ids, n, tie_factor(dim), sums, ctx->dev_err, {}};
         for (uint32_t i = 0; i < m; ++i) a.params[i] = params[done + i];
         cnr_status st;
         switch (bits) {
@@ -1473,6 +1486,7 @@ cnr_status cnr_quantize_rows_batch(cnr_ctx *ctx, const cnr_table_job *jobs, uint
         a.n_dev = j.n_dirty_dev; a.n_max = m;
         a.mode = (int)mode; a.n_iter = n_iter;
         a.num_bins_f = mode == CNR_RANGE_GREEDY ? (float)greedy->num_bins : 1.0f;
+        a.less = tie_factor(dim);
         a.scale = j.scale + k0; a.bias = j.bias + k0;
         a.row_min = j.row_min ? j.row_min + k0 : nullptr;
         a.row_max = j.row_max ? j.row_max + k0 : nullptr;

@@ -8,7 +8,7 @@ import torch
 import oracle as O
 import paper_2010_08679_amd as P
 from paper_2010_08679_amd import synth
-from util_parity import GpuTable, compare_quantized, gpu_encode_all_outputs
+from util_parity import GpuTable, compare_greedy, compare_quantized, gpu_encode_all_outputs
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -203,6 +203,43 @@ def test_greedy_skips_ids_outside_the_table(ctx, dim, bits):
     keep = [k for k in range(n) if k not in bad]
     for o in out:
         assert bool((o[bad] == 0x5A).all()) and bool((o[keep] != 0x5A).any(1).all())
+
+
+# Exact ties: with qmax + 1 bins a step is one code step at the first move already, at 3 bits and 12 bins
+# after five (7 / (12 - 5) = 1), and these rows have nothing but their two ends beyond the bounds then; the
+# setting is the one whose tie lies at the best range of the row length (1 row in 100 to 1000).
+@pytest.mark.parametrize("dim,bits,bins,n,piece", [
+    (16, 2, 4, 60_000, 20_000), (64, 3, 8, 140_000, 12_000), (64, 3, 8, 140_000, 70_000), (256, 3, 12, 34_000, 6_000), (256, 3, 12, 34_000, 17_000),
+    (24, 2, 4, 60_000, 20_000), (48, 2, 4, 60_000, 20_000), (96, 3, 8, 60_000, 15_000), (200, 3, 12, 90_000, 15_000), (272, 3, 12, 24_000, 3_000),
+    (320, 3, 12, 24_000, 3_000)])
+def test_greedy_ranges_do_not_depend_on_the_list_length(ctx, dim, bits, bins, n, piece):
+    print("case greedy ties dim=%d n=%d piece=%d" % (dim, n, piece), flush=True)
+    g = torch.Generator(device=DEV).manual_seed(dim)
+    table = torch.empty(n, dim, device=DEV).normal_(0, 0.02, generator=g)
+    for half, sign in ((0, 1.0), (dim // 2, -1.0)):
+        col = half + torch.randint(0, dim // 2, (n,), generator=g, device=DEV)
+        table[torch.arange(n, device=DEV), col] = torch.empty(n, device=DEV).uniform_(0.1, 0.12, generator=g) * sign
+    prb = P.cnr_packed_row_bytes(dim, bits)
+
+    def encode(parts):
+        scale, bias, packed = torch.empty(n, device=DEV), torch.empty(n, device=DEV), torch.empty(n * prb, dtype=torch.uint8, device=DEV)
+        for a, b in parts:   # whole multiples of 16 rows: aligned pieces of the buffers
+            P.cnr_quantize_rows(ctx, table[a:b], b - a, dim, None, None, b - a, bits, P.CNR_RANGE_GREEDY, (bins, 1.0), scale[a:b], bias[a:b],
+                                packed=packed[a * prb:b * prb])
+        return scale, bias, packed
+
+    piece &= ~15
+    whole = encode([(0, n)])
+    for w, p, what in zip(whole, encode([(a, min(n, a + piece)) for a in range(0, n, piece)]), ("scale", "bias", "packed")):
+        assert torch.equal(w, p), "%s: %d of %d differ" % (what, int((w != p).sum()), w.numel())
+    pos = np.arange(0, n, max(1, n // 6000))
+    rows = table[torch.from_numpy(pos).to(DEV)].cpu().numpy()
+    ora = O.quantize_rows(rows, None, bits, mode=O.RANGE_GREEDY, num_bins=bins, ratio=1.0, n_threads=8)
+    got = dict(scale=whole[0].cpu().numpy()[pos], bias=whole[1].cpu().numpy()[pos], row_min=ora["row_min"], row_max=ora["row_max"],
+               codes=O.unpack(whole[2].view(n, prb)[torch.from_numpy(pos).to(DEV)].cpu().numpy(), dim, bits))
+    ties = compare_greedy(rows, got, ora, bits, bins, 1.0, what="greedy ties d%d" % dim)
+    print("rows whose tie the oracle decided by rounding: %d" % ties, flush=True)
+    _poll(ctx)
 
 
 # ---- min/max and symmetric ranges at row lengths that are no power of two: every shape's first and last -

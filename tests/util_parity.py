@@ -97,6 +97,56 @@ def assert_near_ties(rows: np.ndarray, ora: dict, diff: np.ndarray, what=""):
     return int(np.count_nonzero(diff))
 
 
+def replay_search(rows: np.ndarray, bits: int, num_bins: int, ratio: float):
+    """The greedy search of cnr_greedy_params with its errors added up exactly (squares of fp32 differences
+    have 48 bits, the sums 64), where errors that differ by min(dim, 72) * 2^-52 or less are equal.  Returns
+    lo, hi and whether the row met such a tie between errors that a strict comparison could tell apart."""
+    f = np.float32
+    n, dim = rows.shape
+    qmax = f((1 << bits) - 1)
+    less = np.longdouble(1.0 - min(dim, 72) * 2.0 ** -52)
+
+    def sq(lo, hi):
+        s = ((hi - lo) / qmax)[:, None]
+        c = np.minimum(np.maximum(rows, lo[:, None]), hi[:, None])
+        q = np.clip(np.rint((c - lo[:, None]) / np.where(s == 0, f(1), s)), f(0), qmax)
+        q = np.where(s == 0, f(0), q)
+        d = (rows - ((s * q).astype(f) + lo[:, None]).astype(f)).astype(np.float64)
+        return np.sum((d * d).astype(np.longdouble), axis=1)
+
+    cur_lo, cur_hi = rows.min(axis=1) + f(0), rows.max(axis=1) + f(0)
+    lo, hi = cur_lo.copy(), cur_hi.copy()
+    step = (hi - lo) / f(num_bins)
+    best = sq(lo, hi)
+    tied = np.zeros(n, dtype=bool)
+    for _ in range(int(min(max(np.ceil(float(f(ratio)) * num_bins - 1e-4), 0), num_bins - 1))):
+        c_lo, c_hi = cur_lo + step, cur_hi - step
+        e_lo, e_hi = sq(c_lo, cur_hi), sq(cur_lo, c_hi)
+        move = e_lo < e_hi * less
+        tied |= ~move & (e_lo <= e_hi / less)
+        cur_lo, cur_hi = np.where(move, c_lo, cur_lo), np.where(move, cur_hi, c_hi)
+        e = np.where(move, e_lo, e_hi)
+        better = e < best * less
+        tied |= ~better & (e <= best / less)
+        best, lo, hi = np.where(better, e, best), np.where(better, cur_lo, lo), np.where(better, cur_hi, hi)
+    return lo, hi, tied
+
+
+def compare_greedy(host_rows: np.ndarray, gpu: dict, ora: dict, bits: int, num_bins: int, ratio: float, what=""):
+    """compare_quantized for a greedy search that can meet exact ties, which the oracle's strict comparison of
+    rounded sums decides by their rounding: a row with another range than the oracle's is left out if its
+    search, replayed with exact sums, meets a tie and ends in the range the GPU found.  Returns their number."""
+    differ = np.flatnonzero((ulp_distance(gpu["scale"], ora["scale"]) > 1) | (ulp_distance(gpu["bias"], ora["bias"]) > 1))
+    keep = np.ones(host_rows.shape[0], dtype=bool)
+    if differ.size:
+        lo, hi, tied = replay_search(host_rows[differ], bits, num_bins, ratio)
+        scale = (hi - lo) / np.float32((1 << bits) - 1)
+        keep[differ] = ~(tied & (lo == gpu["bias"][differ]) & (ulp_distance(scale, gpu["scale"][differ]) <= 1))
+    sub = lambda d: {k: d[k][keep] for k in ("scale", "bias", "row_min", "row_max", "codes")}  # noqa: E731
+    compare_quantized(host_rows[keep], sub(gpu), sub(ora), bits, greedy=True, what=what)
+    return int(np.count_nonzero(~keep))
+
+
 def gpu_encode_all_outputs(gt: GpuTable, bits: int, mode=P.CNR_RANGE_MINMAX, greedy=None,
                            row_ids: torch.Tensor | None = "compact", n: int | None = None):
     """Runs cnr_quantize_rows with every optional output on; returns host arrays for n rows."""
