@@ -10,8 +10,9 @@ namespace {
 
 size_t align16(size_t v) { return (v + 15u) & ~(size_t)15u; }
 
-// The caller's scratch: room for the sample's scales, biases, packed codes and errors and for a mean,
-// each 16-byte aligned; partial sums of errors are what it is used for.
+// The caller's scratch.  Only partial sums of errors go there, at most one per workgroup and point (fewer
+// points or workgroups take part where a small sample's scratch holds fewer); its size, one encoded sample
+// with its errors, is part of the interface and stays as it was.
 size_t scratch_bytes(uint64_t n, uint32_t dim, int bits) {
     return 2 * align16(n * sizeof(float)) + align16(n * cnr_packed_row_bytes(dim, bits)) + align16(n * sizeof(double)) + 16;
 }
@@ -65,7 +66,9 @@ cnr_status cnr_select_greedy_params(cnr_ctx *ctx, const float *table, uint64_t n
         cnr_status r = cnr_sample_errors(ctx, table, n_rows, dim, sample_ids, n_sample, bits, points, m,
                                          static_cast<double *>(scratch), scratch_bytes(n_sample, dim, bits) / sizeof(double),
                                          ctx->host_means, hs);
-        return r != CNR_OK ? r : cnr_hip_status(ctx, hipStreamSynchronize(hs));
+        // also when a launch failed: those before it still write the scratch and the context's means
+        const hipError_t e = hipStreamSynchronize(hs);
+        return r != CNR_OK ? r : cnr_hip_status(ctx, e);
     };
 
     points[0] = {0, 1.0f};  // min/max
