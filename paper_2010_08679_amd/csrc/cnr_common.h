@@ -45,6 +45,14 @@ struct cnr_search_params {
     float num_bins_f;
 };
 constexpr uint32_t kSearchBatch = 32;  // points per launch
+// Index of the last error that a lane evaluates in a search of n_iter iterations: 0 is the un-shrunk range's,
+// then come an iteration's two in turn, or one of them where two groups of lanes go side by side.  64 bits
+// where n_iter may be any number; searches of up to 2^20 bins, the ones that do not divide, count in 32.
+template <typename Count>
+constexpr Count last_candidate(uint32_t n_iter, bool side_by_side) {
+    return side_by_side ? (Count)n_iter : 2 * (Count)n_iter;
+}
+constexpr float kFastSearchBins = 0x1p20f;
 // mean_out[p] (device-accessible) = mean l2 error of rows row_ids[0 .. n) quantized with params[p].
 // sums: device, max_sums >= 1 doubles.  Arguments are checked by the caller.
 cnr_status cnr_sample_errors(cnr_ctx *ctx, const float *table, uint64_t n_rows, uint32_t dim, const uint32_t *row_ids,

@@ -505,7 +505,7 @@ __device__ __forceinline__ bool search_divides(float lo, float hi, float num_bin
     const float mag = fmaxf(fabsf(lo), fabsf(hi));
     const bool narrow = hi != lo && (hi - lo) < num_bins_f * num_bins_f * (mag * 0x1p-23f);
     // the last candidates are up to num_bins times narrower than the first
-    return __builtin_amdgcn_ballot_w64(odd_scale || narrow) != 0 || num_bins_f > 0x1p20f;
+    return __builtin_amdgcn_ballot_w64(odd_scale || narrow) != 0 || num_bins_f > kFastSearchBins;
 }
 
 // The 24 code bits of a pair of units at 3 bits.
@@ -808,7 +808,8 @@ struct RowUnits {
         const float step = (hi - lo) / num_bins_f;
         const bool upper = DUAL && (tid_x() / L) & 1;  // this lane's group lowers the upper bound
         double best = 0.0, e_lo = 0.0;
-        for (uint32_t c = 0; c <= (DUAL ? n_iter : 2 * n_iter); ++c) {
+        using Count = std::conditional_t<FAST, uint32_t, uint64_t>;
+        for (Count c = 0; c <= last_candidate<Count>(n_iter, DUAL); ++c) {
             const bool first = c == 0;                               // uniform
             const bool raise = !first && (DUAL ? !upper : (c & 1));  // uniform, but for DUAL
             const bool lower = !first && !raise;

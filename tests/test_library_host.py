@@ -157,6 +157,21 @@ def test_header_is_plain_c_and_every_export_links(tmp_path):
     assert n == len(binding.EXPORTS)
 
 
+def test_a_search_of_any_length_is_counted_to_its_end(tmp_path):
+    # num_bins, and with it the number of iterations, goes up to 2**32 - 1: twice that many candidates.  The
+    # counter has 64 bits where num_bins is not bounded, and 32 bits are enough where it is
+    import subprocess
+    csrc = os.path.join(ROOT, "paper_2010_08679_amd", "csrc")
+    text = open(os.path.join(csrc, "cnr_quantize.hip")).read()
+    assert "using Count = std::conditional_t<FAST, uint32_t, uint64_t>;" in text and "num_bins_f > kFastSearchBins" in text
+    src = tmp_path / "last.cpp"
+    src.write_text('#include "cnr_common.h"\nstatic_assert(kFastSearchBins <= 2147483648.0f, "");\n' + "".join(
+        "static_assert(last_candidate<uint64_t>(%uu, %s) == %uull, \"\");\n" % (n, "true" if dual else "false", n if dual else 2 * n)
+        for n in (0, 1, 99, 2 ** 31 - 1, 2 ** 31, 2 ** 32 - 2) for dual in (False, True)))
+    subprocess.check_call(["g++", "-std=c++17", "-fsyntax-only", "-D__HIP_PLATFORM_AMD__", "-isystem", "/opt/rocm/include",
+                           "-I", os.path.join(ROOT, "include"), "-I", csrc, str(src)])
+
+
 def test_parameter_selection_waits_for_its_kernels_when_a_launch_fails(tmp_path):
     import subprocess
     exe = str(tmp_path / "select_check")
