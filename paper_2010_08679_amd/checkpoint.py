@@ -141,14 +141,16 @@ class BatchCheckpointer:
                     capacity=c.capacity, n_dirty_dev=c.n_dirty, compact_scratch=c.scratch)
 
     @staticmethod
-    def _check_rows(i, c, table, o):
-        if table is not None and table.numel() < c.n_rows * c.dim:
+    def _check_table(i, c, table):
+        if table.numel() < c.n_rows * c.dim:
             raise ValueError("table %d smaller than n_rows * dim" % i)
-        if o is not None:
-            cap = max(1, c.capacity)
-            if (o.scale.numel() < cap or o.bias.numel() < cap
-                    or o.packed.numel() < cap * B.cnr_packed_row_bytes(c.dim, o.bits)):
-                raise ValueError("output %d too small for the table's capacity" % i)
+
+    @staticmethod
+    def _check_output(i, c, o):
+        cap = max(1, c.capacity)
+        if (o.scale.numel() < cap or o.bias.numel() < cap
+                or o.packed.numel() < cap * B.cnr_packed_row_bytes(c.dim, o.bits)):
+            raise ValueError("output %d too small for the table's capacity" % i)
 
     def jobs(self, indices=None, tables=None, outs=None):
         """The job array for these tables; ``indices`` / ``tables`` / ``outs`` are per-table lists
@@ -158,11 +160,12 @@ class BatchCheckpointer:
             d = self._track_fields(c)
             if indices is not None and indices[i] is not None:
                 d["indices"] = indices[i].reshape(-1)
-            self._check_rows(i, c, tables[i] if tables is not None else None, outs[i] if outs is not None else None)
             if tables is not None:
+                self._check_table(i, c, tables[i])
                 d["table"] = tables[i]
             if outs is not None:
                 o = outs[i]
+                self._check_output(i, c, o)
                 d.update(scale=o.scale, bias=o.bias, row_min=o.row_min, row_max=o.row_max, packed=o.packed)
             jobs.append(d)
         return B.make_jobs(jobs)
@@ -200,7 +203,8 @@ class BatchCheckpointer:
         rows = []
         for i, c in enumerate(self.cks):
             t, o = tables[i], outs[i]
-            self._check_rows(i, c, t, o)
+            self._check_table(i, c, t)
+            self._check_output(i, c, o)
             rows.append((B._ptr(t, B.F32, "table"), c.n_rows, 0, 0, 0, 0, B._ptr(c.row_ids, B.U32, "row_ids"), c.capacity,
                          B._ptr(c.n_dirty, B.U64, "n_dirty_dev"), 0, B._ptr(o.scale, B.F32, "scale"),
                          B._ptr(o.bias, B.F32, "bias"), B._ptr(o.row_min, B.F32, "row_min"),

@@ -245,3 +245,18 @@ def test_packed_jobs_hold_the_struct_fields_in_order():
             assert [getattr(job, f) for f in fields] == list(rows[i])
     empty = binding.pack_jobs([(0,) * len(fields)])[0]
     assert all(not getattr(empty, f) for f in fields)
+
+
+def test_a_batch_refuses_a_missing_table_or_output():
+    # also where the table's capacity is 0 and the library would not look at it
+    ck = P.TableCheckpointer(None, 100, 8, capacity=0, device="cpu")
+    batch, out = P.BatchCheckpointer(None, [ck]), ck.alloc_output(4)
+    for call in (lambda: batch.encode([None], [out]), lambda: batch.restore([None], [out]), lambda: batch.jobs(tables=[None]),
+                 lambda: batch.jobs(outs=[None]), lambda: batch.encode([torch.zeros(100, 8)], [None])):
+        with pytest.raises(AttributeError):
+            call()
+    with pytest.raises(ValueError):
+        batch.encode([torch.zeros(99, 8)], [out])
+    out.packed = out.packed[:-1]
+    with pytest.raises(ValueError):
+        batch.restore([torch.zeros(100, 8)], [out])
