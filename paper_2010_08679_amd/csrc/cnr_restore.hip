@@ -390,7 +390,10 @@ void launch_restore(cnr_ctx *ctx, hipStream_t st, uint32_t dim, RestoreJob &a) {
 // (row w * rows_per_wg for workgroup w); one workgroup then adds up the partial sums, and a last launch
 // of the same kernel over just those rows puts their errors there.  Everything happens in the caller's
 // buffer, on the caller's stream.  Lists of up to kDirectMeanRows are added up by one workgroup as they
-// are: below that, it takes no longer than the two launches it saves.
+// are: below that, it takes no longer than the two launches it saves.  Where the length is a count on the
+// device and the capacity allows more, the three launches are there, and the kernels tell by the count: up to
+// kPartsRows rows are added up as they are and the last launch leaves at once (lists of 100 rows of 64
+// 10.8 -> 7.9 us, of 2,000 13.6 -> 11.3; of 16,000 it would lose 1 us).
 // ---------------------------------------------------------------------------------------------
 struct ErrorArgs {
     const float *table;
@@ -403,13 +406,21 @@ struct ErrorArgs {
     const float *scale, *bias;
     double *err;
     uint64_t stride;     // the launch covers rows 0, stride, 2 * stride, ... of the list
-    uint32_t partials;   // leave the workgroup's sum in the place of its first row's error
+    uint64_t cover;      // ... below this one
+    uint32_t parts;      // of a list of more than kPartsRows rows: leave the workgroup's sum in the place of its first row's error
     cnr_dev_errors *dev_err;
 };
-constexpr uint64_t kDirectMeanRows = 16384;
+constexpr uint64_t kDirectMeanRows = 16384, kPartsRows = 8192;
 // Workgroups of the error kernel at most, each with a partial sum: 2048 to 4096 are equally fast on 1.5 M
 // rows of 64 (108 us with the mean), 8192 cost more in the two launches behind it than they gain (115 us).
 constexpr unsigned kErrorMaxBlocks = 4096;
+
+// Rows of the list that a launch works on, of n in all: none where it is the last of three (stride > 1) and
+// the list turned out too short for partial sums.
+__device__ __forceinline__ uint64_t error_items(const ErrorArgs &a, uint64_t n) {
+    if (a.stride > 1 && n <= kPartsRows) return 0;
+    return ((n < a.cover ? n : a.cover) + a.stride - 1) / a.stride;
+}
 
 // sum = this lane's share of what the workgroup's rows came to: the workgroup's total into err[first]
 // by thread 0, whose own earlier store to that place is ahead of it in program order.
@@ -425,21 +436,21 @@ __device__ __forceinline__ void leave_partial_sum(double sum, double *err, uint6
     }
 }
 
-// Rows of whole 16-byte units (dim % 4 == 0, table and codes 16-byte aligned): LPR lanes per row, lane j
-// takes the units j, j + LPR, ... of its row and their codes.  A wave holds kErrorSteps rows per lane
-// group at once, so that as many row loads are in flight per lane.  Bound by the gather of the rows
+// Rows of whole 16-byte units (dim % 4 == 0, table 16-byte, codes 4-byte aligned): LPR lanes per row, lane j
+// takes the units j, j + LPR, ... of its row and their codes.  A wave holds ST rows per lane group at once,
+// so that as many row loads are in flight per lane.  Bound by the gather of the rows
 // (fp64: two conversions, a subtraction and a fused multiply-add per element, a quarter of the time).
 // 1.5 M rows of 64 at 4 bits: a wave per row with byte loads 332 us, this 93 us (5.0 TB/s); with the mean
-// 2018 -> 107 us.
+// 2018 -> 107 us.  Short lists are bound by the chain of loads of one row and by the fetch of the kernel's own
+// code: up to kShortErrorRows rows go with ST = 1, several units of a lane in flight instead.  A row's sum is
+// formed in the same order either way.  Returns this lane's share of the sum of the errors.
 constexpr int kErrorSteps = 4;
-template <int LPR, int BITS>
-__global__ void __launch_bounds__(kBlock) quant_error_units_kernel(const ErrorArgs a) {
-    constexpr int ST = kErrorSteps;
+constexpr uint64_t kShortErrorRows = 128;
+template <int LPR, int ST, int BITS>
+__device__ __forceinline__ double error_rows(const ErrorArgs &a, uint64_t items) {
     constexpr int RPS = kWave / LPR;         // rows per step
     constexpr uint64_t GROUP = RPS * ST;     // rows per wave and pass
     constexpr uint32_t MASK = (1u << BITS) - 1u;
-    const uint64_t n = live_rows(a.n_dev, a.n_max);
-    const uint64_t items = (n + a.stride - 1) / a.stride;
     const uint32_t n4 = a.dim / 4;
     const uint64_t P = (uint64_t)a.dim * BITS / 8;
     const int lane = tid_x() & (kWave - 1);
@@ -483,6 +494,7 @@ __global__ void __launch_bounds__(kBlock) quant_error_units_kernel(const ErrorAr
             acc[t] = 0.0;
         }
         if ((pass + n_waves) * GROUP < items) fetch(pass + n_waves);
+#pragma unroll(ST == 1 ? 4 : 1)
         for (uint32_t u0 = 0; u0 < n4; u0 += LPR) {
             const uint32_t u = u0 + j;
             const bool mine = u < n4;
@@ -525,6 +537,8 @@ __global__ void __launch_bounds__(kBlock) quant_error_units_kernel(const ErrorAr
             v += dpp_d<0x4E>(v);
             if constexpr (LPR >= 8) v += dpp_d<0x141>(v);
             if constexpr (LPR >= 16) v += dpp_d<0x140>(v);
+            if constexpr (LPR >= 32) v += __shfl_xor(v, 16);
+            if constexpr (LPR >= 64) v += __shfl_xor(v, 32);
             if (j == (uint32_t)t) {
                 mine = v;
                 ok = in_table[t];
@@ -537,7 +551,20 @@ __global__ void __launch_bounds__(kBlock) quant_error_units_kernel(const ErrorAr
             sum += e;
         }
     }
-    if (a.partials) leave_partial_sum(sum, a.err, (uint64_t)wg_x() * kWavesPerBlock * GROUP, n);
+    return sum;
+}
+template <int LPR, int BITS>
+__global__ void __launch_bounds__(kBlock) quant_error_units_kernel(const ErrorArgs a) {
+    static_assert(kShortErrorRows <= kPartsRows, "a list with partial sums is no short one");
+    const uint64_t n = live_rows(a.n_dev, a.n_max);
+    const uint64_t items = error_items(a, n);
+    if (n <= kShortErrorRows) {
+        (void)error_rows<LPR, 1, BITS>(a, items);
+        return;
+    }
+    const double sum = error_rows<LPR, kErrorSteps, BITS>(a, items);
+    constexpr uint64_t GROUP = (uint64_t)(kWave / LPR) * kErrorSteps;
+    if (a.parts && n > kPartsRows) leave_partial_sum(sum, a.err, (uint64_t)wg_x() * kWavesPerBlock * GROUP, n);
 }
 
 // Any other dim or alignment: one wavefront per row.
@@ -545,7 +572,7 @@ template <int BITS>
 __global__ void __launch_bounds__(kBlock) quant_error_kernel(const ErrorArgs a) {
     constexpr uint32_t MASK = (1u << BITS) - 1u;
     const uint64_t n = live_rows(a.n_dev, a.n_max);
-    const uint64_t items = (n + a.stride - 1) / a.stride;
+    const uint64_t items = error_items(a, n);
     const int lane = tid_x() & (kWave - 1);
     const uint64_t n_waves = (uint64_t)grid_x() * kWavesPerBlock;
     const uint64_t P = (uint64_t)a.dim * BITS / 8;
@@ -579,19 +606,20 @@ __global__ void __launch_bounds__(kBlock) quant_error_kernel(const ErrorArgs a) 
             sum += e;
         }
     }
-    if (a.partials) leave_partial_sum(sum, a.err, (uint64_t)wg_x() * kWavesPerBlock, n);
+    if (a.parts && n > kPartsRows) leave_partial_sum(sum, a.err, (uint64_t)wg_x() * kWavesPerBlock, n);
 }
 
-// (1/n) * the sum of v[0], v[stride], v[2 * stride], ..., at most `most` of them (the row errors
-// themselves, or the partial sums of the error kernel's workgroups), by one workgroup.
+// (1/n) * the sum of v[0], v[stride], v[2 * stride], ..., at most `most` of them (the partial sums of the error
+// kernel's workgroups), or of all n row errors where the list is too short for partial sums; by one workgroup.
 constexpr int kMeanThreads = 1024;
 __global__ void __launch_bounds__(kMeanThreads) mean_kernel(const double *__restrict__ v, uint64_t stride, uint64_t most,
                                                             const uint64_t *__restrict__ n_dev, uint64_t n_max,
                                                             double *__restrict__ mean_out) {
     __shared__ double part[kMeanThreads];
     const uint64_t n = live_rows(n_dev, n_max);
+    if (n <= kPartsRows) stride = 1;
     uint64_t items = (n + stride - 1) / stride;
-    if (items > most) items = most;
+    if (stride > 1 && items > most) items = most;
     double acc = 0.0;
     for (uint64_t i = tid_x(); i < items; i += kMeanThreads) acc += v[i * stride];
     part[tid_x()] = acc;
@@ -609,6 +637,8 @@ void launch_error_bits(const ErrorArgs &a, unsigned grid, uint32_t lanes, hipStr
         case 4: hipLaunchKernelGGL((quant_error_units_kernel<4, BITS>), dim3(grid), dim3(kBlock), 0, s, a); break;
         case 8: hipLaunchKernelGGL((quant_error_units_kernel<8, BITS>), dim3(grid), dim3(kBlock), 0, s, a); break;
         case 16: hipLaunchKernelGGL((quant_error_units_kernel<16, BITS>), dim3(grid), dim3(kBlock), 0, s, a); break;
+        case 32: hipLaunchKernelGGL((quant_error_units_kernel<32, BITS>), dim3(grid), dim3(kBlock), 0, s, a); break;
+        case 64: hipLaunchKernelGGL((quant_error_units_kernel<64, BITS>), dim3(grid), dim3(kBlock), 0, s, a); break;
         default: hipLaunchKernelGGL((quant_error_kernel<BITS>), dim3(grid), dim3(kBlock), 0, s, a); break;
     }
 }
@@ -622,11 +652,13 @@ void launch_error(const ErrorArgs &a, unsigned grid, uint32_t lanes, int bits, h
 }
 
 // Lanes per row of the error kernel: of 16, 8 and 4 the one that leaves the fewest idle lanes in the
-// last trip through a row (the most lanes among equals: wider runs per load instruction); 0 = one wave
-// per row, for rows that are not whole aligned 16-byte units.
+// last trip through a row (the most lanes among equals: wider runs per load instruction).  Beyond 512 and 1024
+// elements 32 and 64: the trips through a row follow each other, and sixteen lanes would make up to 64.
+// 0 = one wave per row, for rows that are not whole aligned 16-byte units.
 uint32_t error_lanes(uint32_t dim, const void *table, const void *packed) {
     if (dim % 4 || (uintptr_t)table % 16 || (uintptr_t)packed % 4) return 0;
     const uint32_t n4 = dim / 4;
+    if (n4 > 128) return n4 > 256 ? 64 : 32;
     uint32_t best = 16;
     for (uint32_t l : {8u, 4u})
         if ((n4 + l - 1) / l * l < (n4 + best - 1) / best * best) best = l;
@@ -651,26 +683,26 @@ extern "C" cnr_status cnr_quant_error(cnr_ctx *ctx, const float *table, uint64_t
         if (!table || !packed || !scale || !bias || !err || n_rows == 0 || n_rows >= (1ull << 32)) return CNR_E_INVALID;
         const uint32_t lanes = error_lanes(dim, table, packed);
         const uint64_t rows_per_wg = (lanes ? (uint64_t)kErrorSteps * (kWave / lanes) : 1u) * kWavesPerBlock;
-        ErrorArgs a = {table, n_rows, dim, row_ids, n_dev, n_max, packed, scale, bias, err, 1, 0, ctx->dev_err};
-        auto grid_for = [&](uint64_t rows) {
-            const uint64_t need = (rows + rows_per_wg - 1) / rows_per_wg;
-            return (unsigned)(need < kErrorMaxBlocks ? need : kErrorMaxBlocks);
+        ErrorArgs a = {table, n_rows, dim, row_ids, n_dev, n_max, packed, scale, bias, err, 1, ~0ull, 0, ctx->dev_err};
+        auto grid_for = [&](uint64_t rows) {  // of a short list of the units kernel, a wave holds fewer rows
+            const uint64_t few = rows < kShortErrorRows ? rows : kShortErrorRows, few_per_wg = lanes ? rows_per_wg / kErrorSteps : rows_per_wg;
+            const uint64_t need = (rows + rows_per_wg - 1) / rows_per_wg, need_few = (few + few_per_wg - 1) / few_per_wg;
+            const uint64_t most = need > need_few ? need : need_few;
+            return (unsigned)(most < kErrorMaxBlocks ? most : kErrorMaxBlocks);
         };
         const unsigned grid = grid_for(n_max);
         const bool by_parts = mean_out && n_max > kDirectMeanRows;
-        a.partials = by_parts ? 1 : 0;
+        a.parts = by_parts ? 1 : 0;
         launch_error(a, grid, lanes, bits, s);
         if ((st = cnr_launch_status(ctx)) != CNR_OK) return st;
         if (by_parts) {
             hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(kMeanThreads), 0, s, err, rows_per_wg, (uint64_t)grid, n_dev, n_max, mean_out);
             if ((st = cnr_launch_status(ctx)) != CNR_OK) return st;
             // the first row of every workgroup again, whose place held the workgroup's sum
-            const uint64_t firsts = grid;
-            const uint64_t covered = firsts * rows_per_wg;  // rows behind it are no workgroup's first
-            a.partials = 0;
+            a.parts = 0;
             a.stride = rows_per_wg;
-            if (covered < n_max) a.n_max = covered;
-            launch_error(a, grid_for(firsts), lanes, bits, s);
+            a.cover = grid * rows_per_wg;  // rows behind it are no workgroup's first
+            launch_error(a, grid_for(grid), lanes, bits, s);
             return cnr_launch_status(ctx);
         }
     }

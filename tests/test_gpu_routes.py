@@ -48,7 +48,8 @@ def _ids(n_rows, n, seed):
     (64, 4, 1, 0), (64, 3, 63, 0), (64, 2, 16_384, 0), (64, 8, 16_385, 0), (64, 2, 600_001, 0),   # 16 lanes per row; past the grid's cap
     (24, 3, 20_011, 0), (20, 2, 40_003, 0), (40, 3, 16_400, 0),                                  # 8 lanes
     (12, 4, 70_001, 0), (4, 8, 16_641, 0), (4, 2, 300, 0),                                       # 4 lanes
-    (100, 2, 17_001, 0), (96, 3, 33_000, 0), (516, 4, 16_500, 0),                                # several trips, the last one partial
+    (100, 2, 17_001, 0), (96, 3, 33_000, 0), (512, 4, 16_500, 0),                                # several trips, the last one partial
+    (516, 4, 16_500, 0), (1024, 3, 16_500, 0), (1028, 2, 16_500, 0), (4096, 8, 5_000, 0),        # 32 and 64 lanes
     (64, 4, 20_001, 1), (64, 4, 500, 1), (6, 4, 40_001, 0),                                      # a wave per row: unaligned table, odd dim
 ])
 def test_error_metric_routes(ctx, dim, bits, n, shift):
@@ -71,7 +72,9 @@ def test_error_metric_routes(ctx, dim, bits, n, shift):
         table = moved.copy_(table)
     back = _unpack(packed, n, dim, bits) * scale[:, None] + bias[:, None]
     want = (table[ids.long()].double() - back.double()).square().sum(1).sqrt()
-    for live in sorted({n, max(1, n - 777), n // 2, 0}):       # the count on the device
+    # the count on the device: either side of a short list and of one with partial sums
+    first = None
+    for live in sorted({n, max(1, n - 777), n // 2, 0} | {k for k in (1, 128, 129, 8192, 8193, 16_384, 16_385) if k <= n}):
         n_dev = torch.tensor([live], dtype=torch.int64, device=DEV)
         err = torch.full((n,), -1.0, dtype=torch.float64, device=DEV)
         mean = torch.full((1,), -1.0, dtype=torch.float64, device=DEV)
@@ -86,6 +89,9 @@ def test_error_metric_routes(ctx, dim, bits, n, shift):
         plain = torch.full((n,), -1.0, dtype=torch.float64, device=DEV)
         P.cnr_quant_error(ctx, table, n_rows, dim, ids, n_dev, n, bits, packed, scale, bias, plain, None)
         assert torch.equal(plain, err)                         # without a mean: the same errors
+        if live >= 128:                                        # and in lists of other lengths
+            first = err[:128].clone() if first is None else first
+            assert torch.equal(err[:128], first)
     _poll(ctx)
 
 
