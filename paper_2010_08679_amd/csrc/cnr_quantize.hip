@@ -1015,7 +1015,7 @@ __global__ void __launch_bounds__(kBlock) sample_mean_kernel(const double *sums,
 
 // ---------------------------------------------------------------------------------------------
 // Other row lengths, min/max and symmetric range.  Same arithmetic as the tile kernel; bound by the
-// memory traffic.
+// memory traffic, on short lists by the chain of one row's loads and the fetch of the kernel's own code.
 //
 // Up to 512 elements (quantize_units_kernel): LPR lanes per row, U 16-byte units of it per lane (unit j +
 // LPR * t, so that a load instruction reads 16 * LPR contiguous bytes per row), read once and held in
@@ -1027,8 +1027,11 @@ __global__ void __launch_bounds__(kBlock) sample_mean_kernel(const double *sums,
 // stored by twos of bytes 130 us, this 66 us (5.1 TB/s); rows
 // of 8 to 512 elements 1.3 to 2.5 times as fast.
 //
-// Longer rows (quantize_strided_kernel): a wave per row, which reads it twice, for its range and to
-// quantize, the second time from cache; its stores are runs of at least 16 bytes.
+// Longer rows, and short lists: one row (or 64 / LPR short ones) per wave and pass (encode_strided).  It fills
+// the chip sooner and is less code, but it reads a row twice and its last trip through a row stores as little as
+// one unit, 1 to 4 bytes.  On lists of up to 6144 waves of it (SHORT_ROWS: 98 K rows of 4 to 16 elements, 6 K of more than 128) the units
+// kernel goes that way itself, whether the host knows the length or not: 1 K rows of 24 / 96 / 200
+// elements 3.4 / 3.2 / 4.3 us in units, 2.7 / 2.8 / 3.0 this way; 16 K rows of 96 3.8 and 4.5.
 // ---------------------------------------------------------------------------------------------
 // Code of one element, biased by the pattern of 1.5 * 2^23 (see the tile kernel).
 template <int BITS>
@@ -1052,6 +1055,73 @@ __device__ __forceinline__ uint32_t unit_codes(const f32x4 &v, float lo, float f
     return (m << BITS) + b0 - MERGED_BIAS;
 }
 
+// LPR lanes per row, 64 / LPR rows per wave and pass; the row is read twice, for its range and to quantize, the
+// second time from cache, and its codes go straight to memory.
+template <int LPR, int BITS>
+__device__ __forceinline__ void encode_strided(const QuantArgs &a, uint64_t n) {
+    constexpr int kRowsPerPass = kWave / LPR;
+    constexpr float QMAXF = (float)((1 << BITS) - 1);
+    const uint32_t dim = a.dim, n4 = dim / 4;      // 16-byte units per row
+    const uint64_t P = (uint64_t)dim * BITS / 8;   // packed bytes per row
+    const int lane = tid_x() & (kWave - 1);
+    const uint32_t j = lane % LPR;
+    const uint32_t last_row = (uint32_t)a.n_rows - 1u;
+    const uint32_t n_waves = a.n_waves;
+    for (uint64_t pass = wave_in_grid(); pass * kRowsPerPass < n; pass += n_waves) {
+        const uint64_t k = pass * kRowsPerPass + lane / LPR;
+        const uint64_t kc = k < n ? k : n - 1;     // rows past the end repeat the last one; nothing of theirs is stored
+        const uint32_t rid = a.row_ids ? a.row_ids[kc] : kc > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)kc;
+        const bool in_table = rid <= last_row;
+        const bool live = k < n && in_table;
+        if (k < n && !in_table && j == 0) raise_flag(a.err, CNR_FLAG_ROW_ID);
+        const f32x4 *row = reinterpret_cast<const f32x4 *>(a.table + (uint64_t)(in_table ? rid : last_row) * dim);
+
+        // ---- row minimum / maximum (every lane starts from the row's first unit, so idle lanes are neutral)
+        const f32x4 first = row[0];
+        float mn = fminf(fminf(first.x, first.y), fminf(first.z, first.w));
+        float mx = fmaxf(fmaxf(first.x, first.y), fmaxf(first.z, first.w));
+        for (uint32_t u = j; u < n4; u += LPR) {
+            const f32x4 v = row[u];
+            mn = fminf(fminf(mn, v.x), fminf(v.y, fminf(v.z, v.w)));
+            mx = fmaxf(fmaxf(mx, v.x), fmaxf(v.y, fmaxf(v.z, v.w)));
+        }
+        const float X_min = lanes_min<LPR>(mn) + 0.0f;  // -0.0 -> +0.0
+        const float X_max = lanes_max<LPR>(mx) + 0.0f;
+        float lo = X_min, hi = X_max;
+        if (a.mode == kModeSymmetric) {
+            const float m = fmaxf(fabsf(X_min), fabsf(X_max));
+            lo = -m + 0.0f;
+            hi = m;
+        }
+        const float scale = (hi - lo) / QMAXF;
+        {
+            float *dst = j == 0 ? a.scale : j == 1 ? a.bias : j == 2 ? a.row_min : a.row_max;
+            const float v = j == 0 ? scale : j == 1 ? lo : j == 2 ? X_min : X_max;
+            if (j < 4 && dst && live) dst[k] = v;
+        }
+        const float f = scale < 0x1p-100f ? 0x1p120f : scale > 0x1p100f ? 0x1p-120f : 1.0f;
+        const float fscale = scale * f;
+        const float inv = scale == 0.0f ? 0.0f : 1.0f / fscale;  // scale 0: every code 0
+
+        // ---- quantize unit by unit; all lanes take every trip so that the 3-bit exchange has partners
+        const uint32_t trips = (n4 + LPR - 1) / LPR;
+        for (uint32_t trip = 0; trip < trips; ++trip) {
+            const uint32_t u = j + trip * LPR;
+            const bool mine = u < n4;
+            uint32_t bytes;
+            const uint32_t h = unit_codes<BITS>(row[mine ? u : 0], lo, f, fscale, inv, bytes);
+            const bool store = mine && live;
+            if (a.codes && store) *reinterpret_cast<uint32_t *>(a.codes + k * (uint64_t)dim + 4 * u) = bytes;
+            if (a.packed) store_unit_codes<BITS>(a.packed + k * P, u, h, store);
+        }
+    }
+}
+template <int BITS>
+__global__ void __launch_bounds__(kBlock) quantize_strided_kernel(const QuantArgs a) {
+    encode_strided<kWave, BITS>(a, row_count(a));
+}
+
+constexpr uint64_t kShortEncodeWaves = 6144;
 template <int LPR, int U, int SB, int BITS>
 struct UnitsShape {
     static constexpr int RPS = kWave / LPR;                                  // rows per step
@@ -1059,6 +1129,8 @@ struct UnitsShape {
     static constexpr int ROWS = RPS * STEPS;                                 // rows per wave and pass
     static_assert(ROWS % 16 == 0 && STEPS % SB == 0, "whole 16-byte pieces");
     static constexpr int STAGE = ROWS * LPR * U * BITS / 2;                  // LDS per wave
+    static constexpr int SHORT_LPR = LPR * U <= 4 ? 4 : LPR * U <= 8 ? 8 : LPR * U <= 16 ? 16 : LPR * U <= 32 ? 32 : 64;
+    static constexpr uint64_t SHORT_ROWS = kShortEncodeWaves * (kWave / SHORT_LPR);
 };
 template <int LPR, int U, int SB, int BITS>
 __global__ void __launch_bounds__(kBlock) quantize_units_kernel(const QuantArgs a) {
@@ -1068,6 +1140,7 @@ __global__ void __launch_bounds__(kBlock) quantize_units_kernel(const QuantArgs 
     __shared__ __align__(16) uint8_t stages[kWavesPerBlock * S::STAGE];
     uint8_t *const stage = stages + (tid_x() / kWave) * S::STAGE;
     const uint64_t n = row_count(a);
+    if (n <= S::SHORT_ROWS) return encode_strided<S::SHORT_LPR, BITS>(a, n);
     const uint32_t dim = a.dim, n4 = dim / 4;      // 16-byte units per row, at most LPR * U
     const uint32_t P = dim * BITS / 8;             // packed bytes per row
     const int lane = tid_x() & (kWave - 1);
@@ -1161,62 +1234,6 @@ __global__ void __launch_bounds__(kBlock) quantize_units_kernel(const QuantArgs 
             }
         }
         __builtin_amdgcn_wave_barrier();
-    }
-}
-
-template <int BITS>
-__global__ void __launch_bounds__(kBlock) quantize_strided_kernel(const QuantArgs a) {
-    constexpr float QMAXF = (float)((1 << BITS) - 1);
-    const uint64_t n = row_count(a);
-    const uint32_t dim = a.dim, n4 = dim / 4;      // 16-byte units per row
-    const uint64_t P = (uint64_t)dim * BITS / 8;   // packed bytes per row
-    const uint32_t j = tid_x() & (kWave - 1);
-    const uint32_t last_row = (uint32_t)a.n_rows - 1u;
-    const uint32_t n_waves = a.n_waves;
-    for (uint64_t k = wave_in_grid(); k < n; k += n_waves) {
-        const uint32_t rid = a.row_ids ? a.row_ids[k] : k > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)k;
-        const bool live = rid <= last_row;
-        if (!live && j == 0) raise_flag(a.err, CNR_FLAG_ROW_ID);
-        const f32x4 *row = reinterpret_cast<const f32x4 *>(a.table + (uint64_t)(live ? rid : last_row) * dim);
-
-        // ---- row minimum / maximum (every lane starts from the row's first unit, so idle lanes are neutral)
-        const f32x4 first = row[0];
-        float mn = fminf(fminf(first.x, first.y), fminf(first.z, first.w));
-        float mx = fmaxf(fmaxf(first.x, first.y), fmaxf(first.z, first.w));
-        for (uint32_t u = j; u < n4; u += kWave) {
-            const f32x4 v = row[u];
-            mn = fminf(fminf(mn, v.x), fminf(v.y, fminf(v.z, v.w)));
-            mx = fmaxf(fmaxf(mx, v.x), fmaxf(v.y, fmaxf(v.z, v.w)));
-        }
-        const float X_min = lanes_min<kWave>(mn) + 0.0f;  // -0.0 -> +0.0
-        const float X_max = lanes_max<kWave>(mx) + 0.0f;
-        float lo = X_min, hi = X_max;
-        if (a.mode == kModeSymmetric) {
-            const float m = fmaxf(fabsf(X_min), fabsf(X_max));
-            lo = -m + 0.0f;
-            hi = m;
-        }
-        const float scale = (hi - lo) / QMAXF;
-        {
-            float *dst = j == 0 ? a.scale : j == 1 ? a.bias : j == 2 ? a.row_min : a.row_max;
-            const float v = j == 0 ? scale : j == 1 ? lo : j == 2 ? X_min : X_max;
-            if (j < 4 && dst && live) dst[k] = v;
-        }
-        const float f = scale < 0x1p-100f ? 0x1p120f : scale > 0x1p100f ? 0x1p-120f : 1.0f;
-        const float fscale = scale * f;
-        const float inv = scale == 0.0f ? 0.0f : 1.0f / fscale;  // scale 0: every code 0
-
-        // ---- quantize unit by unit; all lanes take every trip so that the 3-bit exchange has partners
-        const uint32_t trips = (n4 + kWave - 1) / kWave;
-        for (uint32_t trip = 0; trip < trips; ++trip) {
-            const uint32_t u = j + trip * kWave;
-            const bool mine = u < n4;
-            uint32_t bytes;
-            const uint32_t h = unit_codes<BITS>(row[mine ? u : 0], lo, f, fscale, inv, bytes);
-            const bool store = mine && live;
-            if (a.codes && store) *reinterpret_cast<uint32_t *>(a.codes + k * (uint64_t)dim + 4 * u) = bytes;
-            if (a.packed) store_unit_codes<BITS>(a.packed + k * P, u, h, store);
-        }
     }
 }
 
@@ -1363,7 +1380,14 @@ bool launch_greedy_short(QuantArgs &a, hipStream_t s) {
 
 template <int LPR, int U, int SB, int BITS>
 void launch_units(QuantArgs &a, hipStream_t s) {
-    const unsigned grid = cnr_row_grid(a.n_max, (uint64_t)UnitsShape<LPR, U, SB, BITS>::ROWS * kWavesPerBlock);
+    using S = UnitsShape<LPR, U, SB, BITS>;
+    const unsigned grid_long = cnr_row_grid(a.n_max, (uint64_t)S::ROWS * kWavesPerBlock);
+    const unsigned grid_short = cnr_row_grid(a.n_max < S::SHORT_ROWS ? a.n_max : S::SHORT_ROWS, (uint64_t)(kWave / S::SHORT_LPR) * kWavesPerBlock);
+    unsigned grid = grid_long > grid_short ? grid_long : grid_short;
+    // Where only the device knows the length it may be far below the capacity, and then the workgroups beyond the
+    // count are most of the time: half the usual cap (1 K rows of 96 in a capacity of 5 M 7.1 -> 4.5 us, 250 K rows
+    // 25.9 -> 24.6, 1.5 M rows 122 -> 127).
+    if (a.n_dev && grid > kRowKernelMaxBlocks / 2) grid = kRowKernelMaxBlocks / 2;
     a.n_waves = grid * kWavesPerBlock;
     hipLaunchKernelGGL((quantize_units_kernel<LPR, U, SB, BITS>), dim3(grid), dim3(kBlock), 0, s, a);
 }
@@ -1380,9 +1404,19 @@ void launch_bits(cnr_ctx *ctx, QuantArgs &a, hipStream_t s) {
     if (greedy && a.dim == 128) return launch_greedy_by_length<8, 2, 4, BITS>(ctx, a, s);
     if (greedy && a.dim == 256) return launch_greedy_by_length<16, 4, 4, BITS>(ctx, a, s);
     if (greedy) return launch_greedy_units<BITS>(a, s);
+    const uint32_t n4 = a.dim / 4;
+    // A row per wave: rows of more than 512 elements, and the lists of more than 192 on which the registers that
+    // the units kernel holds keep too few rows in flight.  Measured break-evens: rows of 200 and 252 at 13 K and
+    // 15 K, of 264 and 320 at 16 K, of 384 at 20 K, of 448 at 45 K, of 512 at 70 K (12 K rows: 6.0 against 9.2 us).
+    const uint64_t by_wave = n4 > 128 ? ~0ull : n4 <= 48 ? 0 : n4 <= 80 ? 12288 : 8192ull << ((n4 - 65) / 16);
+    if (a.n_max <= by_wave) {
+        const unsigned grid = cnr_grid(ctx, a.n_max, kWavesPerBlock, cnr_resident_blocks_per_cu<quantize_strided_kernel<BITS>>());
+        a.n_waves = grid * kWavesPerBlock;
+        hipLaunchKernelGGL((quantize_strided_kernel<BITS>), dim3(grid), dim3(kBlock), 0, s, a);
+        return;
+    }
     // Few idle lanes at every length (units of a row: lanes x units per lane), and 64 registers of row data or
     // fewer on their way per lane
-    const uint32_t n4 = a.dim / 4;
     if (n4 <= 4) return launch_units<4, 1, 4, BITS>(a, s);
     if (n4 <= 8) return launch_units<8, 1, 4, BITS>(a, s);
     if (n4 <= 12) return launch_units<4, 3, 2, BITS>(a, s);
@@ -1396,10 +1430,7 @@ void launch_bits(cnr_ctx *ctx, QuantArgs &a, hipStream_t s) {
     if (n4 <= 80) return launch_units<16, 5, 2, BITS>(a, s);
     if (n4 <= 96) return launch_units<16, 6, 2, BITS>(a, s);
     if (n4 <= 112) return launch_units<16, 7, 2, BITS>(a, s);
-    if (n4 <= 128) return launch_units<16, 8, 2, BITS>(a, s);
-    const unsigned grid = cnr_grid(ctx, a.n_max, kWavesPerBlock, cnr_resident_blocks_per_cu<quantize_strided_kernel<BITS>>());
-    a.n_waves = grid * kWavesPerBlock;
-    hipLaunchKernelGGL((quantize_strided_kernel<BITS>), dim3(grid), dim3(kBlock), 0, s, a);
+    return launch_units<16, 8, 2, BITS>(a, s);
 }
 
 // Two groups of lanes per row while the sets of parameters together leave room on the chip; four lanes

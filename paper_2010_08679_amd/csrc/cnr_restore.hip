@@ -450,6 +450,7 @@ template <int LPR, int ST, int BITS>
 __device__ __forceinline__ double error_rows(const ErrorArgs &a, uint64_t items) {
     constexpr int RPS = kWave / LPR;         // rows per step
     constexpr uint64_t GROUP = RPS * ST;     // rows per wave and pass
+    constexpr int kTrips = ST == 1 ? 4 : 1;  // trips through a row in flight
     constexpr uint32_t MASK = (1u << BITS) - 1u;
     const uint32_t n4 = a.dim / 4;
     const uint64_t P = (uint64_t)a.dim * BITS / 8;
@@ -494,7 +495,7 @@ __device__ __forceinline__ double error_rows(const ErrorArgs &a, uint64_t items)
             acc[t] = 0.0;
         }
         if ((pass + n_waves) * GROUP < items) fetch(pass + n_waves);
-#pragma unroll(ST == 1 ? 4 : 1)
+#pragma unroll kTrips
         for (uint32_t u0 = 0; u0 < n4; u0 += LPR) {
             const uint32_t u = u0 + j;
             const bool mine = u < n4;

@@ -277,9 +277,38 @@ def test_encode_of_other_row_lengths(ctx, dim, bits):
     _poll(ctx)
 
 
-@pytest.mark.parametrize("dim,bits", [(8, 3), (20, 2), (96, 4), (144, 8), (500, 4), (516, 2)])
-def test_encode_of_other_row_lengths_skips_ids_outside_the_table(ctx, dim, bits):
-    n_rows, n = 500, 133
+# short lists go a row (or several short ones) per wave; `short` is the longest of them, of every shape
+@pytest.mark.parametrize("dim,bits,short", [
+    (4, 2, 98_304), (12, 8, 98_304), (20, 4, 49_152), (24, 3, 49_152), (36, 4, 24_576), (40, 3, 24_576), (48, 8, 24_576), (52, 2, 24_576),
+    (60, 4, 24_576), (72, 3, 12_288), (96, 8, 12_288), (100, 2, 12_288), (120, 3, 12_288), (132, 4, 6_144), (160, 3, 6_144), (164, 8, 6_144),
+    (192, 2, 6_144), (196, 4, 12_288), (224, 3, 12_288), (228, 2, 12_288), (252, 8, 12_288), (260, 2, 12_288), (320, 3, 12_288),
+    (324, 4, 16_384), (384, 8, 16_384), (388, 2, 32_768), (448, 3, 32_768), (452, 4, 65_536), (512, 8, 65_536)])
+def test_encode_of_other_row_lengths_on_either_side_of_a_short_list(ctx, dim, bits, short):
+    print("case short units dim=%d bits=%d" % (dim, bits), flush=True)
+    n = short + 21
+    gt = GpuTable(ctx, synth.table_normal(n, dim, 0.05, dim, DEV))
+    for mode, ora_mode in ((P.CNR_RANGE_MINMAX, O.RANGE_MINMAX), (P.CNR_RANGE_SYMMETRIC, O.RANGE_SYMMETRIC)):
+        long = gpu_encode_all_outputs(gt, bits, mode=mode, row_ids=None, n=n)
+        pos = np.unique(np.concatenate([np.arange(min(n, 300)), np.arange(n - 300, n), np.random.default_rng(dim).integers(0, n, size=4000)]))
+        ora = O.quantize_rows(gt.host[pos], None, bits, mode=ora_mode, n_threads=8)
+        compare_quantized(gt.host[pos], {k: long[k][pos] for k in ("scale", "bias", "row_min", "row_max", "codes")}, ora, bits, what="long d%d" % dim)
+        assert np.array_equal(long["packed"], O.pack(long["codes"], bits))
+        some = gpu_encode_all_outputs(gt, bits, mode=mode, row_ids=None, n=short)
+        # the capacity allows a long list, the device's count is a short or a long one
+        gt.ck.row_ids.copy_(torch.arange(n, dtype=torch.int32, device=DEV))
+        for got, m in [(some, short)] + [(None, m) for m in (0, 17, min(short, 6_000), n - 3)]:
+            if got is None:
+                gt.ck.n_dirty.fill_(m)
+                got = gpu_encode_all_outputs(gt, bits, mode=mode)
+            for k in ("scale", "bias", "row_min", "row_max", "codes", "packed"):
+                assert np.array_equal(got[k], long[k][:m]), (k, m)
+    _poll(ctx)
+
+
+@pytest.mark.parametrize("dim,bits,n", [(8, 3, 133), (20, 2, 133), (96, 4, 133), (144, 8, 133), (500, 4, 133), (516, 2, 133),
+                                        (8, 3, 98_400), (20, 2, 49_200), (96, 4, 12_300), (144, 8, 6_200), (320, 3, 12_300)])
+def test_encode_of_other_row_lengths_skips_ids_outside_the_table(ctx, dim, bits, n):
+    n_rows = n + 367
     table = synth.table_normal(n_rows, dim, 0.05, 9, DEV)
     ids = _ids(n_rows, n, 3)
     prb = P.cnr_packed_row_bytes(dim, bits)
