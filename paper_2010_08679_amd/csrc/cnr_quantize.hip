@@ -1361,13 +1361,17 @@ void launch_greedy_units(QuantArgs &a, hipStream_t s) {
 
 // Lists so short that two groups of lanes per row, one candidate each, still leave room on the chip (three
 // waves per SIMD), at the lengths that the kernels above otherwise search with one: 45 bins, 1 K rows of
-// 16 to 128 elements 28-30 -> 14-25 us, of 256 30 -> 25; at the line both take the same.  Only where the
-// host's bound on the length says so: another launch to choose from on the device would cost the longer
-// lists more.
+// 16 to 128 elements 28-30 -> 12-25 us, of 256 30 -> 24; at the line both take the same.  A search of few
+// iterations gains less than the wider spread of its rows costs, so the line comes down with it (up to 10 bins,
+// 12 K rows of 64 8.8 us in one group, 9.6 in two, 6 K rows 8.8 and 7.9; up to 4 bins, 3 K rows of 128 5.4 and 5.9).
+// Only where the host's bound on the length says so: another launch to choose from on the device would cost
+// the longer lists more.
 template <int BITS>
 bool launch_greedy_short(QuantArgs &a, hipStream_t s) {
     const uint32_t lanes = a.dim <= 32 ? 8 : a.dim <= 128 ? 16 : 32;
-    if (a.n_max > 196608u / lanes) return false;
+    const uint32_t many = 196608u / lanes;
+    const uint32_t most = a.n_iter >= 16 ? many : a.dim <= 64 ? (a.n_iter >= 3 ? many / 2 : many / 4) : a.n_iter >= 8 ? many / 4 : 0;
+    if (a.n_max > most) return false;
     switch (a.dim) {
         case 16:
         case 32: launch_greedy_units_shape<4, 2, true, BITS>(a, s, 0, ~0ull); return true;

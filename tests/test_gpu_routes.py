@@ -182,14 +182,17 @@ def test_greedy_short_lists_of_power_of_two_rows(ctx, dim, bits, limit):
     where = np.sort(rng.choice(n_rows - 5, size=special.shape[0], replace=False))
     table[torch.from_numpy(where).to(DEV)] = torch.from_numpy(special).to(DEV)
     gt = GpuTable(ctx, table)
-    params = {2: (12, 0.6), 3: (12, 0.33), 4: (20, 0.2), 8: (12, 0.5)}[bits]  # no exact ties, as above
-    for n in (1, 77, limit, limit + 1):
-        got = gpu_encode_all_outputs(gt, bits, mode=P.CNR_RANGE_GREEDY, greedy=params, row_ids=None, n=n)
-        pos = np.unique(np.concatenate([np.arange(min(40, n)), np.arange(max(0, n - 40), n), where[where < n], rng.integers(0, n, size=1500)]))
-        ora = O.quantize_rows(gt.host[pos], None, bits, mode=O.RANGE_GREEDY, num_bins=params[0], ratio=params[1], n_threads=8)
-        compare_quantized(gt.host[pos], {k: got[k][pos] for k in ("scale", "bias", "row_min", "row_max", "codes")}, ora, bits,
-                          greedy=True, what="greedy short b%d d%d n%d" % (bits, dim, n))
-        assert np.array_equal(got["packed"], O.pack(got["codes"], bits))
+    # up to its last iteration, and a few and the fewest iterations, whose lines lie lower
+    many, few = {2: (25, 1.0), 3: (25, 1.0), 4: (45, 1.0), 8: (20, 1.0)}[bits], (12, 0.75)
+    lines = [(many, limit), (few, limit // 2 if dim <= 64 else limit // 4), ((12, 0.1), limit // 4)]
+    for params, line in lines:
+        for n in (1, 77, line, line + 1):
+            got = gpu_encode_all_outputs(gt, bits, mode=P.CNR_RANGE_GREEDY, greedy=params, row_ids=None, n=n)
+            pos = np.unique(np.concatenate([np.arange(min(40, n)), np.arange(max(0, n - 40), n), where[where < n], rng.integers(0, n, size=1500)]))
+            ora = O.quantize_rows(gt.host[pos], None, bits, mode=O.RANGE_GREEDY, num_bins=params[0], ratio=params[1], n_threads=8)
+            compare_greedy(gt.host[pos], {k: got[k][pos] for k in ("scale", "bias", "row_min", "row_max", "codes")}, ora, bits, *params,
+                           what="greedy short b%d d%d n%d" % (bits, dim, n))
+            assert np.array_equal(got["packed"], O.pack(got["codes"], bits))
     _poll(ctx)
 
 
