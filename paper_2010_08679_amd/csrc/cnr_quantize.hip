@@ -1333,14 +1333,19 @@ void launch_greedy_units_shape(QuantArgs &a, hipStream_t s, uint64_t n_from, uin
 // 32 lanes, which evaluate the two candidates of an iteration side by side (17 instead of 23 us for
 // the shortest lists of rows of 96 at 25 bins, a single group of 16 lanes taking one after the other).
 // The line lies where the long form's waves fill the chip: 768 waves of short rows, or, since a lane with
-// many units works longer on its row, a number in proportion to them.  Measured break-evens: rows of 24
-// at 57 K rows, of 48 at 28 K, of 96 at 30 K, of 200 at 42 K, of 384 at 8.4 K, of 1000 at 20 K.
+// many units works longer on its row, a number in proportion to them (up to 26.6 K rows where four lanes hold
+// up to eight units each).  Measured break-evens, 25 and 45 bins: rows of 24 at 45 K rows, of 48 at 25 K, of 60
+// at 40 K, of 72 at 22 K, of 96 to 140 at 26-28 K, of 144 to 268 within 8 % of each other from 30 K to 90 K, of
+// 288 and 320 at 7 K, of 384 at 8-10 K, of 640 at 15 K, of 1000 at 19 K.  Rows of 272 to 284 keep two groups of eight
+// at any length: sixteen lanes would hold four units and a nearly empty fifth (20-30 % slower from 6 K to 31 K rows).
 template <int BITS>
 void launch_greedy_units(QuantArgs &a, hipStream_t s) {
     const uint32_t n4 = a.dim / 4;
     const uint32_t lanes = n4 <= 8 ? 1 : n4 <= 17 ? 2 : n4 < 68 ? 4 : n4 <= 271 ? 16 : 64;
     const uint64_t fill = 49152u / lanes, busy = (lanes >= 4 ? 20480ull : 8192ull) * n4 / (lanes * lanes);
-    const uint64_t wide_rows = fill > busy ? fill : busy;
+    uint64_t wide_rows = fill > busy ? fill : busy;
+    if (lanes == 4 && n4 < 36 && wide_rows > 26624) wide_rows = 26624;
+    if (n4 >= 68 && n4 < 72) wide_rows = ~0ull;
     const bool may_be_wide = lanes == 64 || a.n_max >= wide_rows;
     const bool may_be_narrow = lanes != 64 && (!may_be_wide || a.n_dev != nullptr);
     const uint64_t below = may_be_wide ? wide_rows : ~0ull, from = may_be_narrow ? wide_rows : 0;
