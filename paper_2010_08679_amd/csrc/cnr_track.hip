@@ -337,7 +337,7 @@ __global__ void __launch_bounds__(kBlock) fold_flags_kernel(const TrackBatch b) 
 // ---------------------------------------------------------------------------------------------
 // compact: set-bit positions in ascending order.
 //
-// Two kernels, no inter-workgroup waiting.  Each workgroup owns kBlock consecutive 64-bit bitmap
+// Two kernels, or the second one alone, no inter-workgroup waiting.  Each workgroup owns kBlock consecutive 64-bit bitmap
 // words (one per thread = 16384 rows).
 //   count:   population count of the tile -> block_count[b]
 //   scatter: base = sum of block_count[0..b) (read back by every workgroup; at most a few thousand
@@ -348,7 +348,10 @@ __global__ void __launch_bounds__(kBlock) fold_flags_kernel(const TrackBatch b) 
 //            to the list with every lane writing consecutive ids.
 // Tables of up to kSelfCountTiles tiles (1 M rows) need the second kernel only: there a workgroup counts
 // the bits of all earlier tiles itself, at most 128 KB of bitmap out of the L2, which takes less than the
-// launch it saves (one table: 100 K rows 7.9 -> 5.7 us, 1 M rows 8.3 -> 7.3; eight tables of 1 M 9.8 -> 9.0).
+// launch it saves (one table: 100 K rows 7.9 -> 5.7 us, 1 M rows 8.3 -> 7.3; eight tables of 1 M 9.8 -> 9.0; at 96
+// tiles 8.2 -> 7.5, at 128 no difference, at 256 8.2 -> 11.5).  What is counted grows with the square of a table's
+// tiles and with the tables of the launch: kSelfCountPairs is where that meets the launch (in graph replays, 16
+// tables of 48 tiles 7.9 -> 7.2 us, 12 of 56 7.9 and 7.8, 10 of 64 7.8 -> 8.3, 16 of 64 8.8 -> 10.5).
 // ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ uint64_t load_tile_word(const uint32_t *__restrict__ bitmap,
                                                    uint64_t n_rows, uint64_t n_words32, uint64_t w64) {
@@ -395,7 +398,7 @@ __global__ void __launch_bounds__(kBlock) compact_count_kernel(const TrackBatch 
     if (tid_x() == 0) block_count[wg_x()] = total;
 }
 
-constexpr uint64_t kSelfCountTiles = 64;
+constexpr uint64_t kSelfCountTiles = 64, kSelfCountPairs = 9 * kSelfCountTiles * kSelfCountTiles;
 
 // This thread's share of the set bits in the first `tiles` (whole) tiles of a bitmap.
 __device__ __forceinline__ unsigned count_tiles_share(const uint32_t *__restrict__ bitmap, uint32_t tiles) {
@@ -714,7 +717,7 @@ cnr_status cnr_compact_dirty_batch(cnr_ctx *ctx, const cnr_table_job *jobs, uint
     for (uint32_t first = 0; first < n_jobs; first += CNR_MAX_BATCH) {
         TrackBatch b = {};
         uint32_t n = 0;
-        uint64_t max_tiles = 1;
+        uint64_t max_tiles = 1, tile_pairs = 0;
         for (uint32_t i = first; i < n_jobs && i < first + CNR_MAX_BATCH; ++i, ++n) {
             const cnr_table_job &j = jobs[i];
             b.job[n].bitmap = j.bitmap;
@@ -725,10 +728,11 @@ cnr_status cnr_compact_dirty_batch(cnr_ctx *ctx, const cnr_table_job *jobs, uint
             b.job[n].block_count = (uint32_t *)j.compact_scratch;
             const uint64_t tiles = (j.n_rows + kCompactRowsPerBlock - 1) / kCompactRowsPerBlock;
             if (tiles > max_tiles) max_tiles = tiles;
+            tile_pairs += tiles * tiles;
         }
         b.grid_x = (uint32_t)max_tiles;
         const dim3 grid(b.grid_x, n);
-        if (max_tiles <= kSelfCountTiles) {
+        if (max_tiles <= kSelfCountTiles && tile_pairs <= kSelfCountPairs) {
             hipLaunchKernelGGL(compact_scatter_kernel<false>, grid, dim3(kBlock), 0, as_stream(stream), b, ctx->dev_err);
         } else {
             hipLaunchKernelGGL(compact_count_kernel, grid, dim3(kBlock), 0, as_stream(stream), b);

@@ -377,6 +377,26 @@ def test_compaction_around_the_self_counting_limit(ctx, n_rows, shift):
         _poll(ctx, 0 if capacity >= want.numel() else P.CNR_FLAG_CAPACITY)
 
 
+@pytest.mark.parametrize("tables,tiles", [(9, 64), (10, 64), (16, 48), (16, 49)])
+def test_batched_compaction_around_the_self_counting_limit(ctx, tables, tiles):
+    # what a launch's workgroups count themselves grows with its tables; they differ in size and share nothing
+    cks, wants = [], []
+    for k in range(tables):
+        n_rows = tiles * 16_384 - (7 * k if k else 0)
+        ck = P.TableCheckpointer(ctx, n_rows, 8, device=DEV)
+        g = torch.Generator(device=DEV).manual_seed(k)
+        ck.bitmap.copy_(torch.randint(-2**31, 2**31, (ck.bitmap.numel(),), generator=g, device=DEV).to(torch.int32))
+        bits = ((ck.bitmap[:, None] >> torch.arange(32, device=DEV, dtype=torch.int32)) & 1).reshape(-1)[:n_rows]
+        wants.append(torch.nonzero(bits).reshape(-1).to(torch.int32))
+        ck.row_ids.fill_(-1)
+        cks.append(ck)
+    P.BatchCheckpointer(ctx, cks).compact()
+    for ck, want in zip(cks, wants):
+        n = int(ck.n_dirty)
+        assert n == want.numel() and torch.equal(ck.row_ids[:n], want) and bool((ck.row_ids[n:] == -1).all())
+    _poll(ctx)
+
+
 # ---- bulk mark of one-slice tables: streams from 64 MB on are read past the caches -------------------------
 
 @pytest.mark.parametrize("dtype,n_idx", [(torch.int64, 1_048_576), (torch.int64, 1_048_577), (torch.int32, 2_097_151), (torch.int32, 2_097_160)])
