@@ -8,7 +8,7 @@ import torch
 import oracle as O
 import paper_2010_08679_amd as P
 from paper_2010_08679_amd import synth
-from util_parity import GpuTable, compare_greedy, compare_quantized, gpu_encode_all_outputs
+from util_parity import GpuTable, compare_greedy, compare_quantized, gpu_encode_all_outputs, tie_rows
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -348,11 +348,25 @@ def test_parameter_selection_routes(ctx, dim, bits, n, bins):
     table[3] = 0.25                        # a constant row: searched by division
     ids = _ids(n_rows, n, 11)
     choice, report = P.select_greedy_params(ctx, table, n_rows, dim, ids, bits, bins, ratios)
-    want_choice, want = O.select_greedy_params(table[ids.long()].cpu().numpy(), bits, bins, ratios, n_threads=8)
+    rows = table[ids.long()].cpu().numpy()
+    want = {"naive": O.mean_l2(rows, bits, O.RANGE_MINMAX)}
+    scale, bias = torch.empty(n, device=DEV), torch.empty(n, device=DEV)
+    packed = torch.empty(n * P.cnr_packed_row_bytes(dim, bits), dtype=torch.uint8, device=DEV)
+    err = torch.empty(n, dtype=torch.float64, device=DEV)
+    for key, num_bins, ratio in [(("bins", b), b, 1.0) for b in bins] + [(("ratio", r), choice[0], r) for r in ratios]:
+        # the oracle's errors, but for the rows whose exact tie it decides by rounding: there the encoder's
+        ora = O.quantize_rows(rows, None, bits, mode=O.RANGE_GREEDY, num_bins=num_bins, ratio=ratio, n_threads=8)
+        errors = O.row_l2(rows, O.dequantize(ora["codes"], ora["scale"], ora["bias"]))[0].copy()
+        P.cnr_quantize_rows(ctx, table, n_rows, dim, ids, None, n, bits, P.CNR_RANGE_GREEDY, (num_bins, ratio), scale, bias, packed=packed)
+        P.cnr_quant_error(ctx, table, n_rows, dim, ids, None, n, bits, packed, scale, bias, err)
+        tied = tie_rows(rows, dict(scale=scale.cpu().numpy(), bias=bias.cpu().numpy()), ora, bits, num_bins, ratio)
+        errors[tied] = err.cpu().numpy()[tied]
+        want[key] = float(errors.mean())
     assert set(report) == set(want)
-    for key in want:                       # fp64 sums in another order; a row that leaves the search's path at a
-        assert report[key] == pytest.approx(want[key], rel=max(1e-9, 0.1 / n if key != "naive" else 0)), key  # near-tie ends within a tenth of its error
-    assert choice == want_choice
+    for key in want:                       # fp64 sums in another order
+        assert report[key] == pytest.approx(want[key], rel=1e-9), key
+    num_bins = O.taper_choice(list(bins), [want[("bins", b)] for b in bins], want["naive"], 0.05)
+    assert choice == (num_bins, O.taper_choice(list(ratios), [want[("ratio", r)] for r in ratios], want["naive"], 0.05))
     _poll(ctx)
 
 

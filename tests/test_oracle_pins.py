@@ -564,3 +564,21 @@ def test_bit_width_falls_back_to_eight_bits_when_failures_exceed_the_estimate():
     assert O.select_bits(3, 3) == 3 and O.select_bits(3, 4) == 8
     assert O.select_bits(20, 20) == 4 and O.select_bits(20, 21) == 8
     assert O.select_bits(50, 51) == 8
+
+
+def test_replayed_search_is_the_oracles_but_for_exact_ties():
+    # the replay that GPU tests use to tell an exact tie from a wrong range: same ranges as the oracle's where
+    # no two candidates tie, and the upper bound moves where they do
+    from util_parity import replay_search
+    rng = np.random.default_rng(3)
+    rows = rng.normal(0, 0.05, size=(300, 40)).astype(np.float32)
+    for bits, bins, ratio in ((2, 25, 1.0), (3, 25, 0.6), (4, 45, 1.0), (8, 12, 0.5)):
+        lo, hi, tied = replay_search(rows, bits, bins, ratio)
+        q = O.quantize_rows(rows, None, bits, mode=O.RANGE_GREEDY, num_bins=bins, ratio=ratio)
+        same = lo == q["bias"]
+        assert np.all(same | tied) and np.mean(same) > 0.99
+        assert np.array_equal((hi[same] - lo[same]) / np.float32(2 ** bits - 1), q["scale"][same])
+    # all on the grid of [-1, 0.5] and of [-0.5, 1] but for one end, half a unit beyond: an exact tie
+    row = np.array([[-1.0, -0.5, 0.0, 0.0, 0.0, 0.0, 0.5, 1.0]], dtype=np.float32)
+    lo, hi, tied = replay_search(row, 2, 4, 0.25)
+    assert tied[0] and lo[0] == -1.0 and hi[0] == 0.5

@@ -132,16 +132,23 @@ def replay_search(rows: np.ndarray, bits: int, num_bins: int, ratio: float):
     return lo, hi, tied
 
 
-def compare_greedy(host_rows: np.ndarray, gpu: dict, ora: dict, bits: int, num_bins: int, ratio: float, what=""):
-    """compare_quantized for a greedy search that can meet exact ties, which the oracle's strict comparison of
-    rounded sums decides by their rounding: a row with another range than the oracle's is left out if its
-    search, replayed with exact sums, meets a tie and ends in the range the GPU found.  Returns their number."""
+def tie_rows(host_rows: np.ndarray, gpu: dict, ora: dict, bits: int, num_bins: int, ratio: float) -> np.ndarray:
+    """Mask of the rows where the GPU's range is another than the oracle's because of an exact tie, which the
+    oracle's strict comparison of rounded sums decides by their rounding: the search, replayed with exact sums,
+    meets a tie and ends in the range the GPU found."""
     differ = np.flatnonzero((ulp_distance(gpu["scale"], ora["scale"]) > 1) | (ulp_distance(gpu["bias"], ora["bias"]) > 1))
-    keep = np.ones(host_rows.shape[0], dtype=bool)
+    tie = np.zeros(host_rows.shape[0], dtype=bool)
     if differ.size:
         lo, hi, tied = replay_search(host_rows[differ], bits, num_bins, ratio)
         scale = (hi - lo) / np.float32((1 << bits) - 1)
-        keep[differ] = ~(tied & (lo == gpu["bias"][differ]) & (ulp_distance(scale, gpu["scale"][differ]) <= 1))
+        tie[differ] = tied & (lo == gpu["bias"][differ]) & (ulp_distance(scale, gpu["scale"][differ]) <= 1)
+    return tie
+
+
+def compare_greedy(host_rows: np.ndarray, gpu: dict, ora: dict, bits: int, num_bins: int, ratio: float, what=""):
+    """compare_quantized for a greedy search that can meet exact ties: those rows (tie_rows) are left out.
+    Returns their number."""
+    keep = ~tie_rows(host_rows, gpu, ora, bits, num_bins, ratio)
     sub = lambda d: {k: d[k][keep] for k in ("scale", "bias", "row_min", "row_max", "codes")}  # noqa: E731
     compare_quantized(host_rows[keep], sub(gpu), sub(ora), bits, greedy=True, what=what)
     return int(np.count_nonzero(~keep))
