@@ -148,8 +148,8 @@ __device__ __forceinline__ T load_stream(const void *p) {
 // ---- cross-lane helpers (wave64) -------------------------------------------------------------
 // DPP controls: quad_perm [1,0,3,2] = 0xB1 (lane ^ 1), quad_perm [2,3,0,1] = 0x4E (lane ^ 2),
 // row_half_mirror = 0x141 (lane i <-> 7 - i within 8), row_mirror = 0x140 (i <-> 15 - i within 16).
-// After those four exchanges, applied in that order with a commutative and associative combine,
-// all 16 lanes of a DPP row hold the combination of the row's 16 values.
+// After the first k of those exchanges, applied in that order with a commutative combine, every lane of an
+// aligned group of 2^k holds the combination of the group's values.
 template <int CTRL>
 __device__ __forceinline__ int dpp_i(int v) {
     return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true);
@@ -163,28 +163,6 @@ __device__ __forceinline__ double dpp_d(double v) {
     int lo = dpp_i<CTRL>(__double2loint(v));
     int hi = dpp_i<CTRL>(__double2hiint(v));
     return __hiloint2double(hi, lo);
-}
-
-__device__ __forceinline__ float row16_min(float v) {
-    v = fminf(v, dpp_f<0xB1>(v));
-    v = fminf(v, dpp_f<0x4E>(v));
-    v = fminf(v, dpp_f<0x141>(v));
-    v = fminf(v, dpp_f<0x140>(v));
-    return v;
-}
-__device__ __forceinline__ float row16_max(float v) {
-    v = fmaxf(v, dpp_f<0xB1>(v));
-    v = fmaxf(v, dpp_f<0x4E>(v));
-    v = fmaxf(v, dpp_f<0x141>(v));
-    v = fmaxf(v, dpp_f<0x140>(v));
-    return v;
-}
-__device__ __forceinline__ double row16_sum(double v) {
-    v += dpp_d<0xB1>(v);
-    v += dpp_d<0x4E>(v);
-    v += dpp_d<0x141>(v);
-    v += dpp_d<0x140>(v);
-    return v;
 }
 
 // Launch coordinates read from the hardware registers: the workgroup id arrives in a scalar

@@ -25,7 +25,6 @@ struct QuantArgs {
     int mode;
     uint32_t n_iter;   // greedy iterations
     float num_bins_f;  // greedy num_bins
-    double less;       // greedy: tie_factor(dim)
     float *scale, *bias, *row_min, *row_max;
     uint8_t *codes, *packed;
     cnr_dev_errors *err;
@@ -373,21 +372,21 @@ quantize_tile_kernel(const QuantBatchArgs b) {
 // codes are exactly 2 * BITS contiguous bytes of the packed row.  What a candidate costs beyond its
 // elements (its scale and reciprocal, the exchange between lanes, the comparison) is paid once per
 // lane, so more elements per lane mean less of it: with 64 instead of 16 (G = 4; a row of 64 floats
-// is then one lane's, with no exchange at all) a long list takes 13 % less time, 0.90 instead of 0.78
-// of the issue bound of the element arithmetic alone.  A lane then works four times as long on a
-// row, so short lists, which cannot fill the SIMDs either way, keep G = 1.  The rows are read in this
+// is then one lane's, with no exchange at all) a long list takes 13 % less time.  A lane then works four times
+// as long on a row, so short lists, which cannot fill the SIMDs either way, keep G = 1.  The rows are read in this
 // layout directly (each lane its own 64 * G bytes): the kernel is far from the memory system's limits,
 // so the transpose through LDS that the tile kernel pays for coalesced loads would buy nothing.
 // A candidate is evaluated with the cheapest sequence that still ranks candidates as F_Q would: eight
-// vector instructions per element (struct Candidate).  What they cost differs (a wave's add or subtract
-// occupies a SIMD for 1.3 ns, a multiply with the clamp modifier 1.2, a median, a round or a conversion
-// 1.9, a fused multiply-add 2.0, in fp64 2.05; single-instruction loops), so
+// vector instructions per element (struct Candidate).  What they cost differs (a loop of nothing but one kind
+// takes 1.3 ns per instruction, wave and SIMD for an add or subtract, 1.2 for a multiply with the clamp modifier, 1.9
+// for a median, a round or a conversion, 2.0 for a fused multiply-add, 2.05 in fp64; mixed, as here, they take
+// less than these add up to, so the figures rank the kinds and are no occupancy), so
 // the clip is the free clamp to [0, 1] of the multiply by 1 / (qmax * scale), the rounding is the fused
 // multiply-add by qmax onto 2^23, and that biased code, with -2^23 * scale as the addend, gives the
 // rounded product scale * code in one fused multiply-add more.  The sequence with a median for the clip
 // and a round instruction (nine instructions) took 12.2 ns per element and candidate, this one takes 9.8
-// in a loop of its own and 9.2 here;
-// 1.5 M rows of 64, 199 candidates: 3.28 -> 2.70 ms.
+// in a loop of its own and 9.2 here; at the published vector rates (fp32 two clocks a wave, fp64 four) the eight
+// cannot take less than 7.5.  1.5 M rows of 64, 199 candidates: 3.28 -> 2.70 ms.
 // The candidate's scale is range / (2^b - 1) correctly rounded (reciprocal multiply plus one FMA
 // residual step), 1 / (qmax * scale) likewise, and the quotient, three roundings in all, is within
 // 1.5 ulp of the exact one, which can move a code of a candidate only where the quotient lies that
@@ -533,7 +532,7 @@ __device__ __forceinline__ void store_unit_codes(uint8_t *out, uint32_t u, uint3
 }
 
 template <int L, int BITS, int G>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L == 1 && G == 4 ? 3 : G == 4 ? 4 : 5, 8))) quantize_greedy_kernel(const QuantArgs a, uint64_t n_from, uint64_t n_below) {
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L == 1 && G == 4 ? 3 : G == 4 ? 4 : 5, 8))) quantize_greedy_kernel(const QuantArgs a, double less /* tie_factor(dim) */, uint64_t n_from, uint64_t n_below) {
     constexpr int EPL = 16 * G;  // elements per lane
     constexpr int DIM = EPL * L;
     constexpr int kRowsPerPass = kWave / L;
@@ -606,11 +605,11 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L =
                 const float c_hi = cur_hi - step;
                 const double e_lo = row_err(c_lo, cur_hi);
                 const double e_hi = row_err(cur_lo, c_hi);
-                const bool move_lo = e_lo < e_hi * a.less;
+                const bool move_lo = e_lo < e_hi * less;
                 cur_lo = move_lo ? c_lo : cur_lo;
                 cur_hi = move_lo ? cur_hi : c_hi;
                 const double e = move_lo ? e_lo : e_hi;
-                if (e < best * a.less) {
+                if (e < best * less) {
                     best = e;
                     lo = cur_lo;
                     hi = cur_hi;
@@ -714,7 +713,9 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L =
 // instructions (range to scale to reciprocal, the sum over the lanes, the comparison), so two groups of L
 // lanes hold the row, one evaluates the raised lower bound and the other the lowered upper one.  (A wave
 // per row that re-read the row from cache and divided for every element: 100 K rows of 96 at 49
-// candidates 874 us, this 117 us.)
+// candidates 874 us, this 106 us.)  The waves that waves_per_eu asks for cost spilled registers (2 in the
+// 16-unit forms at 2 bits, 28 to 30 at 3 and 4, 4 to 8 in some 8-unit forms); all of them are stored and reloaded
+// once per row, outside the loop over the candidates.
 // ---------------------------------------------------------------------------------------------
 // What the same lane of the row's other group of L lanes holds.  (The mirrors reverse the lanes, which is
 // the same for values that all lanes of a group agree on.)
@@ -843,7 +844,7 @@ struct RowUnits {
 
 template <int L, int UMAX, bool DUAL, int BITS>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(UMAX > 8 ? 3 : 4, 8)))
-quantize_greedy_units_kernel(const QuantArgs a, uint64_t n_from, uint64_t n_below) {
+quantize_greedy_units_kernel(const QuantArgs a, double less /* tie_factor(dim) */, uint64_t n_from, uint64_t n_below) {
     using Row = RowUnits<L, UMAX, DUAL>;
     constexpr int kRowsPerPass = kWave / Row::LANES;
     constexpr float QMAXF = (float)((1 << BITS) - 1);
@@ -872,9 +873,9 @@ quantize_greedy_units_kernel(const QuantArgs a, uint64_t n_from, uint64_t n_belo
         row.range(X_min, X_max);
         float lo = X_min, hi = X_max;
         if (search_divides(lo, hi, a.num_bins_f, QMAXF))
-            row.template search<BITS, false>(a.n_iter, a.num_bins_f, a.less, lo, hi);
+            row.template search<BITS, false>(a.n_iter, a.num_bins_f, less, lo, hi);
         else
-            row.template search<BITS, true>(a.n_iter, a.num_bins_f, a.less, lo, hi);
+            row.template search<BITS, true>(a.n_iter, a.num_bins_f, less, lo, hi);
 
         if constexpr (DUAL) live = live && !((lane / L) & 1);  // one of the row's two groups stores
         const float scale = (hi - lo) / QMAXF;
@@ -1305,7 +1306,7 @@ void launch_greedy(cnr_ctx *ctx, QuantArgs &a, hipStream_t s, uint64_t n_from, u
     const uint64_t most = a.n_max < n_below ? a.n_max : n_below;
     const unsigned grid = cnr_row_grid(most, (uint64_t)(kWave / L) * kWavesPerBlock);
     a.n_waves = grid * kWavesPerBlock;
-    hipLaunchKernelGGL((quantize_greedy_kernel<L, BITS, G>), dim3(grid), dim3(kBlock), 0, s, a, n_from, n_below);
+    hipLaunchKernelGGL((quantize_greedy_kernel<L, BITS, G>), dim3(grid), dim3(kBlock), 0, s, a, tie_factor(a.dim), n_from, n_below);
 }
 // Long lists give every lane 64 elements (32 at dim 32); short ones keep 16 per lane, four times the
 // lanes per row and a quarter of the time per row, which is what counts while the list cannot fill
@@ -1327,7 +1328,7 @@ void launch_greedy_units_shape(QuantArgs &a, hipStream_t s, uint64_t n_from, uin
     const uint64_t most = a.n_max < n_below ? a.n_max : n_below;
     const unsigned grid = cnr_row_grid(most, (uint64_t)(kWave / RowUnits<L, UMAX, DUAL>::LANES) * kWavesPerBlock);
     a.n_waves = grid * kWavesPerBlock;
-    hipLaunchKernelGGL((quantize_greedy_units_kernel<L, UMAX, DUAL, BITS>), dim3(grid), dim3(kBlock), 0, s, a, n_from, n_below);
+    hipLaunchKernelGGL((quantize_greedy_units_kernel<L, UMAX, DUAL, BITS>), dim3(grid), dim3(kBlock), 0, s, a, tie_factor(a.dim), n_from, n_below);
 }
 // Other row lengths: long lists give a row as few lanes as hold it; short ones give it two groups of 4 to
 // 32 lanes, which evaluate the two candidates of an iteration side by side (17 instead of 23 us for
@@ -1527,7 +1528,6 @@ cnr_status cnr_quantize_rows_batch(cnr_ctx *ctx, const cnr_table_job *jobs, uint
         a.n_dev = j.n_dirty_dev; a.n_max = m;
         a.mode = (int)mode; a.n_iter = n_iter;
         a.num_bins_f = mode == CNR_RANGE_GREEDY ? (float)greedy->num_bins : 1.0f;
-        a.less = tie_factor(dim);
         a.scale = j.scale + k0; a.bias = j.bias + k0;
         a.row_min = j.row_min ? j.row_min + k0 : nullptr;
         a.row_max = j.row_max ? j.row_max + k0 : nullptr;

@@ -650,9 +650,11 @@ cnr_status cnr_mark_touched_batch(cnr_ctx *ctx, const cnr_table_job *jobs, uint3
         }
         if (n_slices) {
             const dim3 grid((unsigned)slices_team, n_slices);  // the most workgroups any table of the launch has
-            // Streams too long to be found in the memory-side cache (256 MB, and the tables pass through it too) are read
-            // past it; shorter ones may be there still, from the writer or from a mark before this one, and
-            // then the plain loads are the faster ones (64 MB found there: 34 against 36 us).
+            // Long streams are read past the caches.  With the hint, streams of 64 to 256 MB take 0.56-0.90 of the time
+            // where they come from memory (a window's look-ups, marked after other work), 0.93-1.06 where they were
+            // written just before and 0.88-1.18 where they are read a second time in a row (the memory-side cache
+            // holds 256 MB; eight tables at most 1.09); from 384 MB on it is never the slower way.  Below 64 MB the
+            // whole gain is a few microseconds and streams found in the cache are the rule.
             const bool stream = slices_one && slices_bytes >= (64ull << 20);
             if (type == CNR_IDX_I64)
                 hipLaunchKernelGGL((stream ? mark_slices_kernel<int64_t, true> : mark_slices_kernel<int64_t, false>), grid,
