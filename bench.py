@@ -35,10 +35,11 @@ from paper_2010_08679_amd import synth  # noqa: E402
 
 HBM_PEAK_GBPS = 8000.0          # MI355X HBM3E, published
 FP32_VECTOR_PEAK_TFLOPS = 157.3  # MI355X fp32 vector, published
-# SIMD time the greedy search's inner loop takes per element and candidate range for a wave of 64: 9.84 ns
-# (23.6 clocks at 2.4 GHz) for a loop of nothing but its eight instructions (bench_ceilings.hip measures
-# that), with 256 CUs x 4 SIMDs
-GREEDY_SIMD_CLOCKS_PER_ELEMENT = 23.6
+# The fewest SIMD clocks the greedy search's eight instructions per element and candidate range can take for a
+# wave of 64 on 256 CUs x 4 SIMDs at 2.4 GHz: two for each of the six fp32 ones at the published 157.3 TFLOP/s, as
+# many for the conversion, four for the fp64 multiply-add at the published 78.6 TFLOP/s.  (A loop of nothing but
+# the eight takes 23.6, bench_ceilings.hip; the kernel, which overlaps them with what lies between, about 22.)
+GREEDY_SIMD_CLOCKS_PER_ELEMENT = 18.0
 SIMD_CLOCKS_PER_S = 256 * 4 * 2.4e9
 
 # HBM traffic of the two bandwidth-bound kernels from rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE, each
@@ -417,7 +418,7 @@ def main() -> int:
             "roofline": {"bound": "alu", "achieved": round(flops / (g * 1e-3) / 1e12, 2),
                          "peak": FP32_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
                          "frac": round(flops / (g * 1e-3) / 1e12 / FP32_VECTOR_PEAK_TFLOPS, 4),
-                         # the same launch against the time a loop of nothing but its own instructions takes
+                         # the same launch against what its instructions take at the published issue rates
                          "issue_bound_ms": round(issue_ms, 3), "issue_frac": round(issue_ms / g, 4), "traffic": None},
         }
 
