@@ -212,6 +212,56 @@ def test_greedy_skips_ids_outside_the_table(ctx, dim, bits):
         assert bool((o[bad] == 0x5A).all()) and bool((o[keep] != 0x5A).any(1).all())
 
 
+def _early_end_rows(n, dim, bins, seed):
+    """Rows whose search may end early, or must not: a few far elements (the best range comes late), both ends far, two
+    clusters (clipping hurts at once), equal elements but one, a range small against its offset (down to the
+    narrowest that is searched without divisions), values on the grid, scales over 2**120, constant rows."""
+    rng = np.random.default_rng(seed)
+    x = np.empty((n, dim), dtype=np.float64)
+    for i in range(n):
+        kind, v = i % 9, rng.normal(0, 1, dim)
+        if kind == 0:
+            v[rng.integers(0, dim, max(1, dim // 64))] = rng.uniform(5, 200) * rng.choice([-1, 1])
+        elif kind == 1:
+            v[0], v[-1] = rng.uniform(3, 50), -rng.uniform(3, 50)
+        elif kind == 2:
+            v = rng.choice([-1.0, 1.0], dim) + 0.01 * v
+        elif kind == 3:
+            v = np.full(dim, 0.5)
+            v[rng.integers(dim)] = rng.normal()
+        elif kind == 4:
+            v = 1.0 + rng.uniform(1, 4) * bins ** 2 * 2.0 ** -23 * rng.random(dim)
+        elif kind == 5:
+            v = rng.integers(0, 4, dim).astype(np.float64)
+        elif kind == 6:
+            v *= 2.0 ** rng.integers(-60, 61)
+        elif kind == 7:
+            v = rng.random(dim) ** 8
+        else:
+            v = np.full(dim, 0.25) if i % 2 else np.exp(2 * v)
+        x[i] = v * 0.1
+    return x.astype(np.float32)
+
+
+@pytest.mark.parametrize("dim,bits,bins,long", [(16, 2, 25, 0), (32, 3, 45, 262_144), (64, 4, 100, 131_072), (64, 2, 100, 131_072), (64, 8, 20, 0),
+                                                (128, 3, 25, 65_536), (256, 2, 45, 32_768), (256, 4, 45, 0), (8, 4, 45, 49_152),
+                                                (96, 2, 45, 26_624), (96, 3, 25, 0), (200, 4, 45, 64_000), (320, 3, 45, 6_400), (1088, 2, 25, 0)])
+def test_greedy_search_that_ends_early_finds_the_same_range(ctx, dim, bits, bins, long):
+    print("case greedy early end dim=%d bits=%d bins=%d" % (dim, bits, bins), flush=True)
+    n = 900 if dim <= 320 else 300
+    rows = _early_end_rows(n, dim, bins, dim + bits)
+    ora = O.quantize_rows(rows, None, bits, mode=O.RANGE_GREEDY, num_bins=bins, ratio=1.0, n_threads=8)
+    table = torch.from_numpy(rows).to(DEV)
+    for copies in {1, -(-long // n)} - {0}:   # short lists and those of the long forms
+        m = copies * n
+        gt = GpuTable(ctx, table.repeat(copies, 1))
+        got = gpu_encode_all_outputs(gt, bits, mode=P.CNR_RANGE_GREEDY, greedy=(bins, 1.0), row_ids=None, n=m)
+        for at in {0, m - n}:
+            compare_greedy(rows, {k: got[k][at:at + n] for k in ("scale", "bias", "row_min", "row_max", "codes")}, ora, bits, bins, 1.0,
+                           what="early end b%d d%d n%d" % (bits, dim, m))
+    _poll(ctx)
+
+
 # Exact ties: with qmax + 1 bins a step is one code step at the first move already, at 3 bits and 12 bins
 # after five (7 / (12 - 5) = 1), and these rows have nothing but their two ends beyond the bounds then; the
 # setting is the one whose tie lies at the best range of the row length (1 row in 100 to 1000).
