@@ -1429,6 +1429,10 @@ void launch_greedy_units_shape(QuantArgs &a, hipStream_t s, uint64_t n_from, uin
 // at 40 K, of 72 at 22 K, of 96 to 140 at 26-28 K, of 144 to 268 within 8 % of each other from 30 K to 90 K, of
 // 288 and 320 at 7 K, of 384 at 8-10 K, of 640 at 15 K, of 1000 at 19 K.  Rows of 272 to 284 keep two groups of eight
 // at any length: sixteen lanes would hold four units and a nearly empty fifth (20-30 % slower from 6 K to 31 K rows).
+// At 8 bits a search ends after an iteration or two, so two groups save little and the line lies lower (rows of 24 at 22 K
+// rows, of 48 at 12 K, of 96 at 9 K, of 200 at 21 K, of 640 at 5 K; 20 K rows of 96 9.3 us in two groups, 7.9 in one), and so it does
+// for rows of 4 to 16 elements, whose long form is four elements' chain and no exchange between lanes (rows of 8 at 20-30 K;
+// 40 K of them 8.5 and 6.5).
 template <int BITS>
 void launch_greedy_units(QuantArgs &a, hipStream_t s) {
     const uint32_t n4 = a.dim / 4;
@@ -1436,6 +1440,8 @@ void launch_greedy_units(QuantArgs &a, hipStream_t s) {
     const uint64_t fill = 49152u / lanes, busy = (lanes >= 4 ? 20480ull : 8192ull) * n4 / (lanes * lanes);
     uint64_t wide_rows = fill > busy ? fill : busy;
     if (lanes == 4 && n4 < 36 && wide_rows > 26624) wide_rows = 26624;
+    if (n4 <= 4) wide_rows /= 2;
+    if (BITS == 8) wide_rows = wide_rows * 2 / 5;
     if (n4 >= 68 && n4 < 72) wide_rows = ~0ull;
     const bool may_be_wide = lanes == 64 || a.n_max >= wide_rows;
     const bool may_be_narrow = lanes != 64 && (!may_be_wide || a.n_dev != nullptr);
@@ -1460,22 +1466,29 @@ void launch_greedy_units(QuantArgs &a, hipStream_t s) {
 // 16 to 128 elements 28-30 -> 12-25 us, of 256 30 -> 24; at the line both take the same.  A search of few
 // iterations gains less than the wider spread of its rows costs, so the line comes down with it (up to 10 bins,
 // 12 K rows of 64 8.8 us in one group, 9.6 in two, 6 K rows 8.8 and 7.9; up to 4 bins, 3 K rows of 128 5.4 and 5.9).
+// At 8 bits a search ends after an iteration or two and one group is level or better for rows of 64 and more (12 K of them 4.8
+// against 5.8 us) and beyond 6 K shorter rows (4.6 against 4.1-4.3 below, 4.6 and 4.5-4.9 at 12 K); at 3 and 4 bits rows of 64 have the line at half the others' waves (12 K rows, 45 bins: 10.8 against 13.5; 6 K 10.5 either way; at 2
+// bits, 12 K rows, 16.4 against 15.7).
 // Only where the host's bound on the length says so: another launch to choose from on the device would cost
 // the longer lists more.
 template <int BITS>
 bool launch_greedy_short(QuantArgs &a, hipStream_t s) {
     const uint32_t lanes = a.dim <= 32 ? 8 : a.dim <= 128 ? 16 : 32;
-    const uint32_t many = 196608u / lanes;
+    const uint32_t many = 196608u / lanes >> (BITS == 8 ? 2 : a.dim == 64 && BITS != 2 ? 1 : 0);
     const uint32_t most = a.n_iter >= 16 ? many : a.dim <= 64 ? (a.n_iter >= 3 ? many / 2 : many / 4) : a.n_iter >= 8 ? many / 4 : 0;
-    if (a.n_max > most) return false;
-    switch (a.dim) {
-        case 16:
-        case 32: launch_greedy_units_shape<4, 2, true, BITS>(a, s, 0, ~0ull); return true;
-        case 64:
-        case 128: launch_greedy_units_shape<8, 8, true, BITS>(a, s, 0, ~0ull); return true;
-        case 256: launch_greedy_units_shape<16, 4, true, BITS>(a, s, 0, ~0ull); return true;
-        default: return false;
+    if (a.n_max > most || (BITS == 8 && a.dim > 32)) return false;
+    if (a.dim == 16 || a.dim == 32) {
+        launch_greedy_units_shape<4, 2, true, BITS>(a, s, 0, ~0ull);
+        return true;
     }
+    if constexpr (BITS != 8) {
+        switch (a.dim) {
+            case 64:
+            case 128: launch_greedy_units_shape<8, 8, true, BITS>(a, s, 0, ~0ull); return true;
+            case 256: launch_greedy_units_shape<16, 4, true, BITS>(a, s, 0, ~0ull); return true;
+        }
+    }
+    return false;
 }
 
 template <int LPR, int U, int SB, int BITS>
