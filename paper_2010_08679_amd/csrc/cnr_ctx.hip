@@ -20,9 +20,7 @@ cnr_status cnr_enter(cnr_ctx *ctx) {
 }
 
 __global__ void __launch_bounds__(kBlock) fill_u32_kernel(uint32_t *p, uint64_t n, uint32_t v) {
-    uint64_t i = (uint64_t)wg_x() * kBlock + tid_x();
-    const uint64_t stride = (uint64_t)grid_x() * kBlock;
-    for (; i < n; i += stride) p[i] = v;
+    for (uint64_t i = tid_x(); i < n; i += kBlock) p[i] = v;  // one workgroup
 }
 
 extern "C" {

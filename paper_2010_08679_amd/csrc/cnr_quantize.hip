@@ -1014,7 +1014,8 @@ quantize_greedy_units_kernel(const QuantArgs a, double less /* tie_factor(dim) *
 // workgroup.  Grid y = parameters, so that all of them run side by side: a sample of a few thousand rows
 // leaves the chip mostly idle, and the launch takes as long as its longest search.  One launch per set of
 // parameters with the codes stored, read back and compared (encode, error, mean and a synchronization
-// each) took 354 us for 2.5 K rows of 64 and eight sets, this 111 us.
+// each) took 354 us for 2.5 K rows of 64 and eight sets, this 111 us; searches that end early and a grid size that is an
+// argument (36 -> 26 and 24 -> 16 us for the two launches): 68 us.
 // ---------------------------------------------------------------------------------------------
 struct SelectArgs {
     const float *table;
@@ -1024,6 +1025,7 @@ struct SelectArgs {
     uint64_t n;
     double less;   // tie_factor(dim)
     double *sums;  // [parameters][workgroups along x]
+    uint32_t grid;  // workgroups along x
     cnr_dev_errors *err;
     cnr_search_params params[kSearchBatch];
 };
@@ -1039,7 +1041,7 @@ sample_error_kernel(const SelectArgs a) {
     const uint32_t n4 = a.dim / 4;
     const int lane = tid_x() & (kWave - 1);
     const uint32_t j = lane % L;
-    const uint32_t n_waves = grid_x() * kWavesPerBlock;
+    const uint32_t n_waves = a.grid * kWavesPerBlock;
     double sum = 0.0;
     for (uint64_t pass = wave_in_grid(); pass * kRowsPerPass < a.n; pass += n_waves) {
         const uint64_t k = pass * kRowsPerPass + lane / Row::LANES;
@@ -1087,7 +1089,7 @@ sample_error_kernel(const SelectArgs a) {
     if (tid_x() == 0) {
         double total = 0.0;
         for (int w = 0; w < kWavesPerBlock; ++w) total += wave_sum[w];
-        a.sums[(uint64_t)wg_y() * grid_x() + wg_x()] = total;
+        a.sums[(uint64_t)wg_y() * a.grid + wg_x()] = total;
     }
 }
 // mean_out[p] = (the sums of parameters p, added up in a fixed order) / n; one workgroup per p.
@@ -1334,7 +1336,7 @@ __global__ void __launch_bounds__(kBlock) quantize_units_kernel(const QuantArgs 
 template <int BITS>
 __global__ void __launch_bounds__(kBlock)
 pack_kernel(const uint8_t *__restrict__ codes, const uint64_t *__restrict__ n_dev, uint64_t n_max,
-            uint32_t dim, uint8_t *__restrict__ packed) {
+            uint32_t dim, uint8_t *__restrict__ packed, uint64_t stride) {
     uint64_t n = n_max;
     if (n_dev) {
         const uint64_t nd = *n_dev;
@@ -1342,7 +1344,6 @@ pack_kernel(const uint8_t *__restrict__ codes, const uint64_t *__restrict__ n_de
     }
     const uint64_t P = (uint64_t)dim * BITS / 8;
     const uint64_t total = n * P;
-    const uint64_t stride = (uint64_t)grid_x() * kBlock;
     for (uint64_t o = (uint64_t)wg_x() * kBlock + tid_x(); o < total; o += stride) {
         const uint64_t k = o / P, b = o - k * P;
         const uint8_t *row = codes + k * (uint64_t)dim;
@@ -1558,6 +1559,7 @@ cnr_status launch_sample_errors(cnr_ctx *ctx, SelectArgs &a, uint32_t n_sets, ui
     uint64_t grid = (a.n + rows_per_wg - 1) / rows_per_wg;
     if (grid > 4096) grid = 4096;
     if (grid > max_sums / n_sets) grid = max_sums / n_sets;  // at least 1: the caller sees to it
+    a.grid = (uint32_t)grid;
     const dim3 g((unsigned)grid, n_sets);
     if (wide && n4 < 36) hipLaunchKernelGGL((sample_error_kernel<4, 8, false, BITS>), g, dim3(kBlock), 0, s, a);
     else if (wide) hipLaunchKernelGGL((sample_error_kernel<4, 16, false, BITS>), g, dim3(kBlock), 0, s, a);
@@ -1580,7 +1582,7 @@ cnr_status cnr_sample_errors(cnr_ctx *ctx, const float *table, uint64_t n_rows, 
         uint32_t m = n_params - done;
         if (m > kSearchBatch) m = kSearchBatch;
         if (m > max_sums) m = (uint32_t)max_sums;  // >= 1
-        SelectArgs a = {table, n_rows, dim, row_ids, n, tie_factor(dim), sums, ctx->dev_err, {}};
+        SelectArgs a = {table, n_rows, dim, row_ids, n, tie_factor(dim), sums, 0, ctx->dev_err, {}};
         for (uint32_t i = 0; i < m; ++i) a.params[i] = params[done + i];
         cnr_status st;
         switch (bits) {
@@ -1713,10 +1715,10 @@ cnr_status cnr_pack(cnr_ctx *ctx, const uint8_t *codes_u8, const uint64_t *n_dev
     const unsigned grid = cnr_grid(ctx, bytes, kBlock, 16);
     hipStream_t s = as_stream(stream);
     switch (bits) {
-        case 2: hipLaunchKernelGGL(pack_kernel<2>, dim3(grid), dim3(kBlock), 0, s, codes_u8, n_dev, n_max, dim, packed); break;
-        case 3: hipLaunchKernelGGL(pack_kernel<3>, dim3(grid), dim3(kBlock), 0, s, codes_u8, n_dev, n_max, dim, packed); break;
-        case 4: hipLaunchKernelGGL(pack_kernel<4>, dim3(grid), dim3(kBlock), 0, s, codes_u8, n_dev, n_max, dim, packed); break;
-        default: hipLaunchKernelGGL(pack_kernel<8>, dim3(grid), dim3(kBlock), 0, s, codes_u8, n_dev, n_max, dim, packed); break;
+        case 2: hipLaunchKernelGGL(pack_kernel<2>, dim3(grid), dim3(kBlock), 0, s, codes_u8, n_dev, n_max, dim, packed, (uint64_t)grid * kBlock); break;
+        case 3: hipLaunchKernelGGL(pack_kernel<3>, dim3(grid), dim3(kBlock), 0, s, codes_u8, n_dev, n_max, dim, packed, (uint64_t)grid * kBlock); break;
+        case 4: hipLaunchKernelGGL(pack_kernel<4>, dim3(grid), dim3(kBlock), 0, s, codes_u8, n_dev, n_max, dim, packed, (uint64_t)grid * kBlock); break;
+        default: hipLaunchKernelGGL(pack_kernel<8>, dim3(grid), dim3(kBlock), 0, s, codes_u8, n_dev, n_max, dim, packed, (uint64_t)grid * kBlock); break;
     }
     return cnr_launch_status(ctx);
 }

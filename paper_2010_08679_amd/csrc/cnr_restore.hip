@@ -407,12 +407,13 @@ struct ErrorArgs {
     double *err;
     uint64_t stride;     // the launch covers rows 0, stride, 2 * stride, ... of the list
     uint64_t cover;      // ... below this one
+    uint32_t n_waves;    // waves of the grid
     uint32_t parts;      // of a list of more than kPartsRows rows: leave the workgroup's sum in the place of its first row's error
     cnr_dev_errors *dev_err;
 };
 constexpr uint64_t kDirectMeanRows = 16384, kPartsRows = 8192;
-// Workgroups of the error kernel at most, each with a partial sum: 2048 to 4096 are equally fast on 1.5 M
-// rows of 64 (108 us with the mean), 8192 cost more in the two launches behind it than they gain (115 us).
+// Workgroups of the error kernel at most, each with a partial sum: more cost more in the two launches behind it
+// than they gain (1.5 M rows of 64 with the mean: 2048 93.5 us, 4096 91.1, 8192 94.4, 24576 119; without 84.8, 80.3, 78.4, 82.2).
 constexpr unsigned kErrorMaxBlocks = 4096;
 
 // Rows of the list that a launch works on, of n in all: none where it is the last of three (stride > 1) and
@@ -440,8 +441,9 @@ __device__ __forceinline__ void leave_partial_sum(double sum, double *err, uint6
 // takes the units j, j + LPR, ... of its row and their codes.  A wave holds ST rows per lane group at once,
 // so that as many row loads are in flight per lane.  Bound by the gather of the rows
 // (fp64: two conversions, a subtraction and a fused multiply-add per element, a quarter of the time).
-// 1.5 M rows of 64 at 4 bits: a wave per row with byte loads 332 us, this 93 us (5.0 TB/s); with the mean
-// 2018 -> 107 us.  Short lists are bound by the chain of loads of one row and by the fetch of the kernel's own
+// 1.5 M rows of 64 at 4 bits: a wave per row with byte loads 332 us, this 75-80 us (6 TB/s); with the mean
+// 2018 -> 85-91 us.  (93 and 107 while every wave read the size of its grid from the dispatch packet, in host memory:
+// 100 K rows 20 -> 10 us, 16 K 17 -> 9.)  Short lists are bound by the chain of loads of one row and by the fetch of the kernel's own
 // code: up to kShortErrorRows rows go with ST = 1, several units of a lane in flight instead.  A row's sum is
 // formed in the same order either way.  Returns this lane's share of the sum of the errors.
 constexpr int kErrorSteps = 4;
@@ -456,7 +458,7 @@ __device__ __forceinline__ double error_rows(const ErrorArgs &a, uint64_t items)
     const uint64_t P = (uint64_t)a.dim * BITS / 8;
     const int lane = tid_x() & (kWave - 1);
     const uint32_t j = lane % LPR, rho = lane / LPR;
-    const uint64_t n_waves = (uint64_t)grid_x() * kWavesPerBlock;
+    const uint64_t n_waves = a.n_waves;
     // What a lane needs of its rows of one pass: ids, scales and biases, requested one pass ahead.  Rows
     // past the end repeat the list's last one, and nothing of theirs is kept.
     uint32_t rid[ST];
@@ -575,7 +577,7 @@ __global__ void __launch_bounds__(kBlock) quant_error_kernel(const ErrorArgs a) 
     const uint64_t n = live_rows(a.n_dev, a.n_max);
     const uint64_t items = error_items(a, n);
     const int lane = tid_x() & (kWave - 1);
-    const uint64_t n_waves = (uint64_t)grid_x() * kWavesPerBlock;
+    const uint64_t n_waves = a.n_waves;
     const uint64_t P = (uint64_t)a.dim * BITS / 8;
     double sum = 0.0;
     for (uint64_t i = wave_in_grid(); i < items; i += n_waves) {
@@ -643,7 +645,8 @@ void launch_error_bits(const ErrorArgs &a, unsigned grid, uint32_t lanes, hipStr
         default: hipLaunchKernelGGL((quant_error_kernel<BITS>), dim3(grid), dim3(kBlock), 0, s, a); break;
     }
 }
-void launch_error(const ErrorArgs &a, unsigned grid, uint32_t lanes, int bits, hipStream_t s) {
+void launch_error(ErrorArgs &a, unsigned grid, uint32_t lanes, int bits, hipStream_t s) {
+    a.n_waves = grid * kWavesPerBlock;
     switch (bits) {
         case 2: return launch_error_bits<2>(a, grid, lanes, s);
         case 3: return launch_error_bits<3>(a, grid, lanes, s);
@@ -684,7 +687,7 @@ extern "C" cnr_status cnr_quant_error(cnr_ctx *ctx, const float *table, uint64_t
         if (!table || !packed || !scale || !bias || !err || n_rows == 0 || n_rows >= (1ull << 32)) return CNR_E_INVALID;
         const uint32_t lanes = error_lanes(dim, table, packed);
         const uint64_t rows_per_wg = (lanes ? (uint64_t)kErrorSteps * (kWave / lanes) : 1u) * kWavesPerBlock;
-        ErrorArgs a = {table, n_rows, dim, row_ids, n_dev, n_max, packed, scale, bias, err, 1, ~0ull, 0, ctx->dev_err};
+        ErrorArgs a = {table, n_rows, dim, row_ids, n_dev, n_max, packed, scale, bias, err, 1, ~0ull, 0, 0, ctx->dev_err};
         auto grid_for = [&](uint64_t rows) {  // of a short list of the units kernel, a wave holds fewer rows
             const uint64_t few = rows < kShortErrorRows ? rows : kShortErrorRows, few_per_wg = lanes ? rows_per_wg / kErrorSteps : rows_per_wg;
             const uint64_t need = (rows + rows_per_wg - 1) / rows_per_wg, need_few = (few + few_per_wg - 1) / few_per_wg;
