@@ -10,9 +10,8 @@ GPU, these calls fail.
 from __future__ import annotations
 
 import ctypes
-import itertools
+import importlib.util
 import os
-import struct
 import threading
 
 import torch
@@ -79,6 +78,7 @@ class cnr_table_job(ctypes.Structure):
 
 _lock = threading.Lock()
 _lib = None
+_marshal = None
 
 
 def ensure_built() -> str:
@@ -123,12 +123,12 @@ def load() -> ctypes.CDLL:
             "cnr_policy_init": (i32, [ctypes.POINTER(cnr_policy), i32]),
             "cnr_policy_next": (cnr_policy_decision, [ctypes.POINTER(cnr_policy), ctypes.c_double]),
             "cnr_select_bits": (i32, [u32, u32]),
-            "cnr_clear_bitmap_batch": (i32, [vp, ctypes.POINTER(cnr_table_job), u32, vp]),
-            "cnr_mark_touched_batch": (i32, [vp, ctypes.POINTER(cnr_table_job), u32, i32, vp]),
-            "cnr_compact_dirty_batch": (i32, [vp, ctypes.POINTER(cnr_table_job), u32, vp]),
-            "cnr_quantize_rows_batch": (i32, [vp, ctypes.POINTER(cnr_table_job), u32, u32, i32, i32,
+            "cnr_clear_bitmap_batch": (i32, [vp, vp, u32, vp]),
+            "cnr_mark_touched_batch": (i32, [vp, vp, u32, i32, vp]),
+            "cnr_compact_dirty_batch": (i32, [vp, vp, u32, vp]),
+            "cnr_quantize_rows_batch": (i32, [vp, vp, u32, u32, i32, i32,
                                               ctypes.POINTER(cnr_greedy_params), vp]),
-            "cnr_restore_rows_batch": (i32, [vp, ctypes.POINTER(cnr_table_job), u32, u32, i32, vp]),
+            "cnr_restore_rows_batch": (i32, [vp, vp, u32, u32, i32, vp]),
             "cnr_host_writer_device_bytes": (sz, [u32, i32, u64]),
             "cnr_host_writer_create": (i32, [vp, u32, i32, u64, ctypes.POINTER(vp)]),
             "cnr_host_writer_destroy": (i32, [vp]),
@@ -144,8 +144,19 @@ def load() -> ctypes.CDLL:
         for name, (res, args) in sig.items():
             fn = getattr(lib, name)
             fn.restype, fn.argtypes = res, args
+        _bind_marshal()
         _lib = lib
         return lib
+
+
+def _bind_marshal() -> None:
+    """From here on the extension checks the tensors of a call (see csrc/cnr_marshal.cpp)."""
+    global _dev, _marshal
+    spec = importlib.util.spec_from_file_location(__package__ + "._marshal", _build.build_marshal(force=False))
+    m = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(m)
+    m.set_general(_general_dev)
+    _marshal, _dev = m, m.address
 
 
 def status_str(status: int) -> str:
@@ -157,23 +168,30 @@ def _check(status: int, where: str) -> None:
         raise CnrError(status, where)
 
 
-def _dev(t, dtype, name: str):
-    """Device pointer of a contiguous tensor of the given dtype (None passes through as NULL)."""
+def _general_dev(t, dtype, name: str) -> int:
+    """Device address of a contiguous tensor of the given dtype (None: any); 0, NULL, for None."""
     if t is None:
-        return None
+        return 0
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError("%s must be a tensor on the GPU" % name)
-    if t.dtype != dtype:
+    if dtype is not None and t.dtype != dtype:
         raise TypeError("%s must be %s, got %s" % (name, dtype, t.dtype))
     if not t.is_contiguous():
         raise ValueError("%s must be contiguous" % name)
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream(stream):
-    """hipStream_t of a torch stream (the current one when None) as void*."""
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+_dev = _general_dev  # the extension's, once the library is loaded
+
+
+def _stream(stream) -> int:
+    """hipStream_t of a torch stream, of the current one when None.  (A torch.cuda.Stream object made for each call
+    is 2.7 us, the handle alone 0.2.)"""
+    if stream is not None:
+        return stream.cuda_stream
+    if torch.cuda.is_initialized():
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
 
 
 # uint32 / uint64 buffers are held in torch's int32 / int64 tensors (same bits).
@@ -229,8 +247,8 @@ def cnr_mark_touched(ctx, bitmap, n_rows: int, indices, scratch=None, stream=Non
     if scratch is not None and scratch.numel() * scratch.element_size() < cnr_mark_scratch_bytes(n_rows):
         raise ValueError("scratch smaller than cnr_mark_scratch_bytes(n_rows)")
     _check(load().cnr_mark_touched(ctx, _dev(bitmap, U32, "bitmap"), n_rows,
-                                   _dev(indices, indices.dtype, "indices"), indices.numel(), kind,
-                                   None if scratch is None else _dev(scratch, scratch.dtype, "scratch"),
+                                   _dev(indices, None, "indices"), indices.numel(), kind,
+                                   _dev(scratch, None, "scratch"),
                                    _stream(stream)), "cnr_mark_touched")
 
 
@@ -243,7 +261,7 @@ def cnr_compact_dirty(ctx, bitmap, n_rows: int, row_ids, capacity: int, n_dirty_
     _check(load().cnr_compact_dirty(ctx, _dev(bitmap, U32, "bitmap"), n_rows,
                                     _dev(row_ids, U32, "row_ids"), capacity,
                                     _dev(n_dirty_dev, U64, "n_dirty_dev"),
-                                    _dev(scratch, scratch.dtype, "scratch"), _stream(stream)),
+                                    _dev(scratch, None, "scratch"), _stream(stream)),
            "cnr_compact_dirty")
 
 
@@ -265,11 +283,15 @@ def cnr_quantize_rows(ctx, table, n_rows: int, dim: int, row_ids, n_dev, n_max: 
         gp = ctypes.pointer(cnr_greedy_params(int(greedy[0]), float(greedy[1])))
     if table.numel() < n_rows * dim:
         raise ValueError("table smaller than n_rows * dim")
-    for name, t, per_row in (("scale", scale, 1), ("bias", bias, 1), ("row_min", row_min, 1),
-                             ("row_max", row_max, 1), ("codes_u8", codes_u8, dim),
-                             ("packed", packed, cnr_packed_row_bytes(dim, bits))):
-        if t is not None and t.numel() < n_max * per_row:
-            raise ValueError("%s too small for n_max rows" % name)
+    if ((scale is not None and scale.numel() < n_max) or (bias is not None and bias.numel() < n_max)
+            or (row_min is not None and row_min.numel() < n_max) or (row_max is not None and row_max.numel() < n_max)
+            or (codes_u8 is not None and codes_u8.numel() < n_max * dim)
+            or (packed is not None and packed.numel() < n_max * cnr_packed_row_bytes(dim, bits))):
+        for name, t, per_row in (("scale", scale, 1), ("bias", bias, 1), ("row_min", row_min, 1),
+                                 ("row_max", row_max, 1), ("codes_u8", codes_u8, dim),
+                                 ("packed", packed, cnr_packed_row_bytes(dim, bits))):
+            if t is not None and t.numel() < n_max * per_row:
+                raise ValueError("%s too small for n_max rows" % name)
     if row_ids is not None and row_ids.numel() < n_max:
         raise ValueError("row_ids shorter than n_max")
     _check(load().cnr_quantize_rows(ctx, _dev(table, F32, "table"), n_rows, dim,
@@ -332,8 +354,7 @@ def make_jobs(jobs):
         for name, dtype in _JOB_TENSORS.items():
             t = d.get(name)
             if t is not None:
-                p = _dev(t, t.dtype if dtype is None else dtype, name)
-                setattr(j, name, p.value)
+                setattr(j, name, _dev(t, dtype, name))
         j.n_rows = int(d.get("n_rows", 0))
         j.capacity = int(d.get("capacity", 0))
         idx = d.get("indices")
@@ -341,29 +362,26 @@ def make_jobs(jobs):
     return arr
 
 
-def _ptr(t, dtype, name: str) -> int:
-    """Device address of a contiguous GPU tensor of the given dtype (None: any), 0 for None."""
-    if t is None:
-        return 0
-    if not (isinstance(t, torch.Tensor) and t.is_cuda and (dtype is None or t.dtype == dtype) and t.is_contiguous()):
-        _dev(t, t.dtype if dtype is None and isinstance(t, torch.Tensor) else dtype, name)  # raises with the reason
-    return t.data_ptr()
+_JOB_FIELDS = tuple(name for name, _ in cnr_table_job._fields_)
+_JOB_DTYPES = tuple(_JOB_TENSORS.get(name) for name in _JOB_FIELDS)
 
 
-_job_packers = {}
+def job_bytes(rows) -> bytes:
+    """The bytes of a ``cnr_table_job`` array from one 16-tuple per job, the struct's fields in order: numbers, and tensors or
+    None where the struct has addresses.  What :func:`make_jobs` builds field by field, with the same checks, in
+    one step; the batch calls take it."""
+    load()
+    return _marshal.pack_jobs(rows, _JOB_DTYPES, _JOB_FIELDS)
 
 
 def pack_jobs(rows):
-    """A ``cnr_table_job`` array from one 16-tuple of integers per job (the struct's fields in order): what
-    :func:`make_jobs` builds field by field, in one step, for callers that have checked their tensors."""
-    n = len(rows)
-    packer = _job_packers.get(n)
-    if packer is None:
-        packer = _job_packers[n] = (struct.Struct("%dQ" % (n * len(cnr_table_job._fields_))), cnr_table_job * n)
-    return packer[1].from_buffer_copy(packer[0].pack(*itertools.chain.from_iterable(rows)))
+    """:func:`job_bytes` as an array of ``cnr_table_job``."""
+    return (cnr_table_job * len(rows)).from_buffer_copy(job_bytes(rows))
 
 
 def _jobs_arg(jobs):
+    if isinstance(jobs, bytes):
+        return jobs, len(jobs) // ctypes.sizeof(cnr_table_job)
     if isinstance(jobs, (list, tuple)):
         return make_jobs(jobs), len(jobs)
     return jobs, len(jobs)
@@ -416,7 +434,7 @@ def cnr_select_greedy_params(ctx, table, n_rows: int, dim: int, sample_ids, bits
     chosen = cnr_greedy_params()
     _check(load().cnr_select_greedy_params(ctx, _dev(table, F32, "table"), n_rows, dim, _dev(sample_ids, U32, "sample_ids"),
                                            n, bits, bins, len(bins_grid), ratios, len(ratio_grid), float(taper),
-                                           _dev(scratch, scratch.dtype, "scratch"), ctypes.byref(chosen), report,
+                                           _dev(scratch, None, "scratch"), ctypes.byref(chosen), report,
                                            _stream(stream)), "cnr_select_greedy_params")
     return (int(chosen.num_bins), float(chosen.ratio)), list(report)
 

@@ -1,4 +1,5 @@
-"""Compiles libcnr.so (the HIP kernels and their C ABI) in-tree for gfx950."""
+"""Compiles libcnr.so (the HIP kernels and their C ABI) in-tree for gfx950, and the Python extension that hands
+it tensors' addresses."""
 from __future__ import annotations
 
 import glob
@@ -73,5 +74,47 @@ def build_lib(force: bool = True, verbose: bool = False) -> str:
     return LIB
 
 
+# ---- the Python extension (host code only) ---------------------------------------------------------
+
+MARSHAL = os.path.join(PKG, "_marshal.so")
+MARSHAL_SOURCE = os.path.join(CSRC, "cnr_marshal.cpp")
+
+
+def marshal_hash() -> str:
+    """Hash of the extension's source and of the interpreter and torch it is compiled against."""
+    import sys
+
+    import torch
+    h = hashlib.sha256(("%s %s" % (sys.version, torch.__version__)).encode())
+    with open(MARSHAL_SOURCE, "rb") as f:
+        h.update(f.read())
+    return h.hexdigest()
+
+
+def build_marshal(force: bool = True) -> str:
+    """Path of the extension, compiled if asked to or if it was built from another source."""
+    stamp = MARSHAL + ".srchash"
+    built_from = marshal_hash()
+    if not force and os.path.exists(MARSHAL) and os.path.exists(stamp):
+        with open(stamp, "r") as f:
+            if f.read().strip() == built_from:
+                return MARSHAL
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    tmp = MARSHAL + ".tmp.%d" % os.getpid()
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    subprocess.check_call([
+        os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+        *["-isystem" + d for d in cpp_extension.include_paths()], "-I" + sysconfig.get_paths()["include"],
+        "-o", tmp, MARSHAL_SOURCE, "-L" + lib, "-lc10", "-ltorch_cpu", "-ltorch_python"])
+    os.replace(tmp, MARSHAL)
+    with open(stamp, "w") as f:
+        f.write(built_from + "\n")
+    return MARSHAL
+
+
 if __name__ == "__main__":
+    build_marshal(force=True)
     print(build_lib(force=True, verbose=True))

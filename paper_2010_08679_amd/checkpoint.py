@@ -14,6 +14,8 @@ import torch
 
 from . import binding as B
 
+_ZEROS = [(0,) * k for k in range(17)]  # the fields of a job that a stage does not read
+
 
 @dataclass
 class EncodedRows:
@@ -177,27 +179,24 @@ class BatchCheckpointer:
             raise TypeError("the index streams of a batch share one dtype")
         return B.CNR_IDX_I32 if kinds == {torch.int32} else B.CNR_IDX_I64
 
-    # The calls of a training loop pass the fields that their stage reads, checked and packed in one step:
-    # the mark of an iteration takes a few microseconds on the GPU, and the general form above, field by
-    # field through dicts, took 46 us a call for eight tables (this 18 us).  Nothing is kept from one
-    # call to the next: buffers may be exchanged in between.
+    # The calls of a training loop pass the fields that their stage reads, checked and packed in one step by the
+    # extension: the mark of an iteration takes ten microseconds on the GPU, and the general form above, field by
+    # field through dicts, took 46 us a call for eight tables (checks in Python 19).  Nothing is kept from one call
+    # to the next: buffers may be exchanged in between.
     def clear(self, stream=None) -> None:
-        B.cnr_clear_bitmap_batch(self.ctx, B.pack_jobs(
-            [(0, c.n_rows, B._ptr(c.bitmap, B.U32, "bitmap")) + (0,) * 13 for c in self.cks]), stream)
+        B.cnr_clear_bitmap_batch(self.ctx, B.job_bytes([(0, c.n_rows, c.bitmap) + _ZEROS[13] for c in self.cks]), stream)
 
     def mark(self, indices, stream=None) -> None:
         kind = self._index_type(indices)
         flat = [indices[i] for i in range(len(self.cks))]
         flat = [t if t is None or t.is_contiguous() else t.reshape(-1) for t in flat]  # alive until the launch
-        B.cnr_mark_touched_batch(self.ctx, B.pack_jobs(
-            [(0, c.n_rows, B._ptr(c.bitmap, B.U32, "bitmap"), B._ptr(t, None, "indices"), 0 if t is None else t.numel(),
-              B._ptr(c.mark_scratch, None, "mark_scratch")) + (0,) * 10 for c, t in zip(self.cks, flat)]), kind, stream)
+        B.cnr_mark_touched_batch(self.ctx, B.job_bytes(
+            [(0, c.n_rows, c.bitmap, t, 0 if t is None else t.numel(), c.mark_scratch) + _ZEROS[10] for c, t in zip(self.cks, flat)]),
+            kind, stream)
 
     def compact(self, stream=None) -> None:
-        B.cnr_compact_dirty_batch(self.ctx, B.pack_jobs(
-            [(0, c.n_rows, B._ptr(c.bitmap, B.U32, "bitmap"), 0, 0, 0, B._ptr(c.row_ids, B.U32, "row_ids"), c.capacity,
-              B._ptr(c.n_dirty, B.U64, "n_dirty_dev"), B._ptr(c.scratch, None, "compact_scratch")) + (0,) * 6
-             for c in self.cks]), stream)
+        B.cnr_compact_dirty_batch(self.ctx, B.job_bytes(
+            [(0, c.n_rows, c.bitmap, 0, 0, 0, c.row_ids, c.capacity, c.n_dirty, c.scratch) + _ZEROS[6] for c in self.cks]), stream)
 
     def _row_jobs(self, tables, outs):
         rows = []
@@ -205,11 +204,9 @@ class BatchCheckpointer:
             t, o = tables[i], outs[i]
             self._check_table(i, c, t)
             self._check_output(i, c, o)
-            rows.append((B._ptr(t, B.F32, "table"), c.n_rows, 0, 0, 0, 0, B._ptr(c.row_ids, B.U32, "row_ids"), c.capacity,
-                         B._ptr(c.n_dirty, B.U64, "n_dirty_dev"), 0, B._ptr(o.scale, B.F32, "scale"),
-                         B._ptr(o.bias, B.F32, "bias"), B._ptr(o.row_min, B.F32, "row_min"),
-                         B._ptr(o.row_max, B.F32, "row_max"), 0, B._ptr(o.packed, B.U8, "packed")))
-        return B.pack_jobs(rows)
+            rows.append((t, c.n_rows, 0, 0, 0, 0, c.row_ids, c.capacity, c.n_dirty, 0, o.scale, o.bias, o.row_min, o.row_max, 0,
+                         o.packed))
+        return B.job_bytes(rows)
 
     def encode(self, tables, outs, mode: int = B.CNR_RANGE_MINMAX, greedy=None, stream=None) -> None:
         bits = outs[0].bits

@@ -309,3 +309,37 @@ def test_batched_step_replays_from_a_hip_graph(ctx):
             assert np.array_equal(stale[i].cpu().numpy(), want)
             assert not c.mark_scratch.any()
     _poll_clean(ctx)
+
+
+class _Sub(torch.Tensor):
+    pass
+
+
+def test_packed_jobs_are_the_general_ones(ctx):
+    """The extension's addresses and refusals against the general checks, also for parameters and subclasses."""
+    import ctypes
+
+    f, i, l, u = (torch.zeros(8, dtype=d, device=DEV) for d in (torch.float32, torch.int32, torch.int64, torch.uint8))
+    jobs = [dict(table=torch.nn.Parameter(f), n_rows=3, bitmap=i, indices=l, mark_scratch=u, row_ids=i[4:], capacity=5, n_dirty_dev=l[1:],
+                 compact_scratch=l, scale=f, bias=f.as_subclass(_Sub), row_min=None, row_max=f[:0], codes_u8=u, packed=u[1:]),
+            dict(n_rows=2 ** 32 - 1, table=f)]
+    want = bytes(P.binding.make_jobs(jobs))
+    fields = [n for n, _ in P.binding.cnr_table_job._fields_]
+    rows = [tuple(j.get(k, j["indices"].numel() if k == "n_indices" and "indices" in j else 0) for k in fields) for j in jobs]
+    assert P.binding.job_bytes(rows) == want and len(want) == 2 * ctypes.sizeof(P.binding.cnr_table_job)
+    assert P.binding.job_bytes([]) == b""
+    for t, dtype in ((f, torch.int32), (f[::2], None), (f.as_subclass(_Sub)[::2], None), (f.cpu(), None), (f.cpu().as_subclass(_Sub), None),
+                     (7.5, None), ([f], None)):
+        raised = []
+        for check in (P.binding._dev, P.binding._general_dev):
+            with pytest.raises((TypeError, ValueError)) as e:
+                check(t, dtype, "table")
+            raised.append((e.type, str(e.value)))
+        assert raised[0] == raised[1]
+    for bad in ([(0,) * 15], [[0] * 16], [(i,) + (0,) * 15], [(0, -1) + (0,) * 14]):
+        with pytest.raises((TypeError, OverflowError)):
+            P.binding.job_bytes(bad)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        assert P.binding._stream(None) == s.cuda_stream == P.binding._stream(s)
+    assert P.binding._stream(None) == torch.cuda.current_stream().cuda_stream
