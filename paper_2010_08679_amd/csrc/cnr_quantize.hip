@@ -349,12 +349,13 @@ __device__ __forceinline__ void encode_table(const QuantArgs &a, unsigned char *
 // The register budget is pinned to 6 / 4 / 2 waves per SIMD for rows of up to 64 / 128 / 256
 // elements: left alone, the compiler lands a few registers to either side of those limits from one
 // small change to the next.
+template <int N = CNR_MAX_BATCH>
 struct QuantBatchArgs {
-    QuantArgs job[CNR_MAX_BATCH];
+    QuantArgs job[N];
 };
 template <int Q, int BITS>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(Q <= 4 ? 6 : Q == 8 ? 4 : 2, Q <= 4 ? 6 : Q == 8 ? 4 : 2)))
-quantize_tile_kernel(const QuantBatchArgs b) {
+quantize_tile_kernel(const QuantBatchArgs<> b) {
     __shared__ __align__(16) unsigned char tiles[kWavesPerBlock * kTileBytes];
     const QuantArgs &a = b.job[wg_y()];
     if (wg_x() * kWavesPerBlock >= a.n_waves) return;
@@ -1209,8 +1210,20 @@ __device__ __forceinline__ void encode_strided(const QuantArgs &a, uint64_t n) {
         }
     }
 }
-template <int BITS>
-__global__ void __launch_bounds__(kBlock) quantize_strided_kernel(const QuantArgs a) {
+// Tables of a batch in one launch, as for the tile kernel: small tables are bound by their launches (the encode of eight
+// tables of 29 K rows of 8 34.5 us one table per launch, 14.6 all in one; 16 x 20 K rows of 96 66 -> 28; 2 x 2 M 137 -> 133).
+// Both the launch of one table (N = 1) and that of several exist: sixteen tables' arguments are 2 KB for each launch to
+// bring along (0.2 to 0.6 us of 6), and a job is copied out of them, since one that stays behind a reference is
+// loaded again inside the loops (1.5 M rows of 24 50 -> 56 us).
+template <int N>
+__device__ __forceinline__ QuantArgs job_of(const QuantBatchArgs<N> &b) {
+    if constexpr (N == 1) return b.job[0];
+    else return b.job[wg_y()];
+}
+template <int BITS, int N>
+__global__ void __launch_bounds__(kBlock) quantize_strided_kernel(const QuantBatchArgs<N> b) {
+    const QuantArgs a = job_of(b);
+    if (wg_x() * kWavesPerBlock >= a.n_waves) return;  // fewer workgroups than the launch's largest table
     encode_strided<kWave, BITS>(a, row_count(a));
 }
 
@@ -1225,9 +1238,11 @@ struct UnitsShape {
     static constexpr int SHORT_LPR = LPR * U <= 4 ? 4 : LPR * U <= 8 ? 8 : LPR * U <= 16 ? 16 : LPR * U <= 32 ? 32 : 64;
     static constexpr uint64_t SHORT_ROWS = kShortEncodeWaves * (kWave / SHORT_LPR);
 };
-template <int LPR, int U, int SB, int BITS>
-__global__ void __launch_bounds__(kBlock) quantize_units_kernel(const QuantArgs a) {
+template <int LPR, int U, int SB, int BITS, int N>
+__global__ void __launch_bounds__(kBlock) quantize_units_kernel(const QuantBatchArgs<N> b) {
     using S = UnitsShape<LPR, U, SB, BITS>;
+    const QuantArgs a = job_of(b);
+    if (wg_x() * kWavesPerBlock >= a.n_waves) return;
     constexpr int RPS = S::RPS, ROWS = S::ROWS;
     constexpr float QMAXF = (float)((1 << BITS) - 1);
     __shared__ __align__(16) uint8_t stages[kWavesPerBlock * S::STAGE];
@@ -1361,7 +1376,7 @@ pack_kernel(const uint8_t *__restrict__ codes, const uint64_t *__restrict__ n_de
 
 // n tables (or slices) in one launch: every one with the grid its own list calls for (cnr_row_grid).
 template <int Q, int BITS>
-void launch_tile(QuantBatchArgs &b, uint32_t n, hipStream_t s) {
+void launch_tile(QuantBatchArgs<> &b, uint32_t n, hipStream_t s) {
     unsigned grid = 1;
     for (uint32_t i = 0; i < n; ++i) {
         const unsigned g = cnr_row_grid(b.job[i].n_max, (uint64_t)TileShape<Q>::ROWS * kWavesPerBlock);
@@ -1371,7 +1386,7 @@ void launch_tile(QuantBatchArgs &b, uint32_t n, hipStream_t s) {
     hipLaunchKernelGGL((quantize_tile_kernel<Q, BITS>), dim3(grid, n), dim3(kBlock), 0, s, b);
 }
 template <int BITS>
-void launch_tile_bits(QuantBatchArgs &b, uint32_t n, uint32_t dim, hipStream_t s) {
+void launch_tile_bits(QuantBatchArgs<> &b, uint32_t n, uint32_t dim, hipStream_t s) {
     switch (dim) {
         case 16: return launch_tile<1, BITS>(b, n, s);
         case 32: return launch_tile<2, BITS>(b, n, s);
@@ -1380,7 +1395,7 @@ void launch_tile_bits(QuantBatchArgs &b, uint32_t n, uint32_t dim, hipStream_t s
         default: return launch_tile<16, BITS>(b, n, s);
     }
 }
-inline void launch_tile_any(QuantBatchArgs &b, uint32_t n, uint32_t dim, int bits, hipStream_t s) {
+inline void launch_tile_any(QuantBatchArgs<> &b, uint32_t n, uint32_t dim, int bits, hipStream_t s) {
     switch (bits) {
         case 2: return launch_tile_bits<2>(b, n, dim, s);
         case 3: return launch_tile_bits<3>(b, n, dim, s);
@@ -1492,59 +1507,84 @@ bool launch_greedy_short(QuantArgs &a, hipStream_t s) {
     return false;
 }
 
+// n tables in one launch: every one with the grid its own list calls for.
 template <int LPR, int U, int SB, int BITS>
-void launch_units(QuantArgs &a, hipStream_t s) {
+void launch_units(QuantBatchArgs<> &b, uint32_t n, hipStream_t s) {
     using S = UnitsShape<LPR, U, SB, BITS>;
-    const unsigned grid_long = cnr_row_grid(a.n_max, (uint64_t)S::ROWS * kWavesPerBlock);
-    const unsigned grid_short = cnr_row_grid(a.n_max < S::SHORT_ROWS ? a.n_max : S::SHORT_ROWS, (uint64_t)(kWave / S::SHORT_LPR) * kWavesPerBlock);
-    unsigned grid = grid_long > grid_short ? grid_long : grid_short;
-    // Where only the device knows the length it may be far below the capacity, and then the workgroups beyond the
-    // count are most of the time: half the usual cap (1 K rows of 96 in a capacity of 5 M 7.1 -> 4.5 us, 250 K rows
-    // 25.9 -> 24.6, 1.5 M rows 122 -> 127).
-    if (a.n_dev && grid > kRowKernelMaxBlocks / 2) grid = kRowKernelMaxBlocks / 2;
-    a.n_waves = grid * kWavesPerBlock;
-    hipLaunchKernelGGL((quantize_units_kernel<LPR, U, SB, BITS>), dim3(grid), dim3(kBlock), 0, s, a);
+    unsigned most = 1;
+    for (uint32_t i = 0; i < n; ++i) {
+        QuantArgs &a = b.job[i];
+        const unsigned grid_long = cnr_row_grid(a.n_max, (uint64_t)S::ROWS * kWavesPerBlock);
+        const unsigned grid_short = cnr_row_grid(a.n_max < S::SHORT_ROWS ? a.n_max : S::SHORT_ROWS, (uint64_t)(kWave / S::SHORT_LPR) * kWavesPerBlock);
+        unsigned grid = grid_long > grid_short ? grid_long : grid_short;
+        // Where only the device knows the length it may be far below the capacity, and then the workgroups beyond the
+        // count are most of the time: half the usual cap (1 K rows of 96 in a capacity of 5 M 7.1 -> 4.5 us, 250 K rows
+        // 25.9 -> 24.6, 1.5 M rows 122 -> 127).
+        if (a.n_dev && grid > kRowKernelMaxBlocks / 2) grid = kRowKernelMaxBlocks / 2;
+        a.n_waves = grid * kWavesPerBlock;
+        if (grid > most) most = grid;
+    }
+    if (n == 1) hipLaunchKernelGGL((quantize_units_kernel<LPR, U, SB, BITS, 1>), dim3(most), dim3(kBlock), 0, s, QuantBatchArgs<1>{{b.job[0]}});
+    else hipLaunchKernelGGL((quantize_units_kernel<LPR, U, SB, BITS, CNR_MAX_BATCH>), dim3(most, n), dim3(kBlock), 0, s, b);
 }
 
-// The kernels that take one table per launch: the greedy search at any row length, and min/max or
-// symmetric ranges at row lengths the tile kernel does not take.
+// The greedy search, which takes one table per launch.
 template <int BITS>
-void launch_bits(cnr_ctx *ctx, QuantArgs &a, hipStream_t s) {
-    const bool greedy = a.mode == kModeGreedy && a.n_iter > 0;  // zero iterations: plain min/max
-    if (greedy && launch_greedy_short<BITS>(a, s)) return;
-    if (greedy && a.dim == 16) return launch_greedy<1, BITS, 1>(ctx, a, s, 0, ~0ull);
-    if (greedy && a.dim == 32) return launch_greedy_by_length<2, 1, 2, BITS>(ctx, a, s);
-    if (greedy && a.dim == 64) return launch_greedy_by_length<4, 1, 4, BITS>(ctx, a, s);
-    if (greedy && a.dim == 128) return launch_greedy_by_length<8, 2, 4, BITS>(ctx, a, s);
-    if (greedy && a.dim == 256) return launch_greedy_by_length<16, 4, 4, BITS>(ctx, a, s);
-    if (greedy) return launch_greedy_units<BITS>(a, s);
-    const uint32_t n4 = a.dim / 4;
-    // A row per wave: rows of more than 512 elements, and the lists of more than 192 on which the registers that
-    // the units kernel holds keep too few rows in flight.  Measured break-evens: rows of 200 and 252 at 13 K and
-    // 15 K, of 264 and 320 at 16 K, of 384 at 20 K, of 448 at 45 K, of 512 at 70 K (12 K rows: 6.0 against 9.2 us).
-    const uint64_t by_wave = n4 > 128 ? ~0ull : n4 <= 48 ? 0 : n4 <= 80 ? 12288 : 8192ull << ((n4 - 65) / 16);
-    if (a.n_max <= by_wave) {
-        const unsigned grid = cnr_grid(ctx, a.n_max, kWavesPerBlock, cnr_resident_blocks_per_cu<quantize_strided_kernel<BITS>>());
-        a.n_waves = grid * kWavesPerBlock;
-        hipLaunchKernelGGL((quantize_strided_kernel<BITS>), dim3(grid), dim3(kBlock), 0, s, a);
-        return;
+void launch_greedy_bits(cnr_ctx *ctx, QuantArgs &a, hipStream_t s) {
+    if (launch_greedy_short<BITS>(a, s)) return;
+    if (a.dim == 16) return launch_greedy<1, BITS, 1>(ctx, a, s, 0, ~0ull);
+    if (a.dim == 32) return launch_greedy_by_length<2, 1, 2, BITS>(ctx, a, s);
+    if (a.dim == 64) return launch_greedy_by_length<4, 1, 4, BITS>(ctx, a, s);
+    if (a.dim == 128) return launch_greedy_by_length<8, 2, 4, BITS>(ctx, a, s);
+    if (a.dim == 256) return launch_greedy_by_length<16, 4, 4, BITS>(ctx, a, s);
+    return launch_greedy_units<BITS>(a, s);
+}
+
+// Min/max or symmetric ranges at row lengths the tile kernel does not take.
+//
+// Longest list that goes a row per wave: rows of more than 512 elements, and the lists of more than 192 on which the
+// registers that the units kernel holds keep too few rows in flight.  Measured break-evens: rows of 200 and 252 at 13 K and
+// 15 K, of 264 and 320 at 16 K, of 384 at 20 K, of 448 at 45 K, of 512 at 70 K (12 K rows: 6.0 against 9.2 us).
+inline uint64_t rows_by_wave(uint32_t dim) {
+    const uint32_t n4 = dim / 4;
+    return n4 > 128 ? ~0ull : n4 <= 48 ? 0 : n4 <= 80 ? 12288 : 8192ull << ((n4 - 65) / 16);
+}
+template <int BITS>
+void launch_strided(cnr_ctx *ctx, QuantBatchArgs<> &b, uint32_t n, hipStream_t s) {
+    unsigned most = 1;
+    for (uint32_t i = 0; i < n; ++i) {
+        const unsigned grid = cnr_grid(ctx, b.job[i].n_max, kWavesPerBlock, cnr_resident_blocks_per_cu<quantize_strided_kernel<BITS, 1>>());
+        b.job[i].n_waves = grid * kWavesPerBlock;
+        if (grid > most) most = grid;
     }
-    // Few idle lanes at every length (units of a row: lanes x units per lane), and 64 registers of row data or
-    // fewer on their way per lane
-    if (n4 <= 4) return launch_units<4, 1, 4, BITS>(a, s);
-    if (n4 <= 8) return launch_units<8, 1, 4, BITS>(a, s);
-    if (n4 <= 12) return launch_units<4, 3, 2, BITS>(a, s);
-    if (n4 <= 16) return launch_units<8, 2, 4, BITS>(a, s);
-    if (n4 <= 24) return launch_units<8, 3, 2, BITS>(a, s);
-    if (n4 <= 32) return launch_units<8, 4, 2, BITS>(a, s);
-    if (n4 <= 40) return launch_units<8, 5, 2, BITS>(a, s);
-    if (n4 <= 48) return launch_units<8, 6, 2, BITS>(a, s);
-    if (n4 <= 56) return launch_units<8, 7, 2, BITS>(a, s);
-    if (n4 <= 64) return launch_units<8, 8, 2, BITS>(a, s);
-    if (n4 <= 80) return launch_units<16, 5, 2, BITS>(a, s);
-    if (n4 <= 96) return launch_units<16, 6, 2, BITS>(a, s);
-    if (n4 <= 112) return launch_units<16, 7, 2, BITS>(a, s);
-    return launch_units<16, 8, 2, BITS>(a, s);
+    if (n == 1) hipLaunchKernelGGL((quantize_strided_kernel<BITS, 1>), dim3(most), dim3(kBlock), 0, s, QuantBatchArgs<1>{{b.job[0]}});
+    else hipLaunchKernelGGL((quantize_strided_kernel<BITS, CNR_MAX_BATCH>), dim3(most, n), dim3(kBlock), 0, s, b);
+}
+// Few idle lanes at every length (units of a row: lanes x units per lane), and 64 registers of row data or
+// fewer on their way per lane
+template <int BITS>
+void launch_units_any(QuantBatchArgs<> &b, uint32_t n, uint32_t dim, hipStream_t s) {
+    const uint32_t n4 = dim / 4;
+    if (n4 <= 4) return launch_units<4, 1, 4, BITS>(b, n, s);
+    if (n4 <= 8) return launch_units<8, 1, 4, BITS>(b, n, s);
+    if (n4 <= 12) return launch_units<4, 3, 2, BITS>(b, n, s);
+    if (n4 <= 16) return launch_units<8, 2, 4, BITS>(b, n, s);
+    if (n4 <= 24) return launch_units<8, 3, 2, BITS>(b, n, s);
+    if (n4 <= 32) return launch_units<8, 4, 2, BITS>(b, n, s);
+    if (n4 <= 40) return launch_units<8, 5, 2, BITS>(b, n, s);
+    if (n4 <= 48) return launch_units<8, 6, 2, BITS>(b, n, s);
+    if (n4 <= 56) return launch_units<8, 7, 2, BITS>(b, n, s);
+    if (n4 <= 64) return launch_units<8, 8, 2, BITS>(b, n, s);
+    if (n4 <= 80) return launch_units<16, 5, 2, BITS>(b, n, s);
+    if (n4 <= 96) return launch_units<16, 6, 2, BITS>(b, n, s);
+    if (n4 <= 112) return launch_units<16, 7, 2, BITS>(b, n, s);
+    return launch_units<16, 8, 2, BITS>(b, n, s);
+}
+// by_wave: every table of the launch is one of rows_by_wave or fewer rows
+template <int BITS>
+void launch_rows(cnr_ctx *ctx, QuantBatchArgs<> &b, uint32_t n, uint32_t dim, bool by_wave, hipStream_t s) {
+    if (by_wave) launch_strided<BITS>(ctx, b, n, s);
+    else launch_units_any<BITS>(b, n, dim, s);
 }
 
 // Two groups of lanes per row while the sets of parameters together leave room on the chip; four lanes
@@ -1641,47 +1681,52 @@ cnr_status cnr_quantize_rows_batch(cnr_ctx *ctx, const cnr_table_job *jobs, uint
         a.err = ctx->dev_err;
         return a;
     };
-    // The tile kernel takes up to CNR_MAX_BATCH tables per launch.  Small tables (rows of at most
-    // kSideBySideBytes at capacity) and large ones go into launches of their own kind, so that a
-    // small table is not given a large one's grid; a list whose length the host knows is cut into
-    // slices (cnr_slice_rows), each a table of the launch.
-    const bool tile_dim = dim == 16 || dim == 32 || dim == 64 || dim == 128 || dim == 256;
-    if (tile_dim && n_iter == 0) {
-        for (int large = 0; large < 2; ++large) {
-            QuantBatchArgs b = {};
-            uint32_t n = 0;
-            auto flush = [&]() -> cnr_status {
-                if (n == 0) return CNR_OK;
-                launch_tile_any(b, n, dim, bits, s);
-                n = 0;
-                return cnr_launch_status(ctx);
-            };
-            for (uint32_t i = 0; i < n_jobs; ++i) {
-                const cnr_table_job &j = jobs[i];
-                if (j.capacity == 0 || (j.capacity * 4ull * dim > kSideBySideBytes) != (large != 0)) continue;
-                const bool sliceable = !j.n_dirty_dev && (j.row_ids || j.capacity <= j.n_rows);
-                const uint64_t step = sliceable ? cnr_slice_rows(j.capacity, dim) : j.capacity;
-                for (uint64_t k0 = 0; k0 < j.capacity; k0 += step) {
-                    b.job[n++] = part(j, k0, j.capacity - k0 < step ? j.capacity - k0 : step);
-                    if (n == CNR_MAX_BATCH && (st = flush()) != CNR_OK) return st;
-                }
+    if (n_iter) {  // greedy search: one launch per table
+        for (uint32_t i = 0; i < n_jobs; ++i) {
+            const cnr_table_job &j = jobs[i];
+            if (j.capacity == 0) continue;
+            QuantArgs a = part(j, 0, j.capacity);
+            switch (bits) {
+                case 2: launch_greedy_bits<2>(ctx, a, s); break;
+                case 3: launch_greedy_bits<3>(ctx, a, s); break;
+                case 4: launch_greedy_bits<4>(ctx, a, s); break;
+                default: launch_greedy_bits<8>(ctx, a, s); break;
             }
-            if ((st = flush()) != CNR_OK) return st;
+            if ((st = cnr_launch_status(ctx)) != CNR_OK) return st;
         }
         return CNR_OK;
     }
-    // greedy search, other row lengths: one launch per table
-    for (uint32_t i = 0; i < n_jobs; ++i) {
-        const cnr_table_job &j = jobs[i];
-        if (j.capacity == 0) continue;
-        QuantArgs a = part(j, 0, j.capacity);
-        switch (bits) {
-            case 2: launch_bits<2>(ctx, a, s); break;
-            case 3: launch_bits<3>(ctx, a, s); break;
-            case 4: launch_bits<4>(ctx, a, s); break;
-            default: launch_bits<8>(ctx, a, s); break;
+    // Up to CNR_MAX_BATCH tables per launch.  Small tables (rows of at most kSideBySideBytes at capacity) and large
+    // ones go into launches of their own kind, so that a small table is not given a large one's grid, and
+    // so do the tables that go a row per wave; for the tile kernel a list whose length the host knows is cut into
+    // slices (cnr_slice_rows), each a table of the launch.
+    const bool tile_dim = dim == 16 || dim == 32 || dim == 64 || dim == 128 || dim == 256;
+    const uint64_t wave_rows = tile_dim ? 0 : rows_by_wave(dim);
+    QuantBatchArgs<> b;  // 2 KB; what a launch reads of it is written before
+    for (int kind = 0; kind < (wave_rows ? 4 : 2); ++kind) {
+        const bool large = kind & 1, by_wave = kind & 2;
+        uint32_t n = 0;
+        auto flush = [&]() -> cnr_status {
+            if (n == 0) return CNR_OK;
+            if (tile_dim) launch_tile_any(b, n, dim, bits, s);
+            else if (bits == 2) launch_rows<2>(ctx, b, n, dim, by_wave, s);
+            else if (bits == 3) launch_rows<3>(ctx, b, n, dim, by_wave, s);
+            else if (bits == 4) launch_rows<4>(ctx, b, n, dim, by_wave, s);
+            else launch_rows<8>(ctx, b, n, dim, by_wave, s);
+            n = 0;
+            return cnr_launch_status(ctx);
+        };
+        for (uint32_t i = 0; i < n_jobs; ++i) {
+            const cnr_table_job &j = jobs[i];
+            if (j.capacity == 0 || (j.capacity * 4ull * dim > kSideBySideBytes) != large || (j.capacity <= wave_rows) != by_wave) continue;
+            const bool sliceable = tile_dim && !j.n_dirty_dev && (j.row_ids || j.capacity <= j.n_rows);
+            const uint64_t step = sliceable ? cnr_slice_rows(j.capacity, dim) : j.capacity;
+            for (uint64_t k0 = 0; k0 < j.capacity; k0 += step) {
+                b.job[n++] = part(j, k0, j.capacity - k0 < step ? j.capacity - k0 : step);
+                if (n == CNR_MAX_BATCH && (st = flush()) != CNR_OK) return st;
+            }
         }
-        if ((st = cnr_launch_status(ctx)) != CNR_OK) return st;
+        if ((st = flush()) != CNR_OK) return st;
     }
     return CNR_OK;
 }

@@ -274,15 +274,16 @@ __device__ __forceinline__ void restore_table(const RestoreJob &a, cnr_dev_error
 
 // One launch takes up to CNR_MAX_BATCH tables (grid y = table; a slice of a long list counts as a
 // table), swept one after the other because workgroups are handed out x first, as for the encode.
+template <int N = CNR_MAX_BATCH>
 struct RestoreBatch {
-    RestoreJob job[CNR_MAX_BATCH];
+    RestoreJob job[N];
 };
 // The register budget is pinned to eight waves per SIMD (64 registers), which every shape meets without
 // spilling except rows of 256 floats at 8 bits (left to the compiler: 84 registers, five waves): left
 // alone, a few shapes land two registers above the step.
 template <int Q, int BITS>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(Q == 16 && BITS == 8 ? 5 : 8, 8)))
-restore_rows16_kernel(const RestoreBatch b, cnr_dev_errors *err) {
+restore_rows16_kernel(const RestoreBatch<> b, cnr_dev_errors *err) {
     constexpr int kStage = CodeFetch<Q, BITS>::STAGE_BYTES;
     __shared__ __align__(16) unsigned char stages[kStage ? kWavesPerBlock * kStage : 16];
     const RestoreJob &a = b.job[wg_y()];
@@ -294,8 +295,12 @@ restore_rows16_kernel(const RestoreBatch b, cnr_dev_errors *err) {
 // to 64), 64 / LPR rows per wave and pass; lane j takes the units j, j + LPR, ... of its row: it reads
 // the unit's 4 * BITS code bits (one, two or four bytes; at 3 bits the three bytes that hold the
 // unit and its pair partner) and stores 16 bytes.
-template <int LPR, int BITS>
-__global__ void __launch_bounds__(kBlock) restore_strided_kernel(const RestoreJob a, uint32_t dim, cnr_dev_errors *err) {
+// A batch's tables share a launch (eight tables of 29 K rows of 96 32 -> 13.5 us); one table has a launch with less to bring along
+// (0.2 to 0.6 us of 6).
+template <int LPR, int BITS, int N>
+__global__ void __launch_bounds__(kBlock) restore_strided_kernel(const RestoreBatch<N> batch, uint32_t dim, cnr_dev_errors *err) {
+    const RestoreJob a = batch.job[N == 1 ? 0 : wg_y()];
+    if (wg_x() * kWavesPerBlock >= a.n_waves) return;
     constexpr int kRowsPerPass = kWave / LPR;
     constexpr uint32_t MASK = (1u << BITS) - 1u;
     const uint64_t n = live_rows(a.n_dev, a.n_max);
@@ -342,7 +347,7 @@ __global__ void __launch_bounds__(kBlock) restore_strided_kernel(const RestoreJo
 }
 
 template <int Q, int BITS>
-void launch_restore16(cnr_ctx *ctx, hipStream_t st, RestoreBatch &b, uint32_t n) {
+void launch_restore16(cnr_ctx *ctx, hipStream_t st, RestoreBatch<> &b, uint32_t n) {
     unsigned grid = 1;
     for (uint32_t i = 0; i < n; ++i) {
         const unsigned g = cnr_row_grid(b.job[i].n_max, (uint64_t)RestoreShape<Q>::ROWS * kWavesPerBlock);
@@ -352,7 +357,7 @@ void launch_restore16(cnr_ctx *ctx, hipStream_t st, RestoreBatch &b, uint32_t n)
     hipLaunchKernelGGL((restore_rows16_kernel<Q, BITS>), dim3(grid, n), dim3(kBlock), 0, st, b, ctx->dev_err);
 }
 template <int BITS>
-void launch_restore16_bits(cnr_ctx *ctx, hipStream_t st, uint32_t dim, RestoreBatch &b, uint32_t n) {
+void launch_restore16_bits(cnr_ctx *ctx, hipStream_t st, uint32_t dim, RestoreBatch<> &b, uint32_t n) {
     switch (dim) {
         case 16: return launch_restore16<1, BITS>(ctx, st, b, n);
         case 32: return launch_restore16<2, BITS>(ctx, st, b, n);
@@ -363,21 +368,26 @@ void launch_restore16_bits(cnr_ctx *ctx, hipStream_t st, uint32_t dim, RestoreBa
 }
 
 template <int LPR, int BITS>
-void launch_restore_strided(cnr_ctx *ctx, hipStream_t st, uint32_t dim, RestoreJob &a) {
-    const unsigned grid = cnr_row_grid(a.n_max, (uint64_t)(kWave / LPR) * kWavesPerBlock);
-    a.n_waves = grid * kWavesPerBlock;
-    hipLaunchKernelGGL((restore_strided_kernel<LPR, BITS>), dim3(grid), dim3(kBlock), 0, st, a, dim, ctx->dev_err);
+void launch_restore_strided(cnr_ctx *ctx, hipStream_t st, uint32_t dim, RestoreBatch<> &b, uint32_t n) {
+    unsigned grid = 1;
+    for (uint32_t i = 0; i < n; ++i) {
+        const unsigned g = cnr_row_grid(b.job[i].n_max, (uint64_t)(kWave / LPR) * kWavesPerBlock);
+        b.job[i].n_waves = g * kWavesPerBlock;
+        if (g > grid) grid = g;
+    }
+    if (n == 1) hipLaunchKernelGGL((restore_strided_kernel<LPR, BITS, 1>), dim3(grid), dim3(kBlock), 0, st, RestoreBatch<1>{{b.job[0]}}, dim, ctx->dev_err);
+    else hipLaunchKernelGGL((restore_strided_kernel<LPR, BITS, CNR_MAX_BATCH>), dim3(grid, n), dim3(kBlock), 0, st, b, dim, ctx->dev_err);
 }
 
-// other row lengths: one table per launch
 template <int BITS>
-void launch_restore(cnr_ctx *ctx, hipStream_t st, uint32_t dim, RestoreJob &a) {
+void launch_restore(cnr_ctx *ctx, hipStream_t st, uint32_t dim, RestoreBatch<> &b, uint32_t n) {
+    if (dim == 16 || dim == 32 || dim == 64 || dim == 128 || dim == 256) return launch_restore16_bits<BITS>(ctx, st, dim, b, n);
     const uint32_t n4 = dim / 4;
-    if (n4 <= 4) return launch_restore_strided<4, BITS>(ctx, st, dim, a);
-    if (n4 <= 8) return launch_restore_strided<8, BITS>(ctx, st, dim, a);
-    if (n4 <= 16) return launch_restore_strided<16, BITS>(ctx, st, dim, a);
-    if (n4 <= 32) return launch_restore_strided<32, BITS>(ctx, st, dim, a);
-    return launch_restore_strided<64, BITS>(ctx, st, dim, a);
+    if (n4 <= 4) return launch_restore_strided<4, BITS>(ctx, st, dim, b, n);
+    if (n4 <= 8) return launch_restore_strided<8, BITS>(ctx, st, dim, b, n);
+    if (n4 <= 16) return launch_restore_strided<16, BITS>(ctx, st, dim, b, n);
+    if (n4 <= 32) return launch_restore_strided<32, BITS>(ctx, st, dim, b, n);
+    return launch_restore_strided<64, BITS>(ctx, st, dim, b, n);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -748,46 +758,31 @@ extern "C" cnr_status cnr_restore_rows_batch(cnr_ctx *ctx, const cnr_table_job *
     };
     // launches of up to CNR_MAX_BATCH small tables, then of large ones and slices, as for the encode
     const bool tile_dim = dim == 16 || dim == 32 || dim == 64 || dim == 128 || dim == 256;
-    if (tile_dim) {
-        for (int large = 0; large < 2; ++large) {
-            RestoreBatch b = {};
-            uint32_t n = 0;
-            auto flush = [&]() -> cnr_status {
-                if (n == 0) return CNR_OK;
-                switch (bits) {
-                    case 2: launch_restore16_bits<2>(ctx, s, dim, b, n); break;
-                    case 3: launch_restore16_bits<3>(ctx, s, dim, b, n); break;
-                    case 4: launch_restore16_bits<4>(ctx, s, dim, b, n); break;
-                    default: launch_restore16_bits<8>(ctx, s, dim, b, n); break;
-                }
-                n = 0;
-                return cnr_launch_status(ctx);
-            };
-            for (uint32_t i = 0; i < n_jobs; ++i) {
-                const cnr_table_job &j = jobs[i];
-                if (j.capacity == 0 || (j.capacity * 4ull * dim > kSideBySideBytes) != (large != 0)) continue;
-                const bool sliceable = !j.n_dirty_dev && (j.row_ids || j.capacity <= j.n_rows);
-                const uint64_t step = sliceable ? cnr_slice_rows(j.capacity, dim) : j.capacity;
-                for (uint64_t k0 = 0; k0 < j.capacity; k0 += step) {
-                    b.job[n++] = part(j, k0, j.capacity - k0 < step ? j.capacity - k0 : step);
-                    if (n == CNR_MAX_BATCH && (st = flush()) != CNR_OK) return st;
-                }
+    RestoreBatch<> b;  // what a launch reads of it is written before
+    for (int large = 0; large < 2; ++large) {
+        uint32_t n = 0;
+        auto flush = [&]() -> cnr_status {
+            if (n == 0) return CNR_OK;
+            switch (bits) {
+                case 2: launch_restore<2>(ctx, s, dim, b, n); break;
+                case 3: launch_restore<3>(ctx, s, dim, b, n); break;
+                case 4: launch_restore<4>(ctx, s, dim, b, n); break;
+                default: launch_restore<8>(ctx, s, dim, b, n); break;
             }
-            if ((st = flush()) != CNR_OK) return st;
+            n = 0;
+            return cnr_launch_status(ctx);
+        };
+        for (uint32_t i = 0; i < n_jobs; ++i) {
+            const cnr_table_job &j = jobs[i];
+            if (j.capacity == 0 || (j.capacity * 4ull * dim > kSideBySideBytes) != (large != 0)) continue;
+            const bool sliceable = tile_dim && !j.n_dirty_dev && (j.row_ids || j.capacity <= j.n_rows);
+            const uint64_t step = sliceable ? cnr_slice_rows(j.capacity, dim) : j.capacity;
+            for (uint64_t k0 = 0; k0 < j.capacity; k0 += step) {
+                b.job[n++] = part(j, k0, j.capacity - k0 < step ? j.capacity - k0 : step);
+                if (n == CNR_MAX_BATCH && (st = flush()) != CNR_OK) return st;
+            }
         }
-        return CNR_OK;
-    }
-    for (uint32_t i = 0; i < n_jobs; ++i) {  // other row lengths: one launch per table
-        const cnr_table_job &j = jobs[i];
-        if (j.capacity == 0) continue;
-        RestoreJob a = part(j, 0, j.capacity);
-        switch (bits) {
-            case 2: launch_restore<2>(ctx, s, dim, a); break;
-            case 3: launch_restore<3>(ctx, s, dim, a); break;
-            case 4: launch_restore<4>(ctx, s, dim, a); break;
-            default: launch_restore<8>(ctx, s, dim, a); break;
-        }
-        if ((st = cnr_launch_status(ctx)) != CNR_OK) return st;
+        if ((st = flush()) != CNR_OK) return st;
     }
     return CNR_OK;
 }

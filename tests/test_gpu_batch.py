@@ -343,3 +343,46 @@ def test_packed_jobs_are_the_general_ones(ctx):
     with torch.cuda.stream(s):
         assert P.binding._stream(None) == s.cuda_stream == P.binding._stream(s)
     assert P.binding._stream(None) == torch.cuda.current_stream().cuda_stream
+
+
+# other row lengths: more tables than a launch takes, lists on either side of a row per wave (448: 32,768 rows), large tables
+# (rows of over 64 MB) between small ones, an empty one, counts on the device and lengths the host knows, bad row ids
+@pytest.mark.parametrize("dim,bits,sizes", [
+    (8, 3, [1, 3000, 0, 2_200_000, 77, 98_400, 16, 5] + [40] * 11), (96, 4, [200_000, 3, 12_300, 999]), (100, 2, [17, 5000, 6200]),
+    (448, 8, [32_768, 32_769, 40, 45_000, 33_000]), (600, 4, [70, 30_000, 1])])
+def test_other_row_lengths_share_launches(ctx, dim, bits, sizes):
+    print("case shared launches dim=%d bits=%d" % (dim, bits), flush=True)
+    g = torch.Generator(device=DEV).manual_seed(dim)
+    prb = P.cnr_packed_row_bytes(dim, bits)
+    jobs, single, keep = [], [], []
+    for i, n in enumerate(sizes):
+        cap = max(1, n)
+        rows = cap + 7
+        table = torch.randn(rows, dim, device=DEV, generator=g) * 0.05
+        ids = torch.sort(torch.randperm(rows, device=DEV, generator=g)[:cap]).values.to(torch.int32)
+        if n > 20 and i % 2:
+            ids[[0, n // 2, n - 1]] = rows + 3
+        live = torch.tensor([n - n // 3], dtype=torch.int64, device=DEV) if i % 3 else None
+        out = [[torch.full((cap * w,), fill, dtype=d, device=DEV) for d, w, fill in
+                ((torch.float32, 1, -7.0), (torch.float32, 1, -7.0), (torch.float32, 1, -7.0), (torch.uint8, prb, 0xEE), (torch.float32, 0, 0.0))]
+               for _ in range(2)]
+        back = [torch.zeros_like(table) for _ in range(2)]
+        s, b, mn, pk, _ = out[0]
+        jobs.append(dict(table=table, n_rows=rows, row_ids=ids, capacity=n, n_dirty_dev=live, scale=s, bias=b, row_min=mn, packed=pk))
+        single.append((table, rows, ids, live, n, out[1]))
+        keep.append((out, back))
+    P.cnr_quantize_rows_batch(ctx, jobs, dim, bits, P.CNR_RANGE_MINMAX)
+    for j, (_, back) in zip(jobs, keep):
+        j["table"] = back[0]
+    P.cnr_restore_rows_batch(ctx, jobs, dim, bits)
+    for (table, rows, ids, live, n, (s, b, mn, pk, _)), (_, back) in zip(single, keep):
+        if n:
+            P.cnr_quantize_rows(ctx, table, rows, dim, ids, live, n, bits, P.CNR_RANGE_MINMAX, None, s, b, row_min=mn, packed=pk)
+            P.cnr_restore_rows(ctx, back[1], rows, dim, ids, live, n, bits, pk, s, b)
+    torch.cuda.synchronize()
+    for i, (out, back) in enumerate(keep):
+        for k, (x, y) in enumerate(zip(out[0] + [back[0]], out[1] + [back[1]])):
+            assert torch.equal(x, y), (i, sizes[i], k)
+        assert sizes[i] < 20 or bool(back[0].any())
+    st, bad, flags = P.cnr_poll_errors(ctx)
+    assert bad == 0 and flags == P.CNR_FLAG_ROW_ID and st != P.CNR_OK
