@@ -291,8 +291,7 @@ restore_rows16_kernel(const RestoreBatch<> b, cnr_dev_errors *err) {
     restore_table<Q, BITS>(a, err, stages + (tid_x() / kWave) * kStage);
 }
 
-// Other row lengths: LPR lanes per row (a power of two, at least the row's number of 16-byte units up
-// to 64), 64 / LPR rows per wave and pass; lane j takes the units j, j + LPR, ... of its row: it reads
+// Other row lengths: LPR lanes per row (a power of two; launch_restore says which), 64 / LPR rows per wave and pass; lane j takes the units j, j + LPR, ... of its row: it reads
 // the unit's 4 * BITS code bits (one, two or four bytes; at 3 bits the three bytes that hold the
 // unit and its pair partner) and stores 16 bytes.
 // A batch's tables share a launch (eight tables of 29 K rows of 96 32 -> 13.5 us); one table has a launch with less to bring along
@@ -382,11 +381,17 @@ void launch_restore_strided(cnr_ctx *ctx, hipStream_t st, uint32_t dim, RestoreB
 template <int BITS>
 void launch_restore(cnr_ctx *ctx, hipStream_t st, uint32_t dim, RestoreBatch<> &b, uint32_t n) {
     if (dim == 16 || dim == 32 || dim == 64 || dim == 128 || dim == 256) return launch_restore16_bits<BITS>(ctx, st, dim, b, n);
+    // One trip through a row of up to 256 elements, but for rows of whole 64-byte lines that would leave a quarter of the
+    // lanes or more idle: two trips of half the lanes store whole lines just as well and hold twice the rows
+    // (1.04 M rows of 96 at 2 bits 85 -> 66 us, 0.6 M of 80 63.5 -> 47.7, 0.4 M of 160 81 -> 73; but 0.9 M of 112 76.5 and 89).  Where
+    // lines are shared between rows or trips each share is a masked write of its own, and one trip makes the fewest (rows of 72
+    // 73 and 110 us, of 200 62 and 78).
     const uint32_t n4 = dim / 4;
+    const bool lines = n4 % 4 == 0;
     if (n4 <= 4) return launch_restore_strided<4, BITS>(ctx, st, dim, b, n);
     if (n4 <= 8) return launch_restore_strided<8, BITS>(ctx, st, dim, b, n);
-    if (n4 <= 16) return launch_restore_strided<16, BITS>(ctx, st, dim, b, n);
-    if (n4 <= 32) return launch_restore_strided<32, BITS>(ctx, st, dim, b, n);
+    if (n4 <= 16 || (lines && n4 <= 24)) return launch_restore_strided<16, BITS>(ctx, st, dim, b, n);
+    if (n4 <= 32 || (lines && n4 <= 48)) return launch_restore_strided<32, BITS>(ctx, st, dim, b, n);
     return launch_restore_strided<64, BITS>(ctx, st, dim, b, n);
 }
 
@@ -665,18 +670,20 @@ void launch_error(ErrorArgs &a, unsigned grid, uint32_t lanes, int bits, hipStre
     }
 }
 
-// Lanes per row of the error kernel: of 16, 8 and 4 the one that leaves the fewest idle lanes in the
-// last trip through a row (the most lanes among equals: wider runs per load instruction).  Beyond 512 and 1024
-// elements 32 and 64: the trips through a row follow each other, and sixteen lanes would make up to 64.
+// Lanes per row of the error kernel: one trip of 4 or 8 for rows of up to 16 and 32 elements, sixteen beyond.  Fewer lanes
+// with fewer of them idle in the last trip lose more by the trips, which follow each other, and by their shorter runs (60 M
+// elements at 4 bits: rows of 36 16 / 8 / 4 lanes 81 / 98 / 124 us, of 72 69 / 79 / 101, of 112 54 / 64 / 81, of 200 58 / 73 / 103); only
+// three trips of 8 that leave none idle are level with two of 16 (rows of 96 46 and 49).  32 where that takes no more
+// lanes' worth of trips than 16 and there are trips to save (rows of 120 54 instead of 57, of 200 51, of 240 47 instead of 51), and
+// beyond 512 and 1024 elements 32 and 64: sixteen lanes would make up to 64 trips.
 // 0 = one wave per row, for rows that are not whole aligned 16-byte units.
 uint32_t error_lanes(uint32_t dim, const void *table, const void *packed) {
     if (dim % 4 || (uintptr_t)table % 16 || (uintptr_t)packed % 4) return 0;
     const uint32_t n4 = dim / 4;
     if (n4 > 128) return n4 > 256 ? 64 : 32;
-    uint32_t best = 16;
-    for (uint32_t l : {8u, 4u})
-        if ((n4 + l - 1) / l * l < (n4 + best - 1) / best * best) best = l;
-    return best;
+    if (n4 <= 4) return 4;
+    if (n4 <= 8 || n4 == 24) return 8;
+    return n4 >= 30 && (n4 + 31) / 32 * 2 == (n4 + 15) / 16 ? 32 : 16;
 }
 
 }  // namespace

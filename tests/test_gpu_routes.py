@@ -116,6 +116,37 @@ def test_error_metric_skips_ids_outside_the_table(ctx, n):
     _poll(ctx, P.CNR_FLAG_ROW_ID)
 
 
+@pytest.mark.parametrize("dim,bits,n", [
+    (20, 8, 3_001), (32, 4, 129), (36, 2, 16_385), (40, 3, 130), (60, 4, 9_001), (72, 8, 2_049), (92, 2, 700), (96, 4, 16_400), (100, 8, 300),
+    (116, 4, 1_025), (120, 3, 16_390), (128, 2, 128), (132, 4, 2_000), (160, 8, 131), (200, 3, 17_003), (240, 4, 8_200), (256, 3, 8_193),
+    (500, 2, 1_000), (512, 8, 140)])
+def test_error_metric_lanes(ctx, dim, bits, n):
+    test_error_metric_routes(ctx, dim, bits, n, 0)
+
+
+# lanes per row of the restore: whole lines and shared ones at the lengths where the rule changes
+@pytest.mark.parametrize("dim,bits", [(64 - 4, 4), (68, 2), (72, 3), (80, 4), (92, 2), (96, 3), (100, 8), (112, 2), (124, 4), (132, 2), (144, 3), (188, 8),
+                                      (192, 4), (196, 2), (208, 3), (252, 8), (260, 4)])
+def test_restore_lanes(ctx, dim, bits):
+    for n in (1, 5, 3_003):
+        n_rows = n + n // 2 + 3
+        g = torch.Generator(device=DEV).manual_seed(dim + n)
+        ids = _ids(n_rows, n, dim)
+        packed = torch.randint(0, 256, (n * P.cnr_packed_row_bytes(dim, bits),), generator=g, device=DEV, dtype=torch.uint8)
+        scale = torch.empty(n, device=DEV).uniform_(0.001, 0.01, generator=g)
+        bias = torch.empty(n, device=DEV).uniform_(-0.1, 0.0, generator=g)
+        want = torch.full((n_rows, dim), 7.0, device=DEV)
+        table = want.clone()
+        rows = _unpack(packed, n, dim, bits) * scale[:, None] + bias[:, None]
+        live = max(1, n - 2)
+        want[ids[:live].long()] = rows[:live]
+        P.cnr_restore_rows(ctx, table, n_rows, dim, ids, torch.tensor([live], dtype=torch.int64, device=DEV), n, bits, packed, scale, bias)
+        assert torch.equal(table, want), n
+        P.cnr_restore_rows(ctx, table, n, dim, None, None, n, bits, packed, scale, bias)
+        assert torch.equal(table[:n], rows) and torch.equal(table[n:], want[n:]), n
+    _poll(ctx)
+
+
 # ---- greedy search at row lengths that are no power of two: lanes per row, units per lane, list length --
 
 def _special_rows(dim, seed):
