@@ -1593,12 +1593,15 @@ void launch_rows(cnr_ctx *ctx, QuantBatchArgs<> &b, uint32_t n, uint32_t dim, bo
 
 // Two groups of lanes per row while the sets of parameters together leave room on the chip; four lanes
 // beyond that.  Measured break-evens with five and three sets: 100 K rows of 16, 20 K rows of 64, 30 K of
-// 128, 60 K of 256.
+// 128, 60 K of 256.  Rows of 144 to 284 elements have two groups of sixteen lanes while
+// the sets leave half the chip's lanes free even so: the whole call at 3 bits, 256 rows of 144 79 -> 69 us, of 256 99 -> 78, 1 K rows
+// 80 -> 73 and 102 -> 84; 2.5 K rows 91 against 95 and 120 against 113, 4 K level or 5 % slower.  (Rows of up to 140 lose with more lanes.)
 template <int BITS>
 cnr_status launch_sample_errors(cnr_ctx *ctx, SelectArgs &a, uint32_t n_sets, uint64_t max_sums, double *mean_out, hipStream_t s) {
     const uint32_t n4 = a.dim / 4;
     const bool wide = n4 < 68 && a.n * n_sets >= 131072;
-    const uint32_t lanes = wide ? 4 : n4 <= 8 ? 8 : n4 < 72 ? 16 : 64;
+    const bool spread = n4 >= 36 && n4 < 72 && a.n * n_sets <= 8192;
+    const uint32_t lanes = wide ? 4 : n4 <= 8 ? 8 : n4 < 72 && !spread ? 16 : spread ? 32 : 64;
     const uint64_t rows_per_wg = (uint64_t)(kWave / lanes) * kWavesPerBlock;
     uint64_t grid = (a.n + rows_per_wg - 1) / rows_per_wg;
     if (grid > 4096) grid = 4096;
@@ -1607,6 +1610,7 @@ cnr_status launch_sample_errors(cnr_ctx *ctx, SelectArgs &a, uint32_t n_sets, ui
     const dim3 g((unsigned)grid, n_sets);
     if (wide && n4 < 36) hipLaunchKernelGGL((sample_error_kernel<4, 8, false, BITS>), g, dim3(kBlock), 0, s, a);
     else if (wide) hipLaunchKernelGGL((sample_error_kernel<4, 16, false, BITS>), g, dim3(kBlock), 0, s, a);
+    else if (spread) hipLaunchKernelGGL((sample_error_kernel<16, 4, true, BITS>), g, dim3(kBlock), 0, s, a);
     else if (n4 <= 8) hipLaunchKernelGGL((sample_error_kernel<4, 2, true, BITS>), g, dim3(kBlock), 0, s, a);
     else if (n4 < 72) hipLaunchKernelGGL((sample_error_kernel<8, 8, true, BITS>), g, dim3(kBlock), 0, s, a);
     else if (n4 < 288) hipLaunchKernelGGL((sample_error_kernel<32, 8, true, BITS>), g, dim3(kBlock), 0, s, a);

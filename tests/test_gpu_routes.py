@@ -514,3 +514,9 @@ def test_bulk_mark_around_the_streaming_limit(ctx, dtype, n_idx, n_rows):
         assert not bool(ck.mark_scratch.any())
     st, n_bad, flags = P.cnr_poll_errors(ctx)
     assert (n_bad, flags) == (bad, 0)
+
+
+# two groups of sixteen lanes for rows of 144 to 284 elements, up to 8192 rows and sets together
+@pytest.mark.parametrize("dim,bits,n", [(140, 2, 300), (144, 3, 257), (200, 2, 1_639), (200, 4, 1_638), (256, 8, 70), (284, 4, 31), (284, 2, 1)])
+def test_parameter_selection_of_longer_rows(ctx, dim, bits, n):
+    test_parameter_selection_routes(ctx, dim, bits, n, (10, 25, 45, 100))
