@@ -1227,7 +1227,7 @@ __device__ __forceinline__ QuantArgs job_of(const QuantBatchArgs<N> &b) {
 template <int BITS, int N>
 __global__ void __launch_bounds__(kBlock) quantize_strided_kernel(const QuantBatchArgs<N> b) {
     const QuantArgs a = job_of(b);
-    if (wg_x() * kWavesPerBlock >= a.n_waves) return;  // fewer workgroups than the launch's largest table
+    if (N > 1 && wg_x() * kWavesPerBlock >= a.n_waves) return;  // fewer workgroups than the launch's largest table
     encode_strided<kWave, BITS>(a, row_count(a));
 }
 
@@ -1246,7 +1246,7 @@ template <int LPR, int U, int SB, int BITS, int N>
 __global__ void __launch_bounds__(kBlock) quantize_units_kernel(const QuantBatchArgs<N> b) {
     using S = UnitsShape<LPR, U, SB, BITS>;
     const QuantArgs a = job_of(b);
-    if (wg_x() * kWavesPerBlock >= a.n_waves) return;
+    if (N > 1 && wg_x() * kWavesPerBlock >= a.n_waves) return;
     constexpr int RPS = S::RPS, ROWS = S::ROWS;
     constexpr float QMAXF = (float)((1 << BITS) - 1);
     __shared__ __align__(16) uint8_t stages[kWavesPerBlock * S::STAGE];

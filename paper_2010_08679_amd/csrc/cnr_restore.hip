@@ -299,7 +299,7 @@ restore_rows16_kernel(const RestoreBatch<> b, cnr_dev_errors *err) {
 template <int LPR, int BITS, int N>
 __global__ void __launch_bounds__(kBlock) restore_strided_kernel(const RestoreBatch<N> batch, uint32_t dim, cnr_dev_errors *err) {
     const RestoreJob a = batch.job[N == 1 ? 0 : wg_y()];
-    if (wg_x() * kWavesPerBlock >= a.n_waves) return;
+    if (N > 1 && wg_x() * kWavesPerBlock >= a.n_waves) return;
     constexpr int kRowsPerPass = kWave / LPR;
     constexpr uint32_t MASK = (1u << BITS) - 1u;
     const uint64_t n = live_rows(a.n_dev, a.n_max);
