@@ -39,10 +39,10 @@ HBM_PEAK_GBPS = 8000.0          # MI355X HBM3E, published
 # valid only for the kernel source whose hash is recorded with it (profiles/hbm_traffic.txt).
 TRAFFIC_PER_ROW = {
     # _kernel_hash() : {workload/bits : bytes per dirty row}
-    "a2e6a8cd8520d9e7bb6344cdfd2a382c27d08e95db09fef0a95bfb9a9a5ff999": {"cfg4/b4": 300.96, "cfg3/b2": 558.98, "cfg3/b3": 581.12, "cfg5/b8": 658.98, "cfg5/b4": 592.55},
+    "49d873374416ae60a94c90bff98225b782606a8470dd2c2a2949c40105aebff4": {"cfg4/b4": 301.54},
 }
 RESTORE_TRAFFIC_PER_ROW = {
-    "9da3bb04f0f026ab3b207f964f7a0115189d3f1db165cf721d16025fee224303": {"cfg4/b4": 300.01, "cfg3/b2": 556.09, "cfg3/b3": 572.08, "cfg5/b8": 652.09, "cfg5/b4": 588.04},
+    "53422e577636a6c5720da3ea9f67558a5b1fab4589a8438277cc6b821ac1b7d3": {"cfg4/b4": 300.01},
 }
 
 
