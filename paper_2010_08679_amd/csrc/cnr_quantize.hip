@@ -541,12 +541,17 @@ struct ClipBound {
     float mn[N], mx[N];
     float unit, slack;
     double enough;  // the bound is compared with the best error times this
+    // Ends that no element has: parts may stay empty.
     __device__ __forceinline__ void reset() {
 #pragma unroll
         for (int g = 0; g < N; ++g) {
             mn[g] = __builtin_huge_valf();
             mx[g] = -__builtin_huge_valf();
         }
+    }
+    __device__ __forceinline__ void start(int g, const float4 &v) {
+        mn[g] = mx[g] = v.x;
+        take(g, v);
     }
     __device__ __forceinline__ void take(int g, const float4 &v) {
         mn[g] = fminf(mn[g], fminf(fminf(v.x, v.y), fminf(v.z, v.w)));
@@ -655,9 +660,8 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L =
 
         // ---- row minimum / maximum
         ClipBound<G> clip;
-        clip.reset();
 #pragma unroll
-        for (int i = 0; i < 4 * G; ++i) clip.take(i / 4, x[i]);
+        for (int i = 0; i < 4 * G; ++i) i % 4 ? clip.take(i / 4, x[i]) : clip.start(i / 4, x[i]);
         const float X_min = lanes_min<L>(clip.lane_min()) + 0.0f;  // -0.0 -> +0.0
         const float X_max = lanes_max<L>(clip.lane_max()) + 0.0f;
         float lo = X_min, hi = X_max;
@@ -849,7 +853,7 @@ struct RowUnits {
                 x[t] = row[j + L * t];
                 x[t + 1] = row[j + L * (t + 1)];
             }
-        tail = row[in_tail ? j + L * n_full : n4 - 1];  // a unit of the row in any case: the row's range may count it twice
+        tail = row[in_tail ? j + L * n_full : n4 - 1];  // a unit of the row in any case, though only an in_tail lane's counts
         odd = tail;
         if (has_odd) odd = row[j + L * (n_full - 1)];
     }
@@ -865,6 +869,7 @@ struct RowUnits {
             }
         mn = lanes_min<L>(clip.lane_min()) + 0.0f;  // -0.0 -> +0.0
         mx = lanes_max<L>(clip.lane_max()) + 0.0f;
+        if (mn > mx) mn = mx = tail.x;  // none of the row's elements is above or below anything: all of them are NaN, and so is its range
     }
     // Squared l2 error of the row under F_Q with the range [c_lo, c_hi], in every lane.
     template <int BITS, bool FAST>

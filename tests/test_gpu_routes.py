@@ -243,6 +243,27 @@ def test_greedy_skips_ids_outside_the_table(ctx, dim, bits):
         assert bool((o[bad] == 0x5A).all()) and bool((o[keep] != 0x5A).any(1).all())
 
 
+# rows of NaN alone, outside the contract: every form reports NaN as their range, scale and bias, and leaves the rows beside them alone
+@pytest.mark.parametrize("dim,bits", [(8, 4), (16, 3), (24, 2), (32, 4), (48, 8), (64, 2), (96, 3), (128, 4), (200, 2), (256, 8), (280, 4), (320, 3), (1088, 4)])
+def test_greedy_reports_rows_of_nan(ctx, dim, bits):
+    print("case greedy nan dim=%d bits=%d" % (dim, bits), flush=True)
+    rng = np.random.default_rng(dim)
+    rows = rng.normal(0, 0.1, (120, dim)).astype(np.float32)
+    bad = np.arange(0, 120, 7)
+    with_nan = rows.copy()
+    with_nan[bad] = np.nan
+    for copies in (1, 500 if dim <= 320 else 200):   # two groups of lanes per row, and one
+        want, got = (gpu_encode_all_outputs(GpuTable(ctx, torch.from_numpy(r).to(DEV).repeat(copies, 1)), bits, mode=P.CNR_RANGE_GREEDY, greedy=(20, 1.0),
+                                            row_ids=None, n=120 * copies) for r in (rows, with_nan))
+        nan_rows = (np.arange(0, 120 * copies, 120)[:, None] + bad).ravel()
+        for k in ("scale", "bias", "row_min", "row_max"):
+            assert np.isnan(got[k][nan_rows]).all(), (k, got[k][nan_rows][:4])
+        rest = np.setdiff1d(np.arange(120 * copies), nan_rows)
+        for k in ("scale", "bias", "row_min", "row_max", "codes", "packed"):
+            assert np.array_equal(got[k][rest], want[k][rest]), k
+    _poll(ctx)
+
+
 def _early_end_rows(n, dim, bins, seed):
     """Rows whose search may end early, or must not: a few far elements (the best range comes late), both ends far, two
     clusters (clipping hurts at once), equal elements but one, a range small against its offset (down to the
