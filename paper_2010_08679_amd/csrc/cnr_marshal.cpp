@@ -7,6 +7,7 @@
 #include <torch/csrc/Dtype.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/utils/object_ptr.h>
 
 namespace {
 
@@ -19,10 +20,9 @@ bool address_of(PyObject *t, PyObject *dtype, PyObject *name, unsigned long long
     out = 0;
     if (t == Py_None) return true;
     if (!THPVariable_CheckExact(t)) {  // subclasses answer for themselves; the rest is refused there
-        PyObject *r = PyObject_CallFunctionObjArgs(general, t, dtype, name, nullptr);
+        THPObjectPtr r(PyObject_CallFunctionObjArgs(general, t, dtype, name, nullptr));
         if (!r) return false;
-        out = PyLong_AsUnsignedLongLong(r);
-        Py_DECREF(r);
+        out = PyLong_AsUnsignedLongLong(r.get());
         return !PyErr_Occurred();
     }
     const at::Tensor &v = THPVariable_Unpack(t);
@@ -71,36 +71,30 @@ PyObject *pack_jobs(PyObject *, PyObject *const *args, Py_ssize_t n) {
         return nullptr;
     }
     const Py_ssize_t rows = PyList_GET_SIZE(args[0]);
-    PyObject *bytes = PyBytes_FromStringAndSize(nullptr, rows * kJobFields * 8);
+    THPObjectPtr bytes(PyBytes_FromStringAndSize(nullptr, rows * kJobFields * 8));  // given back if a tensor throws, too
     if (!bytes) return nullptr;
     for (Py_ssize_t i = 0; i < rows; ++i) {
         // the list can change hands while a subclass answers: its length is looked at again, the row is held
-        PyObject *row = i < PyList_GET_SIZE(args[0]) ? PyList_GET_ITEM(args[0], i) : nullptr;
-        if (!row || !PyTuple_Check(row) || PyTuple_GET_SIZE(row) != kJobFields) {
+        PyObject *at = i < PyList_GET_SIZE(args[0]) ? PyList_GET_ITEM(args[0], i) : nullptr;
+        if (!at || !PyTuple_Check(at) || PyTuple_GET_SIZE(at) != kJobFields) {
             PyErr_SetString(PyExc_TypeError, "a job has sixteen fields");
-            Py_DECREF(bytes);
             return nullptr;
         }
-        Py_INCREF(row);
-        bool ok = true;
-        for (Py_ssize_t f = 0; ok && f < kJobFields; ++f) {
-            PyObject *v = PyTuple_GET_ITEM(row, f);
+        Py_INCREF(at);
+        THPObjectPtr row(at);
+        for (Py_ssize_t f = 0; f < kJobFields; ++f) {
+            PyObject *v = PyTuple_GET_ITEM(at, f);
             unsigned long long x = 0;
             if (PyLong_Check(v)) {
                 x = PyLong_AsUnsignedLongLong(v);
-                ok = !PyErr_Occurred();
-            } else {
-                ok = address_of(v, PyTuple_GET_ITEM(args[1], f), PyTuple_GET_ITEM(args[2], f), x);
+                if (PyErr_Occurred()) return nullptr;
+            } else if (!address_of(v, PyTuple_GET_ITEM(args[1], f), PyTuple_GET_ITEM(args[2], f), x)) {
+                return nullptr;
             }
-            memcpy(PyBytes_AS_STRING(bytes) + (i * kJobFields + f) * 8, &x, 8);
-        }
-        Py_DECREF(row);
-        if (!ok) {
-            Py_DECREF(bytes);
-            return nullptr;
+            memcpy(PyBytes_AS_STRING(bytes.get()) + (i * kJobFields + f) * 8, &x, 8);
         }
     }
-    return bytes;
+    return bytes.release();
     END_HANDLE_TH_ERRORS
 }
 

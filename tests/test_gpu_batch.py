@@ -345,6 +345,21 @@ def test_packed_jobs_are_the_general_ones(ctx):
     assert P.binding._stream(None) == torch.cuda.current_stream().cuda_stream
 
 
+def test_a_tensor_that_throws_leaves_no_job_behind(ctx):
+    import sys
+
+    def inside(t):   # a tensor without memory of its own: its address is refused by an exception, not by a check
+        row = (t, 1) + (0,) * 14
+        before = sys.getrefcount(t), sys.getrefcount(row)
+        for _ in range(3):
+            with pytest.raises(RuntimeError):
+                P.binding.job_bytes([row])
+        assert (sys.getrefcount(t), sys.getrefcount(row)) == before
+        return t
+
+    torch.vmap(inside)(torch.zeros(2, 8, device=DEV))
+
+
 # other row lengths: more tables than a launch takes, lists on either side of a row per wave (448: 32,768 rows), large tables
 # (rows of over 64 MB) between small ones, an empty one, counts on the device and lengths the host knows, bad row ids
 @pytest.mark.parametrize("dim,bits,sizes", [
