@@ -11,7 +11,9 @@ from __future__ import annotations
 
 import ctypes
 import importlib.util
+import itertools
 import os
+import struct
 import threading
 
 import torch
@@ -363,20 +365,26 @@ def make_jobs(jobs):
 
 
 _JOB_FIELDS = tuple(name for name, _ in cnr_table_job._fields_)
-_JOB_DTYPES = tuple(_JOB_TENSORS.get(name) for name in _JOB_FIELDS)
+_JOB_KINDS = tuple(_JOB_TENSORS.get(name, int) for name in _JOB_FIELDS)  # what job_bytes takes for a field
+_job_packers = {}
 
 
 def job_bytes(rows) -> bytes:
-    """The bytes of a ``cnr_table_job`` array from one 16-tuple per job, the struct's fields in order: numbers, and tensors or
-    None where the struct has addresses.  What :func:`make_jobs` builds field by field, with the same checks, in
-    one step; the batch calls take it."""
+    """The bytes of a ``cnr_table_job`` array from a list of one 16-tuple per job, the struct's fields in order: numbers, and where the
+    struct has addresses a tensor, None, or 0 for a field that the call does not read.  What :func:`make_jobs` builds field
+    by field, with the same checks, in one step; the batch calls take it."""
     load()
-    return _marshal.pack_jobs(rows, _JOB_DTYPES, _JOB_FIELDS)
+    return _marshal.pack_jobs(rows, _JOB_KINDS, _JOB_FIELDS)
 
 
 def pack_jobs(rows):
-    """:func:`job_bytes` as an array of ``cnr_table_job``."""
-    return (cnr_table_job * len(rows)).from_buffer_copy(job_bytes(rows))
+    """A ``cnr_table_job`` array from one 16-tuple of integers per job (the struct's fields in order): what
+    :func:`make_jobs` builds field by field, in one step, for callers that have checked their tensors."""
+    n = len(rows)
+    packer = _job_packers.get(n)
+    if packer is None:
+        packer = _job_packers[n] = (struct.Struct("%dQ" % (n * len(_JOB_FIELDS))), cnr_table_job * n)
+    return packer[1].from_buffer_copy(packer[0].pack(*itertools.chain.from_iterable(rows)))
 
 
 def _jobs_arg(jobs):

@@ -14,7 +14,7 @@ import torch
 
 from . import binding as B
 
-_ZEROS = [(0,) * k for k in range(17)]  # the fields of a job that a stage does not read
+_UNREAD = (None, 0, None, None, 0, None, None, 0) + (None,) * 8  # a job's fields where a stage does not read them
 
 
 @dataclass
@@ -184,19 +184,19 @@ class BatchCheckpointer:
     # field through dicts, took 46 us a call for eight tables (checks in Python 19).  Nothing is kept from one call
     # to the next: buffers may be exchanged in between.
     def clear(self, stream=None) -> None:
-        B.cnr_clear_bitmap_batch(self.ctx, B.job_bytes([(0, c.n_rows, c.bitmap) + _ZEROS[13] for c in self.cks]), stream)
+        B.cnr_clear_bitmap_batch(self.ctx, B.job_bytes([(None, c.n_rows, c.bitmap) + _UNREAD[3:] for c in self.cks]), stream)
 
     def mark(self, indices, stream=None) -> None:
         kind = self._index_type(indices)
         flat = [indices[i] for i in range(len(self.cks))]
         flat = [t if t is None or t.is_contiguous() else t.reshape(-1) for t in flat]  # alive until the launch
         B.cnr_mark_touched_batch(self.ctx, B.job_bytes(
-            [(0, c.n_rows, c.bitmap, t, 0 if t is None else t.numel(), c.mark_scratch) + _ZEROS[10] for c, t in zip(self.cks, flat)]),
+            [(None, c.n_rows, c.bitmap, t, 0 if t is None else t.numel(), c.mark_scratch) + _UNREAD[6:] for c, t in zip(self.cks, flat)]),
             kind, stream)
 
     def compact(self, stream=None) -> None:
         B.cnr_compact_dirty_batch(self.ctx, B.job_bytes(
-            [(0, c.n_rows, c.bitmap, 0, 0, 0, c.row_ids, c.capacity, c.n_dirty, c.scratch) + _ZEROS[6] for c in self.cks]), stream)
+            [(None, c.n_rows, c.bitmap, None, 0, None, c.row_ids, c.capacity, c.n_dirty, c.scratch) + _UNREAD[10:] for c in self.cks]), stream)
 
     def _row_jobs(self, tables, outs):
         rows = []
@@ -204,7 +204,7 @@ class BatchCheckpointer:
             t, o = tables[i], outs[i]
             self._check_table(i, c, t)
             self._check_output(i, c, o)
-            rows.append((t, c.n_rows, 0, 0, 0, 0, c.row_ids, c.capacity, c.n_dirty, 0, o.scale, o.bias, o.row_min, o.row_max, 0,
+            rows.append((t, c.n_rows, None, None, 0, None, c.row_ids, c.capacity, c.n_dirty, None, o.scale, o.bias, o.row_min, o.row_max, None,
                          o.packed))
         return B.job_bytes(rows)
 

@@ -61,13 +61,29 @@ PyObject *address(PyObject *, PyObject *const *args, Py_ssize_t n) {
     END_HANDLE_TH_ERRORS
 }
 
-// pack_jobs(rows, dtypes, names): rows of sixteen numbers, tensors or Nones, the struct's fields in order; the bytes of
-// the array.
+// A field of a job: a number where `kind` is the type int (anything with __index__), else an address, of a tensor of dtype `kind` or for
+// None or the number 0, a field that the call does not read.
+bool field(PyObject *v, PyObject *kind, PyObject *name, unsigned long long &out) {
+    if (kind == reinterpret_cast<PyObject *>(&PyLong_Type)) {
+        THPObjectPtr index(PyNumber_Index(v));
+        if (!index) return false;
+        out = PyLong_AsUnsignedLongLong(index.get());
+        return !PyErr_Occurred();
+    }
+    out = 0;
+    if (PyLong_CheckExact(v)) {
+        int overflow;
+        if (PyLong_AsLongLongAndOverflow(v, &overflow) == 0 && !overflow) return true;
+    }
+    return address_of(v, kind, name, out);
+}
+
+// pack_jobs(rows, kinds, names): rows of sixteen fields, the struct's in order; the bytes of the array.
 PyObject *pack_jobs(PyObject *, PyObject *const *args, Py_ssize_t n) {
     HANDLE_TH_ERRORS
     if (n != 3 || !PyList_Check(args[0]) || !PyTuple_Check(args[1]) || !PyTuple_Check(args[2]) ||
         PyTuple_GET_SIZE(args[1]) != kJobFields || PyTuple_GET_SIZE(args[2]) != kJobFields) {
-        PyErr_SetString(PyExc_TypeError, "pack_jobs(list of rows, dtypes, names)");
+        PyErr_SetString(PyExc_TypeError, "pack_jobs(list of rows, kinds, names)");
         return nullptr;
     }
     const Py_ssize_t rows = PyList_GET_SIZE(args[0]);
@@ -83,14 +99,8 @@ PyObject *pack_jobs(PyObject *, PyObject *const *args, Py_ssize_t n) {
         Py_INCREF(at);
         THPObjectPtr row(at);
         for (Py_ssize_t f = 0; f < kJobFields; ++f) {
-            PyObject *v = PyTuple_GET_ITEM(at, f);
-            unsigned long long x = 0;
-            if (PyLong_Check(v)) {
-                x = PyLong_AsUnsignedLongLong(v);
-                if (PyErr_Occurred()) return nullptr;
-            } else if (!address_of(v, PyTuple_GET_ITEM(args[1], f), PyTuple_GET_ITEM(args[2], f), x)) {
-                return nullptr;
-            }
+            unsigned long long x;
+            if (!field(PyTuple_GET_ITEM(at, f), PyTuple_GET_ITEM(args[1], f), PyTuple_GET_ITEM(args[2], f), x)) return nullptr;
             memcpy(PyBytes_AS_STRING(bytes.get()) + (i * kJobFields + f) * 8, &x, 8);
         }
     }
@@ -108,7 +118,7 @@ PyMethodDef methods[] = {
     {"address", reinterpret_cast<PyCFunction>(reinterpret_cast<void *>(address)), METH_FASTCALL,
      "address(tensor, dtype, name): device address of a contiguous GPU tensor, 0 for None"},
     {"pack_jobs", reinterpret_cast<PyCFunction>(reinterpret_cast<void *>(pack_jobs)), METH_FASTCALL,
-     "pack_jobs(rows, dtypes, names): the bytes of an array of cnr_table_job"},
+     "pack_jobs(rows, kinds, names): the bytes of an array of cnr_table_job"},
     {"set_general", set_general, METH_O, "set_general(f): what answers for tensors of other types"},
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

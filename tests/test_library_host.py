@@ -247,6 +247,28 @@ def test_packed_jobs_hold_the_struct_fields_in_order():
     assert all(not getattr(empty, f) for f in fields)
 
 
+def test_job_fields_take_what_the_struct_holds():
+    # numbers where the struct has numbers, addresses of tensors (none of them on the host) where it has addresses
+    fields = [f for f, _ in binding.cnr_table_job._fields_]
+    numbers = {"n_rows", "n_indices", "capacity"}
+
+    def row(name, value):
+        return tuple(value if f == name else 0 if f in numbers else None for f in fields)
+
+    for f in fields:
+        assert binding.job_bytes([row(f, 0)]) == bytes(128), f
+        for bad in (64, -1, True, False, 2 ** 64 - 1, np.int64(3), 7.5, torch.zeros(4), [0]) if f not in numbers else (None, 7.5, "1", torch.zeros(4)):
+            with pytest.raises(TypeError):
+                binding.job_bytes([row(f, bad)])
+        if f in numbers:
+            for n in (5, np.int64(5), np.uint32(5), torch.tensor(5)):
+                assert getattr(binding.cnr_table_job.from_buffer_copy(binding.job_bytes([row(f, n)])), f) == 5
+            with pytest.raises(OverflowError):
+                binding.job_bytes([row(f, -1)])
+    # any sequences of integers, as long as they fill the structs
+    assert bytes(binding.pack_jobs(([1] * 16, np.arange(16)))) == bytes(binding.pack_jobs([(1,) * 16, tuple(range(16))]))
+
+
 def test_a_batch_refuses_a_missing_table_or_output():
     # also where the table's capacity is 0 and the library would not look at it
     ck = P.TableCheckpointer(None, 100, 8, capacity=0, device="cpu")
