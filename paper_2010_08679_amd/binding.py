@@ -81,6 +81,7 @@ class cnr_table_job(ctypes.Structure):
 _lock = threading.Lock()
 _lib = None
 _marshal = None
+_packed_calls = {}  # the *_batch functions as they take the bytes of a job array
 
 
 def ensure_built() -> str:
@@ -100,7 +101,7 @@ def load() -> ctypes.CDLL:
         lib = ctypes.CDLL(ensure_built())
         vp, u64, u32, i32, f32 = (ctypes.c_void_p, ctypes.c_uint64, ctypes.c_uint32, ctypes.c_int,
                                   ctypes.c_float)
-        sz = ctypes.c_size_t
+        sz, jobs = ctypes.c_size_t, ctypes.POINTER(cnr_table_job)
         sig = {
             "cnr_create": (i32, [ctypes.POINTER(vp), i32]),
             "cnr_destroy": (i32, [vp]),
@@ -125,12 +126,12 @@ def load() -> ctypes.CDLL:
             "cnr_policy_init": (i32, [ctypes.POINTER(cnr_policy), i32]),
             "cnr_policy_next": (cnr_policy_decision, [ctypes.POINTER(cnr_policy), ctypes.c_double]),
             "cnr_select_bits": (i32, [u32, u32]),
-            "cnr_clear_bitmap_batch": (i32, [vp, vp, u32, vp]),
-            "cnr_mark_touched_batch": (i32, [vp, vp, u32, i32, vp]),
-            "cnr_compact_dirty_batch": (i32, [vp, vp, u32, vp]),
-            "cnr_quantize_rows_batch": (i32, [vp, vp, u32, u32, i32, i32,
+            "cnr_clear_bitmap_batch": (i32, [vp, jobs, u32, vp]),
+            "cnr_mark_touched_batch": (i32, [vp, jobs, u32, i32, vp]),
+            "cnr_compact_dirty_batch": (i32, [vp, jobs, u32, vp]),
+            "cnr_quantize_rows_batch": (i32, [vp, jobs, u32, u32, i32, i32,
                                               ctypes.POINTER(cnr_greedy_params), vp]),
-            "cnr_restore_rows_batch": (i32, [vp, vp, u32, u32, i32, vp]),
+            "cnr_restore_rows_batch": (i32, [vp, jobs, u32, u32, i32, vp]),
             "cnr_host_writer_device_bytes": (sz, [u32, i32, u64]),
             "cnr_host_writer_create": (i32, [vp, u32, i32, u64, ctypes.POINTER(vp)]),
             "cnr_host_writer_destroy": (i32, [vp]),
@@ -146,6 +147,9 @@ def load() -> ctypes.CDLL:
         for name, (res, args) in sig.items():
             fn = getattr(lib, name)
             fn.restype, fn.argtypes = res, args
+            if jobs in args:
+                fn = _packed_calls[name] = lib[name]  # another object for the same function
+                fn.restype, fn.argtypes = res, [vp if a is jobs else a for a in args]
         _bind_marshal()
         _lib = lib
         return lib
@@ -387,41 +391,45 @@ def pack_jobs(rows):
     return packer[1].from_buffer_copy(packer[0].pack(*itertools.chain.from_iterable(rows)))
 
 
-def _jobs_arg(jobs):
+def _batch(name: str, jobs):
+    """(library function, argument, number of jobs): the bytes of a job array, an array of ``cnr_table_job``, or a list of dicts."""
+    lib = load()
     if isinstance(jobs, bytes):
-        return jobs, len(jobs) // ctypes.sizeof(cnr_table_job)
+        n, rest = divmod(len(jobs), ctypes.sizeof(cnr_table_job))
+        if rest:
+            raise ValueError("the bytes are no whole number of jobs")
+        return _packed_calls[name], jobs, n
     if isinstance(jobs, (list, tuple)):
-        return make_jobs(jobs), len(jobs)
-    return jobs, len(jobs)
+        return getattr(lib, name), make_jobs(jobs), len(jobs)
+    return getattr(lib, name), jobs, len(jobs)
 
 
 def cnr_clear_bitmap_batch(ctx, jobs, stream=None) -> None:
-    arr, n = _jobs_arg(jobs)
-    _check(load().cnr_clear_bitmap_batch(ctx, arr, n, _stream(stream)), "cnr_clear_bitmap_batch")
+    fn, arr, n = _batch("cnr_clear_bitmap_batch", jobs)
+    _check(fn(ctx, arr, n, _stream(stream)), "cnr_clear_bitmap_batch")
 
 
 def cnr_mark_touched_batch(ctx, jobs, index_type: int, stream=None) -> None:
-    arr, n = _jobs_arg(jobs)
-    _check(load().cnr_mark_touched_batch(ctx, arr, n, index_type, _stream(stream)), "cnr_mark_touched_batch")
+    fn, arr, n = _batch("cnr_mark_touched_batch", jobs)
+    _check(fn(ctx, arr, n, index_type, _stream(stream)), "cnr_mark_touched_batch")
 
 
 def cnr_compact_dirty_batch(ctx, jobs, stream=None) -> None:
-    arr, n = _jobs_arg(jobs)
-    _check(load().cnr_compact_dirty_batch(ctx, arr, n, _stream(stream)), "cnr_compact_dirty_batch")
+    fn, arr, n = _batch("cnr_compact_dirty_batch", jobs)
+    _check(fn(ctx, arr, n, _stream(stream)), "cnr_compact_dirty_batch")
 
 
 def cnr_quantize_rows_batch(ctx, jobs, dim: int, bits: int, mode: int, greedy=None, stream=None) -> None:
-    arr, n = _jobs_arg(jobs)
+    fn, arr, n = _batch("cnr_quantize_rows_batch", jobs)
     gp = None
     if greedy is not None:
         gp = ctypes.pointer(cnr_greedy_params(int(greedy[0]), float(greedy[1])))
-    _check(load().cnr_quantize_rows_batch(ctx, arr, n, dim, bits, mode, gp, _stream(stream)),
-           "cnr_quantize_rows_batch")
+    _check(fn(ctx, arr, n, dim, bits, mode, gp, _stream(stream)), "cnr_quantize_rows_batch")
 
 
 def cnr_restore_rows_batch(ctx, jobs, dim: int, bits: int, stream=None) -> None:
-    arr, n = _jobs_arg(jobs)
-    _check(load().cnr_restore_rows_batch(ctx, arr, n, dim, bits, _stream(stream)), "cnr_restore_rows_batch")
+    fn, arr, n = _batch("cnr_restore_rows_batch", jobs)
+    _check(fn(ctx, arr, n, dim, bits, _stream(stream)), "cnr_restore_rows_batch")
 
 
 # ---- greedy parameters by profiling ----------------------------------------------------------------

@@ -269,6 +269,23 @@ def test_job_fields_take_what_the_struct_holds():
     assert bytes(binding.pack_jobs(([1] * 16, np.arange(16)))) == bytes(binding.pack_jobs([(1,) * 16, tuple(range(16))]))
 
 
+def test_batch_calls_take_arrays_of_jobs_only():
+    import ctypes
+    from types import SimpleNamespace
+
+    stream = SimpleNamespace(cuda_stream=0)   # no GPU here; the arguments are refused before the call
+    calls = [lambda j: P.cnr_clear_bitmap_batch(None, j, stream), lambda j: P.cnr_mark_touched_batch(None, j, 0, stream),
+             lambda j: P.cnr_compact_dirty_batch(None, j, stream), lambda j: P.cnr_quantize_rows_batch(None, j, 64, 4, 0, None, stream),
+             lambda j: P.cnr_restore_rows_batch(None, j, 64, 4, stream)]
+    for call in calls:
+        for bad, error in (((ctypes.c_uint64 * 16)(), ctypes.ArgumentError), (bytearray(128), ctypes.ArgumentError), (bytes(100), ValueError)):
+            with pytest.raises(error):
+                call(bad)
+    for name in ("cnr_clear_bitmap_batch", "cnr_compact_dirty_batch"):
+        with pytest.raises(ctypes.ArgumentError):
+            getattr(P.load(), name)(None, (ctypes.c_uint64 * 16)(), 1, None)
+
+
 def test_a_batch_refuses_a_missing_table_or_output():
     # also where the table's capacity is 0 and the library would not look at it
     ck = P.TableCheckpointer(None, 100, 8, capacity=0, device="cpu")
