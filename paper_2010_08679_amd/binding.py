@@ -12,9 +12,12 @@ from __future__ import annotations
 import ctypes
 import importlib.util
 import itertools
+import operator
 import os
 import struct
+import subprocess
 import threading
+import warnings
 
 import torch
 
@@ -80,7 +83,6 @@ class cnr_table_job(ctypes.Structure):
 
 _lock = threading.Lock()
 _lib = None
-_marshal = None
 _packed_calls = {}  # the *_batch functions as they take the bytes of a job array
 
 
@@ -156,13 +158,18 @@ def load() -> ctypes.CDLL:
 
 
 def _bind_marshal() -> None:
-    """From here on the extension checks the tensors of a call (see csrc/cnr_marshal.cpp)."""
-    global _dev, _marshal
-    spec = importlib.util.spec_from_file_location(__package__ + "._marshal", _build.build_marshal(force=False))
-    m = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(m)
+    """From here on the extension checks the tensors of a call and packs job arrays (see csrc/cnr_marshal.cpp).  It is host code, compiled
+    against this torch and this interpreter: where it is missing and cannot be built, the general checks stay."""
+    global _dev, _pack_fields
+    try:
+        spec = importlib.util.spec_from_file_location(__package__ + "._marshal", _build.build_marshal(force=False))
+        m = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(m)
+    except (ImportError, OSError, subprocess.CalledProcessError) as e:
+        warnings.warn("calls are a few microseconds slower, their tensors are checked in Python: %s" % e, RuntimeWarning)
+        return
     m.set_general(_general_dev)
-    _marshal, _dev = m, m.address
+    _dev, _pack_fields = m.address, m.pack_jobs
 
 
 def status_str(status: int) -> str:
@@ -373,12 +380,28 @@ _JOB_KINDS = tuple(_JOB_TENSORS.get(name, int) for name in _JOB_FIELDS)  # what 
 _job_packers = {}
 
 
+def _general_pack_fields(rows, kinds, names) -> bytes:
+    if not isinstance(rows, list) or any(not isinstance(r, tuple) or len(r) != len(kinds) for r in rows):
+        raise TypeError("a job has sixteen fields")
+    values = []
+    for row in rows:
+        for v, kind, name in zip(row, kinds, names):
+            x = operator.index(v) if kind is int else 0 if type(v) is int and v == 0 else _general_dev(v, kind, name)
+            if not 0 <= x < 2 ** 64:
+                raise OverflowError("%s is no unsigned 64-bit number" % name)
+            values.append(x)
+    return struct.pack("%dQ" % len(values), *values)
+
+
+_pack_fields = _general_pack_fields  # the extension's, once the library is loaded
+
+
 def job_bytes(rows) -> bytes:
     """The bytes of a ``cnr_table_job`` array from a list of one 16-tuple per job, the struct's fields in order: numbers, and where the
     struct has addresses a tensor, None, or 0 for a field that the call does not read.  What :func:`make_jobs` builds field
     by field, with the same checks, in one step; the batch calls take it."""
     load()
-    return _marshal.pack_jobs(rows, _JOB_KINDS, _JOB_FIELDS)
+    return _pack_fields(rows, _JOB_KINDS, _JOB_FIELDS)
 
 
 def pack_jobs(rows):

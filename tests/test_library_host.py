@@ -286,6 +286,28 @@ def test_batch_calls_take_arrays_of_jobs_only():
             getattr(P.load(), name)(None, (ctypes.c_uint64 * 16)(), 1, None)
 
 
+@pytest.mark.parametrize("error", [FileNotFoundError("g++"), PermissionError("read-only"), ImportError("undefined symbol")])
+def test_a_missing_extension_leaves_the_general_checks(monkeypatch, error):
+    def missing(force=True):
+        raise error
+
+    P.load()
+    packed = binding.job_bytes([(None, 3) + (0,) * 14])
+    for name, value in (("_lib", None), ("_dev", binding._general_dev), ("_pack_fields", binding._general_pack_fields)):
+        monkeypatch.setattr(binding, name, value)
+    monkeypatch.setattr(binding._build, "build_marshal", missing)
+    with pytest.warns(RuntimeWarning):
+        lib = P.load()
+    assert lib is P.load() and P.cnr_bitmap_words(33) == 2
+    assert binding._dev is binding._general_dev and binding.job_bytes([(None, 3) + (0,) * 14]) == packed
+    test_job_fields_take_what_the_struct_holds()
+    test_batch_calls_take_arrays_of_jobs_only()
+    test_binding_refuses_host_tensors_and_wrong_dtypes()
+    for bad in ([(0,) * 15], [[0] * 16], ((0,) * 16,)):
+        with pytest.raises(TypeError):
+            binding.job_bytes(bad)
+
+
 def test_a_batch_refuses_a_missing_table_or_output():
     # also where the table's capacity is 0 and the library would not look at it
     ck = P.TableCheckpointer(None, 100, 8, capacity=0, device="cpu")
