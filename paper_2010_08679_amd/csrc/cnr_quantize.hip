@@ -597,9 +597,12 @@ struct ClipBound {
 };
 // Whether it is worth asking: a candidate's error is well above the bound, since the elements within its range
 // have errors too.  (At 2 bits a search stops where its error is about 1.25 times the best, at 4 bits 1.8; an eighth
-// of a binade more in the errors' upper halves is 1.06 to 1.125 times.)
+// of a binade more in the errors' upper halves is 1.06 to 1.125 times.)  ZERO: where the best may be 0, no later error can be
+// smaller, and the question is worth asking whatever the error.
+template <bool ZERO>
 __device__ __forceinline__ bool may_be_done(double error, double best) {
-    return __double2hiint(error) >= __double2hiint(best) + (1 << 17);
+    const int b = __double2hiint(best);
+    return __double2hiint(error) >= b + (ZERO ? min(b, 1 << 17) : 1 << 17);
 }
 
 // The 24 code bits of a pair of units at 3 bits.
@@ -692,6 +695,10 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L =
             const float step = (hi - lo) / a.num_bins_f;
             clip.rescale(lo, hi);
             double best = row_err(lo, hi);
+            // Rows that keep the wave searching.  Not those without an error from the start: constant rows, or two values far
+            // apart; one such row in 64 kept every wave of a list to its last iteration (1.5 M rows of 64 at 4 bits and 100 bins 2580 us
+            // with them, 655 now, 660 without any).  (ZERO instead of this mask: rows of 16 at 3 bits 131 -> 146 us.)
+            const bool open = live & (best != 0.0);
             uint32_t n_iter = a.n_iter;
             for (uint32_t it = 0; it < n_iter; ++it) {
                 const float c_lo = cur_lo + step;
@@ -708,8 +715,8 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L =
                 lo = found ? cur_lo : lo;
                 hi = found ? cur_hi : hi;
                 if constexpr (FAST) {
-                    if (__builtin_amdgcn_ballot_w64(live & !may_be_done(e, best)) == 0)
-                        if (__builtin_amdgcn_ballot_w64(live & !clip.template done<L>(cur_lo, cur_hi, best)) == 0) n_iter = it;
+                    if (__builtin_amdgcn_ballot_w64(open & !may_be_done<false>(e, best)) == 0)
+                        if (__builtin_amdgcn_ballot_w64(open & !clip.template done<L>(cur_lo, cur_hi, best)) == 0) n_iter = it;
                 }
             }
         };
@@ -904,6 +911,7 @@ struct RowUnits {
         float cur_lo = lo, cur_hi = hi;
         const float step = (hi - lo) / num_bins_f;
         if constexpr (FAST) clip.rescale(lo, hi);
+        const uint64_t live_rows = __builtin_amdgcn_ballot_w64(live);
         const bool upper = DUAL && (tid_x() / L) & 1;  // this lane's group lowers the upper bound
         // The first candidate is an iteration whose step is zero.
         float move = 0.0f;
@@ -934,8 +942,8 @@ struct RowUnits {
                 hi = found ? cur_hi : hi;
                 move = step;
                 if constexpr (FAST) {
-                    if (__builtin_amdgcn_ballot_w64(live & !may_be_done(better, best)) == 0)
-                        if (__builtin_amdgcn_ballot_w64(live & !clip.template done<L>(cur_lo, cur_hi, best)) == 0) last = c;
+                    if ((__builtin_amdgcn_ballot_w64(!may_be_done<true>(better, best)) & live_rows) == 0)
+                        if ((__builtin_amdgcn_ballot_w64(!clip.template done<L>(cur_lo, cur_hi, best)) & live_rows) == 0) last = c;
                 }
             }
         }
