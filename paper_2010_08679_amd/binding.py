@@ -377,6 +377,7 @@ def make_jobs(jobs):
 
 _JOB_FIELDS = tuple(name for name, _ in cnr_table_job._fields_)
 _JOB_KINDS = tuple(_JOB_TENSORS.get(name, int) for name in _JOB_FIELDS)  # what job_bytes takes for a field
+_JOB_BYTES = ctypes.sizeof(cnr_table_job)
 _job_packers = {}
 
 
@@ -416,15 +417,15 @@ def pack_jobs(rows):
 
 def _batch(name: str, jobs):
     """(library function, argument, number of jobs): the bytes of a job array, an array of ``cnr_table_job``, or a list of dicts."""
-    lib = load()
     if isinstance(jobs, bytes):
-        n, rest = divmod(len(jobs), ctypes.sizeof(cnr_table_job))
-        if rest:
+        n = len(jobs) // _JOB_BYTES
+        if n * _JOB_BYTES != len(jobs):
             raise ValueError("the bytes are no whole number of jobs")
-        return _packed_calls[name], jobs, n
+        return _packed_calls.get(name) or (load() and _packed_calls[name]), jobs, n
+    fn = getattr(load(), name)
     if isinstance(jobs, (list, tuple)):
-        return getattr(lib, name), make_jobs(jobs), len(jobs)
-    return getattr(lib, name), jobs, len(jobs)
+        return fn, make_jobs(jobs), len(jobs)
+    return fn, jobs, len(jobs)
 
 
 def cnr_clear_bitmap_batch(ctx, jobs, stream=None) -> None:

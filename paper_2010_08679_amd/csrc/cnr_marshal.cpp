@@ -65,12 +65,17 @@ PyObject *address(PyObject *, PyObject *const *args, Py_ssize_t n) {
 // None or the number 0, a field that the call does not read.
 bool field(PyObject *v, PyObject *kind, PyObject *name, unsigned long long &out) {
     if (kind == reinterpret_cast<PyObject *>(&PyLong_Type)) {
-        THPObjectPtr index(PyNumber_Index(v));
-        if (!index) return false;
-        out = PyLong_AsUnsignedLongLong(index.get());
-        return !PyErr_Occurred();
+        if (PyLong_CheckExact(v)) {
+            out = PyLong_AsUnsignedLongLong(v);
+        } else {
+            THPObjectPtr index(PyNumber_Index(v));
+            if (!index) return false;
+            out = PyLong_AsUnsignedLongLong(index.get());
+        }
+        return out != ~0ull || !PyErr_Occurred();
     }
     out = 0;
+    if (v == Py_None) return true;
     if (PyLong_CheckExact(v)) {
         int overflow;
         if (PyLong_AsLongLongAndOverflow(v, &overflow) == 0 && !overflow) return true;
