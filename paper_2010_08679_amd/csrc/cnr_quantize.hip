@@ -534,8 +534,11 @@ __device__ __forceinline__ bool search_divides(float lo, float hi, float num_bin
 // covers their rounding.  (All this for scales that are normal numbers: the sequence without divisions.)
 // 1.5 M rows of 64 at 100 bins and 4 bits stop after 21 of 99 iterations (with every element's clipping error: 21 too,
 // the row's two ends alone: 21), at 2 bits and 25 bins after 18 of 24 (17; 22): 2.69 -> 0.66 ms and 0.73 -> 0.58.  Rows of 8
-// to 512 elements at 4 bits and 45 bins 1.4 to 6 times as fast, at 8 bits 4 to 5 times, at 2 bits and 25 bins, where long rows
-// search nearly to the end, 1.0 to 1.8 times (the worst: 1 K rows of 1024 23.6 -> 25.4 us, of 320 15.9 -> 16.6).
+// to 512 elements at 4 bits and 45 bins 1.4 to 6 times as fast, at 8 bits 4 to 5 times.  At 2 bits it depends on the rows: whole
+// searches of 1024 elements 1.6 times as fast on evenly spread values, 1.3 on normal ones, and up to 8 % slower where outliers
+// let the search go on to nine tenths of its iterations (25 bins: 1 K rows of 1024 23.5 -> 25.2 us, of 320 15.8 -> 16.7; 10 K and more
+// within 3 %).  Searches that stop by themselves about where rows would be finished lose up to as much (1 K rows of 320 at 4 bits,
+// 45 bins, ratio 0.4, 13.1 -> 14.7 us; 60 K 176 -> 184).
 template <int N>
 struct ClipBound {
     float mn[N], mx[N];
@@ -629,7 +632,7 @@ __device__ __forceinline__ void store_unit_codes(uint8_t *out, uint32_t u, uint3
     }
 }
 
-template <int L, int BITS, int G>
+template <int L, int BITS, int G, bool ENDS>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L == 1 && G == 4 ? 3 : G == 4 ? 4 : 5, 8))) quantize_greedy_kernel(const QuantArgs a, double less /* tie_factor(dim) */, uint64_t n_from, uint64_t n_below) {
     constexpr int EPL = 16 * G;  // elements per lane
     constexpr int DIM = EPL * L;
@@ -693,7 +696,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L =
             };
             float cur_lo = lo, cur_hi = hi;
             const float step = (hi - lo) / a.num_bins_f;
-            clip.rescale(lo, hi);
+            if constexpr (FAST && ENDS) clip.rescale(lo, hi);
             double best = row_err(lo, hi);
             // Rows that keep the wave searching.  Not those without an error from the start: constant rows, or two values far
             // apart; one such row in 64 kept every wave of a list to its last iteration (1.5 M rows of 64 at 4 bits and 100 bins 2580 us
@@ -714,7 +717,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L =
                 best = found ? e : best;
                 lo = found ? cur_lo : lo;
                 hi = found ? cur_hi : hi;
-                if constexpr (FAST) {
+                if constexpr (FAST && ENDS) {
                     if (__builtin_amdgcn_ballot_w64(open & !may_be_done<false>(e, best)) == 0)
                         if (__builtin_amdgcn_ballot_w64(open & !clip.template done<L>(cur_lo, cur_hi, best)) == 0) n_iter = it;
                 }
@@ -817,9 +820,9 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L =
 // instructions (range to scale to reciprocal, the sum over the lanes, the comparison), so two groups of L
 // lanes hold the row, one evaluates the raised lower bound and the other the lowered upper one.  (A wave
 // per row that re-read the row from cache and divided for every element: 100 K rows of 96 at 49
-// candidates 874 us, this 106 us.)  The waves that waves_per_eu asks for cost spilled registers (2 in the
-// 16-unit forms at 2 bits, 28 to 30 at 3 and 4, 4 to 8 in some 8-unit forms); all of them are stored and reloaded
-// once per row, outside the loop over the candidates.
+// candidates 874 us, this 106 us.)  The waves that waves_per_eu asks for cost spilled registers: in the 16-unit forms 2 at
+// 2 bits and 30 at 3 and 4, in some 8-unit forms 4 to 8, and where a search may end early 10 to 12 and 6 to 8 more for the ends it keeps.
+// All of them are stored and reloaded outside the loop over the candidates, once per pass.
 // ---------------------------------------------------------------------------------------------
 // What the same lane of the row's other group of L lanes holds.  (The mirrors reverse the lanes, which is
 // the same for values that all lanes of a group agree on.)
@@ -905,12 +908,12 @@ struct RowUnits {
         return lanes_sum<L>(e);
     }
     // The search (header: cnr_greedy_params): [lo, hi] comes in as the row's range and leaves as the chosen one;
-    // rows that are not live do not keep it going.
-    template <int BITS, bool FAST>
+    // rows that are not live do not keep it going.  ENDS: it ends early where it can.
+    template <int BITS, bool FAST, bool ENDS>
     __device__ __forceinline__ void search(uint32_t n_iter, float num_bins_f, double less, bool live, float &lo, float &hi) {
         float cur_lo = lo, cur_hi = hi;
         const float step = (hi - lo) / num_bins_f;
-        if constexpr (FAST) clip.rescale(lo, hi);
+        if constexpr (FAST && ENDS) clip.rescale(lo, hi);
         const uint64_t live_rows = __builtin_amdgcn_ballot_w64(live);
         const bool upper = DUAL && (tid_x() / L) & 1;  // this lane's group lowers the upper bound
         // The first candidate is an iteration whose step is zero.
@@ -941,7 +944,7 @@ struct RowUnits {
                 lo = found ? cur_lo : lo;
                 hi = found ? cur_hi : hi;
                 move = step;
-                if constexpr (FAST) {
+                if constexpr (FAST && ENDS) {
                     if ((__builtin_amdgcn_ballot_w64(!may_be_done<true>(better, best)) & live_rows) == 0)
                         if ((__builtin_amdgcn_ballot_w64(!clip.template done<L>(cur_lo, cur_hi, best)) & live_rows) == 0) last = c;
                 }
@@ -950,7 +953,7 @@ struct RowUnits {
     }
 };
 
-template <int L, int UMAX, bool DUAL, int BITS>
+template <int L, int UMAX, bool DUAL, int BITS, bool ENDS>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(UMAX > 8 ? 3 : 4, 8)))
 quantize_greedy_units_kernel(const QuantArgs a, double less /* tie_factor(dim) */, uint64_t n_from, uint64_t n_below) {
     using Row = RowUnits<L, UMAX, DUAL>;
@@ -981,9 +984,9 @@ quantize_greedy_units_kernel(const QuantArgs a, double less /* tie_factor(dim) *
         row.range(X_min, X_max);
         float lo = X_min, hi = X_max;
         if (search_divides(lo, hi, a.num_bins_f, QMAXF))
-            row.template search<BITS, false>(a.n_iter, a.num_bins_f, less, live, lo, hi);
+            row.template search<BITS, false, ENDS>(a.n_iter, a.num_bins_f, less, live, lo, hi);
         else
-            row.template search<BITS, true>(a.n_iter, a.num_bins_f, less, live, lo, hi);
+            row.template search<BITS, true, ENDS>(a.n_iter, a.num_bins_f, less, live, lo, hi);
 
         if constexpr (DUAL) live = live && !((lane / L) & 1);  // one of the row's two groups stores
         const float scale = (hi - lo) / QMAXF;
@@ -1079,9 +1082,9 @@ sample_error_kernel(const SelectArgs a) {
         row.range(lo, hi);
         if (n_iter) {
             if (search_divides(lo, hi, num_bins_f, QMAXF))
-                row.template search<BITS, false>(n_iter, num_bins_f, a.less, live, lo, hi);
+                row.template search<BITS, false, true>(n_iter, num_bins_f, a.less, live, lo, hi);
             else
-                row.template search<BITS, true>(n_iter, num_bins_f, a.less, live, lo, hi);
+                row.template search<BITS, true, true>(n_iter, num_bins_f, a.less, live, lo, hi);
         }
         const float scale = (hi - lo) / QMAXF;
         double e = 0.0;
@@ -1421,6 +1424,17 @@ inline void launch_tile_any(QuantBatchArgs<> &b, uint32_t n, uint32_t dim, int b
     }
 }
 
+// Whether a search can end before its last iteration: one that covers only the first part of its num_bins moves (a ratio well
+// below 1) is over before any but clustered rows could be finished, and would keep the ends and ask for nothing.  Evenly spread
+// rows, which finish first, do so after 0.48 to 0.52 of the moves at 2 bits, 0.28 to 0.32 at 3, 0.17 to 0.2 at 4, at 8 bits after one or two
+// moves; normal ones after 0.6, 0.35 and 0.2 of them and later.  (Rows of up to 32 elements sooner: they always ask.)  With the questions and
+// without: 20 K rows of 40 elements, 3 bits, ratio 0.3 20.7 and 18.0 us, of 1024 136 and 129; 1 K of 320 at 2 bits, ratio 0.5, 11.4 and 10.8;
+// 78 K of 256 at 4 bits, ratio 0.17, 74.3 and 70.4.
+template <int BITS>
+constexpr float kEarliestEnd = BITS == 2 ? 0.52f : BITS == 3 ? 0.32f : BITS == 4 ? 0.18f : 0.0f;
+template <int BITS>
+bool may_end_early(const QuantArgs &a) { return a.dim <= 32 || (float)a.n_iter > kEarliestEnd<BITS> * a.num_bins_f; }
+
 // Runs for lists of n_from <= n < n_below rows (n is the count on the device where there is one).
 template <int L, int BITS, int G>
 void launch_greedy(cnr_ctx *ctx, QuantArgs &a, hipStream_t s, uint64_t n_from, uint64_t n_below) {
@@ -1429,7 +1443,13 @@ void launch_greedy(cnr_ctx *ctx, QuantArgs &a, hipStream_t s, uint64_t n_from, u
     const uint64_t most = a.n_max < n_below ? a.n_max : n_below;
     const unsigned grid = cnr_row_grid(most, (uint64_t)(kWave / L) * kWavesPerBlock);
     a.n_waves = grid * kWavesPerBlock;
-    hipLaunchKernelGGL((quantize_greedy_kernel<L, BITS, G>), dim3(grid), dim3(kBlock), 0, s, a, tie_factor(a.dim), n_from, n_below);
+    if constexpr (BITS != 8 && 16 * G * L > 32) {
+        if (!may_end_early<BITS>(a)) {
+            hipLaunchKernelGGL((quantize_greedy_kernel<L, BITS, G, false>), dim3(grid), dim3(kBlock), 0, s, a, tie_factor(a.dim), n_from, n_below);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((quantize_greedy_kernel<L, BITS, G, true>), dim3(grid), dim3(kBlock), 0, s, a, tie_factor(a.dim), n_from, n_below);
 }
 // Long lists give every lane 64 elements (32 at dim 32); short ones keep 16 per lane, four times the
 // lanes per row and a quarter of the time per row, which is what counts while the list cannot fill
@@ -1451,7 +1471,13 @@ void launch_greedy_units_shape(QuantArgs &a, hipStream_t s, uint64_t n_from, uin
     const uint64_t most = a.n_max < n_below ? a.n_max : n_below;
     const unsigned grid = cnr_row_grid(most, (uint64_t)(kWave / RowUnits<L, UMAX, DUAL>::LANES) * kWavesPerBlock);
     a.n_waves = grid * kWavesPerBlock;
-    hipLaunchKernelGGL((quantize_greedy_units_kernel<L, UMAX, DUAL, BITS>), dim3(grid), dim3(kBlock), 0, s, a, tie_factor(a.dim), n_from, n_below);
+    if constexpr (BITS != 8 && L > 1 && UMAX > 2) {  // the others have rows of up to 32 elements
+        if (!may_end_early<BITS>(a)) {
+            hipLaunchKernelGGL((quantize_greedy_units_kernel<L, UMAX, DUAL, BITS, false>), dim3(grid), dim3(kBlock), 0, s, a, tie_factor(a.dim), n_from, n_below);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((quantize_greedy_units_kernel<L, UMAX, DUAL, BITS, true>), dim3(grid), dim3(kBlock), 0, s, a, tie_factor(a.dim), n_from, n_below);
 }
 // Other row lengths: long lists give a row as few lanes as hold it; short ones give it two groups of 4 to
 // 32 lanes, which evaluate the two candidates of an iteration side by side (17 instead of 23 us for

@@ -314,6 +314,25 @@ def test_greedy_search_that_ends_early_finds_the_same_range(ctx, dim, bits, bins
     _poll(ctx)
 
 
+# Partial searches up to 0.52, 0.32 and 0.18 of their moves (2, 3, 4 bits) go through kernels that do not ask whether a row is finished
+@pytest.mark.parametrize("dim,bits,long", [(36, 2, 25_000), (40, 3, 25_000), (64, 2, 131_072), (64, 4, 131_072), (96, 4, 26_624), (128, 3, 65_536), (200, 3, 64_000),
+                                           (256, 2, 32_768), (280, 4, 0), (320, 4, 6_400), (1088, 2, 0), (32, 4, 262_144), (8, 3, 49_152)])
+def test_greedy_partial_searches(ctx, dim, bits, long):
+    last = {2: 26, 3: 16, 4: 9}[bits]
+    for n in {300, max(300, long + 3)}:
+        gt = GpuTable(ctx, synth.table_outlier_mix(n, dim, 0.02, dim + bits, DEV))
+        pos = np.unique(np.concatenate([np.arange(200), np.random.default_rng(n).integers(0, n, size=1000), [n - 1]]))
+        for n_iter in (last, last + 1):
+            ratio = (n_iter - 0.5) / 50
+            assert P.cnr_greedy_iterations(50, ratio) == n_iter
+            got = gpu_encode_all_outputs(gt, bits, mode=P.CNR_RANGE_GREEDY, greedy=(50, ratio), row_ids=None, n=n)
+            ora = O.quantize_rows(gt.host[pos], None, bits, mode=O.RANGE_GREEDY, num_bins=50, ratio=ratio, n_threads=8)
+            compare_greedy(gt.host[pos], {k: got[k][pos] for k in ("scale", "bias", "row_min", "row_max", "codes")}, ora, bits, 50, ratio,
+                           what="partial b%d d%d n%d" % (bits, dim, n))
+            assert np.array_equal(got["packed"], O.pack(got["codes"], bits))
+    _poll(ctx)
+
+
 # A row without an error from the start (here constant) is finished: it must not keep the rows that share its wave searching.  Measured, the
 # result is the same either way: with one such row in 64 the long lists took 1.2 to 4 times as long.
 @pytest.mark.parametrize("dim,bits,bins,n", [(64, 4, 100, 300_000), (16, 4, 45, 600_000), (24, 4, 45, 400_000), (48, 4, 100, 300_000), (128, 4, 100, 150_000)])
