@@ -1526,14 +1526,18 @@ void launch_greedy_units(QuantArgs &a, hipStream_t s) {
 // iterations gains less than the wider spread of its rows costs, so the line comes down with it (up to 10 bins,
 // 12 K rows of 64 8.8 us in one group, 9.6 in two, 6 K rows 8.8 and 7.9; up to 4 bins, 3 K rows of 128 5.4 and 5.9).
 // At 8 bits a search ends after an iteration or two and one group is level or better for rows of 64 and more (12 K of them 4.8
-// against 5.8 us) and beyond 6 K shorter rows (4.6 against 4.1-4.3 below, 4.6 and 4.5-4.9 at 12 K); at 3 and 4 bits rows of 64 have the line at half the others' waves (12 K rows, 45 bins: 10.8 against 13.5; 6 K 10.5 either way; at 2
-// bits, 12 K rows, 16.4 against 15.7).
+// against 5.8 us) and beyond 6 K shorter rows (4.6 against 4.1-4.3 below, 4.6 and 4.5-4.9 at 12 K).  At 3 and 4 bits rows of 64 whose
+// search may end early have the line at two waves per SIMD: they hold half of what rows of 128 do in the same form, and one that ends is
+// over sooner (4 bits, 100 bins: 8 K rows 14.5 us in two groups, 17.4 in one, 9 K 17.6 and 17.3; 45 bins 9.7 and 10.0, 11.6 and 10.0; 3 bits,
+// 45 bins 13.3 and 15.5, 16.0 and 15.4).  Partial searches keep three (100 bins, ratio 0.3, 8 K rows 16.7 and 20.8, 12 K 20.5 and 20.8), and
+// so do the other lengths, searched whole or not (12 K rows of 128 at 4 bits, 100 bins, 29.4 and 32.7, 20 K of 16 8.4 and 10.6).
 // Only where the host's bound on the length says so: another launch to choose from on the device would cost
 // the longer lists more.
 template <int BITS>
 bool launch_greedy_short(QuantArgs &a, hipStream_t s) {
     const uint32_t lanes = a.dim <= 32 ? 8 : a.dim <= 128 ? 16 : 32;
-    const uint32_t many = 196608u / lanes >> (BITS == 8 ? 2 : a.dim == 64 && BITS != 2 ? 1 : 0);
+    uint32_t many = 196608u / lanes >> (BITS == 8 ? 2 : 0);
+    if (a.dim == 64 && BITS != 2 && a.n_iter >= 16 && may_end_early<BITS>(a)) many = many * 2 / 3;
     const uint32_t most = a.n_iter >= 16 ? many : a.dim <= 64 ? (a.n_iter >= 3 ? many / 2 : many / 4) : a.n_iter >= 8 ? many / 4 : 0;
     if (a.n_max > most || (BITS == 8 && a.dim > 32)) return false;
     if (a.dim == 16 || a.dim == 32) {

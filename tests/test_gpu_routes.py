@@ -201,9 +201,11 @@ def test_greedy_routes_of_other_row_lengths(ctx, dim, bits, wide):
     _poll(ctx)
 
 
-@pytest.mark.parametrize("dim,bits,limit", [(16, 4, 24_576), (32, 3, 24_576), (64, 2, 12_288), (64, 8, 12_288), (128, 3, 12_288), (256, 4, 6_144)])
+@pytest.mark.parametrize("dim,bits,limit", [(16, 4, 24_576), (32, 3, 24_576), (64, 2, 12_288), (64, 3, 12_288), (64, 4, 12_288), (64, 8, 12_288), (128, 3, 12_288),
+                                            (256, 4, 6_144), (16, 8, 6_144), (32, 8, 6_144)])
 def test_greedy_short_lists_of_power_of_two_rows(ctx, dim, bits, limit):
-    # up to `limit` rows (a bound the host knows) two groups of lanes per row, beyond it one
+    # up to `limit` rows (a bound the host knows) two groups of lanes per row, beyond it one; whole searches of rows of 64 at 3 and 4 bits
+    # up to two thirds of it, at 8 bits rows of 64 and more not at all
     n_rows = limit + 3
     table = synth.table_outlier_mix(n_rows, dim, 0.02, dim + bits, DEV)
     rng = np.random.default_rng(dim)
@@ -213,7 +215,8 @@ def test_greedy_short_lists_of_power_of_two_rows(ctx, dim, bits, limit):
     gt = GpuTable(ctx, table)
     # up to its last iteration, and a few and the fewest iterations, whose lines lie lower
     many, few = {2: (25, 1.0), 3: (25, 1.0), 4: (45, 1.0), 8: (20, 1.0)}[bits], (12, 0.75)
-    lines = [(many, limit), (few, limit // 2 if dim <= 64 else limit // 4), ((12, 0.1), limit // 4)]
+    lines = [(many, limit * 2 // 3 if dim == 64 and bits in (3, 4) else limit), (few, limit // 2 if dim <= 64 else limit // 4), ((12, 0.1), limit // 4),
+             ((100, 0.17), limit)]
     for params, line in lines:
         for n in (1, 77, line, line + 1):
             got = gpu_encode_all_outputs(gt, bits, mode=P.CNR_RANGE_GREEDY, greedy=params, row_ids=None, n=n)
