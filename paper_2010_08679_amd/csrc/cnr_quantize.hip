@@ -1453,8 +1453,11 @@ void launch_greedy(cnr_ctx *ctx, QuantArgs &a, hipStream_t s, uint64_t n_from, u
 }
 // Long lists give every lane 64 elements (32 at dim 32); short ones keep 16 per lane, four times the
 // lanes per row and a quarter of the time per row, which is what counts while the list cannot fill
-// the SIMDs anyway.  The break-even lies between 8 and 11 M elements (45 bins, rows of 64: 130 K rows 155
-// against 186 us, 160 K rows 190 either way, 262 K rows 310 against 247).  Where the
+// the SIMDs anyway.  The break-even lies at 8 M elements at 2 to 4 bits, whether searches end early or not (rows of 64, 45 bins, 4 bits:
+// 93 K rows 32.1 us with 16 elements per lane, 40.6 with 64, 131 K 41.6 and 41.1, 262 K 77.0 and 72.0; 3 bits 52.3 and 66.9, 68.4 and
+// 68.5, 129 and 119; rows of 256 at 16 K, 33 K and 66 K 38.7 and 44.2, 71.0 and 66.5, 134 and 118; rows of 32 level from 4 M on).
+// At 8 bits it depends on the number of bins (100 bins: rows of 64 16.2 and 18.4 at 8 M, 26.9 and 29.9 at 16 M, level at 32 M;
+// rows of 256 22.3 and 21.3, 39.7 and 36.0; 20 bins: 15.0 and 16.0, level from 16 M on).  Where the
 // length is a count on the device and the capacity allows a long list, both kernels are launched
 // and the one whose range the count is not in returns at once.
 template <int L_NARROW, int L_WIDE, int G_WIDE, int BITS>

@@ -672,8 +672,9 @@ void launch_error(ErrorArgs &a, unsigned grid, uint32_t lanes, int bits, hipStre
 
 // Lanes per row of the error kernel: one trip of 4 or 8 for rows of up to 16 and 32 elements, sixteen beyond.  Fewer lanes
 // with fewer of them idle in the last trip lose more by the trips, which follow each other, and by their shorter runs (60 M
-// elements at 4 bits: rows of 36 16 / 8 / 4 lanes 81 / 98 / 124 us, of 72 69 / 79 / 101, of 112 54 / 64 / 81, of 200 58 / 73 / 103); only
-// three trips of 8 that leave none idle are level with two of 16 (rows of 96 46 and 49).  32 where that takes no more
+// elements at 4 bits: rows of 36 16 / 8 / 4 lanes 81 / 98 / 124 us, of 72 69 / 79 / 101, of 112 54 / 64 / 81, of 200 58 / 73 / 103).  Only
+// three trips of 8 that leave no lane idle beat two of 16 with a quarter idle, which 96 elements alone come to (60 M elements at 2, 3, 4
+// and 8 bits 44, 45, 46 and 50 us, with 16 lanes 46, 53, 48 and 50).  32 where that takes no more
 // lanes' worth of trips than 16 and there are trips to save (rows of 120 54 instead of 57, of 200 51, of 240 47 instead of 51), and
 // beyond 512 and 1024 elements 32 and 64: sixteen lanes would make up to 64 trips.
 // 0 = one wave per row, for rows that are not whole aligned 16-byte units.
