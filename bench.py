@@ -9,7 +9,8 @@ checkpointed per second over the whole step.
 
 Default workload: the 8 x 5M x 64 outlier-mix tables with 30 % dirty rows, 4 bits, min/max range.
 The same tables are also encoded once per run with the greedy range search (100 bins, ratio 1),
-reported separately, and the CPU oracle is timed on a bounded sample of the same workload.
+reported separately against the vector-ALU roofline, and the CPU oracle is timed on a bounded sample of the same
+workload.
 
 Prints one JSON line.
 """
@@ -33,6 +34,16 @@ import paper_2010_08679_amd as P  # noqa: E402
 from paper_2010_08679_amd import synth  # noqa: E402
 
 HBM_PEAK_GBPS = 8000.0          # MI355X HBM3E, published
+FP32_VECTOR_PEAK_TFLOPS = 157.3  # MI355X fp32 vector, published
+# The fewest SIMD clocks the greedy search's eight instructions per element and candidate range can take for a
+# wave of 64 on 256 CUs x 4 SIMDs at 2.4 GHz: two for each of the six fp32 ones at the published 157.3 TFLOP/s, as
+# many for the conversion, four for the fp64 multiply-add at the published 78.6 TFLOP/s.  (A loop of nothing but
+# the eight takes 23.6, bench_ceilings.hip; the kernel, which overlaps them with what lies between, about 22.)
+GREEDY_SIMD_CLOCKS_PER_ELEMENT = 18.0
+SIMD_CLOCKS_PER_S = 256 * 4 * 2.4e9
+# Candidate ranges per row that a wave of 64 rows of the workload has tried when the last of its searches can be ended, of
+# 1 + 2 * n_iter: a property of the rows (12,800 of them searched in numpy: 21.07 iterations on average, 23 at most).
+GREEDY_CANDIDATES = {"cfg4/b4": 43.1}
 
 # HBM traffic of the two bandwidth-bound kernels from rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE, each
 # scaled by what a 1 GiB device copy reads on the same counter: 2.000 and 1.000), in bytes per dirty row,
@@ -399,15 +410,21 @@ def main() -> int:
             g_ms.append(a.elapsed_time(b))
         g = min(g_ms)
         n_iter = P.cnr_greedy_iterations(w.num_bins, w.ratio)
-        # ids, rows, scale and bias, codes.  The kernel is bound by vector issue on the candidate ranges it cannot rule out; how
-        # many those are depends on the rows, so no share of an arithmetic peak is given.
-        moved = sum(n_dirty) * (4 + w.dim * 4 + 8 + P.cnr_packed_row_bytes(w.dim, bits))
+        candidates = GREEDY_CANDIDATES.get("%s/b%d" % (w.name, bits))
+        roofline = {"bound": "alu", "achieved": None, "peak": FP32_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": None, "traffic": None}
+        if candidates:
+            # arithmetic the search itself prescribes, per element and candidate range: clip (2), subtract,
+            # divide, round, multiply, add, subtract, square, accumulate = 10
+            tflops = sum(n_dirty) * w.dim * candidates * 10.0 / (g * 1e-3) / 1e12
+            issue_ms = sum(n_dirty) * w.dim * candidates / 64.0 * GREEDY_SIMD_CLOCKS_PER_ELEMENT / SIMD_CLOCKS_PER_S * 1e3
+            roofline.update(achieved=round(tflops, 2), frac=round(tflops / FP32_VECTOR_PEAK_TFLOPS, 4), candidates_per_row=candidates,
+                            # the same launches against what their instructions take at the published issue rates
+                            issue_bound_ms=round(issue_ms, 3), issue_frac=round(issue_ms / g, 4))
         out["greedy"] = {
             "workload": "%d-bit greedy range, num_bins=%d, ratio=%.2f (up to %d candidate ranges per row)"
                         % (bits, w.num_bins, w.ratio, 1 + 2 * n_iter),
             "ms": round(g, 3), "value": round(table_bytes / (g * 1e-3) / 1e9, 2), "unit": "GB/s",
-            "roofline": {"bound": "hbm", "achieved": round(moved / (g * 1e-3) / 1e9, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
-                         "frac": round(moved / (g * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4), "traffic": None},
+            "roofline": roofline,
         }
 
     # ---- a full (baseline) checkpoint: every row of a table, no id list (Section 5.1) ---------------
