@@ -50,10 +50,10 @@ GREEDY_CANDIDATES = {"cfg4/b4": 43.1}
 # valid only for the kernel source whose hash is recorded with it (profiles/hbm_traffic.txt).
 TRAFFIC_PER_ROW = {
     # _kernel_hash() : {workload/bits : bytes per dirty row}
-    "49d873374416ae60a94c90bff98225b782606a8470dd2c2a2949c40105aebff4": {"cfg4/b4": 301.54},
+    "49d873374416ae60a94c90bff98225b782606a8470dd2c2a2949c40105aebff4": {"cfg4/b4": 301.54, "cfg3/b2": 558.98, "cfg3/b3": 581.13, "cfg5/b8": 659.12, "cfg5/b4": 592.60},
 }
 RESTORE_TRAFFIC_PER_ROW = {
-    "53422e577636a6c5720da3ea9f67558a5b1fab4589a8438277cc6b821ac1b7d3": {"cfg4/b4": 300.01},
+    "53422e577636a6c5720da3ea9f67558a5b1fab4589a8438277cc6b821ac1b7d3": {"cfg4/b4": 300.01, "cfg3/b2": 556.06, "cfg3/b3": 572.05, "cfg5/b8": 652.10, "cfg5/b4": 588.06},
 }
 
 
