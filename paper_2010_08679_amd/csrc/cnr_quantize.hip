@@ -523,22 +523,25 @@ __device__ __forceinline__ bool search_divides(float lo, float hi, float num_bin
 }
 
 // What ends a search early: a lower bound for the error of every candidate still to come.  Candidate ranges are
-// nested, so an element that the current bounds clip stays clipped, at least as far, in all later ones, and
+// nested, so an element that a range clips stays clipped, at least as far, in all later ones, and
 // its clipping error is part of their errors.  Each lane keeps the smallest and the largest element of every N-th
-// part of its share of the row and adds up the squares of what those are clipped by; once the row's sum reaches the
+// part of its share of the row and adds up the squares of what those are clipped by; every candidate still to come lies within one of
+// the next iteration's two, so once the row's sums for both reach the
 // best error, no later candidate can be strictly smaller and the range is the one that the whole search would end
 // with.  It holds for the computed errors as well: below, a clipped element's code is 0, its restored value
 // the candidate's bound itself, and the difference is rounded here as there; above, the restored value scale * qmax + lo
 // lies within seven half-spacings of the row's largest magnitude of the candidate's bound, and `slack` is twice
 // that and more.  The sums here are in fp32, of differences in units of a power of two near the row's range; 2^-16
 // covers their rounding.  (All this for scales that are normal numbers: the sequence without divisions.)
-// 1.5 M rows of 64 at 100 bins and 4 bits stop after 21 of 99 iterations (with every element's clipping error: 21 too,
-// the row's two ends alone: 21), at 2 bits and 25 bins after 18 of 24 (17; 22): 2.69 -> 0.66 ms and 0.73 -> 0.58.  Rows of 8
-// to 512 elements at 4 bits and 45 bins 1.4 to 6 times as fast, at 8 bits 4 to 5 times.  At 2 bits it depends on the rows: whole
-// searches of 1024 elements 1.6 times as fast on evenly spread values, 1.3 on normal ones, and up to 8 % slower where outliers
-// let the search go on to nine tenths of its iterations (25 bins: 1 K rows of 1024 23.5 -> 25.2 us, of 320 15.8 -> 16.7; 10 K and more
-// within 3 %).  Searches that stop by themselves about where rows would be finished lose up to as much (1 K rows of 320 at 4 bits,
-// 45 bins, ratio 0.4, 13.1 -> 14.7 us; 60 K 176 -> 184).
+// 1.5 M rows of 64 at 100 bins and 4 bits stop after 20 of 99 iterations (with every element's clipping error: 20 too,
+// the row's two ends alone: 20), at 2 bits and 25 bins after 17 of 24, at 8 bits before the first: 2.69 -> 0.63 ms and 0.73 -> 0.56.  Asked about the
+// current range instead of the next two, every search took one iteration more: 1.5 M rows of 64 at 3 bits and 25 bins 377 -> 352 us now,
+// 4 bits and 45 bins 358 -> 333, 100 bins 653 -> 630, 1.2 M rows of 16 58 -> 47, 8 bits 32 -> 27 (0.3 M rows of 64 29 -> 24).  Rows of 8
+// to 512 elements at 4 bits and 45 bins 1.4 to 6 times as fast as without an end, at 8 bits 4 to 5 times.  At 2 bits it depends on the rows: whole
+// searches of 1024 elements 1.6 times as fast on evenly spread values, 1.3 on normal ones, and a few per cent slower where outliers
+// let the search go on to nine tenths of its iterations (25 bins: 1 K rows of 1024 23.5 -> 24.9 us, of 320 15.8 -> 16.0; 10 K and more
+// within 3 %).  Searches that stop by themselves about where rows would be finished lose up to 7 % (1 K rows of 140 at 2 bits,
+// 25 bins, ratio 0.6, 13.7; 13.0 with the question about the current range).
 template <int N>
 struct ClipBound {
     float mn[N], mx[N];
@@ -584,9 +587,9 @@ struct ClipBound {
             mx[g] *= unit;
         }
     }
-    // Whether a row of L lanes whose current bounds are [lo, hi] is finished.  All lanes have to call it.
+    // Whether what a row of L lanes is clipped by at [lo, hi] comes to its best error.  All lanes have to call it.
     template <int L>
-    __device__ __forceinline__ bool done(float lo, float hi, double best) const {
+    __device__ __forceinline__ bool reached(float lo, float hi, double best) const {
         const float from = lo * unit, to = fmaf(hi, unit, slack);
         float e = 0.0f;
 #pragma unroll
@@ -599,7 +602,7 @@ struct ClipBound {
     }
 };
 // Whether it is worth asking: a candidate's error is well above the bound, since the elements within its range
-// have errors too.  (At 2 bits a search stops where its error is about 1.25 times the best, at 4 bits 1.8; an eighth
+// have errors too.  (At 2 bits a search stops where its error is about 1.2 times the best, at 4 bits 1.7; an eighth
 // of a binade more in the errors' upper halves is 1.06 to 1.125 times.)  ZERO: where the best may be 0, no later error can be
 // smaller, and the question is worth asking whatever the error.
 template <bool ZERO>
@@ -703,6 +706,15 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L =
             // with them, 655 now, 660 without any).  (ZERO instead of this mask: rows of 16 at 3 bits 131 -> 146 us.)
             const bool open = live & (best != 0.0);
             uint32_t n_iter = a.n_iter;
+            auto finished = [&]() -> bool {  // the wave: neither of the next two ranges can lead any row below its best
+                if (__builtin_amdgcn_ballot_w64(open & !clip.template reached<L>(cur_lo + step, cur_hi, best)) != 0) return false;
+                return __builtin_amdgcn_ballot_w64(open & !clip.template reached<L>(cur_lo, cur_hi - step, best)) == 0;
+            };
+            // At 8 bits a step is several code steps as a rule, and no iteration is needed.  (Asked at 2 to 4 bits too, where it takes 10 bins
+            // or fewer for that, 1.5 M rows of 64 at 100 bins took 650 us instead of 630.)
+            if constexpr (FAST && ENDS && BITS == 8) {
+                if (finished()) n_iter = 0;
+            }
             for (uint32_t it = 0; it < n_iter; ++it) {
                 const float c_lo = cur_lo + step;
                 const float c_hi = cur_hi - step;
@@ -718,8 +730,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L =
                 lo = found ? cur_lo : lo;
                 hi = found ? cur_hi : hi;
                 if constexpr (FAST && ENDS) {
-                    if (__builtin_amdgcn_ballot_w64(open & !may_be_done<false>(e, best)) == 0)
-                        if (__builtin_amdgcn_ballot_w64(open & !clip.template done<L>(cur_lo, cur_hi, best)) == 0) n_iter = it;
+                    if (__builtin_amdgcn_ballot_w64(open & !may_be_done<false>(e, best)) == 0 && finished()) n_iter = it;
                 }
             }
         };
@@ -945,8 +956,13 @@ struct RowUnits {
                 hi = found ? cur_hi : hi;
                 move = step;
                 if constexpr (FAST && ENDS) {
-                    if ((__builtin_amdgcn_ballot_w64(!may_be_done<true>(better, best)) & live_rows) == 0)
-                        if ((__builtin_amdgcn_ballot_w64(!clip.template done<L>(cur_lo, cur_hi, best)) & live_rows) == 0) last = c;
+                    if ((BITS == 8 && c == 0) || (__builtin_amdgcn_ballot_w64(!may_be_done<true>(better, best)) & live_rows) == 0) {
+                        // side by side, each group asks for the bound that it moves
+                        bool going = (__builtin_amdgcn_ballot_w64(!clip.template reached<L>(upper ? cur_lo : cur_lo + step, upper ? cur_hi - step : cur_hi, best)) & live_rows) != 0;
+                        if (!DUAL && !going)
+                            going = (__builtin_amdgcn_ballot_w64(!clip.template reached<L>(cur_lo, cur_hi - step, best)) & live_rows) != 0;
+                        if (!going) last = c;
+                    }
                 }
             }
         }

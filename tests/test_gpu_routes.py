@@ -340,6 +340,21 @@ def test_greedy_search_that_ends_early_finds_the_same_range(ctx, dim, bits, bins
     _poll(ctx)
 
 
+# At 8 bits the question is asked before the first iteration too: a step of many codes, of about one, of less than one, and a search of one step.
+@pytest.mark.parametrize("dim,n", [(16, 900), (24, 900), (64, 900), (64, 131_400), (96, 10_800), (256, 900), (320, 900), (1088, 300)])
+@pytest.mark.parametrize("bins,ratio", [(2, 1.0), (20, 0.05), (20, 1.0), (200, 1.0), (400, 0.2)])
+def test_greedy_search_at_8_bits_that_ends_before_it_starts(ctx, dim, n, bins, ratio):
+    some = min(n, 900)
+    rows = _early_end_rows(some, dim, bins, dim + bins)
+    ora = O.quantize_rows(rows, None, 8, mode=O.RANGE_GREEDY, num_bins=bins, ratio=ratio, n_threads=8)
+    gt = GpuTable(ctx, torch.from_numpy(rows).to(DEV).repeat(n // some, 1))
+    got = gpu_encode_all_outputs(gt, 8, mode=P.CNR_RANGE_GREEDY, greedy=(bins, ratio), row_ids=None, n=n)
+    keys = ("scale", "bias", "row_min", "row_max", "codes")
+    for at in {0, n - some}:
+        compare_greedy(rows, {k: got[k][at:at + some] for k in keys}, ora, 8, bins, ratio, what="8 bits d%d n%d bins%d" % (dim, n, bins))
+    _poll(ctx)
+
+
 # Partial searches up to 0.52, 0.32 and 0.18 of their moves (2, 3, 4 bits) go through kernels that do not ask whether a row is finished
 @pytest.mark.parametrize("dim,bits,long", [(36, 2, 25_000), (40, 3, 25_000), (64, 2, 131_072), (64, 4, 131_072), (96, 4, 26_624), (128, 3, 65_536), (200, 3, 64_000),
                                            (256, 2, 32_768), (280, 4, 0), (320, 4, 6_400), (1088, 2, 0), (32, 4, 262_144), (8, 3, 49_152)])
