@@ -45,6 +45,24 @@ struct cnr_search_params {
     float num_bins_f;
 };
 constexpr uint32_t kSearchBatch = 32;  // points per launch
+// Lanes that a sampled row gets where n rows are searched n_searches times side by side.
+// Two groups of lanes per row while the searches together leave room on the chip; four lanes
+// beyond that.  Measured break-evens with five and three searches: 100 K rows of 16, 20 K rows of 64, 30 K of
+// 128, 60 K of 256.  Rows of 144 to 284 elements have two groups of sixteen lanes while
+// the searches leave half the chip's lanes free even so: the whole call at 3 bits, 256 rows of 144 79 -> 69 us, of 256 99 -> 78, 1 K rows
+// 80 -> 73 and 102 -> 84; 2.5 K rows 91 against 95 and 120 against 113, 4 K level or 5 % slower.  (Rows of up to 140 lose with more lanes.)
+static inline uint32_t cnr_sample_lanes(uint32_t dim, uint64_t n, uint32_t n_searches) {
+    const uint32_t n4 = dim / 4;
+    if (n4 < 68 && n * n_searches >= 131072) return 4;
+    if (n4 >= 36 && n4 < 72 && n * n_searches <= 8192) return 32;
+    return n4 <= 8 ? 8 : n4 < 72 ? 16 : 64;
+}
+// Waves that search n sampled rows, in whole workgroups; each leaves a sum for every point.
+static inline uint64_t cnr_sample_waves(uint32_t lanes, uint64_t n) {
+    const uint64_t per_workgroup = (uint64_t)(kWave / lanes) * kWavesPerBlock;
+    const uint64_t workgroups = (n + per_workgroup - 1) / per_workgroup;
+    return (workgroups < 4096 ? workgroups : 4096) * kWavesPerBlock;
+}
 // Index of the last error that a lane evaluates in a search of n_iter iterations: 0 is the un-shrunk range's,
 // then come an iteration's two in turn, or one of them where two groups of lanes go side by side.  64 bits
 // where n_iter may be any number; searches of up to 2^20 bins, the ones that do not divide, count in 32.
@@ -53,10 +71,11 @@ constexpr Count last_candidate(uint32_t n_iter, bool side_by_side) {
     return side_by_side ? (Count)n_iter : 2 * (Count)n_iter;
 }
 constexpr float kFastSearchBins = 0x1p20f;
-// mean_out[p] (device-accessible) = mean l2 error of rows row_ids[0 .. n) quantized with params[p].
-// sums: device, max_sums >= 1 doubles.  Arguments are checked by the caller.
+// mean_out[p] (device-accessible) = mean l2 error of rows row_ids[0 .. n) quantized with points[p].  Points that follow each other
+// with the same num_bins and no fewer iterations share a search.
+// sums: device, max_sums >= 4 doubles.  Arguments are checked by the caller.
 cnr_status cnr_sample_errors(cnr_ctx *ctx, const float *table, uint64_t n_rows, uint32_t dim, const uint32_t *row_ids,
-                             uint64_t n, int bits, const cnr_search_params *params, uint32_t n_params, double *sums,
+                             uint64_t n, int bits, const cnr_search_params *points, uint32_t n_points, double *sums,
                              uint64_t max_sums, double *mean_out, hipStream_t s);
 // Status of the launch that was just enqueued.
 static inline cnr_status cnr_launch_status(cnr_ctx *ctx) { return cnr_hip_status(ctx, hipGetLastError()); }

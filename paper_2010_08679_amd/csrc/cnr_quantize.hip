@@ -922,51 +922,72 @@ struct RowUnits {
     // rows that are not live do not keep it going.  ENDS: it ends early where it can.
     template <int BITS, bool FAST, bool ENDS>
     __device__ __forceinline__ void search(uint32_t n_iter, float num_bins_f, double less, bool live, float &lo, float &hi) {
-        float cur_lo = lo, cur_hi = hi;
-        const float step = (hi - lo) / num_bins_f;
-        if constexpr (FAST && ENDS) clip.rescale(lo, hi);
-        const uint64_t live_rows = __builtin_amdgcn_ballot_w64(live);
-        const bool upper = DUAL && (tid_x() / L) & 1;  // this lane's group lowers the upper bound
+        Search<BITS, FAST, ENDS> s(*this, num_bins_f, less, live, lo, hi);
+        s.run(n_iter, lo, hi);
+    }
+    // A search in steps: run(n, ...) takes it on to the end of iteration n, where [lo, hi] is what a search of n iterations
+    // ends with.
+    template <int BITS, bool FAST, bool ENDS>
+    struct Search {
+        using Count = std::conditional_t<FAST, uint32_t, uint64_t>;
+        RowUnits &row;
+        const float step;
+        const double less;
+        const uint64_t live_rows;
+        const bool upper;  // this lane's group lowers the upper bound
+        float cur_lo, cur_hi;
         // The first candidate is an iteration whose step is zero.
         float move = 0.0f;
         double best = __builtin_huge_val(), e_lo = best;
-        using Count = std::conditional_t<FAST, uint32_t, uint64_t>;
-        Count last = last_candidate<Count>(n_iter, DUAL);
-        for (Count c = 0; c <= last; ++c) {
-            const bool raise = DUAL ? !upper : (c & 1);  // uniform, but for DUAL
-            const float c_lo = raise ? cur_lo + move : cur_lo;
-            const float c_hi = raise ? cur_hi : cur_hi - move;
-            const double limit = best * less;
-            double e = sq_err<BITS, FAST>(c_lo, c_hi);
-            if (!DUAL && raise) {
-                e_lo = e;
-            } else {
-                if constexpr (DUAL) {
-                    const double o = other_group<L>(e);
-                    e_lo = upper ? o : e;
-                    e = upper ? e : o;
-                }
-                const bool move_lo = e_lo < e * less;
-                cur_hi = move_lo ? cur_hi : cur_hi - move;
-                cur_lo = move_lo ? cur_lo + move : cur_lo;
-                const double better = move_lo ? e_lo : e;
-                const bool found = better < limit;
-                best = found ? better : best;
-                lo = found ? cur_lo : lo;
-                hi = found ? cur_hi : hi;
-                move = step;
-                if constexpr (FAST && ENDS) {
-                    if ((BITS == 8 && c == 0) || (__builtin_amdgcn_ballot_w64(!may_be_done<true>(better, best)) & live_rows) == 0) {
-                        // side by side, each group asks for the bound that it moves
-                        bool going = (__builtin_amdgcn_ballot_w64(!clip.template reached<L>(upper ? cur_lo : cur_lo + step, upper ? cur_hi - step : cur_hi, best)) & live_rows) != 0;
-                        if (!DUAL && !going)
-                            going = (__builtin_amdgcn_ballot_w64(!clip.template reached<L>(cur_lo, cur_hi - step, best)) & live_rows) != 0;
-                        if (!going) last = c;
+        Count c = 0;
+        bool over = false;  // the wave's rows are finished: more iterations change nothing
+
+        __device__ __forceinline__ Search(RowUnits &row_, float num_bins_f, double less_, bool live, float lo, float hi)
+            : row(row_), step((hi - lo) / num_bins_f), less(less_), live_rows(__builtin_amdgcn_ballot_w64(live)), upper(DUAL && (tid_x() / L) & 1),
+              cur_lo(lo), cur_hi(hi) {
+            if constexpr (FAST && ENDS) row.clip.rescale(lo, hi);
+        }
+        __device__ __forceinline__ void run(uint32_t n_iter, float &lo, float &hi) {
+            Count last = last_candidate<Count>(n_iter, DUAL);
+            for (; c <= last; ++c) {
+                const bool raise = DUAL ? !upper : (c & 1);  // uniform, but for DUAL
+                const float c_lo = raise ? cur_lo + move : cur_lo;
+                const float c_hi = raise ? cur_hi : cur_hi - move;
+                const double limit = best * less;
+                double e = row.template sq_err<BITS, FAST>(c_lo, c_hi);
+                if (!DUAL && raise) {
+                    e_lo = e;
+                } else {
+                    if constexpr (DUAL) {
+                        const double o = other_group<L>(e);
+                        e_lo = upper ? o : e;
+                        e = upper ? e : o;
+                    }
+                    const bool move_lo = e_lo < e * less;
+                    cur_hi = move_lo ? cur_hi : cur_hi - move;
+                    cur_lo = move_lo ? cur_lo + move : cur_lo;
+                    const double better = move_lo ? e_lo : e;
+                    const bool found = better < limit;
+                    best = found ? better : best;
+                    lo = found ? cur_lo : lo;
+                    hi = found ? cur_hi : hi;
+                    move = step;
+                    if constexpr (FAST && ENDS) {
+                        if ((BITS == 8 && c == 0) || (__builtin_amdgcn_ballot_w64(!may_be_done<true>(better, best)) & live_rows) == 0) {
+                            // side by side, each group asks for the bound that it moves
+                            bool going = (__builtin_amdgcn_ballot_w64(!row.clip.template reached<L>(upper ? cur_lo : cur_lo + step, upper ? cur_hi - step : cur_hi, best)) & live_rows) != 0;
+                            if (!DUAL && !going)
+                                going = (__builtin_amdgcn_ballot_w64(!row.clip.template reached<L>(cur_lo, cur_hi - step, best)) & live_rows) != 0;
+                            if (!going) {
+                                last = c;
+                                over = true;
+                            }
+                        }
                     }
                 }
             }
         }
-    }
+    };
 };
 
 template <int L, int UMAX, bool DUAL, int BITS, bool ENDS>
@@ -1048,11 +1069,13 @@ quantize_greedy_units_kernel(const QuantArgs a, double less /* tie_factor(dim) *
 // ---------------------------------------------------------------------------------------------
 // Mean l2 error of a sample under several greedy parameters at once (parameter selection): the search of
 // the kernel above, the restored row's error in place of its codes, nothing stored but one sum per
-// workgroup.  Grid y = parameters, so that all of them run side by side: a sample of a few thousand rows
-// leaves the chip mostly idle, and the launch takes as long as its longest search.  One launch per set of
-// parameters with the codes stored, read back and compared (encode, error, mean and a synchronization
-// each) took 354 us for 2.5 K rows of 64 and eight sets, this 111 us; searches that end early and a grid size that is an
-// argument (36 -> 26 and 24 -> 16 us for the two launches): 68 us.
+// wave and point.  Grid y = searches, side by side: a sample of a few thousand rows
+// leaves the chip mostly idle, and the launch takes as long as its longest search.  What a search of fewer iterations ends with
+// is what a longer one has found by then, so one search serves every point that differs in its ratio alone: it stops at
+// each of them and works out the errors, unless no row of the wave has found a better range since the last one.
+// One launch per set of parameters with the codes stored, read back and compared (encode, error, mean and a synchronization
+// each) took 354 us for 2.5 K rows of 64 and eight points; all values of num_bins in one launch and all ratios in another,
+// a search each, 64 us, this 43.
 // ---------------------------------------------------------------------------------------------
 struct SelectArgs {
     const float *table;
@@ -1061,10 +1084,11 @@ struct SelectArgs {
     const uint32_t *row_ids;
     uint64_t n;
     double less;   // tie_factor(dim)
-    double *sums;  // [parameters][workgroups along x]
-    uint32_t grid;  // workgroups along x
+    double *sums;  // [points][n_waves]
+    uint32_t n_waves;  // four per workgroup along x
     cnr_dev_errors *err;
-    cnr_search_params params[kSearchBatch];
+    cnr_search_params points[kSearchBatch];
+    uint8_t first[kSearchBatch + 1];  // search y has the points first[y] .. first[y + 1) - 1, in ascending order of iterations
 };
 template <int L, int UMAX, bool DUAL, int BITS>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(UMAX > 8 ? 3 : 4, 8)))
@@ -1072,14 +1096,18 @@ sample_error_kernel(const SelectArgs a) {
     using Row = RowUnits<L, UMAX, DUAL>;
     constexpr int kRowsPerPass = kWave / Row::LANES;
     constexpr float QMAXF = (float)((1 << BITS) - 1);
-    __shared__ double wave_sum[kWavesPerBlock];
-    const uint32_t n_iter = a.params[wg_y()].n_iter;
-    const float num_bins_f = a.params[wg_y()].num_bins_f;
+    const uint32_t p0 = a.first[wg_y()], p1 = a.first[wg_y() + 1];
+    const float num_bins_f = a.points[p0].num_bins_f;
     const uint32_t n4 = a.dim / 4;
     const int lane = tid_x() & (kWave - 1);
     const uint32_t j = lane % L;
-    const uint32_t n_waves = a.grid * kWavesPerBlock;
-    double sum = 0.0;
+    const uint32_t n_waves = a.n_waves;
+    double *const sums = a.sums + wave_in_grid();
+    if ((uint64_t)wave_in_grid() * kRowsPerPass >= a.n) {  // a workgroup's waves beyond the last row
+        for (uint32_t p = p0 + lane; p < p1; p += kWave) sums[(uint64_t)p * n_waves] = 0.0;
+        return;
+    }
+    bool add_up = false;  // not the first pass
     for (uint64_t pass = wave_in_grid(); pass * kRowsPerPass < a.n; pass += n_waves) {
         const uint64_t k = pass * kRowsPerPass + lane / Row::LANES;
         uint64_t rid = 0;
@@ -1096,40 +1124,43 @@ sample_error_kernel(const SelectArgs a) {
         row.load(reinterpret_cast<const float4 *>(a.table + rid * (uint64_t)a.dim), n4, j);
         float lo, hi;
         row.range(lo, hi);
-        if (n_iter) {
-            if (search_divides(lo, hi, num_bins_f, QMAXF))
-                row.template search<BITS, false, true>(n_iter, num_bins_f, a.less, live, lo, hi);
-            else
-                row.template search<BITS, true, true>(n_iter, num_bins_f, a.less, live, lo, hi);
-        }
-        const float scale = (hi - lo) / QMAXF;
-        double e = 0.0;
-        auto add = [&](const float4 &v) {
-            const float x[4] = {v.x, v.y, v.z, v.w};
+        auto points = [&](auto fast_tag) {
+            typename Row::template Search<BITS, decltype(fast_tag)::value, true> search(row, num_bins_f, a.less, live, lo, hi);
+            double sum = 0.0;
+            for (uint32_t p = p0; p < p1; ++p) {
+                const float lo_before = lo, hi_before = hi;
+                const uint32_t n_iter = a.points[p].n_iter;
+                if (n_iter && !search.over) search.run(n_iter, lo, hi);
+                if (p == p0 || __builtin_amdgcn_ballot_w64(lo != lo_before || hi != hi_before) != 0) {
+                    const float scale = (hi - lo) / QMAXF;
+                    double e = 0.0;
+                    auto add = [&](const float4 &v) {
+                        const float x[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const double d = (double)x[i] - (double)fq_value(fq_code_f(x[i], lo, hi, scale, QMAXF), scale, lo);
-                e = fma(d, d, e);
+                        for (int i = 0; i < 4; ++i) {
+                            const double d = (double)x[i] - (double)fq_value(fq_code_f(x[i], lo, hi, scale, QMAXF), scale, lo);
+                            e = fma(d, d, e);
+                        }
+                    };
+#pragma unroll
+                    for (int t = 0; t < UMAX; ++t)
+                        if ((uint32_t)t < 2 * row.pairs) add(row.x[t]);
+                    if (row.has_odd) add(row.odd);
+                    if (row.has_tail && row.in_tail) add(row.tail);
+                    e = lanes_sum<L>(e);
+                    sum = live && lane % Row::LANES == 0 ? sqrt(e) : 0.0;
+                    for (int off = 32; off >= Row::LANES; off >>= 1) sum += __shfl_xor(sum, off);
+                }
+                double *const out = sums + (uint64_t)p * n_waves;
+                if (lane == 0) *out = add_up ? *out + sum : sum;
             }
         };
-#pragma unroll
-        for (int t = 0; t < UMAX; ++t)
-            if ((uint32_t)t < 2 * row.pairs) add(row.x[t]);
-        if (row.has_odd) add(row.odd);
-        if (row.has_tail && row.in_tail) add(row.tail);
-        e = lanes_sum<L>(e);
-        if (live && lane % Row::LANES == 0) sum += sqrt(e);
-    }
-    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
-    if (lane == 0) wave_sum[tid_x() / kWave] = sum;
-    __syncthreads();
-    if (tid_x() == 0) {
-        double total = 0.0;
-        for (int w = 0; w < kWavesPerBlock; ++w) total += wave_sum[w];
-        a.sums[(uint64_t)wg_y() * a.grid + wg_x()] = total;
+        if (search_divides(lo, hi, num_bins_f, QMAXF)) points(std::false_type{});
+        else points(std::true_type{});
+        add_up = true;
     }
 }
-// mean_out[p] = (the sums of parameters p, added up in a fixed order) / n; one workgroup per p.
+// mean_out[p] = (the sums of point p, added up in a fixed order) / n; one workgroup per p.
 __global__ void __launch_bounds__(kBlock) sample_mean_kernel(const double *sums, uint32_t per_set, double n, double *mean_out) {
     __shared__ double part[kBlock];
     double acc = 0.0;
@@ -1653,53 +1684,50 @@ void launch_rows(cnr_ctx *ctx, QuantBatchArgs<> &b, uint32_t n, uint32_t dim, bo
     else launch_units_any<BITS>(b, n, dim, s);
 }
 
-// Two groups of lanes per row while the sets of parameters together leave room on the chip; four lanes
-// beyond that.  Measured break-evens with five and three sets: 100 K rows of 16, 20 K rows of 64, 30 K of
-// 128, 60 K of 256.  Rows of 144 to 284 elements have two groups of sixteen lanes while
-// the sets leave half the chip's lanes free even so: the whole call at 3 bits, 256 rows of 144 79 -> 69 us, of 256 99 -> 78, 1 K rows
-// 80 -> 73 and 102 -> 84; 2.5 K rows 91 against 95 and 120 against 113, 4 K level or 5 % slower.  (Rows of up to 140 lose with more lanes.)
 template <int BITS>
-cnr_status launch_sample_errors(cnr_ctx *ctx, SelectArgs &a, uint32_t n_sets, uint64_t max_sums, double *mean_out, hipStream_t s) {
+cnr_status launch_sample_errors(cnr_ctx *ctx, SelectArgs &a, uint32_t n_points, uint32_t n_searches, uint64_t max_sums, double *mean_out, hipStream_t s) {
     const uint32_t n4 = a.dim / 4;
-    const bool wide = n4 < 68 && a.n * n_sets >= 131072;
-    const bool spread = n4 >= 36 && n4 < 72 && a.n * n_sets <= 8192;
-    const uint32_t lanes = wide ? 4 : n4 <= 8 ? 8 : n4 < 72 && !spread ? 16 : spread ? 32 : 64;
-    const uint64_t rows_per_wg = (uint64_t)(kWave / lanes) * kWavesPerBlock;
-    uint64_t grid = (a.n + rows_per_wg - 1) / rows_per_wg;
-    if (grid > 4096) grid = 4096;
-    if (grid > max_sums / n_sets) grid = max_sums / n_sets;  // at least 1: the caller sees to it
-    a.grid = (uint32_t)grid;
-    const dim3 g((unsigned)grid, n_sets);
-    if (wide && n4 < 36) hipLaunchKernelGGL((sample_error_kernel<4, 8, false, BITS>), g, dim3(kBlock), 0, s, a);
-    else if (wide) hipLaunchKernelGGL((sample_error_kernel<4, 16, false, BITS>), g, dim3(kBlock), 0, s, a);
-    else if (spread) hipLaunchKernelGGL((sample_error_kernel<16, 4, true, BITS>), g, dim3(kBlock), 0, s, a);
-    else if (n4 <= 8) hipLaunchKernelGGL((sample_error_kernel<4, 2, true, BITS>), g, dim3(kBlock), 0, s, a);
-    else if (n4 < 72) hipLaunchKernelGGL((sample_error_kernel<8, 8, true, BITS>), g, dim3(kBlock), 0, s, a);
+    const uint32_t lanes = cnr_sample_lanes(a.dim, a.n, n_searches);
+    uint64_t waves = cnr_sample_waves(lanes, a.n);
+    if (waves > max_sums / n_points) waves = max_sums / n_points & ~3ull;  // at least 4: the caller sees to it
+    a.n_waves = (uint32_t)waves;
+    const dim3 g((unsigned)(waves / kWavesPerBlock), n_searches);
+    if (lanes == 4 && n4 < 36) hipLaunchKernelGGL((sample_error_kernel<4, 8, false, BITS>), g, dim3(kBlock), 0, s, a);
+    else if (lanes == 4) hipLaunchKernelGGL((sample_error_kernel<4, 16, false, BITS>), g, dim3(kBlock), 0, s, a);
+    else if (lanes == 8) hipLaunchKernelGGL((sample_error_kernel<4, 2, true, BITS>), g, dim3(kBlock), 0, s, a);
+    else if (lanes == 16) hipLaunchKernelGGL((sample_error_kernel<8, 8, true, BITS>), g, dim3(kBlock), 0, s, a);
+    else if (lanes == 32) hipLaunchKernelGGL((sample_error_kernel<16, 4, true, BITS>), g, dim3(kBlock), 0, s, a);
     else if (n4 < 288) hipLaunchKernelGGL((sample_error_kernel<32, 8, true, BITS>), g, dim3(kBlock), 0, s, a);
     else hipLaunchKernelGGL((sample_error_kernel<64, 16, false, BITS>), g, dim3(kBlock), 0, s, a);
     cnr_status st = cnr_launch_status(ctx);
     if (st != CNR_OK) return st;
-    hipLaunchKernelGGL(sample_mean_kernel, dim3(n_sets), dim3(kBlock), 0, s, a.sums, (uint32_t)grid, (double)a.n, mean_out);
+    hipLaunchKernelGGL(sample_mean_kernel, dim3(n_points), dim3(kBlock), 0, s, a.sums, (uint32_t)waves, (double)a.n, mean_out);
     return cnr_launch_status(ctx);
 }
 
 }  // namespace
 
 cnr_status cnr_sample_errors(cnr_ctx *ctx, const float *table, uint64_t n_rows, uint32_t dim, const uint32_t *row_ids,
-                             uint64_t n, int bits, const cnr_search_params *params, uint32_t n_params, double *sums,
+                             uint64_t n, int bits, const cnr_search_params *points, uint32_t n_points, double *sums,
                              uint64_t max_sums, double *mean_out, hipStream_t s) {
-    for (uint32_t done = 0; done < n_params;) {
-        uint32_t m = n_params - done;
+    for (uint32_t done = 0; done < n_points;) {
+        uint32_t m = n_points - done;
         if (m > kSearchBatch) m = kSearchBatch;
-        if (m > max_sums) m = (uint32_t)max_sums;  // >= 1
-        SelectArgs a = {table, n_rows, dim, row_ids, n, tie_factor(dim), sums, 0, ctx->dev_err, {}};
-        for (uint32_t i = 0; i < m; ++i) a.params[i] = params[done + i];
+        if (m > max_sums / kWavesPerBlock) m = (uint32_t)(max_sums / kWavesPerBlock);  // >= 1
+        SelectArgs a = {table, n_rows, dim, row_ids, n, tie_factor(dim), sums, 0, ctx->dev_err, {}, {}};
+        uint32_t n_searches = 0;
+        for (uint32_t i = 0; i < m; ++i) {
+            a.points[i] = points[done + i];
+            const bool goes_on = i && a.points[i].num_bins_f == a.points[i - 1].num_bins_f && a.points[i].n_iter >= a.points[i - 1].n_iter;
+            if (!goes_on) a.first[n_searches++] = (uint8_t)i;
+        }
+        a.first[n_searches] = (uint8_t)m;
         cnr_status st;
         switch (bits) {
-            case 2: st = launch_sample_errors<2>(ctx, a, m, max_sums, mean_out + done, s); break;
-            case 3: st = launch_sample_errors<3>(ctx, a, m, max_sums, mean_out + done, s); break;
-            case 4: st = launch_sample_errors<4>(ctx, a, m, max_sums, mean_out + done, s); break;
-            default: st = launch_sample_errors<8>(ctx, a, m, max_sums, mean_out + done, s); break;
+            case 2: st = launch_sample_errors<2>(ctx, a, m, n_searches, max_sums, mean_out + done, s); break;
+            case 3: st = launch_sample_errors<3>(ctx, a, m, n_searches, max_sums, mean_out + done, s); break;
+            case 4: st = launch_sample_errors<4>(ctx, a, m, n_searches, max_sums, mean_out + done, s); break;
+            default: st = launch_sample_errors<8>(ctx, a, m, n_searches, max_sums, mean_out + done, s); break;
         }
         if (st != CNR_OK) return st;
         done += m;
