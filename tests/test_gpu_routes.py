@@ -602,6 +602,33 @@ def test_batched_compaction_around_the_self_counting_limit(ctx, tables, tiles):
 
 # ---- bulk mark of one-slice tables: streams from 64 MB on are read past the caches -------------------------
 
+# Short streams: a workgroup's look-ups of one row agree on one of them (by the top twelve bits of row * 0x9E3779B1).  Repeats of few rows, of
+# rows that meet in one place there, and none, at the edges of a workgroup's 1024 look-ups and over several passes (2048 workgroups).
+@pytest.mark.parametrize("dtype", [torch.int64, torch.int32])
+@pytest.mark.parametrize("n_rows", [1, 33, 200_001, 2_200_000_000])
+@pytest.mark.parametrize("n_idx", [1, 255, 1_024, 1_025, 65_537, 2_097_153 + 1_030])
+def test_short_mark_with_repeats(ctx, dtype, n_rows, n_idx):
+    reach = min(n_rows, 2**31 - 1) if dtype is torch.int32 else n_rows
+    rng = np.random.default_rng(n_rows % 1000 + n_idx)
+    place = (np.arange(min(reach, 200_000), dtype=np.uint64) * 0x9E3779B1 % 2**32) >> 20
+    together = np.flatnonzero(place == place[-1])
+    few = np.concatenate([together[:40], rng.integers(0, reach, 9), [reach - 1]])
+    bitmap = torch.zeros(P.cnr_bitmap_words(n_rows), dtype=torch.int32, device=DEV)
+    for stream in (few[rng.integers(0, len(few), n_idx)], rng.integers(0, reach, n_idx)):
+        stream = stream.astype(np.int64)
+        out = rng.random(n_idx) < 0.01
+        stream[out] = rng.choice([-1, -2**31] + ([n_rows] if n_rows < 2**31 else [2**31 - 1]), int(out.sum()))
+        want = np.unique(stream[(stream >= 0) & (stream < n_rows)])
+        P.cnr_clear_bitmap(ctx, bitmap, n_rows)
+        P.cnr_mark_touched(ctx, bitmap, n_rows, torch.from_numpy(stream).to(DEV).to(dtype))
+        words = torch.nonzero(bitmap).reshape(-1)
+        bits = np.unpackbits(bitmap[words].cpu().numpy().view(np.uint8).reshape(-1, 4), axis=1, bitorder="little")
+        got = (words.cpu().numpy()[:, None] * 32 + np.arange(32))[bits == 1]
+        assert np.array_equal(got, want)
+        _, bad, _ = P.cnr_poll_errors(ctx)
+        assert bad == int(((stream < 0) | (stream >= n_rows)).sum())
+
+
 @pytest.mark.parametrize("dtype,n_idx", [(torch.int64, 1_048_576), (torch.int64, 1_048_577), (torch.int32, 2_097_151), (torch.int32, 2_097_160)])
 @pytest.mark.parametrize("n_rows", [1_310_720, 200_001])
 def test_bulk_mark_around_the_streaming_limit(ctx, dtype, n_idx, n_rows):
