@@ -6,6 +6,7 @@
 // entry points are batches of one.
 #include "cnr_common.h"
 
+#include <cmath>
 #include <type_traits>
 
 // Per-tile counts of cnr_compact_dirty_noalloc: a fixed array in the library's device image instead
@@ -211,8 +212,9 @@ __global__ void __launch_bounds__(kSeenThreads) mark_flags_kernel(const TrackBat
 // the stream) of the scratch buffer, partial bitmaps that fold_slabs_kernel ORs into the bitmap and
 // zeroes again.  Nothing is scattered to memory; the price is that the W = ceil(n_rows / kSliceRows)
 // workgroups of a team read the same part of the stream.  Workgroups are dealt to the eight XCDs in
-// turn along x and the number of parts is a multiple of eight, so x & 7 names both the part (mod 8)
-// and the XCD: a team shares its part of the stream through one L2 and memory is read once.
+// turn along x; where the number of parts is a multiple of eight, x & 7 names both the part (mod 8)
+// and the XCD: a team shares its part of the stream through one L2 and memory is read once.  (Two or four parts, for streams so
+// short that this does not matter, put a team on four or two XCDs.)
 // Where every table is one slice there is no team to share with, and STREAM reads with the non-temporal
 // hint: 8 tables of 1 M rows, 8.2 M look-ups each, from memory 167 -> 107 us, 1 M look-ups 49 -> 38 (with
 // teams of four it costs 20 %: 415 -> 502 us for 8 x 5 M rows, 20 M look-ups).
@@ -220,8 +222,8 @@ __global__ void __launch_bounds__(kSeenThreads) mark_flags_kernel(const TrackBat
 constexpr int kSliceThreads = 1024;
 constexpr uint32_t kSliceWords = 40960;
 constexpr uint64_t kSliceRows = 32ull * kSliceWords;
-constexpr uint32_t kStreamParts = 8;      // parts of a stream, at least
-constexpr uint32_t kStreamPartsMax = 32;  // and at most, where the scratch has room for that many slabs
+constexpr uint32_t kStreamParts = 8;      // parts of a stream that every scratch has room for (slabs)
+constexpr uint32_t kStreamPartsMax = 32;  // parts of a stream at most
 // The scratch of a table: one byte per row (eight slabs, or the flag bytes), and never less than 32
 // slabs of one whole slice, so that a table of one or two slices, whose 8 or 16 workgroups would
 // leave most of the chip idle, can be shared out over 32 or 16 parts of its stream instead.
@@ -597,51 +599,57 @@ cnr_status cnr_mark_touched_batch(cnr_ctx *ctx, const cnr_table_job *jobs, uint3
     hipStream_t s = as_stream(stream);
     for (uint32_t first = 0; first < n_jobs; first += CNR_MAX_BATCH) {
         // Three routes.  Short streams: atomic ORs on the bitmap (about 16 G atomics/s; the other two
-        // pay a pass over n_rows bytes).  Long streams: bitmap slices in LDS, or one flag byte per row
-        // and a fold.  The slices cost every workgroup of a table its part of the stream (an eighth or
-        // less, at the 60 GB/s a workgroup of that kernel gets through it), whatever the stream holds, and
-        // all tables of a call run side by side as long as their workgroups fit the chip; the flag bytes cost
-        // one scattered store per look-up that gets past the table of lately flagged rows (about 17 ps
-        // of the whole chip's time each, a third of the look-ups on the skewed streams that embedding
-        // look-ups are), one table after the other.  So one or two tables marked alone are faster
-        // through flag bytes (a 5 M-row table, 20 M Zipf look-ups: 67-121 against 250-445 us) and a
-        // batch of many tables through slices (8 x 5 M rows, 3 M look-ups each: 89 against 385 us); the
-        // call takes, for all its tables of up to kSliceTeamMax slices together, the route this
-        // estimate makes the cheaper one.  Larger tables always take the flag bytes.
+        // pay a pass over n_rows bytes or more).  Long streams: bitmap slices in LDS, or one flag byte per row
+        // and a fold; tables of more than kSliceTeamMax slices always take the flag bytes, the others of a call take
+        // together what these estimates (in us) make the cheapest:
+        //   slices   two launches, 0.5 for each MB of slabs that the workgroups write and the fold reads and zeroes, and the
+        //            longest part of a stream at 70 GB/s, once for every round the workgroups need on the chip.  Few parts
+        //            for short streams (8 tables of 1.3 M rows, 131 K look-ups each: 13 us in four parts, 30 in thirty-two), many for
+        //            long ones (4.2 M look-ups: 158 and 65, 61 in sixteen).
+        //   flags    two launches, 0.2 for each MB of flags, and 1 to 7 ps for a look-up: 17 ps for one that gets past the
+        //            table of lately flagged rows, more of them the larger the table is and the fewer compute units it gets
+        //            (Zipf(1.05): 2.3 ps with 100 K rows, 5.6 with 1.3 M, 7 with 5 M; Zipf(1.2): half of that; a stream without repeats 17).
+        // Measured over 1 to 16 tables of 60 K to 16 M rows and 70 K to 30 M look-ups each: Zipf(1.05) 2 % from the
+        // best of these on average, Zipf(1.2) 5 %, no repeats 12 %; parts that fill the chip, and slabs and launches taken as free, were 35, 45 and 30 %
+        // away.  (The worst against that, at most 400 K to 1 M look-ups into each of three or four tables of 4 to 8 M rows, which take the
+        // flags: 29 -> 37 us, without repeats 29 -> 56.)
         constexpr uint64_t kSliceTeamMax = 16;
-        constexpr double kSlicePsPerByte = 1e12 / 60e9;                  // a workgroup gets through its part of the stream at 60 GB/s
-        constexpr double kFlagPsPerLookup = 6.0;                         // 17 ps x about a third that become stores
-        uint64_t elig_teams = 0, elig_sum_idx = 0;
-        for (uint32_t i = first; i < n_jobs && i < first + CNR_MAX_BATCH; ++i) {
-            const cnr_table_job &j = jobs[i];
-            const uint64_t team = (j.n_rows + kSliceRows - 1) / kSliceRows;
-            if (j.n_indices == 0 || !(j.mark_scratch && j.n_rows && j.n_indices > j.n_rows / 256 + 65536) || team > kSliceTeamMax)
-                continue;
-            elig_teams += team;
-            elig_sum_idx += j.n_indices;
-        }
-        // Parts per stream: eight, or as many more (in eights, as far as a table's scratch has slabs) as
-        // it takes for the workgroups of the call to fill the chip.
-        uint32_t want_parts = kStreamParts;
-        if (elig_teams) {
-            const uint64_t fill = (((uint64_t)ctx->n_cu + elig_teams - 1) / elig_teams + 7u) & ~7ull;
-            want_parts = (uint32_t)(fill < kStreamParts ? kStreamParts : fill > kStreamPartsMax ? kStreamPartsMax : fill);
-        }
-        uint64_t elig_wgs = 0;
-        double elig_longest = 0;  // the longest part of a stream a workgroup reads, in look-ups
-        for (uint32_t i = first; i < n_jobs && i < first + CNR_MAX_BATCH; ++i) {
-            const cnr_table_job &j = jobs[i];
-            const uint64_t team = (j.n_rows + kSliceRows - 1) / kSliceRows;
-            if (j.n_indices == 0 || !(j.mark_scratch && j.n_rows && j.n_indices > j.n_rows / 256 + 65536) || team > kSliceTeamMax)
-                continue;
+        constexpr double kLaunchesUs = 7.0, kSlabUsPerByte = 0.495e-6, kStreamUsPerByte = 14e-6;
+        constexpr double kFlagLaunchesUs = 5.0, kFlagUsPerByte = 0.22e-6, kFlagUsPerLookup = 0.7e-6;
+        auto bulk_stream = [](const cnr_table_job &j) { return j.mark_scratch && j.n_rows && j.n_indices > j.n_rows / 256 + 65536; };
+        auto slices_of = [](const cnr_table_job &j) { return (j.n_rows + kSliceRows - 1) / kSliceRows; };
+        auto parts_of = [](const cnr_table_job &j, uint32_t want) {
             const uint32_t most = slice_parts_max(j.n_rows);
-            const uint32_t parts = want_parts < most ? want_parts : most;
-            elig_wgs += team * parts;
-            if ((double)j.n_indices / parts > elig_longest) elig_longest = (double)j.n_indices / parts;
+            return want < most ? want : most;
+        };
+        uint32_t tables = 0;
+        for (uint32_t i = first; i < n_jobs && i < first + CNR_MAX_BATCH; ++i) tables += bulk_stream(jobs[i]) && slices_of(jobs[i]) <= kSliceTeamMax;
+        double best_us = kFlagLaunchesUs;  // through flag bytes
+        for (uint32_t i = first; i < n_jobs && i < first + CNR_MAX_BATCH; ++i) {
+            const cnr_table_job &j = jobs[i];
+            if (!bulk_stream(j) || slices_of(j) > kSliceTeamMax) continue;
+            const double spread = std::log2((double)j.n_rows) + 0.32 * std::log2((double)tables) - 14.5;
+            best_us += kFlagUsPerByte * (double)j.n_rows + kFlagUsPerLookup * (spread > 1.0 ? spread : 1.0) * (double)j.n_indices;
         }
-        const uint64_t rounds = (elig_wgs + (uint64_t)ctx->n_cu - 1) / (uint64_t)ctx->n_cu;
-        const bool slices_pay = elig_longest * (type == CNR_IDX_I64 ? 8.0 : 4.0) * kSlicePsPerByte * (double)rounds <
-                                (double)elig_sum_idx * kFlagPsPerLookup;
+        uint32_t want_parts = 0;  // 0: flag bytes
+        for (uint32_t want = 2; tables && want <= kStreamPartsMax; want *= 2) {
+            uint64_t workgroups = 0, slab_bytes = 0, longest = 0;
+            for (uint32_t i = first; i < n_jobs && i < first + CNR_MAX_BATCH; ++i) {
+                const cnr_table_job &j = jobs[i];
+                if (!bulk_stream(j) || slices_of(j) > kSliceTeamMax) continue;
+                const uint32_t parts = parts_of(j, want);
+                workgroups += slices_of(j) * parts;
+                slab_bytes += cnr_bitmap_words(j.n_rows) * 4u * parts;
+                if (j.n_indices / parts > longest) longest = j.n_indices / parts;
+            }
+            const uint64_t rounds = (workgroups + (uint64_t)ctx->n_cu - 1) / (uint64_t)ctx->n_cu;
+            const double us = kLaunchesUs + kSlabUsPerByte * (double)slab_bytes +
+                              kStreamUsPerByte * (type == CNR_IDX_I64 ? 8.0 : 4.0) * (double)(longest * rounds);
+            if (us < best_us) {
+                best_us = us;
+                want_parts = want;
+            }
+        }
         TrackBatch slices = {}, bulk = {}, direct = {};
         uint32_t n_slices = 0, n_bulk = 0, n_direct = 0;
         bool slices_one = true;     // every table of the slices route is one slice
@@ -650,9 +658,9 @@ cnr_status cnr_mark_touched_batch(cnr_ctx *ctx, const cnr_table_job *jobs, uint3
         for (uint32_t i = first; i < n_jobs && i < first + CNR_MAX_BATCH; ++i) {
             const cnr_table_job &j = jobs[i];
             if (j.n_indices == 0) continue;
-            const bool long_stream = j.mark_scratch && j.n_rows && j.n_indices > j.n_rows / 256 + 65536;
-            const uint64_t team = (j.n_rows + kSliceRows - 1) / kSliceRows;
-            const bool use_slices = long_stream && team <= kSliceTeamMax && slices_pay;
+            const bool long_stream = bulk_stream(j);
+            const uint64_t team = slices_of(j);
+            const bool use_slices = long_stream && team <= kSliceTeamMax && want_parts != 0;
             TrackJob &t = use_slices ? slices.job[n_slices++] : long_stream ? bulk.job[n_bulk++] : direct.job[n_direct++];
             t.bitmap = j.bitmap;
             t.n_rows = j.n_rows;
@@ -661,8 +669,7 @@ cnr_status cnr_mark_touched_batch(cnr_ctx *ctx, const cnr_table_job *jobs, uint3
             t.flags = (uint8_t *)j.mark_scratch;
             const uint64_t words = cnr_bitmap_words(j.n_rows);
             if (use_slices) {
-                const uint32_t most = slice_parts_max(j.n_rows);
-                t.parts = want_parts < most ? want_parts : most;
+                t.parts = parts_of(j, want_parts);
                 if (team * t.parts > slices_team) slices_team = team * t.parts;
                 if (team > 1) slices_one = false;
                 slices_bytes += j.n_indices * (type == CNR_IDX_I64 ? 8u : 4u);

@@ -602,6 +602,39 @@ def test_batched_compaction_around_the_self_counting_limit(ctx, tables, tiles):
 
 # ---- bulk mark of one-slice tables: streams from 64 MB on are read past the caches -------------------------
 
+# Long streams of a batch: slices in two to thirty-two parts of the streams, or flag bytes, by what the call's tables come to; tables of one and several
+# slices, of different sizes, some of whose scratch has room for eight parts only.
+@pytest.mark.parametrize("dtype", [torch.int64, torch.int32])
+@pytest.mark.parametrize("tables,n_rows,n_idx", [(16, 1_310_720, 70_661), (16, 5_000_003, 85_100), (8, 1_310_721, 131_073), (8, 400_001, 524_289), (8, 1_000_003, 1_500_000),
+                                                 (4, 1_310_719, 3_000_001), (2, 4_000_000, 2_000_001), (1, 1_310_720, 9_000_001), (1, 777_777, 70_001), (3, 200_033, 150_000)])
+def test_bulk_mark_of_a_batch_in_parts(ctx, dtype, tables, n_rows, n_idx):
+    rng = np.random.default_rng(tables + n_idx)
+    g = torch.Generator(device=DEV).manual_seed(n_idx)
+    rows = [n_rows if i % 3 == 0 else max(66, n_rows // (i % 5 + 1) - i) for i in range(tables)]
+    scratch = [P.TableCheckpointer.new_mark_scratch(n, DEV) for n in rows]
+    cks = [P.TableCheckpointer(ctx, n, 64, device=DEV, mark_scratch=m) for n, m in zip(rows, scratch)]
+    batch = P.BatchCheckpointer(ctx, cks)
+    batch.clear()
+    want, skipped = [torch.zeros(n + 64, dtype=torch.bool, device=DEV) for n in rows], 0
+    for call in range(2):
+        streams = []
+        for t, n in enumerate(rows):
+            u = torch.rand(n_idx + int(rng.integers(0, 9)), generator=g, device=DEV, dtype=torch.float64)
+            idx = ((u ** 3 * (n + 3)).long() - 1)[int(rng.integers(0, 3)):]   # skewed; -1, n and n + 1 are outside
+            idx[-1], idx[0] = n - 1, 0
+            good = (idx >= 0) & (idx < n)
+            want[t][idx[good]] = True
+            skipped += int((~good).sum())
+            streams.append(idx.to(dtype))
+        batch.mark(streams)
+    for t, n in enumerate(rows):
+        bits = ((cks[t].bitmap[:, None] >> torch.arange(32, device=DEV, dtype=torch.int32)) & 1).reshape(-1)[:n]
+        assert torch.equal(bits.bool(), want[t][:n]), (t, n)
+        assert not scratch[t].any()
+    _, bad, _ = P.cnr_poll_errors(ctx)
+    assert bad == skipped
+
+
 # Short streams: a workgroup's look-ups of one row agree on one of them (by the top twelve bits of row * 0x9E3779B1).  Repeats of few rows, of
 # rows that meet in one place there, and none, at the edges of a workgroup's 1024 look-ups and over several passes (2048 workgroups).
 @pytest.mark.parametrize("dtype", [torch.int64, torch.int32])
