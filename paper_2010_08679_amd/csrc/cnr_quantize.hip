@@ -635,18 +635,16 @@ __device__ __forceinline__ void store_unit_codes(uint8_t *out, uint32_t u, uint3
     }
 }
 
+// Rows of the n of a list that the waves of a grid of n_waves search.
 template <int L, int BITS, int G, bool ENDS>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L == 1 && G == 4 ? 3 : G == 4 ? 4 : 5, 8))) quantize_greedy_kernel(const QuantArgs a, double less /* tie_factor(dim) */, uint64_t n_from, uint64_t n_below) {
+__device__ __forceinline__ void search_rows(const QuantArgs &a, double less /* tie_factor(dim) */, uint64_t n, uint32_t n_waves) {
     constexpr int EPL = 16 * G;  // elements per lane
     constexpr int DIM = EPL * L;
     constexpr int kRowsPerPass = kWave / L;
     constexpr float QMAXF = (float)((1 << BITS) - 1);
     constexpr uint64_t P = (uint64_t)DIM * BITS / 8;  // packed bytes per row
-    const uint64_t n = row_count(a);
-    if (n < n_from || n >= n_below) return;  // this list length is the other launch's (uniform over the grid)
     const int lane = tid_x() & (kWave - 1);
     const int j = lane % L;  // lane within the row
-    const uint32_t n_waves = a.n_waves;
     for (uint64_t pass = wave_in_grid(); pass * kRowsPerPass < n; pass += n_waves) {
         const uint64_t k = pass * kRowsPerPass + lane / L;
         // ---- gather
@@ -818,6 +816,22 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L =
     }
 }
 
+template <int L, int BITS, int G, bool ENDS>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L == 1 && G == 4 ? 3 : G == 4 ? 4 : 5, 8))) quantize_greedy_kernel(const QuantArgs a, double less) {
+    search_rows<L, BITS, G, ENDS>(a, less, row_count(a), a.n_waves);
+}
+// Lists whose length only the device knows, in buffers that may hold long ones: fewer than `line` rows go as L_NARROW lanes of sixteen elements
+// each, more as L_WIDE of 16 * G_WIDE.  Two launches, of which one found that the list was the other's, were 2 to 5 us more (500 rows of 64 at 45 bins
+// and 4 bits in a capacity of 655 K 11.7 -> 9.0 us, 52 K 23.5 -> 21.0, 131 K rows of 256 208 -> 196).  Together the forms have the registers of the
+// wide one, which costs lists below the line a wave per SIMD and no time that shows.
+template <int L_NARROW, int L_WIDE, int G_WIDE, int BITS, bool ENDS>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L_WIDE == 1 && G_WIDE == 4 ? 3 : 4, 8)))
+quantize_greedy_pair_kernel(const QuantArgs a, double less, uint64_t line, uint32_t narrow_waves) {
+    const uint64_t n = row_count(a);
+    if (n >= line) search_rows<L_WIDE, BITS, G_WIDE, ENDS>(a, less, n, a.n_waves);
+    else if (wave_in_grid() < narrow_waves) search_rows<L_NARROW, BITS, 1, ENDS>(a, less, n, narrow_waves);
+}
+
 // ---------------------------------------------------------------------------------------------
 // Greedy search at any other dim (dim % 4 == 0, dim * bits % 8 == 0): L lanes per row, lane j holds the
 // row's 16-byte units j, j + L, ... in registers, up to UMAX of them that every lane has plus the last,
@@ -832,7 +846,8 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(L =
 // lanes hold the row, one evaluates the raised lower bound and the other the lowered upper one.  (A wave
 // per row that re-read the row from cache and divided for every element: 100 K rows of 96 at 49
 // candidates 874 us, this 106 us.)  The waves that waves_per_eu asks for cost spilled registers: in the 16-unit forms 2 at
-// 2 bits and 30 at 3 and 4, in some 8-unit forms 4 to 8, and where a search may end early 10 to 12 and 6 to 8 more for the ends it keeps.
+// 2 bits and 30 at 3 and 4, in some 8-unit forms 4 to 8, where a search may end early 10 to 12 and 6 to 8 more for the ends it keeps, and 2 to 26 in the
+// kernels of both forms.
 // All of them are stored and reloaded outside the loop over the candidates, once per pass.
 // ---------------------------------------------------------------------------------------------
 // What the same lane of the row's other group of L lanes holds.  (The mirrors reverse the lanes, which is
@@ -991,18 +1006,14 @@ struct RowUnits {
 };
 
 template <int L, int UMAX, bool DUAL, int BITS, bool ENDS>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(UMAX > 8 ? 3 : 4, 8)))
-quantize_greedy_units_kernel(const QuantArgs a, double less /* tie_factor(dim) */, uint64_t n_from, uint64_t n_below) {
+__device__ __forceinline__ void search_unit_rows(const QuantArgs &a, double less /* tie_factor(dim) */, uint64_t n, uint32_t n_waves) {
     using Row = RowUnits<L, UMAX, DUAL>;
     constexpr int kRowsPerPass = kWave / Row::LANES;
     constexpr float QMAXF = (float)((1 << BITS) - 1);
-    const uint64_t n = row_count(a);
-    if (n < n_from || n >= n_below) return;  // this list length is the other launch's (uniform over the grid)
     const uint32_t dim = a.dim, n4 = dim / 4;
     const uint64_t P = (uint64_t)dim * BITS / 8;
     const int lane = tid_x() & (kWave - 1);
     const uint32_t j = lane % L;
-    const uint32_t n_waves = a.n_waves;
     for (uint64_t pass = wave_in_grid(); pass * kRowsPerPass < n; pass += n_waves) {
         const uint64_t k = pass * kRowsPerPass + lane / Row::LANES;
         uint64_t rid = 0;
@@ -1064,6 +1075,25 @@ quantize_greedy_units_kernel(const QuantArgs a, double less /* tie_factor(dim) *
         if (row.has_odd) emit(row.odd, j + L * (n_full - 1), true);
         if (row.has_tail) emit(row.tail, j + L * n_full, row.in_tail);
     }
+}
+
+// Lists of n_from to n_below - 1 rows; the others are another launch's.
+template <int L, int UMAX, bool DUAL, int BITS, bool ENDS>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(UMAX > 8 ? 3 : 4, 8)))
+quantize_greedy_units_kernel(const QuantArgs a, double less, uint64_t n_from, uint64_t n_below) {
+    const uint64_t n = row_count(a);
+    if (n >= n_from && n < n_below) search_unit_rows<L, UMAX, DUAL, BITS, ENDS>(a, less, n, a.n_waves);
+}
+// Both forms, as above (500 rows of 96 at 45 bins and 4 bits in a capacity of 133 K 11.9 -> 9.2 us, 25 K 27.6 -> 25.2, 106 K 58.8 -> 55.3).  Where the long form has
+// sixteen units its registers leave three waves per SIMD, and the short form, throughput-bound just below the line, loses more than a launch with
+// that (36 K rows of 144 48.7 against 52.9 us, 10 K of 640 71 and 77, 14 K of 1000 145 and 158; with the line anywhere from where it is to three quarters of
+// that): there the two stay apart.
+template <int L_NARROW, int U_NARROW, int L_WIDE, int U_WIDE, int BITS, bool ENDS>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(U_WIDE > 8 ? 3 : 4, 8)))
+quantize_greedy_units_pair_kernel(const QuantArgs a, double less, uint64_t line, uint32_t narrow_waves) {
+    const uint64_t n = row_count(a);
+    if (n >= line) search_unit_rows<L_WIDE, U_WIDE, false, BITS, ENDS>(a, less, n, a.n_waves);
+    else if (wave_in_grid() < narrow_waves) search_unit_rows<L_NARROW, U_NARROW, true, BITS, ENDS>(a, less, n, narrow_waves);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1482,21 +1512,33 @@ constexpr float kEarliestEnd = BITS == 2 ? 0.52f : BITS == 3 ? 0.32f : BITS == 4
 template <int BITS>
 bool may_end_early(const QuantArgs &a) { return a.dim <= 32 || (float)a.n_iter > kEarliestEnd<BITS> * a.num_bins_f; }
 
-// Runs for lists of n_from <= n < n_below rows (n is the count on the device where there is one).
 template <int L, int BITS, int G>
-void launch_greedy(cnr_ctx *ctx, QuantArgs &a, hipStream_t s, uint64_t n_from, uint64_t n_below) {
+void launch_greedy(QuantArgs &a, hipStream_t s) {
     // the large grid here too: the search is bound by arithmetic, but workgroups handed out as others
     // finish even out the end of the launch (4 % on a 1.5 M-row list)
-    const uint64_t most = a.n_max < n_below ? a.n_max : n_below;
-    const unsigned grid = cnr_row_grid(most, (uint64_t)(kWave / L) * kWavesPerBlock);
+    const unsigned grid = cnr_row_grid(a.n_max, (uint64_t)(kWave / L) * kWavesPerBlock);
     a.n_waves = grid * kWavesPerBlock;
     if constexpr (BITS != 8 && 16 * G * L > 32) {
         if (!may_end_early<BITS>(a)) {
-            hipLaunchKernelGGL((quantize_greedy_kernel<L, BITS, G, false>), dim3(grid), dim3(kBlock), 0, s, a, tie_factor(a.dim), n_from, n_below);
+            hipLaunchKernelGGL((quantize_greedy_kernel<L, BITS, G, false>), dim3(grid), dim3(kBlock), 0, s, a, tie_factor(a.dim));
             return;
         }
     }
-    hipLaunchKernelGGL((quantize_greedy_kernel<L, BITS, G, true>), dim3(grid), dim3(kBlock), 0, s, a, tie_factor(a.dim), n_from, n_below);
+    hipLaunchKernelGGL((quantize_greedy_kernel<L, BITS, G, true>), dim3(grid), dim3(kBlock), 0, s, a, tie_factor(a.dim));
+}
+template <int L_NARROW, int L_WIDE, int G_WIDE, int BITS>
+void launch_greedy_pair(QuantArgs &a, hipStream_t s, uint64_t line) {
+    const unsigned wide = cnr_row_grid(a.n_max, (uint64_t)(kWave / L_WIDE) * kWavesPerBlock);
+    const unsigned narrow = cnr_row_grid(line, (uint64_t)(kWave / L_NARROW) * kWavesPerBlock);
+    const unsigned grid = wide > narrow ? wide : narrow;
+    a.n_waves = grid * kWavesPerBlock;
+    if constexpr (BITS != 8 && 16 * L_NARROW > 32) {
+        if (!may_end_early<BITS>(a)) {
+            hipLaunchKernelGGL((quantize_greedy_pair_kernel<L_NARROW, L_WIDE, G_WIDE, BITS, false>), dim3(grid), dim3(kBlock), 0, s, a, tie_factor(a.dim), line, narrow * kWavesPerBlock);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((quantize_greedy_pair_kernel<L_NARROW, L_WIDE, G_WIDE, BITS, true>), dim3(grid), dim3(kBlock), 0, s, a, tie_factor(a.dim), line, narrow * kWavesPerBlock);
 }
 // Long lists give every lane 64 elements (32 at dim 32); short ones keep 16 per lane, four times the
 // lanes per row and a quarter of the time per row, which is what counts while the list cannot fill
@@ -1505,15 +1547,13 @@ void launch_greedy(cnr_ctx *ctx, QuantArgs &a, hipStream_t s, uint64_t n_from, u
 // 68.5, 129 and 119; rows of 256 at 16 K, 33 K and 66 K 38.7 and 44.2, 71.0 and 66.5, 134 and 118; rows of 32 level from 4 M on).
 // At 8 bits it depends on the number of bins (100 bins: rows of 64 16.2 and 18.4 at 8 M, 26.9 and 29.9 at 16 M, level at 32 M;
 // rows of 256 22.3 and 21.3, 39.7 and 36.0; 20 bins: 15.0 and 16.0, level from 16 M on).  Where the
-// length is a count on the device and the capacity allows a long list, both kernels are launched
-// and the one whose range the count is not in returns at once.
+// length is a count on the device and the capacity allows a long list, the kernel has both forms.
 template <int L_NARROW, int L_WIDE, int G_WIDE, int BITS>
-void launch_greedy_by_length(cnr_ctx *ctx, QuantArgs &a, hipStream_t s) {
+void launch_greedy_by_length(QuantArgs &a, hipStream_t s) {
     const uint64_t wide_rows = (1ull << 23) / a.dim;
-    const bool may_be_wide = a.n_max >= wide_rows;
-    const bool may_be_narrow = !may_be_wide || a.n_dev != nullptr;
-    if (may_be_narrow) launch_greedy<L_NARROW, BITS, 1>(ctx, a, s, 0, may_be_wide ? wide_rows : ~0ull);
-    if (may_be_wide) launch_greedy<L_WIDE, BITS, G_WIDE>(ctx, a, s, may_be_narrow ? wide_rows : 0, ~0ull);
+    if (a.n_max < wide_rows) launch_greedy<L_NARROW, BITS, 1>(a, s);
+    else if (a.n_dev) launch_greedy_pair<L_NARROW, L_WIDE, G_WIDE, BITS>(a, s, wide_rows);
+    else launch_greedy<L_WIDE, BITS, G_WIDE>(a, s);
 }
 
 template <int L, int UMAX, bool DUAL, int BITS>
@@ -1528,6 +1568,20 @@ void launch_greedy_units_shape(QuantArgs &a, hipStream_t s, uint64_t n_from, uin
         }
     }
     hipLaunchKernelGGL((quantize_greedy_units_kernel<L, UMAX, DUAL, BITS, true>), dim3(grid), dim3(kBlock), 0, s, a, tie_factor(a.dim), n_from, n_below);
+}
+template <int L_NARROW, int U_NARROW, int L_WIDE, int U_WIDE, int BITS>
+void launch_greedy_units_pair(QuantArgs &a, hipStream_t s, uint64_t line) {
+    const unsigned wide = cnr_row_grid(a.n_max, (uint64_t)(kWave / RowUnits<L_WIDE, U_WIDE, false>::LANES) * kWavesPerBlock);
+    const unsigned narrow = cnr_row_grid(line, (uint64_t)(kWave / RowUnits<L_NARROW, U_NARROW, true>::LANES) * kWavesPerBlock);
+    const unsigned grid = wide > narrow ? wide : narrow;
+    a.n_waves = grid * kWavesPerBlock;
+    if constexpr (BITS != 8 && U_NARROW > 2) {
+        if (!may_end_early<BITS>(a)) {
+            hipLaunchKernelGGL((quantize_greedy_units_pair_kernel<L_NARROW, U_NARROW, L_WIDE, U_WIDE, BITS, false>), dim3(grid), dim3(kBlock), 0, s, a, tie_factor(a.dim), line, narrow * kWavesPerBlock);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((quantize_greedy_units_pair_kernel<L_NARROW, U_NARROW, L_WIDE, U_WIDE, BITS, true>), dim3(grid), dim3(kBlock), 0, s, a, tie_factor(a.dim), line, narrow * kWavesPerBlock);
 }
 // Other row lengths: long lists give a row as few lanes as hold it; short ones give it two groups of 4 to
 // 32 lanes, which evaluate the two candidates of an iteration side by side (17 instead of 23 us for
@@ -1554,6 +1608,12 @@ void launch_greedy_units(QuantArgs &a, hipStream_t s) {
     if (n4 >= 68 && n4 < 72) wide_rows = ~0ull;
     const bool may_be_wide = lanes == 64 || a.n_max >= wide_rows;
     const bool may_be_narrow = lanes != 64 && (!may_be_wide || a.n_dev != nullptr);
+    if (may_be_wide && may_be_narrow && n4 < 36) {
+        if (lanes == 1) launch_greedy_units_pair<4, 2, 1, 8, BITS>(a, s, wide_rows);
+        else if (lanes == 2) launch_greedy_units_pair<8, 8, 2, 8, BITS>(a, s, wide_rows);
+        else launch_greedy_units_pair<8, 8, 4, 8, BITS>(a, s, wide_rows);
+        return;
+    }
     const uint64_t below = may_be_wide ? wide_rows : ~0ull, from = may_be_narrow ? wide_rows : 0;
     if (may_be_narrow) {
         if (n4 <= 8) launch_greedy_units_shape<4, 2, true, BITS>(a, s, 0, below);
@@ -1627,13 +1687,13 @@ void launch_units(QuantBatchArgs<> &b, uint32_t n, hipStream_t s) {
 
 // The greedy search, which takes one table per launch.
 template <int BITS>
-void launch_greedy_bits(cnr_ctx *ctx, QuantArgs &a, hipStream_t s) {
+void launch_greedy_bits(QuantArgs &a, hipStream_t s) {
     if (launch_greedy_short<BITS>(a, s)) return;
-    if (a.dim == 16) return launch_greedy<1, BITS, 1>(ctx, a, s, 0, ~0ull);
-    if (a.dim == 32) return launch_greedy_by_length<2, 1, 2, BITS>(ctx, a, s);
-    if (a.dim == 64) return launch_greedy_by_length<4, 1, 4, BITS>(ctx, a, s);
-    if (a.dim == 128) return launch_greedy_by_length<8, 2, 4, BITS>(ctx, a, s);
-    if (a.dim == 256) return launch_greedy_by_length<16, 4, 4, BITS>(ctx, a, s);
+    if (a.dim == 16) return launch_greedy<1, BITS, 1>(a, s);
+    if (a.dim == 32) return launch_greedy_by_length<2, 1, 2, BITS>(a, s);
+    if (a.dim == 64) return launch_greedy_by_length<4, 1, 4, BITS>(a, s);
+    if (a.dim == 128) return launch_greedy_by_length<8, 2, 4, BITS>(a, s);
+    if (a.dim == 256) return launch_greedy_by_length<16, 4, 4, BITS>(a, s);
     return launch_greedy_units<BITS>(a, s);
 }
 
@@ -1785,10 +1845,10 @@ cnr_status cnr_quantize_rows_batch(cnr_ctx *ctx, const cnr_table_job *jobs, uint
             if (j.capacity == 0) continue;
             QuantArgs a = part(j, 0, j.capacity);
             switch (bits) {
-                case 2: launch_greedy_bits<2>(ctx, a, s); break;
-                case 3: launch_greedy_bits<3>(ctx, a, s); break;
-                case 4: launch_greedy_bits<4>(ctx, a, s); break;
-                default: launch_greedy_bits<8>(ctx, a, s); break;
+                case 2: launch_greedy_bits<2>(a, s); break;
+                case 3: launch_greedy_bits<3>(a, s); break;
+                case 4: launch_greedy_bits<4>(a, s); break;
+                default: launch_greedy_bits<8>(a, s); break;
             }
             if ((st = cnr_launch_status(ctx)) != CNR_OK) return st;
         }

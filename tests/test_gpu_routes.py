@@ -340,6 +340,31 @@ def test_greedy_search_that_ends_early_finds_the_same_range(ctx, dim, bits, bins
     _poll(ctx)
 
 
+# Lists whose length only the device knows, in buffers that may hold long ones: one launch has both forms.  On either side of the line, empty, of one row, and
+# longer than the buffers; whole searches and partial ones.  The same rows with the length known to the host have to come out the same.
+@pytest.mark.parametrize("dim,bits,line", [(8, 4, 24_576), (24, 3, 49_152), (32, 2, 262_144), (40, 2, 24_576), (64, 4, 131_072), (64, 8, 131_072), (96, 3, 26_624), (128, 2, 65_536),
+                                           (140, 8, 10_649), (140, 4, 26_624), (256, 3, 32_768), (200, 4, 64_000)])
+def test_greedy_lists_of_a_length_that_only_the_device_knows(ctx, dim, bits, line):
+    cap = line * 5 // 4
+    table = synth.table_outlier_mix(cap, dim, 0.02, dim + bits, DEV)
+    ids = _ids(cap, cap, 3)
+    for bins, ratio in ((20, 1.0), (20, 0.15)):
+        out = {}
+        for n, known in ((cap, True), (0, False), (1, False), (777, False), (line - 1, False), (line, False), (cap + 5, False)):
+            sc, bi = torch.full((cap,), -7.0, device=DEV), torch.full((cap,), -7.0, device=DEV)
+            pk = torch.full((cap * P.cnr_packed_row_bytes(dim, bits),), 77, dtype=torch.uint8, device=DEV)
+            n_dev = None if known else torch.tensor([n], dtype=torch.int64, device=DEV)
+            P.cnr_quantize_rows(ctx, table, cap, dim, ids, n_dev, cap, bits, P.CNR_RANGE_GREEDY, (bins, ratio), sc, bi, packed=pk)
+            if known:
+                out = dict(scale=sc, bias=bi, packed=pk.reshape(cap, -1))
+                continue
+            live = min(n, cap)
+            assert torch.equal(sc[:live], out["scale"][:live]) and torch.equal(bi[:live], out["bias"][:live]), n
+            assert torch.equal(pk.reshape(cap, -1)[:live], out["packed"][:live]), n
+            assert (sc[live:] == -7.0).all() and (bi[live:] == -7.0).all() and (pk.reshape(cap, -1)[live:] == 77).all(), n
+    _poll(ctx)
+
+
 # At 8 bits the question is asked before the first iteration too: a step of many codes, of about one, of less than one, and a search of one step.
 @pytest.mark.parametrize("dim,n", [(16, 900), (24, 900), (64, 900), (64, 131_400), (96, 10_800), (256, 900), (320, 900), (1088, 300)])
 @pytest.mark.parametrize("bins,ratio", [(2, 1.0), (20, 0.05), (20, 1.0), (200, 1.0), (400, 0.2)])
