@@ -160,7 +160,7 @@ def load() -> ctypes.CDLL:
 def _bind_marshal() -> None:
     """From here on the extension checks the tensors of a call and packs job arrays (see csrc/cnr_marshal.cpp).  It is host code, compiled
     against this torch and this interpreter: where it is missing and cannot be built, the general checks stay."""
-    global _dev, _pack_fields
+    global _dev, _pack_fields, batch_jobs
     try:
         spec = importlib.util.spec_from_file_location(__package__ + "._marshal", _build.build_marshal(force=False))
         m = importlib.util.module_from_spec(spec)
@@ -169,7 +169,7 @@ def _bind_marshal() -> None:
         warnings.warn("calls are a few microseconds slower, their tensors are checked in Python: %s" % e, RuntimeWarning)
         return
     m.set_general(_general_dev)
-    _dev, _pack_fields = m.address, m.pack_jobs
+    _dev, _pack_fields, batch_jobs = m.address, m.pack_jobs, m.batch_jobs
 
 
 def status_str(status: int) -> str:
@@ -395,6 +395,14 @@ def _general_pack_fields(rows, kinds, names) -> bytes:
 
 
 _pack_fields = _general_pack_fields  # the extension's, once the library is loaded
+
+STAGE_CLEAR, STAGE_MARK, STAGE_COMPACT, STAGE_ROWS = range(4)
+
+
+def batch_jobs(checkpointers, stage, tensors, outputs):
+    """The job array of one stage of a batch from its checkpointers, tensors and outputs (for the mark with whether the indices are
+    64 bits long), or None where something is out of the ordinary and has to go field by field.  The extension's, once the library is loaded."""
+    return None
 
 
 def job_bytes(rows) -> bytes:

@@ -401,3 +401,61 @@ def test_other_row_lengths_share_launches(ctx, dim, bits, sizes):
         assert sizes[i] < 20 or bool(back[0].any())
     st, bad, flags = P.cnr_poll_errors(ctx)
     assert bad == 0 and flags == P.CNR_FLAG_ROW_ID and st != P.CNR_OK
+
+
+def test_job_arrays_from_the_extension_are_those_of_the_general_way(ctx, monkeypatch):
+    # what the extension packs in one step against field by field, and what it leaves to that: everything out of the ordinary
+    from paper_2010_08679_amd import binding as B
+    sent = []
+    for name in ("cnr_clear_bitmap_batch", "cnr_mark_touched_batch", "cnr_compact_dirty_batch", "cnr_quantize_rows_batch", "cnr_restore_rows_batch"):
+        monkeypatch.setattr(B, name, lambda ctx, jobs, *rest, name=name: sent.append((name, bytes(jobs), rest)))
+    n_rows, dim = (50, 1_000, 33), 24
+    cks = [P.TableCheckpointer(ctx, n, dim, capacity=c, device=DEV, mark_scratch=P.TableCheckpointer.new_mark_scratch(n, DEV) if n != 33 else None)
+           for n, c in zip(n_rows, (50, 7, 0))]
+    batch = P.BatchCheckpointer(ctx, cks)
+    tables = [torch.zeros(n, dim, device=DEV) for n in n_rows]
+    fast, took = B.batch_jobs, []
+
+    def counting(*args):
+        took.append(fast(*args))
+        return took[-1]
+
+    def both(call, by_extension):
+        def outcome(f):
+            monkeypatch.setattr(B, "batch_jobs", f)
+            sent.clear()
+            try:
+                call()
+            except Exception as e:
+                return type(e)
+            return list(sent)
+        took.clear()
+        one, other = outcome(counting), outcome(lambda *a: None)
+        assert one == other and len(took) == 1 and (took[0] is not None) == by_extension, (one, other, took)
+
+    both(batch.clear, True)
+    both(batch.compact, True)
+    ix = [torch.arange(5, device=DEV), None, torch.arange(6, device=DEV).reshape(2, 3)]
+    both(lambda: batch.mark(ix), True)
+    both(lambda: batch.mark(tuple(t if t is None else t.int() for t in ix) + (None,)), True)
+    for odd in (ix[:2], [None] * 3, [ix[0], ix[0].int(), None], [torch.arange(9, device=DEV)[::2], None, None], [ix[0].cpu(), None, None], [ix[0].short(), None, None],
+                [3, None, None], dict(enumerate(ix))):
+        both(lambda: batch.mark(odd), False)
+    for bits, ranges in ((2, False), (3, True), (4, True), (8, False)):
+        outs = [c.alloc_output(bits, want_range=ranges) for c in cks]
+        both(lambda: batch.encode(tables, outs), True)
+        both(lambda: batch.restore(tuple(tables), outs), True)
+        for i, field in ((0, "scale"), (1, "bias"), (2, "packed")):
+            good = getattr(outs[i], field)
+            for bad in (None, good[:-1], good.cpu(), good.double()):
+                setattr(outs[i], field, bad)
+                both(lambda: batch.encode(tables, outs), False)
+            setattr(outs[i], field, good)
+        for bad in (tables[:2], [tables[0], tables[1].t().contiguous().t(), tables[2]], [tables[0], tables[1][:-1], tables[2]], [tables[0].half()] + tables[1:], [None] + tables[1:]):
+            both(lambda: batch.restore(bad, outs), False)
+    ids, cks[0].row_ids = cks[0].row_ids, cks[0].row_ids.long()
+    both(batch.compact, False)
+    cks[0].row_ids, cks[1].n_rows = ids, -1
+    both(batch.clear, False)
+    cks[1].n_rows = True
+    both(batch.clear, False)
