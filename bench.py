@@ -42,8 +42,8 @@ FP32_VECTOR_PEAK_TFLOPS = 157.3  # MI355X fp32 vector, published
 GREEDY_SIMD_CLOCKS_PER_ELEMENT = 18.0
 SIMD_CLOCKS_PER_S = 256 * 4 * 2.4e9
 # Candidate ranges per row that a wave of 64 rows of the workload has tried when the last of its searches can be ended, of
-# 1 + 2 * n_iter: a property of the rows (12,800 of them searched in numpy: 21.07 iterations on average, 23 at most).
-GREEDY_CANDIDATES = {"cfg4/b4": 43.1}
+# 1 + 2 * n_iter: a property of the rows (12,800 of them searched on the host: 20.09 iterations on average, 21 at most).
+GREEDY_CANDIDATES = {"cfg4/b4": 41.2}
 
 # HBM traffic of the two bandwidth-bound kernels from rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE, each
 # scaled by what a 1 GiB device copy reads on the same counter: 2.000 and 1.000), in bytes per dirty row,

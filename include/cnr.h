@@ -242,8 +242,8 @@ cnr_status cnr_quant_error(cnr_ctx *ctx, const float *table, uint64_t n_rows, ui
  * error tapers off, then does the same over `ratio_grid` at that num_bins.  "Tapers off" is read as:
  * with I(p) = 1 - E(p) / E_minmax, the first p of the grid with I(p) >= (1 - taper) * max I (the
  * first grid value when nothing improves on min/max).  Grids are taken in the order given.
- * Synchronizes `stream` once after each of the two grids, a grid whose launch failed included: no
- * work of the call is left behind when it returns.
+ * Synchronizes `stream` once, or once after each of the two grids where they do not fit one launch, a launch
+ * that failed included: no work of the call is left behind when it returns.
  *   sample_ids  device uint32 [n_sample], 16-byte aligned
  *   bins_grid   host uint32 [n_bins], ratio_grid host float [n_ratios]; at most CNR_SELECT_MAX_GRID each
  *   taper       in [0, 1), e.g. 0.05
