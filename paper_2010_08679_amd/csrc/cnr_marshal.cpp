@@ -204,6 +204,13 @@ PyObject *batch_jobs(PyObject *, PyObject *const *args, Py_ssize_t n) {
             good = job(owner, stage, t, o, f, index_type);
             memcpy(PyBytes_AS_STRING(bytes.get()) + i * kJobFields * 8, f, sizeof(f));
         }
+        // look-ups beyond the last table are not marked, but none may be of another type
+        if (stage == kMark)
+            for (Py_ssize_t i = rows; good; ++i) {
+                PyObject *t = item(args[2], i);
+                if (!t) break;
+                good = t == Py_None || (THPVariable_CheckExact(t) && THPVariable_Unpack(t).scalar_type() == index_type);
+            }
     } catch (...) {  // a tensor that has no address; the general way meets and reports it
         good = false;
     }

@@ -459,3 +459,20 @@ def test_job_arrays_from_the_extension_are_those_of_the_general_way(ctx, monkeyp
     both(batch.clear, False)
     cks[1].n_rows = True
     both(batch.clear, False)
+
+
+def test_look_ups_beyond_the_tables_share_the_dtype_too(ctx):
+    # tensors beyond the last table are not marked, but a dtype of their own, or no dtype, is refused as it is among the tables' own
+    cks = [P.TableCheckpointer(ctx, 100, 16, device=DEV) for _ in range(2)]
+    batch = P.BatchCheckpointer(ctx, cks)
+    ix = [torch.tensor([3 * i + 1], device=DEV) for i in range(3)]
+    for seq in (list, tuple):
+        batch.clear()
+        for more in ([ix[2]], [None], [ix[2], None, ix[2].cpu()], []):
+            batch.mark(seq(ix[:2] + more))
+        assert [torch.nonzero(c.bitmap).numel() for c in cks] == [1, 1]
+        assert [int(c.bitmap[0]) for c in cks] == [2, 16]
+        for more, error in (([ix[2].int()], TypeError), ([None, ix[2].int()], TypeError), ([3], AttributeError)):
+            with pytest.raises(error):
+                batch.mark(seq(ix[:2] + more))
+    assert P.cnr_poll_errors(ctx)[1:] == (0, 0)
