@@ -57,11 +57,16 @@ static inline uint32_t cnr_sample_lanes(uint32_t dim, uint64_t n, uint32_t n_sea
     if (n4 >= 36 && n4 < 72 && n * n_searches <= 8192) return 32;
     return n4 <= 8 ? 8 : n4 < 72 ? 16 : 64;
 }
-// Waves that search n sampled rows, in whole workgroups; each leaves a sum for every point.
-static inline uint64_t cnr_sample_waves(uint32_t lanes, uint64_t n) {
-    const uint64_t per_workgroup = (uint64_t)(kWave / lanes) * kWavesPerBlock;
-    const uint64_t workgroups = (n + per_workgroup - 1) / per_workgroup;
-    return (workgroups < 4096 ? workgroups : 4096) * kWavesPerBlock;
+// Workgroups that search n sampled rows; each leaves a sum for every point.
+static inline uint64_t cnr_sample_workgroups(uint32_t lanes, uint64_t n) {
+    const uint64_t rows = (uint64_t)(kWave / lanes) * kWavesPerBlock;
+    const uint64_t workgroups = (n + rows - 1) / rows;
+    return workgroups < 4096 ? workgroups : 4096;
+}
+// The workgroups that a launch gets: that many, or as many as max_sums >= n_points sums allow.
+static inline uint32_t cnr_sample_grid(uint32_t lanes, uint64_t n, uint32_t n_points, uint64_t max_sums) {
+    const uint64_t most = max_sums / n_points, workgroups = cnr_sample_workgroups(lanes, n);
+    return (uint32_t)(workgroups < most ? workgroups : most);
 }
 // Index of the last error that a lane evaluates in a search of n_iter iterations: 0 is the un-shrunk range's,
 // then come an iteration's two in turn, or one of them where two groups of lanes go side by side.  64 bits
@@ -73,7 +78,7 @@ constexpr Count last_candidate(uint32_t n_iter, bool side_by_side) {
 constexpr float kFastSearchBins = 0x1p20f;
 // mean_out[p] (device-accessible) = mean l2 error of rows row_ids[0 .. n) quantized with points[p].  Points that follow each other
 // with the same num_bins and no fewer iterations share a search.
-// sums: device, max_sums >= 4 doubles.  Arguments are checked by the caller.
+// sums: device, max_sums >= 1 doubles.  Arguments are checked by the caller.
 cnr_status cnr_sample_errors(cnr_ctx *ctx, const float *table, uint64_t n_rows, uint32_t dim, const uint32_t *row_ids,
                              uint64_t n, int bits, const cnr_search_params *points, uint32_t n_points, double *sums,
                              uint64_t max_sums, double *mean_out, hipStream_t s);

@@ -1099,10 +1099,12 @@ quantize_greedy_units_pair_kernel(const QuantArgs a, double less, uint64_t line,
 // ---------------------------------------------------------------------------------------------
 // Mean l2 error of a sample under several greedy parameters at once (parameter selection): the search of
 // the kernel above, the restored row's error in place of its codes, nothing stored but one sum per
-// wave and point.  Grid y = searches, side by side: a sample of a few thousand rows
+// workgroup and point.  Grid y = searches, side by side: a sample of a few thousand rows
 // leaves the chip mostly idle, and the launch takes as long as its longest search.  What a search of fewer iterations ends with
 // is what a longer one has found by then, so one search serves every point that differs in its ratio alone: it stops at
 // each of them and works out the errors, unless no row of the wave has found a better range since the last one.
+// One sum per workgroup, not per wave: with four times the sums the caller's scratch is full four times as early, and fewer waves then take a sample
+// in several passes (31 values of num_bins at 2 bits, 256 rows of 40: 65 us against 95, 2.5 K rows of 64: 134 and 152; where either fits, level).
 // One launch per set of parameters with the codes stored, read back and compared (encode, error, mean and a synchronization
 // each) took 354 us for 2.5 K rows of 64 and eight points; all values of num_bins in one launch and all ratios in another,
 // a search each, 64 us, this 43.
@@ -1114,8 +1116,8 @@ struct SelectArgs {
     const uint32_t *row_ids;
     uint64_t n;
     double less;   // tie_factor(dim)
-    double *sums;  // [points][n_waves]
-    uint32_t n_waves;  // four per workgroup along x
+    double *sums;  // [points][workgroups along x]
+    uint32_t grid;  // workgroups along x
     cnr_dev_errors *err;
     cnr_search_params points[kSearchBatch];
     uint8_t first[kSearchBatch + 1];  // search y has the points first[y] .. first[y + 1) - 1, in ascending order of iterations
@@ -1131,13 +1133,11 @@ sample_error_kernel(const SelectArgs a) {
     const uint32_t n4 = a.dim / 4;
     const int lane = tid_x() & (kWave - 1);
     const uint32_t j = lane % L;
-    const uint32_t n_waves = a.n_waves;
-    double *const sums = a.sums + wave_in_grid();
-    if ((uint64_t)wave_in_grid() * kRowsPerPass >= a.n) {  // a workgroup's waves beyond the last row
-        for (uint32_t p = p0 + lane; p < p1; p += kWave) sums[(uint64_t)p * n_waves] = 0.0;
-        return;
-    }
+    const uint32_t n_waves = a.grid * kWavesPerBlock;
+    __shared__ double wave_sums[kWavesPerBlock][kSearchBatch];
+    double *const sums = wave_sums[tid_x() / kWave];
     bool add_up = false;  // not the first pass
+    if ((uint64_t)wave_in_grid() * kRowsPerPass >= a.n && lane < (int)kSearchBatch) sums[lane] = 0.0;  // a wave beyond the last row
     for (uint64_t pass = wave_in_grid(); pass * kRowsPerPass < a.n; pass += n_waves) {
         const uint64_t k = pass * kRowsPerPass + lane / Row::LANES;
         uint64_t rid = 0;
@@ -1181,15 +1181,18 @@ sample_error_kernel(const SelectArgs a) {
                     sum = live && lane % Row::LANES == 0 ? sqrt(e) : 0.0;
                     for (int off = 32; off >= Row::LANES; off >>= 1) sum += __shfl_xor(sum, off);
                 }
-                double *const out = sums + (uint64_t)p * n_waves;
-                if (lane == 0) *out = add_up ? *out + sum : sum;
+                if (lane == 0) sums[p] = add_up ? sums[p] + sum : sum;
             }
         };
         if (search_divides(lo, hi, num_bins_f, QMAXF)) points(std::false_type{});
         else points(std::true_type{});
         add_up = true;
     }
+    __syncthreads();
+    const uint32_t p = p0 + tid_x();
+    if (p < p1) a.sums[(uint64_t)p * a.grid + wg_x()] = (wave_sums[0][p] + wave_sums[1][p]) + (wave_sums[2][p] + wave_sums[3][p]);
 }
+static_assert(kWavesPerBlock == 4 && kSearchBatch <= kWave && kSearchBatch <= kBlock, "");
 // mean_out[p] = (the sums of point p, added up in a fixed order) / n; one workgroup per p.
 __global__ void __launch_bounds__(kBlock) sample_mean_kernel(const double *sums, uint32_t per_set, double n, double *mean_out) {
     __shared__ double part[kBlock];
@@ -1748,10 +1751,8 @@ template <int BITS>
 cnr_status launch_sample_errors(cnr_ctx *ctx, SelectArgs &a, uint32_t n_points, uint32_t n_searches, uint64_t max_sums, double *mean_out, hipStream_t s) {
     const uint32_t n4 = a.dim / 4;
     const uint32_t lanes = cnr_sample_lanes(a.dim, a.n, n_searches);
-    uint64_t waves = cnr_sample_waves(lanes, a.n);
-    if (waves > max_sums / n_points) waves = max_sums / n_points & ~3ull;  // at least 4: the caller sees to it
-    a.n_waves = (uint32_t)waves;
-    const dim3 g((unsigned)(waves / kWavesPerBlock), n_searches);
+    a.grid = cnr_sample_grid(lanes, a.n, n_points, max_sums);
+    const dim3 g(a.grid, n_searches);
     if (lanes == 4 && n4 < 36) hipLaunchKernelGGL((sample_error_kernel<4, 8, false, BITS>), g, dim3(kBlock), 0, s, a);
     else if (lanes == 4) hipLaunchKernelGGL((sample_error_kernel<4, 16, false, BITS>), g, dim3(kBlock), 0, s, a);
     else if (lanes == 8) hipLaunchKernelGGL((sample_error_kernel<4, 2, true, BITS>), g, dim3(kBlock), 0, s, a);
@@ -1761,7 +1762,7 @@ cnr_status launch_sample_errors(cnr_ctx *ctx, SelectArgs &a, uint32_t n_points, 
     else hipLaunchKernelGGL((sample_error_kernel<64, 16, false, BITS>), g, dim3(kBlock), 0, s, a);
     cnr_status st = cnr_launch_status(ctx);
     if (st != CNR_OK) return st;
-    hipLaunchKernelGGL(sample_mean_kernel, dim3(n_points), dim3(kBlock), 0, s, a.sums, (uint32_t)waves, (double)a.n, mean_out);
+    hipLaunchKernelGGL(sample_mean_kernel, dim3(n_points), dim3(kBlock), 0, s, a.sums, a.grid, (double)a.n, mean_out);
     return cnr_launch_status(ctx);
 }
 
@@ -1773,7 +1774,7 @@ cnr_status cnr_sample_errors(cnr_ctx *ctx, const float *table, uint64_t n_rows, 
     for (uint32_t done = 0; done < n_points;) {
         uint32_t m = n_points - done;
         if (m > kSearchBatch) m = kSearchBatch;
-        if (m > max_sums / kWavesPerBlock) m = (uint32_t)(max_sums / kWavesPerBlock);  // >= 1
+        if (m > max_sums) m = (uint32_t)max_sums;  // >= 1
         SelectArgs a = {table, n_rows, dim, row_ids, n, tie_factor(dim), sums, 0, ctx->dev_err, {}, {}};
         uint32_t n_searches = 0;
         for (uint32_t i = 0; i < m; ++i) {

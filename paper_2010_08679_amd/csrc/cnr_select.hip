@@ -11,8 +11,8 @@ namespace {
 
 size_t align16(size_t v) { return (v + 15u) & ~(size_t)15u; }
 
-// The caller's scratch.  Only partial sums of errors go there, at most one per wave and point (fewer
-// points or waves take part where a small sample's scratch holds fewer); its size, one encoded sample
+// The caller's scratch.  Only partial sums of errors go there, at most one per workgroup and point (fewer
+// points or workgroups take part where a small sample's scratch holds fewer); its size, one encoded sample
 // with its errors, is part of the interface and stays as it was.
 size_t scratch_bytes(uint64_t n, uint32_t dim, int bits) {
     return 2 * align16(n * sizeof(float)) + align16(n * cnr_packed_row_bytes(dim, bits)) + align16(n * sizeof(double)) + 16;
@@ -96,10 +96,11 @@ cnr_status cnr_select_greedy_params(cnr_ctx *ctx, const float *table, uint64_t n
     };
 
     const uint64_t n_points = 1 + (uint64_t)n_bins * n_stops;
-    if (n_points <= kSearchBatch && n_points * cnr_sample_waves(cnr_sample_lanes(dim, n_sample, n_bins), n_sample) <= max_sums) {
-        // Both grids in a launch, one search for each num_bins: as long as the scratch has room for all sums with as many waves as the
-        // sample calls for (four and three values: all rows but those of 36 elements at 2 bits).  2.5 K rows of 64, 3 bits, four and three
-        // values 64 -> 43 us; 100 to 20 K rows of 8 to 320 elements 1.1 to 1.9 times as fast.  With fewer waves than that a
+    const uint64_t workgroups = cnr_sample_workgroups(cnr_sample_lanes(dim, n_sample, n_bins), n_sample);
+    if (n_points <= kSearchBatch && n_points * (workgroups > 4 ? workgroups : 4) <= max_sums) {
+        // Both grids in a launch, one search for each num_bins: as long as the scratch has room for all sums with as many workgroups as the
+        // sample calls for, or four where that is more (four and three values: at every row length from 21 rows on).  2.5 K rows of 64, 3 bits, four and three
+        // values 64 -> 43 us; 100 to 20 K rows of 8 to 320 elements 1.1 to 1.9 times as fast.  With fewer workgroups than that a
         // wave searches several rows one after the other, which costs more than the second launch.
         points[0] = {0, (float)bins_grid[0]};  // min/max
         for (uint32_t i = 0; i < n_bins; ++i)
@@ -119,7 +120,7 @@ cnr_status cnr_select_greedy_params(cnr_ctx *ctx, const float *table, uint64_t n
         best = taper_choice(by_bins, n_bins, naive, taper);
         // One search for all ratios, or, in descending order, one for each while they have room side by side: the stops of one
         // search are behind each other.
-        const bool apart = n_ratios * cnr_sample_waves(cnr_sample_lanes(dim, n_sample, n_ratios), n_sample) <= 16u * (uint64_t)ctx->n_cu;
+        const bool apart = n_ratios * cnr_sample_workgroups(cnr_sample_lanes(dim, n_sample, n_ratios), n_sample) <= 4u * (uint64_t)ctx->n_cu;
         uint32_t slot[CNR_SELECT_MAX_GRID + 1], m = 0;
         for (uint32_t i = 0; i < n_stops; ++i) {
             const uint32_t k = apart ? n_stops - 1 - i : i;

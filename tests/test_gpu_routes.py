@@ -584,6 +584,47 @@ def test_parameter_selection_routes(ctx, dim, bits, n, bins):
     _poll(ctx)
 
 
+# Points that share a search: grids in any order, values twice, no ratio 1, ratios without an iteration, one stop only; in one launch (up to 32 points that fit the
+# scratch) and in two, whose ratios are searched apart or (many rows) together; launches in which a wave takes several passes (4096 workgroups).
+@pytest.mark.parametrize("dim,bits,n,bins,ratios", [
+    (64, 3, 700, (45, 10, 25, 10), (1.0, 0.3, 0.6, 0.3)),
+    (36, 2, 300, (25, 9, 45, 16), (0.2, 0.0, 0.6)),
+    (40, 2, 500, (12, 30), (0.0,)), (96, 4, 130, (30, 30), (1.0,)), (288, 2, 257, (20, 8, 14, 11), (0.7, 0.2)),
+    (16, 4, 900, (2, 1, 40), (0.5, 1.5, 0.05)), (144, 2, 1001, (1,), (0.4, 0.0, 0.9)),
+    (64, 2, 300, (40, 3, 22, 3, 17, 9, 30, 12, 5, 26, 33), (0.8, 0.25, 0.5)), (24, 8, 90_000, tuple(range(13, 2, -1)), (0.9, 0.0, 0.3)),
+    (8, 4, 262_500, (9, 3), (0.6, 0.3)), (32, 4, 2, (14, 6), (0.5, 0.9)), (64, 4, 5, (14, 6), (0.5, 0.9)),
+])
+def test_parameter_selection_with_shared_searches(ctx, dim, bits, n, bins, ratios):
+    print("case select dim=%d bits=%d n=%d" % (dim, bits, n), flush=True)
+    table = synth.table_outlier_mix(n, dim, 0.02, dim + n, DEV)
+    table[1] = 0.25                        # searched by division
+    ids = torch.arange(n, dtype=torch.int32, device=DEV)
+    choice, report = P.select_greedy_params(ctx, table, n, dim, ids, bits, bins, ratios)
+    rows = table.cpu().numpy()
+    scale, bias = torch.empty(n, device=DEV), torch.empty(n, device=DEV)
+    packed = torch.empty(n * P.cnr_packed_row_bytes(dim, bits), dtype=torch.uint8, device=DEV)
+    err = torch.empty(n, dtype=torch.float64, device=DEV)
+
+    def mean(num_bins, ratio):             # the oracle's, but for the rows whose exact tie it decides by rounding: there the encoder's
+        ora = O.quantize_rows(rows, None, bits, mode=O.RANGE_GREEDY, num_bins=num_bins, ratio=ratio, n_threads=8)
+        errors = O.row_l2(rows, O.dequantize(ora["codes"], ora["scale"], ora["bias"]))[0].copy()
+        P.cnr_quantize_rows(ctx, table, n, dim, ids, None, n, bits, P.CNR_RANGE_GREEDY, (num_bins, ratio), scale, bias, packed=packed)
+        P.cnr_quant_error(ctx, table, n, dim, ids, None, n, bits, packed, scale, bias, err)
+        tied = tie_rows(rows, dict(scale=scale.cpu().numpy(), bias=bias.cpu().numpy()), ora, bits, num_bins, ratio)
+        errors[tied] = err.cpu().numpy()[tied]
+        return float(errors.mean())
+
+    want = {"naive": O.mean_l2(rows, bits, O.RANGE_MINMAX)}
+    want.update({("bins", b): mean(b, 1.0) for b in bins})
+    assert choice[0] == O.taper_choice(list(bins), [want[("bins", b)] for b in bins], want["naive"], 0.05)
+    want.update({("ratio", r): mean(choice[0], r) for r in ratios})
+    assert set(report) == set(want)
+    for key in want:                       # fp64 sums in another order
+        assert report[key] == pytest.approx(want[key], rel=1e-9), key
+    assert choice[1] == np.float32(O.taper_choice(list(ratios), [want[("ratio", r)] for r in ratios], want["naive"], 0.05))
+    _poll(ctx)
+
+
 # ---- compaction: workgroups that count the tiles before theirs, up to 64 tiles; counted tiles beyond ------
 
 @pytest.mark.parametrize("n_rows", [16_384, 16_385, 8 * 16_384 + 1, 64 * 16_384, 64 * 16_384 + 1])

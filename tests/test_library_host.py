@@ -194,6 +194,17 @@ def test_parameter_selection_in_one_launch_chooses_as_in_two(tmp_path):
     assert out.returncode == 0, out.stdout + out.stderr
 
 
+def test_parameter_selection_has_room_for_its_sums(tmp_path):
+    import subprocess
+    exe = str(tmp_path / "select_room")
+    csrc = os.path.join(ROOT, "paper_2010_08679_amd", "csrc")
+    subprocess.check_call(["g++", "-std=c++17", "-O2", "-D__HIP_PLATFORM_AMD__", "-isystem", "/opt/rocm/include", "-I", os.path.join(ROOT, "include"),
+                           "-I", csrc, "-x", "c++", os.path.join(csrc, "cnr_select.hip"), os.path.join(ROOT, "tests", "c", "select_room.cpp"),
+                           "-o", exe])
+    out = subprocess.run([exe], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout + out.stderr
+
+
 def test_bit_width_selection_equals_the_oracle():
     for expected in list(range(0, 30)) + [99, 100, 101, 10_000]:
         for observed in (0, 1, expected, expected + 1):
