@@ -5,8 +5,8 @@
 // of that table's work, so the tables of a batch run side by side in one launch.  The single-table
 // entry points are batches of one.
 #include "cnr_common.h"
+#include "cnr_mark_rule.h"
 
-#include <cmath>
 #include <type_traits>
 
 // Per-tile counts of cnr_compact_dirty_noalloc: a fixed array in the library's device image instead
@@ -206,8 +206,8 @@ __global__ void __launch_bounds__(kSeenThreads) mark_flags_kernel(const TrackBat
 // mark, second bulk variant, for tables of up to a few tens of millions of rows: bitmap slices in LDS.
 //
 // A workgroup owns kSliceRows consecutive rows of one table as a bitmap in LDS (all 160 KB of a
-// compute unit) and one part of the table's index stream (an eighth; down to a thirty-second for
-// small tables, see slice_parts_max): it reads its share of the stream, sets the bits of the
+// compute unit) and one part of the table's index stream (a half down to a thirty-second, see
+// bulk_mark_parts): it reads its share of the stream, sets the bits of the
 // look-ups that fall into its rows with LDS atomics, and stores the slice to slab s (= its part of
 // the stream) of the scratch buffer, partial bitmaps that fold_slabs_kernel ORs into the bitmap and
 // zeroes again.  Nothing is scattered to memory; the price is that the W = ceil(n_rows / kSliceRows)
@@ -220,27 +220,6 @@ __global__ void __launch_bounds__(kSeenThreads) mark_flags_kernel(const TrackBat
 // teams of four it costs 20 %: 415 -> 502 us for 8 x 5 M rows, 20 M look-ups).
 // ---------------------------------------------------------------------------------------------
 constexpr int kSliceThreads = 1024;
-constexpr uint32_t kSliceWords = 40960;
-constexpr uint64_t kSliceRows = 32ull * kSliceWords;
-constexpr uint32_t kStreamParts = 8;      // parts of a stream that every scratch has room for (slabs)
-constexpr uint32_t kStreamPartsMax = 32;  // parts of a stream at most
-// The scratch of a table: one byte per row (eight slabs, or the flag bytes), and never less than 32
-// slabs of one whole slice, so that a table of one or two slices, whose 8 or 16 workgroups would
-// leave most of the chip idle, can be shared out over 32 or 16 parts of its stream instead.
-constexpr uint64_t kScratchFloorBytes = (uint64_t)kStreamPartsMax * kSliceWords * 4u;
-inline uint64_t mark_scratch_bytes(uint64_t n_rows) {
-    const uint64_t words = cnr_bitmap_words(n_rows);
-    const uint64_t per_row = words * 32u, slabs32 = words * 4u * kStreamPartsMax;
-    const uint64_t floor = slabs32 < kScratchFloorBytes ? slabs32 : kScratchFloorBytes;
-    return per_row > floor ? per_row : floor;
-}
-// The most parts (a multiple of eight) a table's scratch has slabs for.
-inline uint32_t slice_parts_max(uint64_t n_rows) {
-    const uint64_t words = cnr_bitmap_words(n_rows);
-    if (words == 0) return kStreamParts;
-    const uint64_t fit = (mark_scratch_bytes(n_rows) / (words * 4u)) & ~7ull;
-    return (uint32_t)(fit > kStreamPartsMax ? kStreamPartsMax : fit < kStreamParts ? kStreamParts : fit);
-}
 
 template <typename IdxT, bool STREAM>
 __global__ void __launch_bounds__(kSliceThreads) mark_slices_kernel(const TrackBatch b, cnr_dev_errors *err) {
@@ -600,56 +579,9 @@ cnr_status cnr_mark_touched_batch(cnr_ctx *ctx, const cnr_table_job *jobs, uint3
     for (uint32_t first = 0; first < n_jobs; first += CNR_MAX_BATCH) {
         // Three routes.  Short streams: atomic ORs on the bitmap (about 16 G atomics/s; the other two
         // pay a pass over n_rows bytes or more).  Long streams: bitmap slices in LDS, or one flag byte per row
-        // and a fold; tables of more than kSliceTeamMax slices always take the flag bytes, the others of a call take
-        // together what these estimates (in us) make the cheapest:
-        //   slices   two launches, 0.5 for each MB of slabs that the workgroups write and the fold reads and zeroes, and the
-        //            longest part of a stream at 70 GB/s, once for every round the workgroups need on the chip.  Few parts
-        //            for short streams (8 tables of 1.3 M rows, 131 K look-ups each: 13 us in four parts, 30 in thirty-two), many for
-        //            long ones (4.2 M look-ups: 158 and 65, 61 in sixteen).
-        //   flags    two launches, 0.2 for each MB of flags, and 1 to 7 ps for a look-up: 17 ps for one that gets past the
-        //            table of lately flagged rows, more of them the larger the table is and the fewer compute units it gets
-        //            (Zipf(1.05): 2.3 ps with 100 K rows, 5.6 with 1.3 M, 7 with 5 M; Zipf(1.2): half of that; a stream without repeats 17).
-        // Measured over 1 to 16 tables of 60 K to 16 M rows and 70 K to 30 M look-ups each: Zipf(1.05) 2 % from the
-        // best of these on average, Zipf(1.2) 5 %, no repeats 12 %; parts that fill the chip, and slabs and launches taken as free, were 35, 45 and 30 %
-        // away.  (The worst against that, at most 400 K to 1 M look-ups into each of three or four tables of 4 to 8 M rows, which take the
-        // flags: 29 -> 37 us, without repeats 29 -> 56.)
-        constexpr uint64_t kSliceTeamMax = 16;
-        constexpr double kLaunchesUs = 7.0, kSlabUsPerByte = 0.495e-6, kStreamUsPerByte = 14e-6;
-        constexpr double kFlagLaunchesUs = 5.0, kFlagUsPerByte = 0.22e-6, kFlagUsPerLookup = 0.7e-6;
-        auto bulk_stream = [](const cnr_table_job &j) { return j.mark_scratch && j.n_rows && j.n_indices > j.n_rows / 256 + 65536; };
-        auto slices_of = [](const cnr_table_job &j) { return (j.n_rows + kSliceRows - 1) / kSliceRows; };
-        auto parts_of = [](const cnr_table_job &j, uint32_t want) {
-            const uint32_t most = slice_parts_max(j.n_rows);
-            return want < most ? want : most;
-        };
-        uint32_t tables = 0;
-        for (uint32_t i = first; i < n_jobs && i < first + CNR_MAX_BATCH; ++i) tables += bulk_stream(jobs[i]) && slices_of(jobs[i]) <= kSliceTeamMax;
-        double best_us = kFlagLaunchesUs;  // through flag bytes
-        for (uint32_t i = first; i < n_jobs && i < first + CNR_MAX_BATCH; ++i) {
-            const cnr_table_job &j = jobs[i];
-            if (!bulk_stream(j) || slices_of(j) > kSliceTeamMax) continue;
-            const double spread = std::log2((double)j.n_rows) + 0.32 * std::log2((double)tables) - 14.5;
-            best_us += kFlagUsPerByte * (double)j.n_rows + kFlagUsPerLookup * (spread > 1.0 ? spread : 1.0) * (double)j.n_indices;
-        }
-        uint32_t want_parts = 0;  // 0: flag bytes
-        for (uint32_t want = 2; tables && want <= kStreamPartsMax; want *= 2) {
-            uint64_t workgroups = 0, slab_bytes = 0, longest = 0;
-            for (uint32_t i = first; i < n_jobs && i < first + CNR_MAX_BATCH; ++i) {
-                const cnr_table_job &j = jobs[i];
-                if (!bulk_stream(j) || slices_of(j) > kSliceTeamMax) continue;
-                const uint32_t parts = parts_of(j, want);
-                workgroups += slices_of(j) * parts;
-                slab_bytes += cnr_bitmap_words(j.n_rows) * 4u * parts;
-                if (j.n_indices / parts > longest) longest = j.n_indices / parts;
-            }
-            const uint64_t rounds = (workgroups + (uint64_t)ctx->n_cu - 1) / (uint64_t)ctx->n_cu;
-            const double us = kLaunchesUs + kSlabUsPerByte * (double)slab_bytes +
-                              kStreamUsPerByte * (type == CNR_IDX_I64 ? 8.0 : 4.0) * (double)(longest * rounds);
-            if (us < best_us) {
-                best_us = us;
-                want_parts = want;
-            }
-        }
+        // and a fold, as bulk_mark_parts estimates.
+        const uint32_t n_here = n_jobs - first < CNR_MAX_BATCH ? n_jobs - first : CNR_MAX_BATCH;
+        const uint32_t want_parts = bulk_mark_parts(jobs + first, n_here, type == CNR_IDX_I64 ? 8 : 4, (uint32_t)ctx->n_cu);  // 0: flag bytes
         TrackBatch slices = {}, bulk = {}, direct = {};
         uint32_t n_slices = 0, n_bulk = 0, n_direct = 0;
         bool slices_one = true;     // every table of the slices route is one slice
@@ -669,7 +601,7 @@ cnr_status cnr_mark_touched_batch(cnr_ctx *ctx, const cnr_table_job *jobs, uint3
             t.flags = (uint8_t *)j.mark_scratch;
             const uint64_t words = cnr_bitmap_words(j.n_rows);
             if (use_slices) {
-                t.parts = parts_of(j, want_parts);
+                t.parts = slice_parts(j.n_rows, want_parts);
                 if (team * t.parts > slices_team) slices_team = team * t.parts;
                 if (team > 1) slices_one = false;
                 slices_bytes += j.n_indices * (type == CNR_IDX_I64 ? 8u : 4u);

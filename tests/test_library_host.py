@@ -194,6 +194,15 @@ def test_parameter_selection_in_one_launch_chooses_as_in_two(tmp_path):
     assert out.returncode == 0, out.stdout + out.stderr
 
 
+def test_bulk_mark_takes_the_faster_way(tmp_path):
+    import subprocess
+    exe = str(tmp_path / "mark_rule")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2010_08679_amd", "csrc"),
+                           os.path.join(ROOT, "tests", "c", "mark_rule.cpp"), "-o", exe])
+    out = subprocess.run([exe], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout + out.stderr
+
+
 def test_parameter_selection_has_room_for_its_sums(tmp_path):
     import subprocess
     exe = str(tmp_path / "select_room")
