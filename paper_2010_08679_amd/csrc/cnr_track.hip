@@ -54,10 +54,19 @@ __global__ void __launch_bounds__(kBlock) clear_kernel(const TrackBatch b) {
 // there afterwards if that one's row is the same.  (Where two rows share a slot one of them may issue
 // more than one.)  And all words of a pass are loaded before its first OR, which the compiler would not move a load past.
 // 8 tables of 1 M rows, 40,960 Zipf(1.1) look-ups each: first call after a clear 44 -> 11 us, mean of 32 calls 12.1 -> 6.5 (3.5
-// where all bits are set); one table of 100 K rows, 4096 look-ups 6.5 -> 3.0; 1.5 M look-ups of different rows in no order
-// 128 -> 92, in ascending order, where nothing repeats and a wave's ORs meet in few words, 62 -> 65.
+// where all bits are set); one table of 100 K rows, 4096 look-ups 6.5 -> 3.0; 1.5 M look-ups of different rows in no order into 5 M
+// 128 -> 92.  Without repeats the agreement is in vain, and where the bitmap is larger than the caches its barriers cost: 500 K different rows in no
+// order of 64 M 24 -> 27, of 256 M 24 -> 29 (Zipf(1.05) look-ups into 64 M, 131 K: 45 -> 9).
+// A list of rows in order has no repeats either, but its ORs meet in few words, up to 32 of a wave in one, and the loads ahead of them made that worse (750 K
+// of 2.5 M rows 31.2 -> 33.0 us, 1 M of 1 M 84 -> 102).  So a wave whose rows ascend collects the bits of each word first, and
+// its first lane there issues the OR: 6.0 and 4.7 us.  Other waves pay a comparison with the lane before, while they wait for the words.
 // ---------------------------------------------------------------------------------------------
 constexpr uint32_t kMarkUnroll = 4, kMarkSlots = 4096;
+// Whether this lane's row is above the one of the lane before.
+__device__ __forceinline__ bool lane_ascends(uint32_t r) {
+    const uint32_t left = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)r, 0x138 /* wave_shr:1 */, 0xf, 0xf, false);
+    return r > left || (tid_x() & (kWave - 1)) == 0;
+}
 template <typename IdxT>
 __global__ void __launch_bounds__(kBlock) mark_kernel(const TrackBatch b, cnr_dev_errors *err) {
     __shared__ uint16_t slot[kMarkSlots];
@@ -84,6 +93,25 @@ __global__ void __launch_bounds__(kBlock) mark_kernel(const TrackBatch b, cnr_de
             const bool valid = r >= 0 && (uint64_t)r < n_rows;
             if (p < n && !valid) ++bad;
             word[u] = p < n && valid ? bitmap[(uint64_t)r >> 5] : ~0u;
+        }
+        bool ascending = true;
+#pragma unroll
+        for (uint32_t u = 0; u < kMarkUnroll; ++u) ascending = ascending && lane_ascends((uint32_t)v[u]);
+        // (Expected not to: the code then lies apart.  In the way of the others it cost every call 0.15 us.)
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!ascending) == 0, 0)) {
+#pragma unroll
+            for (uint32_t u = 0; u < kMarkUnroll; ++u) {
+                const uint32_t r = (uint32_t)v[u];
+                uint32_t bits = ~word[u] & (1u << (r & 31u));
+#pragma unroll
+                for (int off = 1; off < 32; off *= 2) {  // at most 32 lanes have a word in common
+                    const uint32_t theirs = (uint32_t)__shfl_down((int)bits, off);
+                    if ((uint32_t)__shfl_down((int)r, off) >> 5 == r >> 5) bits |= theirs;
+                }
+                const uint32_t left = (uint32_t)__shfl_up((int)r, 1);
+                if (bits && (left >> 5 != r >> 5 || (tid & (kWave - 1)) == 0)) atomicOr(bitmap + (r >> 5), bits);
+                word[u] = ~0u;
+            }
         }
         bool wants[kMarkUnroll];
 #pragma unroll
