@@ -54,8 +54,8 @@ static inline bool bulk_stream(const cnr_table_job &j) { return j.mark_scratch &
 // look-up, so there they are taken only if a stream without repeats loses no more than a fifth of the time by it.  (In other calls every
 // look-up of a skewed stream gains: two tables of 4 M rows, 10 M look-ups each, Zipf(1.2) 77 against 201, without repeats 308 against 137.)
 // Measured over 884 calls of 64-bit look-ups, 1 to 16 tables of 60 K to 16 M rows and 70 K to 30 M look-ups each, against parts that fill the
-// chip and slabs and launches taken as free: 1.32 times as fast with Zipf(1.05), 1.36 with Zipf(1.2), 1.20 without repeats, two of the skewed
-// ones 5 to 10 % slower; 335 of 32 bits: 1.37, 1.45 and 1.22.  Without the exception, and with other figures, a batch could lose: three
+// chip and slabs and launches taken as free: 1.32 times as fast with Zipf(1.05), 1.36 with Zipf(1.2), 1.20 without repeats; two skewed streams and
+// six without repeats 5 to 10 % slower, one more a third.  335 of 32 bits: 1.37, 1.45 and 1.22.  Without the exception, and with other figures, a batch could lose: three
 // tables of 4 M rows, 1.5 M look-ups each, 25 -> 39 us, without repeats 32 -> 78.
 static inline uint32_t bulk_mark_parts(const cnr_table_job *jobs, uint32_t n_jobs, uint32_t index_bytes, uint32_t n_cu) {
     auto eligible = [](const cnr_table_job &j) { return bulk_stream(j) && slices_of(j) <= kSliceTeamMax; };

@@ -538,10 +538,12 @@ __device__ __forceinline__ bool search_divides(float lo, float hi, float num_bin
 // current range instead of the next two, every search took one iteration more: 1.5 M rows of 64 at 3 bits and 25 bins 377 -> 352 us now,
 // 4 bits and 45 bins 358 -> 333, 100 bins 653 -> 630, 1.2 M rows of 16 58 -> 47, 8 bits 32 -> 27 (0.3 M rows of 64 29 -> 24).  Rows of 8
 // to 512 elements at 4 bits and 45 bins 1.4 to 6 times as fast as without an end, at 8 bits 4 to 5 times.  At 2 bits it depends on the rows: whole
-// searches of 1024 elements 1.6 times as fast on evenly spread values, 1.3 on normal ones, and a few per cent slower where outliers
-// let the search go on to nine tenths of its iterations (25 bins: 1 K rows of 1024 23.5 -> 24.9 us, of 320 15.8 -> 16.0; 10 K and more
-// within 3 %).  Searches that stop by themselves about where rows would be finished lose up to 7 % (1 K rows of 140 at 2 bits,
-// 25 bins, ratio 0.6, 13.7; 13.0 with the question about the current range).
+// searches of 1024 elements 1.6 times as fast on evenly spread values, 1.3 on normal ones, and a few per cent slower than without an end where outliers
+// let the search go on to nine tenths of its iterations (25 bins: 1 K rows of 1024 23.5 -> 24.9 us, of 320 15.8 -> 16.2; 10 K and more
+// within 3 %), as are searches that stop by themselves about where rows would be finished (1 K rows of 320 at 4 bits, 45 bins, ratio 0.4, 13.1 -> 14.6).
+// Short lists are up to 13 % slower or 10 % faster by where their loop lies in the code: a few waves then wait for their own
+// instructions (1.7 K rows of 16 at 2 bits and 94 bins 14.0 us where the loop begins at byte 36 of a line of 128, 16.2 at byte 116, 15.6 at 0; the
+// same instructions).  Loops aligned throughout win and lose as much: rows of 96 38.8 -> 34.6, of 24 19.5 -> 21.4, 1.5 M rows of 64 at 100 bins 626 -> 668.
 template <int N>
 struct ClipBound {
     float mn[N], mx[N];
