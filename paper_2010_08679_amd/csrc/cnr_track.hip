@@ -55,8 +55,8 @@ __global__ void __launch_bounds__(kBlock) clear_kernel(const TrackBatch b) {
 // more than one.)  And all words of a pass are loaded before its first OR, which the compiler would not move a load past.
 // 8 tables of 1 M rows, 40,960 Zipf(1.1) look-ups each: first call after a clear 44 -> 11 us, mean of 32 calls 12.1 -> 6.5 (3.5
 // where all bits are set); one table of 100 K rows, 4096 look-ups 6.5 -> 3.0; 1.5 M look-ups of different rows in no order into 5 M
-// 128 -> 92.  Without repeats the agreement is in vain, and where the bitmap is larger than the caches its barriers cost: 500 K different rows in no
-// order of 64 M 24 -> 27, of 256 M 24 -> 29 (Zipf(1.05) look-ups into 64 M, 131 K: 45 -> 9).
+// 128 -> 92.  Where the bitmap is larger than the caches and nothing repeats, an OR that follows its word's load at once is faster: 500 K different rows in
+// no order of 64 M 24 -> 27, of 256 M 24 -> 29, without the agreement and its barriers as well (Zipf(1.05) look-ups into 64 M, 131 K: 45 -> 9).
 // A list of rows in order has no repeats either, but its ORs meet in few words, up to 32 of a wave in one, and the loads ahead of them made that worse (750 K
 // of 2.5 M rows 31.2 -> 33.0 us, 1 M of 1 M 84 -> 102).  So a wave whose rows ascend collects the bits of each word first, and
 // its first lane there issues the OR: 6.0 and 4.7 us.  Other waves pay a comparison with the lane before, while they wait for the words.
